@@ -302,8 +302,7 @@ def bench_hard(torch, args):
     # kernel's measured launch time, against the published FP32 peak
     roofline = {
         "bound": "alu",
-        "kernel": (f"k_assign<{s.params.wg_size},true,{'true' if s.params.table_mode else 'false'}> "
-                   "(fused assignment + update sums)"),
+        "kernel": f"k_assign<{s.params.wg_size or 256},true> (fused assignment + update sums)",
         "achieved": round(achieved, 3),
         "peak": FP32_PEAK_TFLOPS,
         "unit": "TFLOP/s",
@@ -466,7 +465,7 @@ def bench_window(torch, args, img, tuned):
     H, W = img.contour.shape
     lab = torch.from_numpy(img.lab).cuda()
     con = torch.from_numpy(img.contour).cuda()
-    s = Scalp(W, H, wl.k, iterations=wl.iterations, assign_mode=ASSIGN_WINDOW, **tuned)
+    s = Scalp(W, H, wl.k, iterations=wl.iterations, assign_mode=ASSIGN_WINDOW)
     out = s.new_state()
     for _ in range(args.warmup):
         s.run(lab, con, out=out)

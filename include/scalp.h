@@ -71,13 +71,16 @@ typedef struct {
     int32_t reuse_prepared;  /* 1: the workspace already holds this image's
                                 packed (l, a, b, w) from an earlier call with
                                 the same lab/contour/sigma; skip re-packing  */
-    int32_t lds_pixels;      /* tuning: LDS budget of the assignment in 16-byte
-                                units (per-candidate tables of 8-byte entries,
-                                two of this many; one table of twice as many
-                                with table_mode 1 and for the window form),
-                                0..9728; 0 selects the default (4800)        */
-    int32_t wg_size;         /* tuning: assignment workgroup size, 0 (default
-                                1024), 256, 512 or 1024                      */
+    int32_t lds_pixels;      /* tuning of the window form and of the soft
+                                kernels: LDS budget in 16-byte units (the
+                                window form's one table of twice this many
+                                8-byte entries, the soft forward's two tables
+                                of this many), 0..9728; 0 selects the default
+                                (4800).  The 3x3 form has no tables.  The
+                                results do not depend on it                  */
+    int32_t wg_size;         /* tuning: assignment workgroup size, 0 (default:
+                                256 for the 3x3 form, 1024 for the window form
+                                and the soft forward), 256, 512 or 1024      */
     int32_t assign_mode;     /* SCALP_ASSIGN_GRID3X3 (default) or
                                 SCALP_ASSIGN_WINDOW, see below               */
     int32_t contour_source;  /* SCALP_CONTOUR_INPUT (default) or
@@ -95,18 +98,10 @@ typedef struct {
                                 batched persistent launch, 0 (default: as many
                                 as fit) or 1..16 (capped at what fits); the
                                 results do not depend on it                  */
-    int32_t table_mode;      /* tuning of the 3x3 assignment: 0 (default): a
-                                (colour distance, w) table per candidate over
-                                the rectangle of the work item's pixels and the
-                                endpoint, two tables of lds_pixels entries
-                                alternating, one barrier per candidate; 1: the
-                                waves with a lane that walks the candidate vote
-                                the table down to the box of their pixels and
-                                the endpoint, one table of twice as many
-                                entries, two barriers per candidate, no table
-                                when no lane walks (pays off for cells much
-                                larger than the workgroup).  The results do
-                                not depend on it; 0 or 1, else SCALP_ERR_ARG */
+    int32_t table_mode;      /* 0 (default) or 1, else SCALP_ERR_ARG.  Chose
+                                between two table schedules of the 3x3
+                                assignment, which has no tables any more: kept
+                                for callers that set it, without effect      */
 } scalp_params_t;
 
 /* Candidate rule of the assignment.

@@ -64,12 +64,22 @@ bool pack_inputs_ok(const scalp_params_t* p, const float* lab, const float* cont
     return lab && (contour || p->contour_source == SCALP_CONTOUR_GRADIENT);
 }
 
+// Launch shape of the window form and of the soft kernels (default: 1024 lanes).
 Tuning tuning_of(const scalp_params_t* p) {
     Tuning t;
     t.wg = p->wg_size == 0 ? 1024 : p->wg_size;
     t.lds_pixels = p->lds_pixels > 0 ? p->lds_pixels : default_lds_pixels();
     t.blocks_per_cu = p->persistent_blocks;
-    t.voted = p->table_mode;
+    return t;
+}
+
+// Launch shape of the grid form.  256 lanes by default: an item's waves meet
+// at three barriers, and the more items a CU holds, the less it waits there
+// (10 iterations of 1920x1080, k = 2000: 0.848, 0.864 and 0.897 ms at 256,
+// 512 and 1024 lanes; the 64-image batch: 34.0, 36.0 and 39.2 ms).
+Tuning grid_tuning_of(const scalp_params_t* p) {
+    Tuning t = tuning_of(p);
+    t.wg = p->wg_size == 0 ? 256 : p->wg_size;
     return t;
 }
 
@@ -93,7 +103,7 @@ Img img_of(const scalp_grid_t* g, const scalp_params_t* p, long long pix, int sp
     const double r = grid_r(g->width, g->height, g->k_requested);
     im.spw = (float)(((double)p->m * (double)p->m) / (r * r));          // Eq. (3)
     im.gamma = p->gamma < 0.0f ? (float)(2.0 * r) : p->gamma;           // Sec. III-A.3
-    im.spl = slices_of(g, tuning_of(p).wg);
+    im.spl = slices_of(g, grid_tuning_of(p).wg);
     im.rad = (int)std::floor(r + 0.5);
     im.prune = p->exact_pruning;
     // Each XCD (own L2) takes a contiguous run of the cell order; strips of
@@ -101,6 +111,7 @@ Img img_of(const scalp_grid_t* g, const scalp_params_t* p, long long pix, int sp
     // cells, so fewer table texels sit in cells that another XCD reads too.
     im.strips = std::max(1, std::min({8, g->nx,
         (int)std::lround(std::sqrt(8.0 * g->nx / std::max(1, g->ny)))}));
+    finish_img(im);
     return im;
 }
 
@@ -214,7 +225,7 @@ int enq_window_pass(const Img& im, const scalp_params_t* p, const Views& v, int 
 int enq_iterations(const Img& im, const scalp_params_t* p, const Views& v, float* centers,
                    int* endpoints, int* labels, int* counts, hipStream_t s, int R,
                    long long clear_n) {
-    const Tuning t = tuning_of(p);
+    const Tuning t = grid_tuning_of(p);
     for (int it = 0; it < p->iterations; ++it) {
         int e = p->assign_mode == SCALP_ASSIGN_WINDOW
                     ? enq_window_pass(im, p, v, R, centers, endpoints, labels, clear_n, it == 0, s)
@@ -357,7 +368,7 @@ int scalp_assign(const scalp_grid_t* g, const scalp_params_t* p, const float* la
                                        s));
     else
         CHECK_HIP(launch_assign(img_of(g, p, 0, 0), v.packed, centers, endpoints, labels, v.acc,
-                                v.ctrl, p->lambda, false, tuning_of(p), s));
+                                v.ctrl, p->lambda, false, grid_tuning_of(p), s));
     return SCALP_OK;
 }
 
@@ -395,7 +406,7 @@ int scalp_assign_accumulate(const scalp_grid_t* g, const scalp_params_t* p, cons
                                   labels, clear_words(L), true, (hipStream_t)stream));
     else
         CHECK_HIP(launch_assign(img_of(g, p, 0, 0), v.packed, centers, endpoints, labels, v.acc,
-                                v.ctrl, p->lambda, true, tuning_of(p), (hipStream_t)stream));
+                                v.ctrl, p->lambda, true, grid_tuning_of(p), (hipStream_t)stream));
     return SCALP_OK;
 }
 
@@ -562,7 +573,7 @@ int enq_batched(const scalp_batch_desc_t* d, int n, const scalp_params_t* p, con
     if (e == hipSuccess)
         e = launch_finalize_batched(imgs, starts, n, (int)BL.K, centers, endpoints, counts, v.acc,
                                     labels, v.ctrl, v.plist, false, s);
-    const Tuning t = tuning_of(p);
+    const Tuning t = grid_tuning_of(p);
     long long max_block = 0;
     for (int i = 0; i < n; ++i)
         max_block = std::max(max_block, block_pixels(d[i].grid.width, d[i].grid.height,
@@ -600,7 +611,7 @@ int scalp_run_batched(const scalp_batch_desc_t* descs, int32_t n, const scalp_pa
     if (!p->reuse_prepared && !pack_inputs_ok(p, lab, contour)) return SCALP_ERR_ARG;
     if (!ws || ws_bytes < BL.total) return SCALP_ERR_WORKSPACE;
     library_init();
-    const int grid = persistent_grid(tuning_of(p));
+    const int grid = persistent_grid(grid_tuning_of(p));
     if (grid < 1) return SCALP_ERR_HIP;
     CHECK_HIP(enq_batched(descs, n, p, lab, contour, centers, endpoints, labels, counts, ws, BL,
                           grid, (hipStream_t)stream));
@@ -619,7 +630,7 @@ int scalp_batched_graph_create(const scalp_batch_desc_t* descs, int32_t n, const
     if (!ws || ws_bytes < BL.total) return SCALP_ERR_WORKSPACE;
     library_init();
     // the occupancy query runs before the capture
-    const int grid = persistent_grid(tuning_of(p));
+    const int grid = persistent_grid(grid_tuning_of(p));
     if (grid < 1) return SCALP_ERR_HIP;
     return capture(out, [&](hipStream_t s) {
         return enq_batched(descs, n, p, lab, contour, centers, endpoints, labels, counts, ws, BL,

@@ -16,6 +16,18 @@ __device__ __forceinline__ int cell_lo(int idx, int len, int n) {
     return (int)(((long long)idx * len + n - 1) / n);
 }
 
+__device__ __forceinline__ int fdiv(int v, const FastDiv& f) {
+    if (f.m) return (int)__umulhi((unsigned)v, f.m);      // uniform
+    return f.d == 1u ? v : (int)((unsigned)v / f.d);
+}
+
+// cell_lo by f = the image's FastDiv for n cells over len pixels.
+__device__ __forceinline__ int cell_lo(int idx, int len, int n, const FastDiv& f) {
+    if (f.m)                                              // uniform
+        return (int)__umulhi((unsigned)idx * (unsigned)len + (unsigned)(n - 1), f.m);
+    return cell_lo(idx, len, n);
+}
+
 // Grid cell of coordinate c along an axis of `len` pixels cut into n cells:
 // floor(c * n / len), in 32 bits when len < 2^16.
 __device__ __forceinline__ int cell_of(int c, int n, int len) {
@@ -140,11 +152,11 @@ __device__ __forceinline__ void walk_path(const float4* __restrict__ base, int i
 // the window for every n up to 1094.  Longer paths take the correctly
 // rounded double quotient, rounded up.
 __device__ __forceinline__ unsigned step_increment(int am, int n) {
-    if (am == n) return 0xffffffffu;
     if (n < 1023) {
         const float sf = (float)am * __builtin_amdgcn_rcpf((float)n);
-        return (unsigned)(sf * 4294967296.0f) + 1025u;
+        return __builtin_elementwise_add_sat((unsigned)(sf * 4294967296.0f), 1025u);
     }
+    if (am == n) return 0xffffffffu;
     return (unsigned)ceil((double)am * 4294967296.0 / (double)n);
 }
 
@@ -215,6 +227,102 @@ __device__ __forceinline__ void fill_table_cols(float2* tab, const float4* __res
         tab[e] = make_float2(colour_dist(f, l, a, b), f.w);
     }
 }
+
+// The steps of a path from (dx, dy): major and diagonal index strides and the
+// carry-counting increment (see walk_table), for strides sx, sy of one pixel.
+struct PathStep {
+    int n, smaj, sdiag;
+    unsigned F;
+};
+
+__device__ __forceinline__ PathStep path_step(int dx, int dy, int sx, int sy) {
+    const int adx = dx < 0 ? -dx : dx;
+    const int ady = dy < 0 ? -dy : dy;
+    PathStep s;
+    s.n = max(adx, ady);
+    const int stx = dx < 0 ? -sx : sx, sty = dy < 0 ? -sy : sy;
+    s.smaj = adx >= ady ? stx : sty;
+    s.sdiag = stx + sty;
+    s.F = step_increment(min(adx, ady), s.n);
+    return s;
+}
+
+#define SCALP_STEP(off)                                           \
+    do {                                                          \
+        const bool c_ = __builtin_add_overflow(acc, s.F, &acc);   \
+        off += c_ ? s.sdiag : s.smaj;                             \
+    } while (0)
+#define SCALP_ACC(f)                                              \
+    do {                                                          \
+        sc = sc + colour_dist(f, l, a, b);                        \
+        sw = sw + (f).w;                                          \
+    } while (0)
+
+// When a walk may stop: from the sums so far, lo = fl(fl(fl(a0 + f sc) fl(1 +
+// g sw)) + dsp) with f = (1 - lambda) / |P|, g = gamma / |P| (approximate) and
+// a0 = lambda dcp is Eq. (3)'s D of the path cut short.  Every summand
+// of D is >= 0, so D is at least the exact value of lo, and lo is within 2^-20
+// of that (a dozen roundings and one reciprocal good to an ulp): lo > thr =
+// best (1 + 2^-16) proves D > best.  thr is at least 2^-70, far above any
+// absolute error that underflow can leave, and walks are never cut where gamma
+// exceeds 2^40 (which could raise such an error above it).
+struct Cut {
+    bool on;               // uniform
+    float a0, f, g, dsp, thr;
+};
+
+__device__ __forceinline__ bool cut_now(const Cut& c, float sc, float sw) {
+    return (c.a0 + c.f * sc) * (1.0f + c.g * sw) + c.dsp > c.thr;
+}
+
+// Samples i = 1 .. n (the endpoint) of the path s over the packed image, at
+// 32-bit byte offsets from a uniform base (images of up to 2^28 pixels, paths
+// of up to 46340 steps), from the texel at `off`: 13 VALU instructions per
+// sample, of which 8 are the colour distance.  Four samples per trip, their
+// loads in flight together.  A walk that is cut returns an infinite sc.
+__device__ __forceinline__ void walk_near(const float4* __restrict__ img, unsigned off,
+                                          const PathStep& s, float l, float a, float b,
+                                          const Cut& cut, float& sc, float& sw) {
+    unsigned acc = 0x80000000u;
+    const char* q = reinterpret_cast<const char*>(img);
+#define SCALP_LOAD() (*reinterpret_cast<const float4*>(q + off))
+    unsigned trips = (unsigned)s.n >> 2;
+    while (!__builtin_sub_overflow(trips, 1u, &trips)) {
+        SCALP_STEP(off);
+        const float4 fa = SCALP_LOAD();
+        SCALP_STEP(off);
+        const float4 fb = SCALP_LOAD();
+        SCALP_STEP(off);
+        const float4 fc = SCALP_LOAD();
+        SCALP_STEP(off);
+        const float4 fd = SCALP_LOAD();
+        SCALP_ACC(fa);
+        SCALP_ACC(fb);
+        SCALP_ACC(fc);
+        SCALP_ACC(fd);
+        asm volatile("" : "+v"(acc));
+        if (cut.on && cut_now(cut, sc, sw)) {
+            sc = INFINITY;
+            return;
+        }
+    }
+    if (s.n & 2) {
+        SCALP_STEP(off);
+        const float4 fa = SCALP_LOAD();
+        SCALP_STEP(off);
+        const float4 fb = SCALP_LOAD();
+        SCALP_ACC(fa);
+        SCALP_ACC(fb);
+    }
+    if (s.n & 1) {
+        SCALP_STEP(off);
+        const float4 fa = SCALP_LOAD();
+        SCALP_ACC(fa);
+    }
+#undef SCALP_LOAD
+}
+#undef SCALP_STEP
+#undef SCALP_ACC
 
 // The walk over a per-candidate LDS table of (colour distance, w) pairs: the
 // colour distance of a texel to the candidate does not depend on the pixel
@@ -329,7 +437,9 @@ __device__ __forceinline__ double path_recip(int n) { return kRecip.v[(n < 1023 
 // the IEEE division itself.
 __device__ __forceinline__ void div_path_len(float a, float b, int n, double inv, float& qa,
                                              float& qb) {
-    const bool fast = n < 1024 && !(a > 0.0f && a < 0x1p-100f) && !(b > 0.0f && b < 0x1p-100f);
+    // tiny operands: bits in [1, 2^-100), i.e. bits - 1 below those of 2^-100 - 1
+    const unsigned ta = __float_as_uint(a) - 1u, tb = __float_as_uint(b) - 1u;
+    const bool fast = n < 1024 && min(ta, tb) >= __float_as_uint(0x1p-100f) - 1u;
     if (fast) {
         qa = (float)((double)a * inv);
         qb = (float)((double)b * inv);
@@ -355,20 +465,23 @@ __device__ __forceinline__ int xcd_remap(int b, int G) {
     return x < rem ? x * (q + 1) + slot : rem * (q + 1) + (x - rem) * q + slot;
 }
 
-// Cell at position i of the cell order of the grid assignment: column
-// strips ceil(nx / strips) cells wide (the last one narrower), row-major
-// within a strip.  A bijection of [0, nx ny); strips = 1 is row-major order.
-__device__ __forceinline__ int cell_in_strips(int i, int nx, int ny, int strips) {
-    const int tw = (nx + strips - 1) / strips;
-    const int s = i / (tw * ny);
+// Cell (row ci, column cj) at position i of the cell order of the grid
+// assignment: column strips ceil(nx / strips) cells wide (the last one
+// narrower), row-major within a strip.  A bijection of [0, nx ny); strips = 1
+// is row-major order.
+__device__ __forceinline__ void cell_in_strips(int i, const Img& im, int& ci, int& cj) {
+    const int tw = (int)im.dcol.d;
+    const int s = fdiv(i, im.dstrip);
     const int x0 = s * tw;
-    const int w = min(tw, nx - x0);
-    const int l = i - s * tw * ny;
-    const int r = l / w;
-    return r * nx + x0 + (l - r * w);
+    const int l = i - s * tw * im.ny;
+    const bool last = im.nx - x0 < tw;
+    const int w = last ? im.nx - x0 : tw;
+    ci = last ? fdiv(l, im.dlast) : fdiv(l, im.dcol);
+    cj = x0 + (l - ci * w);
 }
 
-__device__ __forceinline__ int find_image(const int* start, int n, int v) {
+template <typename Table>
+__device__ __forceinline__ int find_image(Table start, int n, int v) {
     int lo = 0, hi = n - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -398,6 +511,52 @@ __device__ __forceinline__ void cell_pixel(int t, int cw, int ch, int& x, int& y
     }
     y = (s & 1) ? (ch - 1 - row) : row;
     x = col;
+}
+
+// cell_pixel with its two divisions, by numbers uniform over the work item,
+// as high multiplications (FastDiv; `fast` says that both are exact over the
+// cell: t < cw ch against 8 ch, and against the last strip's 2 to 7 columns).
+struct PixelMap {
+    int cw, ch, per, fullpx;
+    unsigned mper, mwr;
+    bool fast;
+};
+
+// ceil(2^32 / d) for a last strip of d = 2 .. 7 columns.
+__constant__ const unsigned kLastStrip[8] = {0u, 0u, 0x80000000u, 0x55555556u, 0x40000000u,
+                                             0x33333334u, 0x2aaaaaabu, 0x24924925u};
+
+__device__ __forceinline__ PixelMap pixel_map(const Img& im, int cw, int ch) {
+    PixelMap p;
+    p.cw = cw;
+    p.ch = ch;
+    p.per = 8 * ch;
+    p.fullpx = (cw >> 3) * p.per;
+    p.mper = ch == (int)(im.dper[0].d >> 3) ? im.dper[0].m : im.dper[1].m;
+    p.mwr = kLastStrip[cw & 7];
+    p.fast = p.mper != 0u;
+    return p;
+}
+
+__device__ __forceinline__ void pixel_at(const PixelMap& p, int t, int& x, int& y) {
+    if (!p.fast) {                                 // uniform
+        cell_pixel(t, p.cw, p.ch, x, y);
+        return;
+    }
+    int s, row;
+    if (t < p.fullpx) {
+        s = (int)__umulhi((unsigned)t, p.mper);
+        const int r = t - s * p.per;
+        row = r >> 3;
+        x = 8 * s + (r & 7);
+    } else {
+        const int wr = p.cw & 7;
+        const int r = t - p.fullpx;
+        row = wr > 1 ? (int)__umulhi((unsigned)r, p.mwr) : r;
+        s = p.cw >> 3;
+        x = 8 * s + (r - row * wr);
+    }
+    y = (s & 1) ? (p.ch - 1 - row) : row;
 }
 
 // Strip (8-column band) of cell pixel t, in the order of cell_pixel.

@@ -34,6 +34,21 @@ enum Ctrl : int {
 constexpr int kGradSlots = 32, kGradStride = 16;
 constexpr int kGradBytes = kGradSlots * kGradStride * 8;
 
+// Division of numbers below a known limit by an invariant d, as one high
+// multiplication: floor(v / d) = floor(v m / 2^32) with m = ceil(2^32 / d)
+// whenever v (m d - 2^32) < 2^32, hence for every v with v d < 2^32; m = 0
+// (d = 1, or a limit beyond that): the division itself.
+struct FastDiv {
+    unsigned m, d;
+};
+
+inline FastDiv fast_div(long long d, long long limit) {
+    FastDiv f;
+    f.d = (unsigned)d;
+    f.m = d > 1 && limit < (1LL << 32) / d ? (unsigned)((0x100000000LL + d - 1) / d) : 0u;
+    return f;
+}
+
 // One image as the kernels see it.
 struct Img {
     int W, H, nx, ny;
@@ -45,7 +60,14 @@ struct Img {
     int rad;          // R = r rounded to whole pixels (the window form's half-width)
     int prune;        // 1: skip the walks that the exact lower bound of D rules out
     int strips;       // column strips of the grid assignment's cell order (see cell_in_strips)
+    int far;          // 1: byte offsets of texels need more than 32 bits
+    FastDiv dnx, dny;               // cell boundaries: x ny / H and x nx / W
+    FastDiv dspl;                   // work item -> cell
+    FastDiv dstrip, dcol, dlast;    // cell order: strips, columns of a strip, of the last strip
+    FastDiv dper[2];                // 8 x the two cell heights: 8-column strips of a cell
 };
+// Fills the derived fields above from W, H, nx, ny, spl and strips.
+void finish_img(Img& im);
 
 // An assignment work item has at most as many pixels as its workgroup has
 // lanes (one pixel per lane): cells larger than that are split into several
@@ -54,15 +76,14 @@ constexpr int kMinAssignWG = 256;
 
 struct Tuning {
     int wg;           // workgroup size of the assignment kernel (256, 512 or 1024)
-    int lds_pixels;   // LDS table budget in 16-byte units
+    int lds_pixels;   // LDS table budget in 16-byte units (window form)
     int blocks_per_cu = 0;   // persistent launch: workgroups per CU (0: as many as fit)
-    int voted = 0;           // 1: voted per-candidate tables (one buffer, two barriers)
 };
 
 int default_lds_pixels();
-// LDS budget of the assignment kernels in 16-byte units (two 8-byte tables of
-// this many entries for the grid form; one table of twice as many for the
-// window form): 152 KiB of the 160 KiB of a gfx950 CU.
+// LDS budget of the table-walking kernels in 16-byte units (the window form's
+// one table of twice as many 8-byte entries; the soft forward's two tables):
+// 152 KiB of the 160 KiB of a gfx950 CU.
 constexpr int kMaxLdsPixels = 9728;
 
 // Raises the per-kernel dynamic LDS limit of the assignment kernels (once per

@@ -5,17 +5,15 @@
 //   k_init_cells      Algorithm 1 initialisation: labels = grid cell, per-cell
 //                     integer sums (Sec. II-A regular grid).
 //   k_assign*         Algorithm 1 assignment: one workgroup per (cell, slice)
-//                     work item, one pixel per lane.  For each of the <= 9
-//                     candidates in turn the workgroup writes an LDS table of
-//                     (colour distance, w) over the rectangle of the item and
-//                     the candidate's endpoint; every lane then walks the
-//                     discrete line (Sec. II-B) from its pixel to the endpoint
-//                     over the table, accumulating Eq. (1)'s colour term and
-//                     Eq. (2)'s contour term in a fixed FP32 order, forms D of
-//                     Eq. (3) and keeps the first strict minimum.  A lane
-//                     skips the walk of a candidate whose exact lower bound
-//                     on D (colour at the pixel and spatial term only) cannot
-//                     win, which leaves the labels unchanged.  With ACCUM
+//                     work item, one pixel per lane.  Each pixel orders its
+//                     <= 9 candidates by an exact lower bound of their D
+//                     (colour at the pixel and spatial term only), walks the
+//                     discrete line (Sec. II-B) to the endpoint of the first,
+//                     accumulating Eq. (1)'s colour term and Eq. (2)'s contour
+//                     term in a fixed FP32 order, and forms D of Eq. (3); the
+//                     candidates whose bound does not exceed that D are listed
+//                     and walked by full waves.  The first strict minimum
+//                     wins, as if every candidate had been walked.  With ACCUM
 //                     the update's sums are fused in: each pixel can only
 //                     choose among the cell's 9 candidates, so they reduce
 //                     into 9 LDS bins and leave the workgroup as at most 54
@@ -37,17 +35,6 @@ namespace {
 
 using namespace dev;
 
-
-struct Cand {
-    int k;            // superpixel index within the image, -1 outside the grid
-    float l, a, b, x, y;
-    int cx, cy;       // path endpoint
-    float dcc, wc;    // colour distance and w of the endpoint sample
-    int tx0, ty0, tw, th;   // its LDS table: origin, row pitch, rows; tw == 0: paths read global memory
-    int rpp;                // rows per pass of the column-wise fill (WG / tw, 0 when tw > WG)
-    unsigned mag;           // ceil(2^24 / tw): lane tid's first row is tid * mag >> 24
-};
-
 // Copies of the update bins: the lanes of a wave mostly pick the same
 // candidate, and 64-bit LDS atomics on one word serialise, so lane t adds to
 // copy (t ^ (t >> 3)) mod kBinCopies: every row and every column of the
@@ -55,324 +42,338 @@ struct Cand {
 // wave share one word.
 constexpr int kBinCopies = 8;
 
-// Per work item: the candidates and the update bins, [slot * 6 + sum][copy].
-struct CellShared {
-    Cand cand[9];
-    int box[9][4];    // voted tables: per slot, min x, min y, max x, max y of the waves that walk it
+// Per work item, by pixel (lane of the first pass): its coordinates and its
+// smallest (FP32 bits of D) << 32 | slot so far; the (pixel, slot) pairs of
+// the second pass, and their number; and the update bins, [slot * 6 + sum][copy].
+template <int WG>
+struct ItemShared {
     unsigned long long bins[9 * 6][kBinCopies];
+    unsigned long long win[WG];
+    int2 xy[WG];
+    unsigned short list[8 * WG];
+    int pairs;
 };
+
+constexpr unsigned kInfBits = 0x7f800000u;
+
+// The candidates' centres as the bounds read them: the item's 9 superpixels
+// are uniform over the workgroup, so their values come through the scalar
+// cache into scalar registers (nothing writes centres or endpoints while an
+// assignment pass runs).
+typedef const __attribute__((address_space(4))) float* ConstF;
+typedef const __attribute__((address_space(4))) int* ConstI;
+
+// A descriptor read through the scalar cache, word by word (p uniform).
+__device__ __forceinline__ Img load_const(const Img* p) {
+    static_assert(sizeof(Img) % 4 == 0, "words");
+    union {
+        Img im;
+        int w[sizeof(Img) / 4];
+    } u;
+    const ConstI c = (ConstI)(uintptr_t)p;
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(Img) / 4; ++i) u.w[i] = __builtin_amdgcn_readfirstlane(c[i]);
+    return u.im;
+}
+
+// Rows and columns of the 3x3 candidates of a cell, clamped into the grid (a
+// clamped one repeats another candidate of the cell), and which are inside
+// (bit j: slot j).
+struct Neighbours {
+    int row[3], col[3];   // superpixel index of (row, column 0); column
+    unsigned inside;
+};
+
+__device__ __forceinline__ Neighbours neighbours_of(const Img& im, int ci, int cj) {
+    Neighbours g;
+    g.row[0] = max(ci - 1, 0) * im.nx;
+    g.row[1] = ci * im.nx;
+    g.row[2] = min(ci + 1, im.ny - 1) * im.nx;
+    g.col[0] = max(cj - 1, 0);
+    g.col[1] = cj;
+    g.col[2] = min(cj + 1, im.nx - 1);
+    g.inside = 0x1ffu;
+    if (ci == 0) g.inside &= ~0x007u;
+    if (ci == im.ny - 1) g.inside &= ~0x1c0u;
+    if (cj == 0) g.inside &= ~0x049u;
+    if (cj == im.nx - 1) g.inside &= ~0x124u;
+    return g;
+}
+
+// Keys of the 9 candidates of a pixel with texel f: the upper 28 bits of
+// LB = fl(fl(lambda dcp) + fl(ds spw)), which is >= 0, with the slot in the
+// low 4 bits; all ones for a slot outside the grid.  A key at or above
+// kInfBits belongs to no walk: LB is infinite or NaN, and so is D.  The
+// centres are read one row of candidates at a time (the barrier keeps the
+// scheduler from holding all 45 scalars at once, which spilled).
+__device__ __forceinline__ void bound_keys(const Img& im, const Neighbours& g, ConstF cen,
+                                           float4 f, int x, int y, float lambda,
+                                           unsigned (&key)[9]) {
+    const float fx = (float)x, fy = (float)y;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        ConstF row = cen + 5LL * __builtin_amdgcn_readfirstlane(g.row[i]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int jj = 0; jj < 3; ++jj) {
+            const int j = 3 * i + jj;
+            ConstF c = row + 5 * __builtin_amdgcn_readfirstlane(g.col[jj]);
+            const float ex = fx - c[3], ey = fy - c[4];
+            const float lb = lambda * colour_dist(f, c[0], c[1], c[2]) +
+                             (ex * ex + ey * ey) * im.spw;
+            const unsigned tag = (g.inside >> j) & 1u ? (unsigned)j : 0xffffffffu;   // uniform
+            key[j] = (__float_as_uint(lb) & ~15u) | tag;
+        }
+    }
+}
+
+// First 64-pixel chunk of slice i of a cell of `chunks` chunks.
+__device__ __forceinline__ int slice_chunk(int chunks, int i, const Img& im) {
+    const long long v = (long long)chunks * i;
+    return v < (1LL << 31) ? fdiv((int)v, im.dspl) : (int)(v / im.spl);
+}
+
+// The smallest key above `cur` (0xffffffff: the smallest of all), all ones
+// when there is none; at least kInfBits when no candidate with a finite bound
+// is left.
+__device__ __forceinline__ unsigned next_key(const unsigned (&key)[9], unsigned cur) {
+    const unsigned c1 = cur + 1u;          // keys up to cur wrap to [2^32 - c1, 2^32)
+    const unsigned a = min(min(key[0] - c1, key[1] - c1), key[2] - c1);
+    const unsigned b = min(min(key[3] - c1, key[4] - c1), key[5] - c1);
+    const unsigned c = min(min(key[6] - c1, key[7] - c1), key[8] - c1);
+    unsigned next;
+    return __builtin_add_overflow(min(min(a, b), c), c1, &next) ? 0xffffffffu : next;
+}
 
 // Work item (cell, slice): pixels [t0, t1) of the cell in cell_pixel order,
 // one per lane.  The cell's ceil(P / 64) 64-pixel chunks are split evenly
 // over its spl slices (spl is chosen on the host so that no slice has more
 // than WG pixels), and every wave keeps an 8x8 block.
 //
-// Candidates are taken one at a time, the pixel's own cell first, then the
-// four edge neighbours, then the corners; the winner is the smallest
-// (D, slot) pair, which is the first strict minimum in ascending slot (hence
-// ascending k) whatever the visiting order.  A lane skips a candidate whose
-// lower bound fl(fl(lambda dcp) + fl(ds spw)) cannot beat the current best
-// pair: with lambda in [0, 1], gamma >= 0 and every colour distance and w
-// non-negative, A >= fl(lambda dcp) and B >= 1 in Eqs. (1)-(2), so
-// D = fl(fl(A B) + fl(ds spw)) is at least that bound (FP32 rounding is
-// monotone) and the skipped D could not have been chosen.  The labels are
-// those of evaluating every candidate; a wave skips the walk when all of its
-// lanes do (a NaN bound never skips).
-// For candidate j the workgroup first writes, for every texel q of the
-// rectangle spanned by the item's pixels and j's endpoint (every path to j
-// lies inside it), the pair (d_c(q, j), w_q) into an LDS table; lanes then
-// walk their paths over the table, two adds per sample.  Two tables
-// alternate, so one barrier per candidate separates writing a table from
-// reading it and reading it from overwriting it.  A candidate whose
-// rectangle exceeds the budget (cap entries) walks its paths from global
-// memory, computing d_c per sample.  All of these give the same FP32 values
-// in the same order as the plain definition.
-template <int WG, bool ACCUM, bool VOTED>
-__device__ __forceinline__ void process_cell(const Img& im, int cell, int slice,
+// Every pixel visits its candidates in ascending order of a lower bound of
+// their D and stops at the first bound above its best D: with lambda in
+// [0, 1], gamma >= 0 and every colour distance and w non-negative,
+// A >= fl(lambda dcp) and B >= 1 in Eqs. (1)-(2), so D = fl(fl(A B) +
+// fl(ds spw)) is at least LB = fl(fl(lambda dcp) + fl(ds spw)) (FP32 rounding
+// is monotone), and the candidates left out could not have been chosen.  The
+// winner is the smallest (D, slot) pair, which is the first strict minimum in
+// ascending slot (hence ascending k) whatever the visiting order, and a
+// candidate whose bound equals the best D is walked: the labels are those of
+// evaluating every candidate.  An infinite or NaN bound makes D infinite or
+// NaN, which never wins.
+//
+// The first candidate decides 80 % of the pixels; the others whose bound does
+// not exceed its D, 0.2 per pixel and most of them losers, are listed and
+// walked by full waves of (pixel, slot) pairs, whose results meet in a 64-bit
+// minimum per pixel.  A walk of that second pass stops as soon as its partial
+// sums prove that D exceeds the pixel's first one (Cut).
+//
+// What bounds it: VALU issue.  33.4 M wave instructions per launch at
+// 1920x1080, k = 2000 (the bounds 180 of a wave's 1023, the first walk 300,
+// its evaluation 150, the second pass 200), 0.93 issued per CU-clock; 0.070
+// ms per launch.  Tables of (d_c, w) per candidate in LDS, all nine taken in
+// turn by the whole workgroup behind a barrier each, made a sample cost 5
+// instructions instead of 13 but walked 85 samples per pixel in 64-lane slots
+// instead of 33, filled 20 table entries per pixel and waited at the barriers:
+// 51.5 M instructions, 0.72 per CU-clock, 0.117 ms.  The texels are read
+// through L1 and L2: a box of them staged in LDS per item left two items per
+// CU and was slower (0.132 ms against 0.105 with the rest equal), as was a
+// counting sort of the first walks by length (18 instead of 23 slots per
+// pixel, but 100 more instructions and two more barriers).
+template <int WG, bool ACCUM>
+__device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int slice,
                                              const float4* __restrict__ packed,
                                              const float* __restrict__ centres,
                                              const int* __restrict__ endpoints,
                                              int* __restrict__ labels,
-                                             long long* __restrict__ acc, float lambda, int cap,
-                                             float2* lds, CellShared& sh) {
+                                             long long* __restrict__ acc, float lambda,
+                                             ItemShared<WG>& sh) {
     const int tid = threadIdx.x;
-    const int W = im.W, H = im.H, nx = im.nx, ny = im.ny;
-    const int ci = cell / nx, cj = cell - ci * nx;
-    const int x0 = cell_lo(cj, W, nx), x1 = cell_lo(cj + 1, W, nx);
-    const int y0 = cell_lo(ci, H, ny), y1 = cell_lo(ci + 1, H, ny);
-    const float4* __restrict__ img = packed + im.pix;
+    const int W = im.W, H = im.H;
+    const int x0 = cell_lo(cj, W, im.nx, im.dnx), x1 = cell_lo(cj + 1, W, im.nx, im.dnx);
+    const int y0 = cell_lo(ci, H, im.ny, im.dny), y1 = cell_lo(ci + 1, H, im.ny, im.dny);
     const int cw = x1 - x0, ch = y1 - y0;
     const int P = cw * ch;
-    const int spl = im.spl;
-    const int chunks = (P + 63) >> 6;
-    const int t0 = 64 * (int)((long long)chunks * slice / spl);
-    const int t1 = min(P, 64 * (int)((long long)chunks * (slice + 1) / spl));
-    // columns of the item's pixels: the 8-column strips its range touches
-    int ix0 = x0, ix1 = x1;
-    if (spl > 1 && t1 > t0) {
-        ix0 = x0 + 8 * strip_of(t0, cw, ch);
-        ix1 = min(x1, x0 + 8 * strip_of(t1 - 1, cw, ch) + 8);
+    int t0 = 0, t1 = P;
+    if (im.spl > 1) {                              // uniform
+        const int chunks = (P + 63) >> 6;
+        t0 = 64 * slice_chunk(chunks, slice, im);
+        t1 = min(P, 64 * slice_chunk(chunks, slice + 1, im));
+        if (t1 <= t0) return;                      // an empty slice
     }
-
-    if (tid < 9) {
-        Cand c;
-        const int ii = ci + tid / 3 - 1, jj = cj + tid % 3 - 1;
-        c.tw = 0;
-        c.tx0 = c.ty0 = c.th = 0;
-        c.rpp = 0;
-        c.mag = 0u;
-        if (ii >= 0 && ii < ny && jj >= 0 && jj < nx) {
-            const int k = ii * nx + jj;
-            const float* ck = centres + 5LL * (im.sp + k);
-            c.k = k;
-            c.l = ck[0]; c.a = ck[1]; c.b = ck[2]; c.x = ck[3]; c.y = ck[4];
-            // endpoints outside the image are clamped into it
-            c.cx = min(max(endpoints[2LL * (im.sp + k)], 0), W - 1);
-            c.cy = min(max(endpoints[2LL * (im.sp + k) + 1], 0), H - 1);
-            const float4 fc = img[(long long)c.cy * W + c.cx];
-            c.dcc = colour_dist(fc, c.l, c.a, c.b);
-            c.wc = fc.w;
-            const int ax0 = min(ix0, c.cx), ax1 = max(ix1, c.cx + 1);
-            const int ay0 = min(y0, c.cy), ay1 = max(y1, c.cy + 1);
-            // row pitch = 8 (mod 16) entries: the 8 rows of a wave's 8x8
-            // block then start on 4 different quarters of the LDS banks
-            const int pitch = (ax1 - ax0) + ((24 - (ax1 - ax0) % 16) % 16);
-            if ((long long)pitch * (ay1 - ay0) <= cap) {
-                c.tx0 = ax0; c.ty0 = ay0; c.tw = pitch; c.th = ay1 - ay0;
-                c.rpp = WG / pitch;
-                c.mag = (0x1000000u + (unsigned)pitch - 1u) / (unsigned)pitch;
+    const float4* __restrict__ img = packed + im.pix;
+    const int sp = __builtin_amdgcn_readfirstlane(im.sp);
+    const float* __restrict__ cen = centres + 5LL * sp;
+    const int* __restrict__ end = endpoints + 2LL * sp;
+    const Neighbours nb = neighbours_of(im, ci, cj);
+    const float oml = 1.0f - lambda;
+    const float gamma = im.gamma, spw = im.spw;
+    // candidate slot j -> superpixel
+    const int k0 = (ci - 1) * im.nx + cj - 1;
+    auto superpixel = [&](int j) -> int {
+        const int di = (j * 11) >> 5;              // j / 3 for j <= 8
+        return k0 + di * im.nx + (j - 3 * di);
+    };
+    // D of Eqs. (1)-(3) of pixel (px, py) to superpixel k, or an infinite
+    // value once it is known to exceed `best` (cut)
+    auto distance = [&](int k, int px, int py, float best, bool cut_on) -> float {
+        const float* ck = cen + 5 * k;
+        const float l = ck[0], a = ck[1], b = ck[2];
+        const float ax = (float)px - ck[3], ay = (float)py - ck[4];
+        // endpoints outside the image are clamped into it
+        const int cx = min(max(end[2 * k], 0), W - 1), cy = min(max(end[2 * k + 1], 0), H - 1);
+        const int p = py * W + px;
+        const float4 fp = img[p];
+        const int dx = cx - px, dy = cy - py;
+        const int n = max(abs(dx), abs(dy));
+        const double inv = path_recip(n);
+        const float dsp = (ax * ax + ay * ay) * spw;
+        const float dcp = colour_dist(fp, l, a, b);
+        float sc = dcp, sw = fp.w;                 // sample i = 0 is p itself
+        if (!im.far && W + H < 46340) {            // uniform
+            Cut cut;
+            cut.on = cut_on;
+            if (cut_on) {
+                const float rnp = __builtin_amdgcn_rcpf((float)(n + 1));
+                cut.a0 = lambda * dcp;
+                cut.f = oml * rnp;
+                cut.g = gamma * rnp;
+                cut.dsp = dsp;
+                cut.thr = fmaxf(best * (1.0f + 0x1p-16f), 0x1p-70f);
             }
+            walk_near(img, 16u * (unsigned)p, path_step(dx, dy, 16, 16 * W), l, a, b, cut, sc, sw);
         } else {
-            c.k = -1;
-            c.l = c.a = c.b = c.x = c.y = 0.0f;
-            c.cx = c.cy = 0;
-            c.dcc = c.wc = 0.0f;
+            walk_path(img, p, 1, W, dx, dy, l, a, b, sc, sw);
+            if (n > 0) {                           // sample i = n is the endpoint
+                const float4 fc = img[(long long)cy * W + cx];
+                sc = sc + colour_dist(fc, l, a, b);
+                sw = sw + fc.w;
+            }
         }
-        sh.cand[tid] = c;
-    }
-    if (VOTED && tid < 36) (&sh.box[0][0])[tid] = (tid & 2) ? INT_MIN : INT_MAX;
+        float qc, qw;                              // sc / |P|, sw / |P|
+        div_path_len(sc, sw, n, inv, qc, qw);
+        const float A = lambda * dcp + oml * qc;             // Eq. (1)
+        const float B = 1.0f + gamma * qw;                   // Eq. (2)
+        return A * B + dsp;                                  // Eq. (3)
+    };
+    // the label of pixel (px, py) and its share of the update's sums
+    auto settle = [&](int px, int py, int bestj) {
+        const int j = bestj < 0 ? 4 : bestj;       // no slot only with non-finite input
+        const long long p = (long long)py * W + px;
+        labels[im.pix + p] = superpixel(j);
+        if (ACCUM) {
+            const float4 f = img[p];
+            const int cp = (tid ^ (tid >> 3)) & (kBinCopies - 1);
+            unsigned long long(*bin)[kBinCopies] = sh.bins + 6 * j;
+            atomicAdd(&bin[0][cp], 1ULL);
+            atomicAdd(&bin[1][cp], (unsigned long long)px);
+            atomicAdd(&bin[2][cp], (unsigned long long)py);
+            atomicAdd(&bin[3][cp], (unsigned long long)to_fixed(f.x));
+            atomicAdd(&bin[4][cp], (unsigned long long)to_fixed(f.y));
+            atomicAdd(&bin[5][cp], (unsigned long long)to_fixed(f.z));
+        }
+    };
+
+    if (tid == 0) sh.pairs = 0;
     if (ACCUM) {
         for (int t = tid; t < 54 * kBinCopies; t += WG) (&sh.bins[0][0])[t] = 0ULL;
     }
     __syncthreads();
 
-    const float oml = 1.0f - lambda;
-    const float gamma = im.gamma, spw = im.spw;
-    const bool mine = tid < t1 - t0;               // this lane's pixel exists
-    int x = 0, y = 0;
+    // first pass: the candidate with the smallest bound; then every other one
+    // whose bound does not exceed that D is listed
+    const bool prune = im.prune != 0;
+    const bool mine = tid < t1 - t0;
+    bool again = false;
+    int px = 0, py = 0, bestj = -1;
     if (mine) {
-        cell_pixel(t0 + tid, cw, ch, x, y);
-        x += x0;
-        y += y0;
-    }
-    float best = INFINITY;
-    int bestj = -1;
-    int buf = 0;
-    // the pixel's own texel, for the lower bounds
-    const float4 fown = mine ? img[(long long)y * W + x] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    constexpr unsigned long long kOrder = 0x862075314ULL;   // slots 4, 1, 3, 5, 7, 0, 2, 6, 8
-    if constexpr (VOTED) {
-    // Voted tables: before each candidate's table is filled, the waves with
-    // a lane that walks it report the box of their pixels; the table covers
-    // that box and the endpoint, in one buffer of twice the entries (the
-    // vote's barrier already orders the previous candidate's walks before
-    // the fill), and is not filled at all when no lane walks.  Two barriers
-    // per candidate instead of one, in return for smaller fills and more
-    // tables within the budget (cells much larger than the workgroup).
-    const int wx0 = wave_min_i32(mine ? x : INT_MAX), wy0 = wave_min_i32(mine ? y : INT_MAX);
-    const int wx1 = wave_max_i32(mine ? x : INT_MIN), wy1 = wave_max_i32(mine ? y : INT_MIN);
-#pragma unroll 1
-    for (int t = 0; t < 9; ++t) {
-        const int j = (int)((kOrder >> (4 * t)) & 15ULL);
-        const int k = sh.cand[j].k;
-        if (k < 0) continue;                       // uniform
-        const float l = sh.cand[j].l, a = sh.cand[j].a, b = sh.cand[j].b;
-        const int cx = sh.cand[j].cx, cy = sh.cand[j].cy;
-        const float ccx = sh.cand[j].x, ccy = sh.cand[j].y;
-        const float ex = (float)x - ccx;
-        const float ey = (float)y - ccy;
-        const float ds = ex * ex + ey * ey;
-        const float lb = lambda * colour_dist(fown, l, a, b) + ds * spw;   // <= D
-        const bool walks = mine && !(im.prune && (lb > best || (lb == best && j > bestj)));
-        if (__ballot(walks) != 0ULL && (tid & 63) == 0) {
-            atomicMin(&sh.box[j][0], wx0);
-            atomicMin(&sh.box[j][1], wy0);
-            atomicMax(&sh.box[j][2], wx1);
-            atomicMax(&sh.box[j][3], wy1);
-        }
-        __syncthreads();   // the box is complete, and every wave is done with the table
-        const int bx0 = __builtin_amdgcn_readfirstlane(sh.box[j][0]);
-        const int bx1 = __builtin_amdgcn_readfirstlane(sh.box[j][2]);
-        if (bx0 > bx1) continue;                   // uniform: no lane of the item walks j
-        const int by0 = __builtin_amdgcn_readfirstlane(sh.box[j][1]);
-        const int by1 = __builtin_amdgcn_readfirstlane(sh.box[j][3]);
-        const int tx0 = min(bx0, cx), tx1 = max(bx1, cx) + 1;
-        const int ty0 = min(by0, cy), ty1 = max(by1, cy) + 1;
-        const int tw = (tx1 - tx0) + ((24 - (tx1 - tx0) % 16) % 16);
-        const bool staged = (long long)tw * (ty1 - ty0) <= 2LL * cap;   // uniform
-        if (staged) {
-            if (tw <= WG)                          // uniform
-                fill_table_cols<WG>(lds, img, W, tx0, ty0, tw, ty1 - ty0, WG / tw,
-                                    (0x1000000u + (unsigned)tw - 1u) / (unsigned)tw, l, a, b);
-            else
-                fill_table<WG>(lds, img, W, tx0, ty0, tw, tw * (ty1 - ty0), l, a, b);
-            __syncthreads();
-        }
-        if (walks) {
-            const float dcc = sh.cand[j].dcc, wc = sh.cand[j].wc;
-            const int dx = cx - x, dy = cy - y;
-            const int adx = dx < 0 ? -dx : dx, ady = dy < 0 ? -dy : dy;
-            const int n = adx > ady ? adx : ady;
-            const double inv = path_recip(n);
-            float dcp, sc, sw;
-            if (staged) {
-                const int lidx = (y - ty0) * tw + (x - tx0);
-                const float2 e0 = lds[lidx];
-                dcp = e0.x;
-                sc = dcp;                          // sample i = 0 is p itself
-                sw = e0.y;
-                walk_table(lds, lidx, tw, dx, dy, sc, sw);
-            } else {
-                const int p = y * W + x;
-                const float4 fp = img[p];
-                dcp = colour_dist(fp, l, a, b);
-                sc = dcp;
-                sw = fp.w;
-                walk_path(img, p, 1, W, dx, dy, l, a, b, sc, sw);
-            }
-            if (n > 0) {                           // sample i = n is the endpoint
-                sc = sc + dcc;
-                sw = sw + wc;
-            }
-            float qc, qw;                          // sc / |P|, sw / |P|
-            div_path_len(sc, sw, n, inv, qc, qw);
-            const float A = lambda * dcp + oml * qc;             // Eq. (1)
-            const float B = 1.0f + gamma * qw;                   // Eq. (2)
-            const float D = A * B + ds * spw;                    // Eq. (3)
-            if (D < best || (D == best && j < bestj)) {
+        pixel_at(pixel_map(im, cw, ch), t0 + tid, px, py);
+        px += x0;
+        py += y0;
+        unsigned key[9];
+        bound_keys(im, nb, (ConstF)(uintptr_t)cen, img[py * W + px], px, py, lambda, key);
+        unsigned nk = next_key(key, 0xffffffffu);
+        float best = INFINITY;
+        if (nk < kInfBits) {
+            const int j = (int)(nk & 15u);
+            const float D = distance(superpixel(j), px, py, best, false);
+            if (D < best) {
                 best = D;
                 bestj = j;
             }
         }
-    }
-    } else {
-#pragma unroll 1
-    for (int t = 0; t < 9; ++t) {
-        const int j = (int)((kOrder >> (4 * t)) & 15ULL);
-        const int k = sh.cand[j].k;
-        if (k < 0) continue;                       // uniform
-        const float l = sh.cand[j].l, a = sh.cand[j].a, b = sh.cand[j].b;
-        const int cx = sh.cand[j].cx, cy = sh.cand[j].cy;
-        const int tw = sh.cand[j].tw, tx0 = sh.cand[j].tx0, ty0 = sh.cand[j].ty0;
-        float2* tab = lds + (buf ? cap : 0);
-        if (tw > 0) {                              // uniform
-            const int rpp = sh.cand[j].rpp;
-            if (rpp > 0)                           // uniform
-                fill_table_cols<WG>(tab, img, W, tx0, ty0, tw, sh.cand[j].th, rpp,
-                                    sh.cand[j].mag, l, a, b);
-            else
-                fill_table<WG>(tab, img, W, tx0, ty0, tw, tw * sh.cand[j].th, l, a, b);
-            __syncthreads();
-            buf ^= 1;
+        while (nk < kInfBits) {
+            nk = next_key(key, nk);
+            const bool more = nk < kInfBits && !(prune && __uint_as_float(nk & ~15u) > best);
+            const unsigned long long m = __ballot(more);
+            if (m == 0ULL) break;                  // uniform over the lanes still here
+            int at = 0;
+            if (__ffsll((long long)m) - 1 == (tid & 63)) at = atomicAdd(&sh.pairs, __popcll(m));
+            at = __builtin_amdgcn_readlane(at, __ffsll((long long)m) - 1) +
+                 (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+            if (!more) break;
+            sh.list[at] = (unsigned short)(tid | ((nk & 15u) << 10));
+            again = true;
         }
-        const float ccx = sh.cand[j].x, ccy = sh.cand[j].y;
-        const float dcc = sh.cand[j].dcc, wc = sh.cand[j].wc;
-        const float ex = (float)x - ccx;
-        const float ey = (float)y - ccy;
-        const float ds = ex * ex + ey * ey;
-        const float lb = lambda * colour_dist(fown, l, a, b) + ds * spw;   // <= D
-        if (mine && !(im.prune && (lb > best || (lb == best && j > bestj)))) {
-            const int dx = cx - x, dy = cy - y;
-            const int adx = dx < 0 ? -dx : dx, ady = dy < 0 ? -dy : dy;
-            const int n = adx > ady ? adx : ady;
-            const double inv = path_recip(n);
-            float dcp, sc, sw;
-            if (tw > 0) {
-                const int lidx = (y - ty0) * tw + (x - tx0);
-                const float2 e0 = tab[lidx];
-                dcp = e0.x;
-                sc = dcp;                          // sample i = 0 is p itself
-                sw = e0.y;
-                walk_table(tab, lidx, tw, dx, dy, sc, sw);
-            } else {
-                const int p = y * W + x;
-                const float4 fp = img[p];
-                dcp = colour_dist(fp, l, a, b);
-                sc = dcp;
-                sw = fp.w;
-                walk_path(img, p, 1, W, dx, dy, l, a, b, sc, sw);
-            }
-            if (n > 0) {                           // sample i = n is the endpoint
-                sc = sc + dcc;
-                sw = sw + wc;
-            }
-            float qc, qw;                          // sc / |P|, sw / |P|
-            div_path_len(sc, sw, n, inv, qc, qw);
-            const float A = lambda * dcp + oml * qc;             // Eq. (1)
-            const float B = 1.0f + gamma * qw;                   // Eq. (2)
-            const float D = A * B + ds * spw;                    // Eq. (3)
-            if (D < best || (D == best && j < bestj)) {
-                best = D;
-                bestj = j;
-            }
+        if (again) {
+            sh.xy[tid] = make_int2(px, py);
+            sh.win[tid] = ((unsigned long long)__float_as_uint(best) << 32) | (unsigned)bestj;
+        } else {
+            settle(px, py, bestj);
         }
     }
+    __syncthreads();
+    // second pass: the listed pairs, by full waves
+    const int pairs = __builtin_amdgcn_readfirstlane(sh.pairs);
+    for (int i = tid; i < pairs; i += WG) {
+        const unsigned e = sh.list[i];
+        const int id = (int)(e & 1023u), j = (int)(e >> 10);
+        const int2 q = sh.xy[id];
+        const float best = __uint_as_float((unsigned)(sh.win[id] >> 32));
+        const float D = distance(superpixel(j), q.x, q.y, best, prune && gamma <= 0x1p40f);
+        if (D < INFINITY)
+            atomicMin(&sh.win[id], ((unsigned long long)__float_as_uint(D) << 32) | (unsigned)j);
     }
+    __syncthreads();
+    if (again) settle(px, py, (int)(unsigned)sh.win[tid]);
+    __syncthreads();
 
-    if (mine) {
-        const int p = y * W + x;
-        const int bj = bestj < 0 ? 4 : bestj;   // bestj < 0 only with non-finite input
-        labels[im.pix + p] = sh.cand[bj].k;
-        if (ACCUM) {
-            const float4 fp = img[p];
-            const int cp = (tid ^ (tid >> 3)) & (kBinCopies - 1);
-            unsigned long long(*bin)[kBinCopies] = sh.bins + 6 * bj;
-            atomicAdd(&bin[0][cp], 1ULL);
-            atomicAdd(&bin[1][cp], (unsigned long long)x);
-            atomicAdd(&bin[2][cp], (unsigned long long)y);
-            atomicAdd(&bin[3][cp], (unsigned long long)to_fixed(fp.x));
-            atomicAdd(&bin[4][cp], (unsigned long long)to_fixed(fp.y));
-            atomicAdd(&bin[5][cp], (unsigned long long)to_fixed(fp.z));
-        }
-    }
     if (ACCUM) {
-        __syncthreads();
         if (tid < 54) {
             const int j = tid / 6;
-            const int k = sh.cand[j].k;
             unsigned long long n = 0, v = 0;
             for (int c = 0; c < kBinCopies; ++c) {
                 n += sh.bins[6 * j][c];
                 v += sh.bins[tid][c];
             }
-            if (k >= 0 && n != 0ULL)
-                atomicAdd((unsigned long long*)(acc + kAccStride * (long long)(im.sp + k) +
+            if (n != 0ULL)
+                atomicAdd((unsigned long long*)(acc + kAccStride * (long long)(sp + superpixel(j)) +
                                                 (tid - 6 * j)),
                           v);
         }
     }
-    __syncthreads();   // shared state is reused by the next cell of a persistent workgroup
 }
 
-template <int WG, bool ACCUM, bool VOTED>
-__global__ __launch_bounds__(WG) void k_assign(Img im, const float4* __restrict__ packed,
+template <int WG, bool ACCUM>
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_assign(Img im, const float4* __restrict__ packed,
                                                const float* __restrict__ centres,
                                                const int* __restrict__ endpoints,
                                                int* __restrict__ labels,
                                                long long* __restrict__ acc, int* ctrl,
-                                               float lambda, int cap) {
-    extern __shared__ float2 tab_dyn[];
-    __shared__ CellShared sh;
+                                               float lambda) {
+    __shared__ ItemShared<WG> sh;
     if (ACCUM && blockIdx.x == 0 && threadIdx.x == 0) ctrl[kCtrlProjCount] = 0;
     const int item = xcd_remap(blockIdx.x, gridDim.x);
-    const int pos = item / im.spl;
-    process_cell<WG, ACCUM, VOTED>(im, cell_in_strips(pos, im.nx, im.ny, im.strips),
-                                   item - pos * im.spl, packed, centres, endpoints, labels, acc,
-                                   lambda, cap, tab_dyn, sh);
+    const int pos = fdiv(item, im.dspl);
+    int ci, cj;
+    cell_in_strips(pos, im, ci, cj);
+    process_cell<WG, ACCUM>(im, ci, cj, item - pos * im.spl, packed, centres, endpoints, labels,
+                            acc, lambda, sh);
 }
 
 // At most 64 VGPRs (8 waves per SIMD): two 1024-thread workgroups per CU.
-template <int WG, bool VOTED>
+template <int WG>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8)))
 void k_assign_persistent(const Img* __restrict__ imgs,
                                                           const int* __restrict__ item_start,
@@ -382,9 +383,8 @@ void k_assign_persistent(const Img* __restrict__ imgs,
                                                           const int* __restrict__ endpoints,
                                                           int* __restrict__ labels,
                                                           long long* __restrict__ acc, int* ctrl,
-                                                          float lambda, int cap) {
-    extern __shared__ float2 tab_dyn[];
-    __shared__ CellShared sh;
+                                                          float lambda) {
+    __shared__ ItemShared<WG> sh;
     __shared__ int item;
     if (blockIdx.x == 0 && threadIdx.x == 0) ctrl[kCtrlProjCount] = 0;
     // XCD x (workgroup b runs on XCD b mod 8) has its own run of items and
@@ -394,9 +394,11 @@ void k_assign_persistent(const Img* __restrict__ imgs,
     // paths).  run x = item_start + (n_img + 1) (1 + x) holds where each
     // image's share starts in the run.  A workgroup takes the items of its
     // XCD's run, then those left in the other runs, in turn.
+    // (the tables are constant during the launch: scalar loads)
+    const ConstI starts = (ConstI)(uintptr_t)item_start;
     for (int q = 0; q < 8;) {
         const int x = (int)((blockIdx.x + q) & 7u);
-        const int* __restrict__ run = item_start + (n_img + 1) * (1 + x);
+        const ConstI run = starts + (n_img + 1) * (1 + x);
         if (threadIdx.x == 0) item = atomicAdd(&ctrl[kCtrlQueue + 32 * x], 1);
         __syncthreads();
         const int h = __builtin_amdgcn_readfirstlane(item);   // uniform: kept in SGPRs
@@ -406,13 +408,15 @@ void k_assign_persistent(const Img* __restrict__ imgs,
             continue;
         }
         const int i = find_image(run, n_img, h);
-        const Img im = imgs[i];
-        const int ni = item_start[i + 1] - item_start[i];
-        const int local = (int)((long long)ni * x >> 3) + (h - run[i]);
-        const int pos = local / im.spl;
-        process_cell<WG, true, VOTED>(im, cell_in_strips(pos, im.nx, im.ny, im.strips),
-                                      local - pos * im.spl, packed, centres, endpoints, labels,
-                                      acc, lambda, cap, tab_dyn, sh);
+        const Img im = load_const(imgs + i);
+        const int ni = starts[i + 1] - starts[i];
+        const int local = __builtin_amdgcn_readfirstlane((int)((long long)ni * x >> 3) + (h - run[i]));
+        const int pos = fdiv(local, im.dspl);
+        int ci, cj;
+        cell_in_strips(pos, im, ci, cj);
+        process_cell<WG, true>(im, ci, cj, local - pos * im.spl, packed, centres, endpoints,
+                               labels, acc, lambda, sh);
+        __syncthreads();   // shared state is reused by the next item
     }
 }
 
@@ -978,6 +982,22 @@ void allow_lds(K kernel, size_t bytes) {
 
 }  // namespace
 
+void finish_img(Img& im) {
+    const long long W = im.W, H = im.H, nx = im.nx, ny = im.ny, K = nx * ny;
+    im.far = W * H >= (1LL << 28);
+    im.dnx = fast_div(nx, nx * (W + 1));
+    im.dny = fast_div(ny, ny * (H + 1));
+    im.dspl = fast_div(im.spl, std::max(K, (W / nx + 1) * (H / ny + 1) / 64 + 2) * im.spl);
+    const long long tw = (nx + im.strips - 1) / im.strips;
+    im.dcol = fast_div(tw, tw * ny);
+    im.dstrip = fast_div(tw * ny, K);
+    im.dlast = fast_div(nx % tw ? nx % tw : tw, tw * ny);
+    for (int i = 0; i < 2; ++i) {
+        const long long ch = H / ny + i, cw = W / nx + 1;
+        im.dper[i] = fast_div(8 * ch, cw * ch);
+    }
+}
+
 // 4800 x 16 B of tables (75 KiB) fit twice in 160 KiB: two 1024-thread
 // workgroups per CU.
 int default_lds_pixels() { return 4800; }
@@ -997,28 +1017,10 @@ int launch_write_bytes(void* dst, const void* src, size_t n, hipStream_t s) {
 }
 
 void lift_lds_limits() {
-    const size_t cap = 160 * 1024 - sizeof(CellShared) - 64;
+    const size_t cap = 152 * 1024;
     allow_lds(k_assign_window<256>, cap);
     allow_lds(k_assign_window<512>, cap);
     allow_lds(k_assign_window<1024>, cap);
-    allow_lds(k_assign<256, true, false>, cap);
-    allow_lds(k_assign<256, false, false>, cap);
-    allow_lds(k_assign<512, true, false>, cap);
-    allow_lds(k_assign<512, false, false>, cap);
-    allow_lds(k_assign<1024, true, false>, cap);
-    allow_lds(k_assign<1024, false, false>, cap);
-    allow_lds(k_assign<256, true, true>, cap);
-    allow_lds(k_assign<256, false, true>, cap);
-    allow_lds(k_assign<512, true, true>, cap);
-    allow_lds(k_assign<512, false, true>, cap);
-    allow_lds(k_assign<1024, true, true>, cap);
-    allow_lds(k_assign<1024, false, true>, cap);
-    allow_lds(k_assign_persistent<256, false>, cap);
-    allow_lds(k_assign_persistent<512, false>, cap);
-    allow_lds(k_assign_persistent<1024, false>, cap);
-    allow_lds(k_assign_persistent<256, true>, cap);
-    allow_lds(k_assign_persistent<512, true>, cap);
-    allow_lds(k_assign_persistent<1024, true>, cap);
 }
 
 int launch_prepare(long long n, const float* lab, const float* contour, float sigma,
@@ -1051,92 +1053,65 @@ int launch_init_cells_batched(const Img* imgs, const int* cell_start, int n_img,
     return hipGetLastError();
 }
 
-template <int WG, bool ACCUM, bool VOTED>
+template <int WG, bool ACCUM>
 static int launch_assign_t(const Img& im, const float4* packed, const float* centres,
                            const int* endpoints, int* labels, long long* acc, int* ctrl,
                            float lambda, const Tuning& t, hipStream_t s) {
-    const size_t bytes = dyn_lds(t);
-    hipLaunchKernelGGL((k_assign<WG, ACCUM, VOTED>), dim3(im.nx * im.ny * im.spl), dim3(WG), bytes,
-                       s, im, packed, centres, endpoints, labels, acc, ctrl, lambda,
-                       t.lds_pixels);
+    hipLaunchKernelGGL((k_assign<WG, ACCUM>), dim3(im.nx * im.ny * im.spl), dim3(WG), 0, s, im,
+                       packed, centres, endpoints, labels, acc, ctrl, lambda);
     return hipGetLastError();
 }
 
-template <int WG, bool VOTED>
+template <int WG>
 static int launch_assign_wg(const Img& im, const float4* packed, const float* centres,
                             const int* endpoints, int* labels, long long* acc, int* ctrl,
                             float lambda, bool accumulate, const Tuning& t, hipStream_t s) {
-    return accumulate ? launch_assign_t<WG, true, VOTED>(im, packed, centres, endpoints, labels,
-                                                         acc, ctrl, lambda, t, s)
-                      : launch_assign_t<WG, false, VOTED>(im, packed, centres, endpoints, labels,
-                                                          acc, ctrl, lambda, t, s);
-}
-
-template <bool VOTED>
-static int launch_assign_v(const Img& im, const float4* packed, const float* centres,
-                           const int* endpoints, int* labels, long long* acc, int* ctrl,
-                           float lambda, bool accumulate, const Tuning& t, hipStream_t s) {
-    if (t.wg == 1024)
-        return launch_assign_wg<1024, VOTED>(im, packed, centres, endpoints, labels, acc, ctrl,
-                                             lambda, accumulate, t, s);
-    if (t.wg == 512)
-        return launch_assign_wg<512, VOTED>(im, packed, centres, endpoints, labels, acc, ctrl,
-                                            lambda, accumulate, t, s);
-    return launch_assign_wg<256, VOTED>(im, packed, centres, endpoints, labels, acc, ctrl, lambda,
-                                        accumulate, t, s);
+    return accumulate ? launch_assign_t<WG, true>(im, packed, centres, endpoints, labels, acc,
+                                                  ctrl, lambda, t, s)
+                      : launch_assign_t<WG, false>(im, packed, centres, endpoints, labels, acc,
+                                                   ctrl, lambda, t, s);
 }
 
 int launch_assign(const Img& im, const float4* packed, const float* centres,
                   const int* endpoints, int* labels, long long* acc, int* ctrl, float lambda,
                   bool accumulate, const Tuning& t, hipStream_t s) {
-    return t.voted ? launch_assign_v<true>(im, packed, centres, endpoints, labels, acc, ctrl,
-                                           lambda, accumulate, t, s)
-                   : launch_assign_v<false>(im, packed, centres, endpoints, labels, acc, ctrl,
-                                            lambda, accumulate, t, s);
+    if (t.wg == 1024)
+        return launch_assign_wg<1024>(im, packed, centres, endpoints, labels, acc, ctrl, lambda,
+                                      accumulate, t, s);
+    if (t.wg == 512)
+        return launch_assign_wg<512>(im, packed, centres, endpoints, labels, acc, ctrl, lambda,
+                                     accumulate, t, s);
+    return launch_assign_wg<256>(im, packed, centres, endpoints, labels, acc, ctrl, lambda,
+                                 accumulate, t, s);
 }
 
-template <int WG, bool VOTED>
+template <int WG>
 static int launch_persistent_t(const Img* imgs, const int* item_start, int n_img, int total,
                                const float4* packed, const float* centres, const int* endpoints,
                                int* labels, long long* acc, int* ctrl, float lambda,
                                const Tuning& t, int grid, hipStream_t s) {
-    hipLaunchKernelGGL((k_assign_persistent<WG, VOTED>), dim3(grid), dim3(WG), dyn_lds(t), s,
-                       imgs, item_start, n_img, total, packed, centres, endpoints, labels, acc,
-                       ctrl, lambda, t.lds_pixels);
+    hipLaunchKernelGGL(k_assign_persistent<WG>, dim3(grid), dim3(WG), 0, s, imgs, item_start,
+                       n_img, total, packed, centres, endpoints, labels, acc, ctrl, lambda);
     return hipGetLastError();
-}
-
-template <bool VOTED>
-static int launch_persistent_v(const Img* imgs, const int* item_start, int n_img, int total,
-                               const float4* packed, const float* centres, const int* endpoints,
-                               int* labels, long long* acc, int* ctrl, float lambda,
-                               const Tuning& t, int grid, hipStream_t s) {
-    if (t.wg == 1024)
-        return launch_persistent_t<1024, VOTED>(imgs, item_start, n_img, total, packed, centres,
-                                                endpoints, labels, acc, ctrl, lambda, t, grid, s);
-    if (t.wg == 512)
-        return launch_persistent_t<512, VOTED>(imgs, item_start, n_img, total, packed, centres,
-                                               endpoints, labels, acc, ctrl, lambda, t, grid, s);
-    return launch_persistent_t<256, VOTED>(imgs, item_start, n_img, total, packed, centres,
-                                           endpoints, labels, acc, ctrl, lambda, t, grid, s);
 }
 
 int launch_assign_persistent(const Img* imgs, const int* item_start, int n_img, int total_items,
                              const float4* packed, const float* centres, const int* endpoints,
                              int* labels, long long* acc, int* ctrl, float lambda,
                              const Tuning& t, int grid, hipStream_t s) {
-    return t.voted ? launch_persistent_v<true>(imgs, item_start, n_img, total_items, packed,
-                                               centres, endpoints, labels, acc, ctrl, lambda, t,
-                                               grid, s)
-                   : launch_persistent_v<false>(imgs, item_start, n_img, total_items, packed,
-                                                centres, endpoints, labels, acc, ctrl, lambda, t,
-                                                grid, s);
+    if (t.wg == 1024)
+        return launch_persistent_t<1024>(imgs, item_start, n_img, total_items, packed, centres,
+                                         endpoints, labels, acc, ctrl, lambda, t, grid, s);
+    if (t.wg == 512)
+        return launch_persistent_t<512>(imgs, item_start, n_img, total_items, packed, centres,
+                                        endpoints, labels, acc, ctrl, lambda, t, grid, s);
+    return launch_persistent_t<256>(imgs, item_start, n_img, total_items, packed, centres,
+                                    endpoints, labels, acc, ctrl, lambda, t, grid, s);
 }
 
-template <int WG, bool VOTED>
-static int persistent_occupancy(int* per, size_t lds) {
-    return (int)hipOccupancyMaxActiveBlocksPerMultiprocessor(per, k_assign_persistent<WG, VOTED>,
-                                                             WG, lds);
+template <int WG>
+static int persistent_occupancy(int* per) {
+    return (int)hipOccupancyMaxActiveBlocksPerMultiprocessor(per, k_assign_persistent<WG>, WG, 0);
 }
 
 int persistent_grid(const Tuning& t) {
@@ -1144,17 +1119,9 @@ int persistent_grid(const Tuning& t) {
     if (hipGetDevice(&dev) != hipSuccess) return -1;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return -1;
-    const size_t lds = dyn_lds(t);
-    int e;
-    if (t.wg == 1024)
-        e = t.voted ? persistent_occupancy<1024, true>(&per, lds)
-                    : persistent_occupancy<1024, false>(&per, lds);
-    else if (t.wg == 512)
-        e = t.voted ? persistent_occupancy<512, true>(&per, lds)
-                    : persistent_occupancy<512, false>(&per, lds);
-    else
-        e = t.voted ? persistent_occupancy<256, true>(&per, lds)
-                    : persistent_occupancy<256, false>(&per, lds);
+    const int e = t.wg == 1024 ? persistent_occupancy<1024>(&per)
+                  : t.wg == 512 ? persistent_occupancy<512>(&per)
+                                : persistent_occupancy<256>(&per);
     if (e != (int)hipSuccess || per < 1) per = 1;
     if (t.blocks_per_cu > 0 && t.blocks_per_cu < per) per = t.blocks_per_cu;
     return cus * per;

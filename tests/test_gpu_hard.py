@@ -148,6 +148,24 @@ def test_assign_paths_beyond_carry_range(orc):
     assert (lbl == ol).all(), f"{int((lbl != ol).sum())} labels differ"
 
 
+@pytest.mark.parametrize("W,H,k", [(64, 64, 16), (68, 64, 16), (92, 60, 16), (130, 128, 64),
+                                   (15, 1024, 60), (257, 16, 1), (516, 512, 4)])
+@pytest.mark.parametrize("tune", [{}, {"exact_pruning": 0}, {"wg_size": 1024}])
+def test_assign_item_edges(orc, W, H, k, tune):
+    """Work items around the workgroup's and the 8-column strips' edges: cells
+    of exactly 256 pixels, last strips of 1 to 7 columns, a cell of one pixel
+    more than an item, items whose pairs of the second pass outnumber the
+    lanes (no pruning), cells cut into many slices."""
+    img = _image(W, H, 12)
+    g = orc.grid(W, H, k)
+    c, e = perturbed_state(orc, g, img.lab, seed=W * 3 + H, jitter=0.4 * g.r + 1)
+    s = _scalp(W, H, k, **tune)
+    say("assign edges", W, H, k, tune)
+    lbl = host(s.assign(dev(img.lab), dev(img.contour), dev(c), dev(e)))
+    ol, _, _ = orc.assign(g, img.lab, orc.wmap(img.contour), c, e)
+    assert (lbl == ol).all(), f"{int((lbl != ol).sum())} labels differ"
+
+
 @pytest.mark.parametrize("scale", [1e-21, 1e-17])
 def test_assign_tiny_colour_sums(orc, scale):
     """Lab values so small that the path colour sums fall below 2^-100 (down
