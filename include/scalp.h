@@ -72,15 +72,14 @@ typedef struct {
                                 packed (l, a, b, w) from an earlier call with
                                 the same lab/contour/sigma; skip re-packing  */
     int32_t lds_pixels;      /* tuning of the window form and of the soft
-                                kernels: LDS budget in 16-byte units (the
+                                backward: LDS budget in 16-byte units (the
                                 window form's one table of twice this many
-                                8-byte entries, the soft forward's two tables
-                                of this many), 0..9728; 0 selects the default
-                                (4800).  The 3x3 form has no tables.  The
-                                results do not depend on it                  */
+                                8-byte entries), 0..9728; 0 selects the default
+                                (4800).  The 3x3 form and the soft forward have
+                                no tables.  The results do not depend on it  */
     int32_t wg_size;         /* tuning: assignment workgroup size, 0 (default:
-                                256 for the 3x3 form, 1024 for the window form
-                                and the soft forward), 256, 512 or 1024      */
+                                256, and 1024 for the window form), 256, 512 or
+                                1024                                         */
     int32_t assign_mode;     /* SCALP_ASSIGN_GRID3X3 (default) or
                                 SCALP_ASSIGN_WINDOW, see below               */
     int32_t contour_source;  /* SCALP_CONTOUR_INPUT (default) or
@@ -286,8 +285,9 @@ int scalp_batched_graph_create(const scalp_batch_desc_t* descs, int32_t n_images
  *   centers_t : float32 [iters+1][B][K'][5]   (output; Theta_0 .. Theta_T)
  *   q_t       : float32 [iters][B][9][H][W]   (output)
  *   saved     : scalp_soft_saved_bytes() bytes (output of forward, input of
- *               backward): per-iteration factors A, B of Eqs. (1)-(2) and
- *               the FP64 masses sum Q (A and B are written only for slots
+ *               backward): per-iteration factors A, B of Eqs. (1)-(2), the
+ *               FP64 masses sum Q and, per pixel, which of its Q are not 0:
+ *               the backward reads no others (A and B are written only for slots
  *               inside the grid whose Q the exact bound does not prove to
  *               be 0: the only ones the backward reads).
  * lab: float32 [B][H][W][3]; contour: float32 [B][H][W]; 1 <= B <= 65535.

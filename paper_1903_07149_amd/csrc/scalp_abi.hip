@@ -64,7 +64,7 @@ bool pack_inputs_ok(const scalp_params_t* p, const float* lab, const float* cont
     return lab && (contour || p->contour_source == SCALP_CONTOUR_GRADIENT);
 }
 
-// Launch shape of the window form and of the soft kernels (default: 1024 lanes).
+// Launch shape of the window form (default: 1024 lanes).
 Tuning tuning_of(const scalp_params_t* p) {
     Tuning t;
     t.wg = p->wg_size == 0 ? 1024 : p->wg_size;
@@ -73,7 +73,7 @@ Tuning tuning_of(const scalp_params_t* p) {
     return t;
 }
 
-// Launch shape of the grid form.  256 lanes by default: an item's waves meet
+// Launch shape of the grid form and of the soft forward.  256 lanes by default: an item's waves meet
 // at three barriers, and the more items a CU holds, the less it waits there
 // (10 iterations of 1920x1080, k = 2000: 0.848, 0.864 and 0.897 ms at 256,
 // 512 and 1024 lanes; the 64-image batch: 34.0, 36.0 and 39.2 ms).
@@ -644,9 +644,10 @@ int scalp_batched_graph_create(const scalp_batch_desc_t* descs, int32_t n, const
 
 namespace {
 
-// saved: [A: T][B][9][N] float, [Bf: T][B][9][N] float, [Z: T][B][K] double
+// saved: [A: T][B][9][N] float, [Bf: T][B][9][N] float, [Z: T][B][K] double,
+// [masks of the Q that are not 0: T][B][N] uint16
 struct SoftSaved {
-    size_t a, bf, z, total;
+    size_t a, bf, z, pmask, total;
 };
 
 SoftSaved soft_saved_layout(const scalp_grid_t* g, long long B, long long T) {
@@ -655,7 +656,8 @@ SoftSaved soft_saved_layout(const scalp_grid_t* g, long long B, long long T) {
     s.a = 0;
     s.bf = align_up((size_t)(T * B * 9 * N) * 4);
     s.z = s.bf + align_up((size_t)(T * B * 9 * N) * 4);
-    s.total = s.z + align_up((size_t)(T * B * K) * 8);
+    s.pmask = s.z + align_up((size_t)(T * B * K) * 8);
+    s.total = s.pmask + align_up((size_t)(T * B * N) * 2);
     return s;
 }
 
@@ -729,7 +731,7 @@ int scalp_soft_forward(const scalp_grid_t* g, const scalp_params_t* p, float tem
     const int T = p->iterations;
     const Img im = img_of(g, p, 0, 0);
     const SoftGeom geo = soft_geom(g->width, g->height, g->nx, g->ny, batch, im.spw, im.gamma,
-                                   p->lambda, temperature, tuning_of(p).wg,
+                                   p->lambda, temperature, grid_tuning_of(p).wg,
                                    p->exact_pruning);
     const SoftSaved S = soft_saved_layout(g, B, T);
     char* wb = static_cast<char*>(ws);
@@ -738,14 +740,15 @@ int scalp_soft_forward(const scalp_grid_t* g, const scalp_params_t* p, float tem
     float* fa = reinterpret_cast<float*>(sb + S.a);
     float* fb = reinterpret_cast<float*>(sb + S.bf);
     double* z = reinterpret_cast<double*>(sb + S.z);
-    const int cap = soft_cap_bytes(p) / 16;
+    unsigned short* pmask = reinterpret_cast<unsigned short*>(sb + S.pmask);
     if (!p->reuse_prepared) CHECK_HIP(launch_prepare(B * N, lab, contour, p->sigma, packed, s));
     CHECK_HIP(launch_soft_init(geo, packed, centers_t, s));
     for (int t = 0; t < T; ++t) {
         const long long qo = (long long)t * B * 9 * N;
         CHECK_HIP(launch_soft_assign(geo, packed, centers_t + (long long)t * B * K * 5, q_t + qo,
-                                     fa + qo, fb + qo, cap, s));
-        CHECK_HIP(launch_soft_update(geo, q_t + qo, packed, centers_t + (long long)t * B * K * 5,
+                                     fa + qo, fb + qo, pmask + (long long)t * B * N, s));
+        CHECK_HIP(launch_soft_update(geo, q_t + qo, pmask + (long long)t * B * N, packed,
+                                     centers_t + (long long)t * B * K * 5,
                                      centers_t + (long long)(t + 1) * B * K * 5,
                                      z + (long long)t * B * K, s));
     }
@@ -772,7 +775,7 @@ int scalp_soft_backward(const scalp_grid_t* g, const scalp_params_t* p, float te
     const int T = p->iterations;
     const Img im = img_of(g, p, 0, 0);
     const SoftGeom geo = soft_geom(g->width, g->height, g->nx, g->ny, batch, im.spw, im.gamma,
-                                   p->lambda, temperature, tuning_of(p).wg,
+                                   p->lambda, temperature, grid_tuning_of(p).wg,
                                    p->exact_pruning);
     const SoftSaved S = soft_saved_layout(g, B, T);
     char* wb = static_cast<char*>(ws);
@@ -787,6 +790,7 @@ int scalp_soft_backward(const scalp_grid_t* g, const scalp_params_t* p, float te
     const float* fa = reinterpret_cast<const float*>(sb + S.a);
     const float* fb = reinterpret_cast<const float*>(sb + S.bf);
     const double* z = reinterpret_cast<const double*>(sb + S.z);
+    const unsigned short* pmask = reinterpret_cast<const unsigned short*>(sb + S.pmask);
     const int cap = soft_cap_bytes(p);
     if (!p->reuse_prepared) CHECK_HIP(launch_prepare(B * N, lab, contour, p->sigma, packed, s));
     CHECK_HIP(launch_clear(reinterpret_cast<long long*>(gf), B * N * 2, s));
@@ -795,7 +799,7 @@ int scalp_soft_backward(const scalp_grid_t* g, const scalp_params_t* p, float te
     for (int t = T - 1; t >= 0; --t) {
         const long long qo = (long long)t * B * 9 * N;
         const double* zt = z + (long long)t * B * K;
-        CHECK_HIP(launch_soft_bwd_update(geo, t == T - 1, q_t + qo, zt,
+        CHECK_HIP(launch_soft_bwd_update(geo, t == T - 1, q_t + qo, pmask + (long long)t * B * N, zt,
                                          centers_t + (long long)(t + 1) * B * K * 5, packed,
                                          gth[cur], grad_q, gd, gmask, gf, cand, s));
         CHECK_HIP(launch_soft_bwd_pass(geo, zt, gth[cur], gth[1 - cur], s));

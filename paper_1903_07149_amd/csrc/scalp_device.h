@@ -260,12 +260,10 @@ __device__ __forceinline__ PathStep path_step(int dx, int dy, int sx, int sy) {
 
 // When a walk may stop: from the sums so far, lo = fl(fl(fl(a0 + f sc) fl(1 +
 // g sw)) + dsp) with f = (1 - lambda) / |P|, g = gamma / |P| (approximate) and
-// a0 = lambda dcp is Eq. (3)'s D of the path cut short.  Every summand
-// of D is >= 0, so D is at least the exact value of lo, and lo is within 2^-20
-// of that (a dozen roundings and one reciprocal good to an ulp): lo > thr =
-// best (1 + 2^-16) proves D > best.  thr is at least 2^-70, far above any
-// absolute error that underflow can leave, and walks are never cut where gamma
-// exceeds 2^40 (which could raise such an error above it).
+// a0 = lambda dcp is Eq. (3)'s D of the path cut short.  Every summand of D is
+// >= 0, so lo > thr, a threshold() or more, proves that D exceeds it.  Walks
+// are never cut where gamma exceeds 2^40 (which could raise an underflow's
+// error above 2^-70).
 struct Cut {
     bool on;               // uniform
     float a0, f, g, dsp, thr;
@@ -450,6 +448,59 @@ __device__ __forceinline__ void div_path_len(float a, float b, int n, double inv
     }
 }
 
+// The parameters of Eqs. (1)-(3), and the image they are evaluated on.
+struct Eqs {
+    const float4* img;     // packed texels
+    int W;
+    bool near;             // 32-bit byte offsets reach every texel, and every path is below
+                           // 46340 steps
+    float lambda, oml, gamma, spw;
+};
+
+// D of Eq. (3) of pixel (px, py), whose texel is fp, to the cluster at ck =
+// (l, a, b, x, y) with endpoint (cx, cy), and its factors A, B of Eqs.
+// (1)-(2); FP32, operation by operation.  cut: an infinite D may be returned
+// once D is known to exceed thr's best (see Cut; A and B are then
+// meaningless).
+__device__ __forceinline__ float path_distance(const Eqs& q, const float (&ck)[5], float4 fp,
+                                               int cx, int cy, int px, int py, bool cut_on,
+                                               float thr, float& A, float& B) {
+    const float l = ck[0], a = ck[1], b = ck[2];
+    const float ax = (float)px - ck[3], ay = (float)py - ck[4];
+    const int p = py * q.W + px;
+    const int dx = cx - px, dy = cy - py;
+    const int n = max(abs(dx), abs(dy));
+    const double inv = path_recip(n);
+    const float dsp = (ax * ax + ay * ay) * q.spw;
+    const float dcp = colour_dist(fp, l, a, b);
+    float sc = dcp, sw = fp.w;                     // sample i = 0 is p itself
+    if (q.near) {                                  // uniform
+        Cut cut;
+        cut.on = cut_on;
+        if (cut_on) {
+            const float rnp = __builtin_amdgcn_rcpf((float)(n + 1));
+            cut.a0 = q.lambda * dcp;
+            cut.f = q.oml * rnp;
+            cut.g = q.gamma * rnp;
+            cut.dsp = dsp;
+            cut.thr = thr;
+        }
+        walk_near(q.img, 16u * (unsigned)p, path_step(dx, dy, 16, 16 * q.W), l, a, b, cut, sc, sw);
+    } else {
+        walk_path(q.img, p, 1, q.W, dx, dy, l, a, b, sc, sw);
+        if (n > 0) {                               // sample i = n is the endpoint
+            const float4 fc = q.img[(long long)cy * q.W + cx];
+            sc = sc + colour_dist(fc, l, a, b);
+            sw = sw + fc.w;
+        }
+    }
+    float qc, qw;                                  // sc / |P|, sw / |P|
+    div_path_len(sc, sw, n, inv, qc, qw);
+    A = q.lambda * dcp + q.oml * qc;               // Eq. (1)
+    B = 1.0f + q.gamma * qw;                       // Eq. (2)
+    return A * B + dsp;                            // Eq. (3)
+}
+
 __device__ __forceinline__ int round_coord(float v, int hi) {
     int e = (int)floorf(v + 0.5f);
     e = e < 0 ? 0 : e;
@@ -526,13 +577,13 @@ struct PixelMap {
 __constant__ const unsigned kLastStrip[8] = {0u, 0u, 0x80000000u, 0x55555556u, 0x40000000u,
                                              0x33333334u, 0x2aaaaaabu, 0x24924925u};
 
-__device__ __forceinline__ PixelMap pixel_map(const Img& im, int cw, int ch) {
+__device__ __forceinline__ PixelMap pixel_map(const FastDiv (&dper)[2], int cw, int ch) {
     PixelMap p;
     p.cw = cw;
     p.ch = ch;
     p.per = 8 * ch;
     p.fullpx = (cw >> 3) * p.per;
-    p.mper = ch == (int)(im.dper[0].d >> 3) ? im.dper[0].m : im.dper[1].m;
+    p.mper = ch == (int)(dper[0].d >> 3) ? dper[0].m : dper[1].m;
     p.mwr = kLastStrip[cw & 7];
     p.fast = p.mper != 0u;
     return p;
@@ -564,6 +615,102 @@ __device__ __forceinline__ int strip_of(int t, int cw, int ch) {
     const int fullpx = (cw >> 3) * 8 * ch;
     return t < fullpx ? t / (8 * ch) : (cw >> 3);
 }
+
+// The candidates' centres as the bounds read them: the item's 9 superpixels
+// are uniform over the workgroup, so their values come through the scalar
+// cache into scalar registers (nothing writes centres or endpoints while an
+// assignment pass runs).
+typedef const __attribute__((address_space(4))) float* ConstF;
+typedef const __attribute__((address_space(4))) int* ConstI;
+
+// Rows and columns of the 3x3 candidates of a cell, clamped into the grid (a
+// clamped one repeats another candidate of the cell), and which are inside
+// (bit j: slot j).
+struct Neighbours {
+    int row[3], col[3];   // superpixel index of (row, column 0); column
+    unsigned inside;
+};
+
+__device__ __forceinline__ Neighbours neighbours_of(int nx, int ny, int ci, int cj) {
+    Neighbours g;
+    g.row[0] = max(ci - 1, 0) * nx;
+    g.row[1] = ci * nx;
+    g.row[2] = min(ci + 1, ny - 1) * nx;
+    g.col[0] = max(cj - 1, 0);
+    g.col[1] = cj;
+    g.col[2] = min(cj + 1, nx - 1);
+    g.inside = 0x1ffu;
+    if (ci == 0) g.inside &= ~0x007u;
+    if (ci == ny - 1) g.inside &= ~0x1c0u;
+    if (cj == 0) g.inside &= ~0x049u;
+    if (cj == nx - 1) g.inside &= ~0x124u;
+    return g;
+}
+
+constexpr unsigned kNoKey = 0xffffffffu;
+
+// Keys of the 9 candidates of a pixel with texel f: the upper 28 bits of
+// LB = lambda dcp + ds spw, with the slot in the low 4 bits; kNoKey for a slot
+// outside the grid.  LB is what D of Eq. (3) cannot fall below: lambda is in
+// [0, 1], gamma >= 0 and every colour distance and w is >= 0, so
+// A >= lambda dcp and B >= 1, and FP32 rounding is monotone.  Here it is
+// evaluated with fused operations (13 per candidate instead of 16), within
+// 2^-21 of its exact value: a candidate is left out only when its key, cut to
+// 28 bits, exceeds threshold(best).  The centres are read one row of
+// candidates at a time (the barrier keeps the scheduler from holding all 45
+// scalars at once, which spilled).
+__device__ __forceinline__ void bound_keys(const Neighbours& g, ConstF cen, float spw, float4 f,
+                                           int x, int y, float lambda, unsigned (&key)[9]) {
+    const float fx = (float)x, fy = (float)y;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        ConstF row = cen + 5LL * __builtin_amdgcn_readfirstlane(g.row[i]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int jj = 0; jj < 3; ++jj) {
+            const int j = 3 * i + jj;
+            ConstF c = row + 5 * __builtin_amdgcn_readfirstlane(g.col[jj]);
+            const float dl = f.x - c[0], da = f.y - c[1], db = f.z - c[2];
+            const float ex = fx - c[3], ey = fy - c[4];
+            const float dcp = __builtin_fmaf(db, db, __builtin_fmaf(da, da, dl * dl));
+            const float lb = __builtin_fmaf(ex * ex + ey * ey, spw, lambda * dcp);
+            const unsigned tag = (g.inside >> j) & 1u ? (unsigned)j : kNoKey;   // uniform
+            key[j] = (__float_as_uint(lb) & ~15u) | tag;
+        }
+    }
+}
+
+// What a bound, or the value of a path cut short, must exceed to prove that D
+// exceeds best: the margin of 2^-16 covers their rounding (a dozen operations
+// and one reciprocal good to an ulp), and 2^-70 any absolute error that
+// underflow can leave.
+__device__ __forceinline__ float threshold(float best) {
+    return fmaxf(best * (1.0f + 0x1p-16f), 0x1p-70f);
+}
+
+// The smallest key above `cur` (0xffffffff: the smallest of all), all ones
+// when there is none.
+__device__ __forceinline__ unsigned next_key(const unsigned (&key)[9], unsigned cur) {
+    const unsigned c1 = cur + 1u;          // keys up to cur wrap to [2^32 - c1, 2^32)
+    const unsigned a = min(min(key[0] - c1, key[1] - c1), key[2] - c1);
+    const unsigned b = min(min(key[3] - c1, key[4] - c1), key[5] - c1);
+    const unsigned c = min(min(key[6] - c1, key[7] - c1), key[8] - c1);
+    unsigned next;
+    return __builtin_add_overflow(min(min(a, b), c), c1, &next) ? 0xffffffffu : next;
+}
+
+// Adds the number of lanes in m (a ballot of the lanes here, not 0) to *count
+// and gives the n-th of them the old value + n.
+__device__ __forceinline__ int wave_claim(int* count, unsigned long long m) {
+    const int leader = __ffsll((long long)m) - 1;
+    int at = 0;
+    if ((int)(threadIdx.x & 63) == leader) at = atomicAdd(count, __popcll(m));
+    return __builtin_amdgcn_readlane(at, leader) +
+           (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                          __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
+
+__device__ __forceinline__ float key_bound(unsigned key) { return __uint_as_float(key & ~15u); }
 
 // x of lane i - CTRL's shift, 0 where that lane is outside the row or the
 // row is not in ROW_MASK (DPP: gfx9 row_shr / row_bcast controls).

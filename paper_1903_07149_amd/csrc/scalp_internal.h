@@ -156,13 +156,16 @@ void lift_soft_lds_limits();
 // is cut into slices of whole 64-pixel chunks, at most wg pixels each.
 int soft_slices(int W, int H, int nx, int ny, int wg);
 int launch_soft_init(const SoftGeom& g, const float4* packed, float* theta0, hipStream_t st);
+// pmask [B][N]: bit j of a pixel: its Q of slot j is not 0
 int launch_soft_assign(const SoftGeom& g, const float4* packed, const float* theta_prev, float* q,
-                       float* fa, float* fb, int cap, hipStream_t st);
-int launch_soft_update(const SoftGeom& g, const float* q, const float4* packed,
-                       const float* theta_prev, float* theta_next, double* z, hipStream_t st);
+                       float* fa, float* fb, unsigned short* pmask, hipStream_t st);
+int launch_soft_update(const SoftGeom& g, const float* q, const unsigned short* pmask,
+                       const float4* packed, const float* theta_prev, float* theta_next, double* z,
+                       hipStream_t st);
 // cand: scratch of 2 * B * K float4 (per-superpixel terms of the update backward);
 // gd receives the nonzero dL/dD only, gmask ([B][N]) which of the 9 slots they are
-int launch_soft_bwd_update(const SoftGeom& g, int first, const float* q, const double* z,
+int launch_soft_bwd_update(const SoftGeom& g, int first, const float* q,
+                           const unsigned short* pmask, const double* z,
                            const float* theta, const float4* packed, const double* gth,
                            const float* gq_in, float* gd, unsigned short* gmask, float4* gf,
                            float4* cand, hipStream_t st);

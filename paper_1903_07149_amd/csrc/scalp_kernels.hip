@@ -54,15 +54,6 @@ struct ItemShared {
     int pairs;
 };
 
-constexpr unsigned kInfBits = 0x7f800000u;
-
-// The candidates' centres as the bounds read them: the item's 9 superpixels
-// are uniform over the workgroup, so their values come through the scalar
-// cache into scalar registers (nothing writes centres or endpoints while an
-// assignment pass runs).
-typedef const __attribute__((address_space(4))) float* ConstF;
-typedef const __attribute__((address_space(4))) int* ConstI;
-
 // A descriptor read through the scalar cache, word by word (p uniform).
 __device__ __forceinline__ Img load_const(const Img* p) {
     static_assert(sizeof(Img) % 4 == 0, "words");
@@ -76,73 +67,10 @@ __device__ __forceinline__ Img load_const(const Img* p) {
     return u.im;
 }
 
-// Rows and columns of the 3x3 candidates of a cell, clamped into the grid (a
-// clamped one repeats another candidate of the cell), and which are inside
-// (bit j: slot j).
-struct Neighbours {
-    int row[3], col[3];   // superpixel index of (row, column 0); column
-    unsigned inside;
-};
-
-__device__ __forceinline__ Neighbours neighbours_of(const Img& im, int ci, int cj) {
-    Neighbours g;
-    g.row[0] = max(ci - 1, 0) * im.nx;
-    g.row[1] = ci * im.nx;
-    g.row[2] = min(ci + 1, im.ny - 1) * im.nx;
-    g.col[0] = max(cj - 1, 0);
-    g.col[1] = cj;
-    g.col[2] = min(cj + 1, im.nx - 1);
-    g.inside = 0x1ffu;
-    if (ci == 0) g.inside &= ~0x007u;
-    if (ci == im.ny - 1) g.inside &= ~0x1c0u;
-    if (cj == 0) g.inside &= ~0x049u;
-    if (cj == im.nx - 1) g.inside &= ~0x124u;
-    return g;
-}
-
-// Keys of the 9 candidates of a pixel with texel f: the upper 28 bits of
-// LB = fl(fl(lambda dcp) + fl(ds spw)), which is >= 0, with the slot in the
-// low 4 bits; all ones for a slot outside the grid.  A key at or above
-// kInfBits belongs to no walk: LB is infinite or NaN, and so is D.  The
-// centres are read one row of candidates at a time (the barrier keeps the
-// scheduler from holding all 45 scalars at once, which spilled).
-__device__ __forceinline__ void bound_keys(const Img& im, const Neighbours& g, ConstF cen,
-                                           float4 f, int x, int y, float lambda,
-                                           unsigned (&key)[9]) {
-    const float fx = (float)x, fy = (float)y;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        ConstF row = cen + 5LL * __builtin_amdgcn_readfirstlane(g.row[i]);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int jj = 0; jj < 3; ++jj) {
-            const int j = 3 * i + jj;
-            ConstF c = row + 5 * __builtin_amdgcn_readfirstlane(g.col[jj]);
-            const float ex = fx - c[3], ey = fy - c[4];
-            const float lb = lambda * colour_dist(f, c[0], c[1], c[2]) +
-                             (ex * ex + ey * ey) * im.spw;
-            const unsigned tag = (g.inside >> j) & 1u ? (unsigned)j : 0xffffffffu;   // uniform
-            key[j] = (__float_as_uint(lb) & ~15u) | tag;
-        }
-    }
-}
-
 // First 64-pixel chunk of slice i of a cell of `chunks` chunks.
 __device__ __forceinline__ int slice_chunk(int chunks, int i, const Img& im) {
     const long long v = (long long)chunks * i;
     return v < (1LL << 31) ? fdiv((int)v, im.dspl) : (int)(v / im.spl);
-}
-
-// The smallest key above `cur` (0xffffffff: the smallest of all), all ones
-// when there is none; at least kInfBits when no candidate with a finite bound
-// is left.
-__device__ __forceinline__ unsigned next_key(const unsigned (&key)[9], unsigned cur) {
-    const unsigned c1 = cur + 1u;          // keys up to cur wrap to [2^32 - c1, 2^32)
-    const unsigned a = min(min(key[0] - c1, key[1] - c1), key[2] - c1);
-    const unsigned b = min(min(key[3] - c1, key[4] - c1), key[5] - c1);
-    const unsigned c = min(min(key[6] - c1, key[7] - c1), key[8] - c1);
-    unsigned next;
-    return __builtin_add_overflow(min(min(a, b), c), c1, &next) ? 0xffffffffu : next;
 }
 
 // Work item (cell, slice): pixels [t0, t1) of the cell in cell_pixel order,
@@ -150,17 +78,12 @@ __device__ __forceinline__ unsigned next_key(const unsigned (&key)[9], unsigned 
 // over its spl slices (spl is chosen on the host so that no slice has more
 // than WG pixels), and every wave keeps an 8x8 block.
 //
-// Every pixel visits its candidates in ascending order of a lower bound of
-// their D and stops at the first bound above its best D: with lambda in
-// [0, 1], gamma >= 0 and every colour distance and w non-negative,
-// A >= fl(lambda dcp) and B >= 1 in Eqs. (1)-(2), so D = fl(fl(A B) +
-// fl(ds spw)) is at least LB = fl(fl(lambda dcp) + fl(ds spw)) (FP32 rounding
-// is monotone), and the candidates left out could not have been chosen.  The
-// winner is the smallest (D, slot) pair, which is the first strict minimum in
-// ascending slot (hence ascending k) whatever the visiting order, and a
-// candidate whose bound equals the best D is walked: the labels are those of
-// evaluating every candidate.  An infinite or NaN bound makes D infinite or
-// NaN, which never wins.
+// Every pixel walks the candidate with the smallest lower bound of D first
+// (bound_keys), and then only those whose bound does not exceed its D: the
+// others could not have been chosen.  The winner is the smallest (D, slot)
+// pair, which is the first strict minimum in ascending slot (hence ascending
+// k) whatever the visiting order: the labels are those of evaluating every
+// candidate.  An infinite or NaN D never wins.
 //
 // The first candidate decides 80 % of the pixels; the others whose bound does
 // not exceed its D, 0.2 per pixel and most of them losers, are listed and
@@ -205,56 +128,31 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
     const int sp = __builtin_amdgcn_readfirstlane(im.sp);
     const float* __restrict__ cen = centres + 5LL * sp;
     const int* __restrict__ end = endpoints + 2LL * sp;
-    const Neighbours nb = neighbours_of(im, ci, cj);
-    const float oml = 1.0f - lambda;
-    const float gamma = im.gamma, spw = im.spw;
+    const Neighbours nb = neighbours_of(im.nx, im.ny, ci, cj);
+    Eqs eqs;
+    eqs.img = img;
+    eqs.W = W;
+    eqs.near = !im.far && W + H < 46340;
+    eqs.lambda = lambda;
+    eqs.oml = 1.0f - lambda;
+    eqs.gamma = im.gamma;
+    eqs.spw = im.spw;
     // candidate slot j -> superpixel
     const int k0 = (ci - 1) * im.nx + cj - 1;
     auto superpixel = [&](int j) -> int {
         const int di = (j * 11) >> 5;              // j / 3 for j <= 8
         return k0 + di * im.nx + (j - 3 * di);
     };
-    // D of Eqs. (1)-(3) of pixel (px, py) to superpixel k, or an infinite
-    // value once it is known to exceed `best` (cut)
-    auto distance = [&](int k, int px, int py, float best, bool cut_on) -> float {
-        const float* ck = cen + 5 * k;
-        const float l = ck[0], a = ck[1], b = ck[2];
-        const float ax = (float)px - ck[3], ay = (float)py - ck[4];
-        // endpoints outside the image are clamped into it
-        const int cx = min(max(end[2 * k], 0), W - 1), cy = min(max(end[2 * k + 1], 0), H - 1);
-        const int p = py * W + px;
-        const float4 fp = img[p];
-        const int dx = cx - px, dy = cy - py;
-        const int n = max(abs(dx), abs(dy));
-        const double inv = path_recip(n);
-        const float dsp = (ax * ax + ay * ay) * spw;
-        const float dcp = colour_dist(fp, l, a, b);
-        float sc = dcp, sw = fp.w;                 // sample i = 0 is p itself
-        if (!im.far && W + H < 46340) {            // uniform
-            Cut cut;
-            cut.on = cut_on;
-            if (cut_on) {
-                const float rnp = __builtin_amdgcn_rcpf((float)(n + 1));
-                cut.a0 = lambda * dcp;
-                cut.f = oml * rnp;
-                cut.g = gamma * rnp;
-                cut.dsp = dsp;
-                cut.thr = fmaxf(best * (1.0f + 0x1p-16f), 0x1p-70f);
-            }
-            walk_near(img, 16u * (unsigned)p, path_step(dx, dy, 16, 16 * W), l, a, b, cut, sc, sw);
-        } else {
-            walk_path(img, p, 1, W, dx, dy, l, a, b, sc, sw);
-            if (n > 0) {                           // sample i = n is the endpoint
-                const float4 fc = img[(long long)cy * W + cx];
-                sc = sc + colour_dist(fc, l, a, b);
-                sw = sw + fc.w;
-            }
-        }
-        float qc, qw;                              // sc / |P|, sw / |P|
-        div_path_len(sc, sw, n, inv, qc, qw);
-        const float A = lambda * dcp + oml * qc;             // Eq. (1)
-        const float B = 1.0f + gamma * qw;                   // Eq. (2)
-        return A * B + dsp;                                  // Eq. (3)
+    // D of pixel (px, py) with texel fp to candidate slot j (endpoints outside
+    // the image are clamped into it); its loads do not wait for one another
+    auto distance = [&](int j, float4 fp, int px, int py, bool cut, float thr) -> float {
+        const int kk = superpixel(j);
+        const int2 ep = *reinterpret_cast<const int2*>(end + 2 * kk);
+        const float* cp = cen + 5 * kk;
+        const float ck[5] = {cp[0], cp[1], cp[2], cp[3], cp[4]};
+        float A, B;
+        return path_distance(eqs, ck, fp, min(max(ep.x, 0), W - 1), min(max(ep.y, 0), H - 1), px,
+                             py, cut, thr, A, B);
     };
     // the label of pixel (px, py) and its share of the update's sums
     auto settle = [&](int px, int py, int bestj) {
@@ -287,31 +185,29 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
     bool again = false;
     int px = 0, py = 0, bestj = -1;
     if (mine) {
-        pixel_at(pixel_map(im, cw, ch), t0 + tid, px, py);
+        pixel_at(pixel_map(im.dper, cw, ch), t0 + tid, px, py);
         px += x0;
         py += y0;
         unsigned key[9];
-        bound_keys(im, nb, (ConstF)(uintptr_t)cen, img[py * W + px], px, py, lambda, key);
-        unsigned nk = next_key(key, 0xffffffffu);
+        const float4 fp = img[py * W + px];
+        bound_keys(nb, (ConstF)(uintptr_t)cen, im.spw, fp, px, py, lambda, key);
+        unsigned nk = next_key(key, kNoKey);
         float best = INFINITY;
-        if (nk < kInfBits) {
+        {
             const int j = (int)(nk & 15u);
-            const float D = distance(superpixel(j), px, py, best, false);
+            const float D = distance(j, fp, px, py, false, 0.0f);
             if (D < best) {
                 best = D;
                 bestj = j;
             }
         }
-        while (nk < kInfBits) {
+        const float thr = threshold(best);
+        for (;;) {
             nk = next_key(key, nk);
-            const bool more = nk < kInfBits && !(prune && __uint_as_float(nk & ~15u) > best);
+            const bool more = nk != kNoKey && !(prune && key_bound(nk) > thr);
             const unsigned long long m = __ballot(more);
             if (m == 0ULL) break;                  // uniform over the lanes still here
-            int at = 0;
-            if (__ffsll((long long)m) - 1 == (tid & 63)) at = atomicAdd(&sh.pairs, __popcll(m));
-            at = __builtin_amdgcn_readlane(at, __ffsll((long long)m) - 1) +
-                 (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
-                                                __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+            const int at = wave_claim(&sh.pairs, m);
             if (!more) break;
             sh.list[at] = (unsigned short)(tid | ((nk & 15u) << 10));
             again = true;
@@ -326,12 +222,13 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
     __syncthreads();
     // second pass: the listed pairs, by full waves
     const int pairs = __builtin_amdgcn_readfirstlane(sh.pairs);
+    const bool cut = prune && im.gamma <= 0x1p40f;
     for (int i = tid; i < pairs; i += WG) {
         const unsigned e = sh.list[i];
         const int id = (int)(e & 1023u), j = (int)(e >> 10);
         const int2 q = sh.xy[id];
         const float best = __uint_as_float((unsigned)(sh.win[id] >> 32));
-        const float D = distance(superpixel(j), q.x, q.y, best, prune && gamma <= 0x1p40f);
+        const float D = distance(j, img[q.y * W + q.x], q.x, q.y, cut, threshold(best));
         if (D < INFINITY)
             atomicMin(&sh.win[id], ((unsigned long long)__float_as_uint(D) << 32) | (unsigned)j);
     }

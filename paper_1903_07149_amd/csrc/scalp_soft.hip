@@ -9,13 +9,14 @@
 //
 // Forward, per iteration:
 //   k_soft_assign  workgroup per (image, cell, slice), one pixel per lane:
-//                  per-candidate LDS tables of (colour distance, w) and
-//                  per-lane path walks as in the hard kernel; writes D and
-//                  the factors A (Eq. (1)) and B (Eq. (2)).
-//   k_soft_softmax FP64 softmax of -D/T over the 9 slots, written as Q.
-//   k_soft_update  workgroup per (image, superpixel): gathers Q over the 3x3
-//                  cell block in a fixed order (FP64 partial sums, tree
-//                  reduction): deterministic, no atomics.
+//                  the candidate with the smallest bound of D is walked first,
+//                  then, by full waves, those whose softmax weight that bound
+//                  does not prove to be 0; then the FP64 softmax of -D/T over
+//                  the 9 slots.  Writes Q, the factors A (Eq. (1)) and B
+//                  (Eq. (2)) of the walked slots, and which Q are not 0.
+//   k_soft_update  workgroup per (image, superpixel): gathers the Q that are not
+//                  0 over the 3x3 cell block in a fixed order (FP64 partial
+//                  sums, tree reduction): deterministic, no atomics.
 // Backward, per iteration in reverse:
 //   k_soft_bwd_update  thread per pixel: soft-update and softmax backward,
 //                      giving dL/dD for the 9 slots.
@@ -41,6 +42,8 @@ struct SoftImg {
     float spw, gamma, lambda, inv_t;
     double temp;
     int prune;   // 1: skip the walks of slots whose softmax weight is provably 0
+    int near;    // 32-bit byte offsets reach every texel of an image
+    FastDiv dper[2];   // 8 x the two cell heights (see PixelMap)
 };
 
 // A superpixel whose soft mass is below a millionth of a pixel counts as
@@ -54,43 +57,11 @@ struct SoftCand {
     int k;
     float l, a, b, x, y;
     int cx, cy;
-    float dcc, wc;
-    int tx0, ty0, tw, th;       // forward: table origin, row pitch, rows; tw == 0: not staged
-    int rpp;                    // rows per pass of the column-wise fill (WG / tw, 0 when tw > WG)
-    unsigned mag;               // ceil(2^24 / tw): lane tid's first row is tid * mag >> 24
 };
 
 struct SoftShared {
     SoftCand cand[9];
 };
-
-// Candidates of cell (ci, cj) from theta [K][5]; endpoint = rounded barycenter.
-__device__ __forceinline__ void load_candidates(const SoftImg& s, int ci, int cj,
-                                                const float* __restrict__ theta,
-                                                const float4* __restrict__ img, SoftShared& sh) {
-    const int tid = threadIdx.x;
-    if (tid < 9) {
-        SoftCand c;
-        const int ii = ci + tid / 3 - 1, jj = cj + tid % 3 - 1;
-        if (ii >= 0 && ii < s.ny && jj >= 0 && jj < s.nx) {
-            const int k = ii * s.nx + jj;
-            const float* ck = theta + 5LL * k;
-            c.k = k;
-            c.l = ck[0]; c.a = ck[1]; c.b = ck[2]; c.x = ck[3]; c.y = ck[4];
-            c.cx = round_coord(c.x, s.W - 1);
-            c.cy = round_coord(c.y, s.H - 1);
-            const float4 fc = img[(long long)c.cy * s.W + c.cx];
-            c.dcc = colour_dist(fc, c.l, c.a, c.b);
-            c.wc = fc.w;
-        } else {
-            c.k = -1;
-            c.l = c.a = c.b = c.x = c.y = 0.0f;
-            c.cx = c.cy = 0;
-            c.dcc = c.wc = 0.0f;
-        }
-        sh.cand[tid] = c;
-    }
-}
 
 // ------------------------------------------------------------------ forward
 
@@ -122,22 +93,43 @@ __global__ __launch_bounds__(WG) void k_soft_init(SoftImg s, const float4* __res
     if (tid < 5) theta0[(5LL * b) * s.K + 5LL * k + tid] = (float)(red[tid][0] / red[5][0]);
 }
 
-// One workgroup per (image, cell, slice) work item, one pixel per lane, as
-// in the hard assignment: a cell with more pixels than the workgroup has
-// lanes is cut into spl slices of whole 64-pixel chunks.  Candidates are
-// taken one at a time: the workgroup writes a table of (d_c(q, k), w_q) over
-// the rectangle spanned by the item's pixels and the candidate's endpoint
-// (two tables alternate, one barrier per candidate), and every lane walks
-// its pixel's path over it, two adds per sample; a rectangle beyond the
-// budget walks from global memory.  Same FP32 operations, same order.
+// Per work item, by pixel (lane of the first pass): D per slot, then Q; the
+// coordinates; the (pixel, slot) pairs of the second pass; the first D, and
+// the pixels with more than one walk.
 template <int WG>
-__global__ __launch_bounds__(WG) void k_soft_assign(SoftImg s, const float4* __restrict__ packed,
-                                                    const float* __restrict__ theta_prev,
-                                                    float* __restrict__ q, float* __restrict__ fa,
-                                                    float* __restrict__ fb, int cap) {
-    extern __shared__ float4 lds_dyn[];
-    float2* tabs = reinterpret_cast<float2*>(lds_dyn);          // two tables of cap entries
-    __shared__ SoftShared sh;
+struct SoftItem {
+    float D[9][WG];
+    int2 xy[WG];
+    unsigned short list[8 * WG];
+    float best[WG];
+    unsigned short multi[WG];
+    int pairs, multis;
+};
+
+// One workgroup per (image, cell, slice) work item, one pixel per lane, in two
+// passes of walks as in the hard assignment (process_cell), and the softmax.
+// The softmax gives a slot Q = 0 exactly when (D - Dmin) / T > 110 in FP64.
+// With best the D of the candidate walked first, Dmin <= best, so a slot whose
+// bound exceeds (best + 111 T) (1 + 2^-15) gets Q = 0 whatever its walk would
+// give (the margins cover the bound's rounding and the FP64 division's); such
+// a slot, and a walk whose partial sums exceed that, counts as D = +inf.  Its
+// saved factors are not written: the backward reads them only where dL/dD, a
+// multiple of Q, is not 0.
+//
+// The pixels that walked one candidate have one Q, 1; the others are listed
+// and take the FP64 softmax by full waves.
+//
+// What bounds it: VALU issue, as in the hard assignment.  A softmax pass of its
+// own (it read D and wrote Q back) took 64 us per iteration of 16 x 512x512.
+// The update's sums could be taken here too, as FP64 matrix products of the Q
+// and the features of each wave's pixels, but in another order than the
+// gather's, and one centre in 10^5 then rounds to the other FP32 neighbour.
+template <int WG>
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_soft_assign(
+    SoftImg s, const float4* __restrict__ packed, const float* __restrict__ theta_prev,
+    float* __restrict__ q, float* __restrict__ fa, float* __restrict__ fb,
+    unsigned short* __restrict__ pmask) {
+    __shared__ SoftItem<WG> sh;
     const int item = xcd_remap(blockIdx.x, gridDim.x);
     const int bc = item / s.spl, slice = item - bc * s.spl;
     const int b = bc / s.K, cell = bc - b * s.K;
@@ -151,121 +143,130 @@ __global__ __launch_bounds__(WG) void k_soft_assign(SoftImg s, const float4* __r
     const int t0 = 64 * (int)((long long)chunks * slice / s.spl);
     const int t1 = min(P, 64 * (int)((long long)chunks * (slice + 1) / s.spl));
     if (t1 <= t0) return;                                       // uniform: an empty slice
-    // columns of the item's pixels: the 8-column strips its range touches
-    int ix0 = x0, ix1 = x1;
-    if (s.spl > 1) {
-        ix0 = x0 + 8 * strip_of(t0, cw, ch);
-        ix1 = min(x1, x0 + 8 * strip_of(t1 - 1, cw, ch) + 8);
-    }
     const float4* __restrict__ img = packed + (long long)b * s.N;
-    load_candidates(s, ci, cj, theta_prev + 5LL * s.K * b, img, sh);
-    if (tid < 9) {                                              // the thread that loaded it
-        SoftCand& c = sh.cand[tid];
-        c.tw = 0;
-        c.tx0 = c.ty0 = c.th = 0;
-        c.rpp = 0;
-        c.mag = 0u;
-        if (c.k >= 0) {
-            const int tx0 = min(ix0, c.cx), ty0 = min(y0, c.cy);
-            const int rwid = max(ix1, c.cx + 1) - tx0, th = max(y1, c.cy + 1) - ty0;
-            const int tw = rwid + (24 - rwid % 16) % 16;        // pitch: 8 (mod 16) entries
-            if ((long long)tw * th <= cap) {
-                c.tx0 = tx0; c.ty0 = ty0; c.tw = tw; c.th = th;
-                c.rpp = WG / tw;
-                c.mag = (0x1000000u + (unsigned)tw - 1u) / (unsigned)tw;
+    const float* __restrict__ cen = theta_prev + 5LL * s.K * b;
+    const Neighbours nb = neighbours_of(s.nx, s.ny, ci, cj);
+    Eqs eqs;
+    eqs.img = img;
+    eqs.W = W;
+    eqs.near = s.near != 0;
+    eqs.lambda = s.lambda;
+    eqs.oml = 1.0f - s.lambda;
+    eqs.gamma = s.gamma;
+    eqs.spw = s.spw;
+    const int k0 = (ci - 1) * s.nx + cj - 1;
+    const long long base = 9LL * s.N * b;
+    // D of pixel (px, py) with texel fp to slot j, its factors saved unless the
+    // walk was cut
+    auto distance = [&](int j, float4 fp, int px, int py, bool cut, float thr) -> float {
+        const int di = (j * 11) >> 5;                           // j / 3 for j <= 8
+        const float* cp = cen + 5 * (k0 + di * s.nx + (j - 3 * di));
+        const float ck[5] = {cp[0], cp[1], cp[2], cp[3], cp[4]};
+        float A, B;
+        const float D = path_distance(eqs, ck, fp, round_coord(ck[3], W - 1),
+                                      round_coord(ck[4], H - 1), px, py, cut, thr, A, B);
+        if (D < INFINITY) {
+            const long long o = base + (long long)j * s.N + (long long)py * W + px;
+            fa[o] = A;
+            fb[o] = B;
+        }
+        return D;
+    };
+    auto limit = [&](float best) -> float {
+        return fmaxf((best + 111.0f * (float)s.temp) * (1.0f + 0x1p-15f), 0x1p-70f);
+    };
+    if (tid == 0) sh.pairs = sh.multis = 0;
+    __syncthreads();
+    const bool prune = s.prune != 0;
+    const bool mine = tid < t1 - t0;
+    int px = 0, py = 0, first = 9;
+    float D = INFINITY;
+    bool again = false;
+    if (mine) {
+        pixel_at(pixel_map(s.dper, cw, ch), t0 + tid, px, py);
+        px += x0;
+        py += y0;
+        unsigned key[9];
+        const float4 fp = img[py * W + px];
+        bound_keys(nb, (ConstF)(uintptr_t)cen, s.spw, fp, px, py, s.lambda, key);
+        unsigned nk = next_key(key, kNoKey);
+        first = (int)(nk & 15u);
+        D = distance(first, fp, px, py, false, 0.0f);
+        const float best = D < INFINITY ? D : INFINITY;         // NaN: nothing is known
+        const float thr = limit(best);
+        for (;;) {
+            nk = next_key(key, nk);
+            const bool more = nk != kNoKey && !(prune && key_bound(nk) > thr);
+            const unsigned long long m = __ballot(more);
+            if (m == 0ULL) break;                               // uniform over the lanes still here
+            const int at = wave_claim(&sh.pairs, m);
+            if (!more) break;
+            sh.list[at] = (unsigned short)(tid | ((nk & 15u) << 10));
+            again = true;
+        }
+        const unsigned long long m = __ballot(again);
+        if (m != 0ULL) {
+            const int at = wave_claim(&sh.multis, m);
+            if (again) {
+                sh.multi[at] = (unsigned short)tid;
+                sh.best[tid] = best;
             }
         }
     }
-    const bool mine = tid < t1 - t0;
-    int x = 0, y = 0;
-    if (mine) {
-        cell_pixel(t0 + tid, cw, ch, x, y);
-        x += x0;
-        y += y0;
-    }
-    const int p = y * W + x;
+    // the D walked so far; or Q, where there is one walk only
+    const float rest = again ? INFINITY : 0.0f;
+    const float one = again ? D : (D < INFINITY ? 1.0f : 0.0f);
+#pragma unroll
+    for (int j = 0; j < 9; ++j) sh.D[j][tid] = j == first ? one : rest;
+    sh.xy[tid] = make_int2(px, py);
     __syncthreads();
-    const float lambda = s.lambda, oml = 1.0f - lambda;
-    const long long base = 9LL * s.N * b + p;
-    int buf = 0;
-    // Exact pruning: D >= LB = fl(fl(lambda dcp) + fl(ds spw)) (the hard
-    // kernel's bound), and the softmax gives a slot Q = 0 exactly when
-    // (D - Dmin) / T > 110 in FP64; Dmin <= best, the smallest D computed so
-    // far, and both FP64 steps are monotone, so a slot with
-    // (LB - best) / T > 110 gets Q = 0 whatever its walk would give: its D is
-    // written as +inf (the softmax maps it to 0) and its saved factors are not
-    // written (the backward reads them only where dL/dD, a multiple of Q, is
-    // not 0; slots outside the grid likewise).
-    // The own cell is visited first, then the edge neighbours, then the
-    // corners; each slot is written separately, so the order changes nothing.
-    const float4 fown = mine ? img[p] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    float best = INFINITY;
-    constexpr unsigned long long kOrder = 0x862075314ULL;   // slots 4, 1, 3, 5, 7, 0, 2, 6, 8
-#pragma unroll 1
-    for (int t = 0; t < 9; ++t) {
-        const int j = (int)((kOrder >> (4 * t)) & 15ULL);
-        const int k = sh.cand[j].k;
-        const long long o = base + (long long)j * s.N;
-        if (k < 0) continue;                                    // uniform
-        const float l = sh.cand[j].l, a = sh.cand[j].a, bb = sh.cand[j].b;
-        const int cx = sh.cand[j].cx, cy = sh.cand[j].cy;
-        const int tx0 = sh.cand[j].tx0, ty0 = sh.cand[j].ty0, tw = sh.cand[j].tw;
-        const bool staged = tw > 0;
-        float2* tab = tabs + (buf ? cap : 0);
-        if (staged) {                                           // uniform
-            const int rpp = sh.cand[j].rpp;
-            if (rpp > 0)                                        // uniform
-                fill_table_cols<WG>(tab, img, W, tx0, ty0, tw, sh.cand[j].th, rpp,
-                                    sh.cand[j].mag, l, a, bb);
-            else
-                fill_table<WG>(tab, img, W, tx0, ty0, tw, tw * sh.cand[j].th, l, a, bb);
-            __syncthreads();
-            buf ^= 1;
+    const int pairs = __builtin_amdgcn_readfirstlane(sh.pairs);
+    const bool cut = prune && s.gamma <= 0x1p40f;
+    for (int i = tid; i < pairs; i += WG) {
+        const unsigned e = sh.list[i];
+        const int id = (int)(e & 1023u), j = (int)(e >> 10);
+        const int2 xy = sh.xy[id];
+        sh.D[j][id] = distance(j, img[xy.y * W + xy.x], xy.x, xy.y, cut, limit(sh.best[id]));
+    }
+    __syncthreads();
+    // Q_pj = softmax_j(-D_pj / T) in FP64, rounded once to FP32 (the FP32
+    // distances differ by far more than FP32's exponent range allows at small
+    // T).  A slot with (D - Dmin) / T > 110 has exp < 2^-158: added to the sum
+    // (at least 1, the minimum's term) it changes nothing in FP64, and its Q
+    // rounds to 0 in FP32, so neither the exponential nor the quotient is
+    // computed (same results, most slots at low T).
+    if (tid < sh.multis) {
+        const int id = (int)sh.multi[tid];
+        float v[9], dmin = INFINITY;
+#pragma unroll
+        for (int j = 0; j < 9; ++j) {
+            v[j] = sh.D[j][id];
+            dmin = fminf(dmin, v[j]);
         }
-        if (!mine) continue;
-        const float dcc = sh.cand[j].dcc, wc = sh.cand[j].wc;
-        const float ccx = sh.cand[j].x, ccy = sh.cand[j].y;
-        const float ex = (float)x - ccx, ey = (float)y - ccy;
-        const float ds = ex * ex + ey * ey;
-        const float lb = lambda * colour_dist(fown, l, a, bb) + ds * s.spw;
-        if (s.prune && ((double)lb - (double)best) / s.temp > 110.0) {
-            q[o] = INFINITY;
-            continue;
+        double e[9], sum = 0.0;
+#pragma unroll
+        for (int j = 0; j < 9; ++j) {
+            e[j] = 0.0;
+            if (v[j] < INFINITY) {
+                const double t = ((double)v[j] - (double)dmin) / s.temp;
+                if (t <= 110.0) e[j] = exp(-t);
+            }
+            sum += e[j];
         }
-        const int dx = cx - x, dy = cy - y;
-        const int adx = dx < 0 ? -dx : dx, ady = dy < 0 ? -dy : dy;
-        const int n = adx > ady ? adx : ady;
-        const double inv = path_recip(n);
-        float dcp, sc, sw;
-        if (staged) {
-            const int lidx = (y - ty0) * tw + (x - tx0);
-            const float2 e0 = tab[lidx];
-            dcp = e0.x;
-            sc = dcp;
-            sw = e0.y;
-            walk_table(tab, lidx, tw, dx, dy, sc, sw);
-        } else {
-            const float4 fp = img[p];
-            dcp = colour_dist(fp, l, a, bb);
-            sc = dcp;
-            sw = fp.w;
-            walk_path(img, p, 1, W, dx, dy, l, a, bb, sc, sw);
+#pragma unroll
+        for (int j = 0; j < 9; ++j) sh.D[j][id] = e[j] == 0.0 ? 0.0f : (float)(e[j] / sum);
+    }
+    __syncthreads();
+    if (mine) {
+        unsigned mask = 0;
+        const long long o = base + (long long)py * W + px;
+#pragma unroll
+        for (int j = 0; j < 9; ++j) {
+            const float Q = sh.D[j][tid];
+            q[o + (long long)j * s.N] = Q;
+            mask |= Q != 0.0f ? 1u << j : 0u;
         }
-        if (n > 0) {
-            sc = sc + dcc;
-            sw = sw + wc;
-        }
-        float qc, qw;
-        div_path_len(sc, sw, n, inv, qc, qw);
-        const float A = lambda * dcp + oml * qc;
-        const float Bw = 1.0f + s.gamma * qw;
-        const float D = A * Bw + ds * s.spw;
-        best = fminf(best, D);
-        // D goes to the Q buffer (k_soft_softmax turns it into Q); A and B
-        // go straight to the saved factors
-        q[o] = D;
-        fa[o] = A;
-        fb[o] = Bw;
+        pmask[(long long)b * s.N + (long long)py * W + px] = (unsigned short)mask;
     }
 }
 
@@ -276,43 +277,6 @@ __global__ __launch_bounds__(WG) void k_soft_assign(SoftImg s, const float4* __r
     const int x = blockIdx.x * 256 + threadIdx.x;                            \
     for (int y = blockIdx.y; y < (s).H; y += gridDim.y)                      \
         if (x < (s).W)
-
-// Q_pj = softmax_j(-D_pj / T) in FP64 over the slots inside the grid, rounded
-// once to FP32 (the FP32 distances differ by far more than FP32's exponent
-// range allows at small T).  In place over the D values.  A separate kernel
-// so that the FP64 exponentials do not raise the register count of the path
-// walk.
-__global__ __launch_bounds__(256) void k_soft_softmax(SoftImg s, float* __restrict__ q) {
-    SOFT_FOR_PIXELS(s) {
-        const long long p = (long long)y * s.W + x;
-        const int ci = cell_of(y, s.ny, s.H), cj = cell_of(x, s.nx, s.W);
-        const long long base = 9LL * s.N * b + p;
-        float D[9];
-        bool ok[9];
-        float dmin = INFINITY;
-#pragma unroll
-        for (int j = 0; j < 9; ++j) {
-            const int ii = ci + j / 3 - 1, jj = cj + j % 3 - 1;
-            ok[j] = ii >= 0 && ii < s.ny && jj >= 0 && jj < s.nx;
-            D[j] = ok[j] ? q[base + (long long)j * s.N] : INFINITY;
-            dmin = fminf(dmin, D[j]);
-        }
-        // a slot with (D - Dmin) / T > 110 has exp < 2^-158: added to the sum
-        // (at least 1, the minimum's term) it changes nothing in FP64, and its
-        // Q rounds to 0 in FP32, so neither the exponential nor the quotient
-        // is computed (same results, most slots at low T)
-        double e[9], sum = 0.0;
-#pragma unroll
-        for (int j = 0; j < 9; ++j) {
-            const double t = ((double)D[j] - (double)dmin) / s.temp;
-            e[j] = ok[j] && t <= 110.0 ? exp(-t) : 0.0;
-            sum += e[j];
-        }
-#pragma unroll
-        for (int j = 0; j < 9; ++j)
-            q[base + (long long)j * s.N] = e[j] == 0.0 ? 0.0f : (float)(e[j] / sum);
-    }
-}
 
 template <int WG>
 __device__ __forceinline__ void block_sum6(double (&v)[6], double (*red)[WG]) {
@@ -332,6 +296,7 @@ __device__ __forceinline__ void block_sum6(double (&v)[6], double (*red)[WG]) {
 // under which it sees k.
 template <int WG>
 __global__ __launch_bounds__(WG) void k_soft_update(SoftImg s, const float* __restrict__ q,
+                                                    const unsigned short* __restrict__ pmask,
                                                     const float4* __restrict__ packed,
                                                     const float* __restrict__ theta_prev,
                                                     float* __restrict__ theta_next,
@@ -345,6 +310,7 @@ __global__ __launch_bounds__(WG) void k_soft_update(SoftImg s, const float* __re
     const int bw = X1 - X0, area = bw * (Y1 - Y0);
     const float4* img = packed + (long long)b * s.N;
     const float* qb = q + 9LL * s.N * b;
+    const unsigned short* pm = pmask + (long long)b * s.N;
     // the block's inner cell boundaries: a pixel's cell row is ci - 1 + (y >= yb1)
     // + (y >= yb2), likewise for columns
     const int yb1 = cell_lo(ci, s.H, s.ny), yb2 = cell_lo(ci + 1, s.H, s.ny);
@@ -353,14 +319,14 @@ __global__ __launch_bounds__(WG) void k_soft_update(SoftImg s, const float* __re
     // element e = r * bw + c; lanes step by WG elements = (dr rows, dc columns)
     const int dr = WG / bw, dc = WG - dr * bw;
     int r = tid / bw, c = tid - r * bw;
-    // kU elements per trip (e, e + WG, ...: the thread's order is unchanged),
-    // their Q loads issued first; a texel is read only where its Q is not 0
-    // (at low T most slots underflow to 0, and 0 * f adds exactly nothing)
-    constexpr int kU = 4;
+    // kU elements per trip (e, e + WG, ...), their masks loaded first; a Q is
+    // read only where its mask says that it is not 0 (at low T one slot in
+    // eight; 0 * f adds exactly nothing), and a texel only with it
+    constexpr int kU = 8;
     for (int e = tid; e < area; e += kU * WG) {
-        int xs[kU], ys[kU];
-        long long ps[kU];
-        double Qs[kU];
+        int xs[kU], ys[kU], js[kU];
+        unsigned ms[kU];
+        float Qs[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             xs[u] = X0 + c;
@@ -371,15 +337,18 @@ __global__ __launch_bounds__(WG) void k_soft_update(SoftImg s, const float* __re
             r += dr + (wrap ? 1 : 0);
             const int di = (ys[u] >= yb1 ? 1 : 0) + (ys[u] >= yb2 ? 1 : 0);
             const int dj = (xs[u] >= xb1 ? 1 : 0) + (xs[u] >= xb2 ? 1 : 0);
-            const int j = (2 - di) * 3 + (2 - dj);  // the pixel's slot that points at k
-            ps[u] = (long long)ys[u] * s.W + xs[u];
-            Qs[u] = e + u * WG < area ? (double)qb[(long long)j * s.N + ps[u]] : 0.0;
+            js[u] = (2 - di) * 3 + (2 - dj);        // the pixel's slot that points at k
+            ms[u] = e + u * WG < area ? pm[ys[u] * s.W + xs[u]] : 0u;
         }
 #pragma unroll
+        for (int u = 0; u < kU; ++u)
+            Qs[u] = (ms[u] >> js[u]) & 1u
+                        ? qb[(long long)js[u] * s.N + (ys[u] * s.W + xs[u])] : 0.0f;
+#pragma unroll
         for (int u = 0; u < kU; ++u) {
-            if (Qs[u] == 0.0) continue;
-            const double Q = Qs[u];
-            const float4 f = img[ps[u]];
+            if (Qs[u] == 0.0f) continue;
+            const double Q = (double)Qs[u];
+            const float4 f = img[ys[u] * s.W + xs[u]];
             acc[0] += Q;
             acc[1] += Q * f.x;
             acc[2] += Q * f.y;
@@ -428,6 +397,7 @@ __global__ void k_soft_bwd_cand(SoftImg s, const double* __restrict__ z,
 // dL/df_p += Q_pk u[0..2].
 __global__ __launch_bounds__(256) void k_soft_bwd_update(SoftImg s, int first,
                                                          const float* __restrict__ q,
+                                                         const unsigned short* __restrict__ pmask,
                                                          const float4* __restrict__ cand,
                                                          const float4* __restrict__ packed,
                                                          const float* __restrict__ gq_in,
@@ -444,8 +414,10 @@ __global__ __launch_bounds__(256) void k_soft_bwd_update(SoftImg s, int first,
         const float4* cb = cand + 2LL * s.K * b;
         float Q[9], G[9];
         float gfl = 0.0f, gfa = 0.0f, gfb = 0.0f, dot = 0.0f;
+        const unsigned nz = pmask[i];              // which Q are not 0
 #pragma unroll
-        for (int j = 0; j < 9; ++j) Q[j] = q[qb + (long long)j * s.N];
+        for (int j = 0; j < 9; ++j)
+            Q[j] = (nz >> j) & 1u ? q[qb + (long long)j * s.N] : 0.0f;
         // a slot with Q_pj = 0 adds nothing to the softmax dot product, to
         // dL/df or to dL/dD (Q_pj < 2^-24): its dL/dQ and candidate terms
         // are not loaded
@@ -628,7 +600,6 @@ __global__ __launch_bounds__(WG, 4) void k_soft_bwd_path(SoftImg s, const float4
         c.l = cl; c.a = ca; c.b = cb; c.x = cxf; c.y = cyf;
         c.cx = ck >= 0 ? round_coord(cxf, W - 1) : 0;
         c.cy = ck >= 0 ? round_coord(cyf, H - 1) : 0;
-        c.dcc = c.wc = 0.0f;   // not used by this pass
         sh.cand[tid] = c;
     }
     __syncthreads();
@@ -997,6 +968,11 @@ static SoftImg to_img(const SoftGeom& g) {
     s.W = g.W; s.H = g.H; s.nx = g.nx; s.ny = g.ny; s.K = g.nx * g.ny; s.B = g.B;
     s.N = (long long)g.W * g.H;
     s.spl = soft_slices(g.W, g.H, g.nx, g.ny, g.wg);
+    s.near = s.N < (1LL << 28) && g.W + g.H < 46340;
+    for (int i = 0; i < 2; ++i) {
+        const long long ch = g.H / g.ny + i, cw = g.W / g.nx + 1;
+        s.dper[i] = fast_div(8 * ch, cw * ch);
+    }
     s.spw = g.spw; s.gamma = g.gamma; s.lambda = g.lambda; s.inv_t = 1.0f / g.temperature;
     s.temp = (double)g.temperature;
     s.prune = g.prune;
@@ -1004,14 +980,6 @@ static SoftImg to_img(const SoftGeom& g) {
 }
 
 void lift_soft_lds_limits() {
-    const size_t cap = 160 * 1024 - sizeof(SoftShared) - 64;
-    for (const void* k : {reinterpret_cast<const void*>(k_soft_assign<256>),
-                          reinterpret_cast<const void*>(k_soft_assign<512>),
-                          reinterpret_cast<const void*>(k_soft_assign<1024>)}) {
-        static_cast<void>(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                              (int)cap));
-        static_cast<void>(hipGetLastError());
-    }
     static_cast<void>(hipFuncSetAttribute(
         reinterpret_cast<const void*>(k_soft_bwd_path<kSoftBwdWG>),
         hipFuncAttributeMaxDynamicSharedMemorySize, kBwdLdsBytes));
@@ -1027,40 +995,38 @@ int launch_soft_init(const SoftGeom& g, const float4* packed, float* theta0, hip
 
 template <int WG>
 static int soft_assign_t(const SoftImg& s, const float4* packed, const float* theta_prev, float* q,
-                         float* fa, float* fb, int cap, hipStream_t st) {
-    hipLaunchKernelGGL(k_soft_assign<WG>, dim3(s.B * s.K * s.spl), dim3(WG), (size_t)cap * sizeof(float4),
-                       st, s, packed, theta_prev, q, fa, fb, cap);
+                         float* fa, float* fb, unsigned short* pmask, hipStream_t st) {
+    hipLaunchKernelGGL(k_soft_assign<WG>, dim3(s.B * s.K * s.spl), dim3(WG), 0, st, s, packed,
+                       theta_prev, q, fa, fb, pmask);
     return hipGetLastError();
 }
 
 int launch_soft_assign(const SoftGeom& g, const float4* packed, const float* theta_prev, float* q,
-                       float* fa, float* fb, int cap, hipStream_t st) {
+                       float* fa, float* fb, unsigned short* pmask, hipStream_t st) {
     const SoftImg s = to_img(g);
-    int e;
-    if (g.wg == 1024) e = soft_assign_t<1024>(s, packed, theta_prev, q, fa, fb, cap, st);
-    else if (g.wg == 512) e = soft_assign_t<512>(s, packed, theta_prev, q, fa, fb, cap, st);
-    else e = soft_assign_t<256>(s, packed, theta_prev, q, fa, fb, cap, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_soft_softmax, pixel_grid(s), dim3(256), 0, st, s, q);
+    if (g.wg == 1024) return soft_assign_t<1024>(s, packed, theta_prev, q, fa, fb, pmask, st);
+    if (g.wg == 512) return soft_assign_t<512>(s, packed, theta_prev, q, fa, fb, pmask, st);
+    return soft_assign_t<256>(s, packed, theta_prev, q, fa, fb, pmask, st);
+}
+
+int launch_soft_update(const SoftGeom& g, const float* q, const unsigned short* pmask,
+                       const float4* packed, const float* theta_prev, float* theta_next, double* z,
+                       hipStream_t st) {
+    const SoftImg s = to_img(g);
+    hipLaunchKernelGGL(k_soft_update<kSoftWG>, dim3(s.B * s.K), dim3(kSoftWG), 0, st, s, q, pmask,
+                       packed, theta_prev, theta_next, z);
     return hipGetLastError();
 }
 
-int launch_soft_update(const SoftGeom& g, const float* q, const float4* packed,
-                       const float* theta_prev, float* theta_next, double* z, hipStream_t st) {
-    const SoftImg s = to_img(g);
-    hipLaunchKernelGGL(k_soft_update<kSoftWG>, dim3(s.B * s.K), dim3(kSoftWG), 0, st, s, q, packed,
-                       theta_prev, theta_next, z);
-    return hipGetLastError();
-}
-
-int launch_soft_bwd_update(const SoftGeom& g, int first, const float* q, const double* z,
+int launch_soft_bwd_update(const SoftGeom& g, int first, const float* q,
+                           const unsigned short* pmask, const double* z,
                            const float* theta, const float4* packed, const double* gth,
                            const float* gq_in, float* gd, unsigned short* gmask, float4* gf,
                            float4* cand, hipStream_t st) {
     const SoftImg s = to_img(g);
     hipLaunchKernelGGL(k_soft_bwd_cand, dim3(grid_for((long long)s.B * s.K)), dim3(256), 0, st, s,
                        z, theta, gth, cand);
-    hipLaunchKernelGGL(k_soft_bwd_update, pixel_grid(s), dim3(256), 0, st, s, first, q, cand,
+    hipLaunchKernelGGL(k_soft_bwd_update, pixel_grid(s), dim3(256), 0, st, s, first, q, pmask, cand,
                        packed, gq_in, gd, gmask, gf);
     return hipGetLastError();
 }
