@@ -303,10 +303,11 @@ int scalp_soft_forward(const scalp_grid_t* g, const scalp_params_t* p, float tem
  * (grad_centers: [B][K'][5]) with respect to lab (grad_lab: [B][H][W][3],
  * output) and contour (grad_contour: [B][H][W], output).  Path samples are
  * recomputed, not stored; slots whose Q is below 2^-24 contribute no path
- * terms (each is proportional to Q).  Per cell, each slot's per-sample
- * weights go to an LDS tile over the box of its walked paths (FP64, at most
- * min(16 lds_pixels, 58 KiB) bytes of tiles in all); a slot whose tile does
- * not fit scatters to global memory instead.  contour is always required (dw/dC
+ * terms (each is proportional to Q).  Per superpixel, the per-sample weights
+ * of the paths to it go to LDS tiles over their box (FP64 and FP32, at most
+ * min(16 lds_pixels, 60 KiB) bytes, the paths taken in parts where their box
+ * is larger); what does not fit scatters to global memory instead.
+ * contour is always required (dw/dC
  * needs it); lab may be null when reuse_prepared is set and the workspace
  * holds the packed image of the forward call.  FP32 with float atomics, the
  * centre gradients summed in FP64: not bit-reproducible. */

@@ -735,6 +735,26 @@ __device__ __forceinline__ float wave_sum_last(float v) {
     return v;
 }
 
+// Sum over the lanes up to and including this one, in six DPP steps (see
+// wave_sum_last).  All lanes must be active.
+__device__ __forceinline__ int wave_scan_incl(int v) {
+#define SCALP_SCAN_STEP(ctrl, rows) \
+    v += __builtin_amdgcn_update_dpp(0, v, ctrl, rows, 0xf, false)
+    SCALP_SCAN_STEP(0x111, 0xf);
+    SCALP_SCAN_STEP(0x112, 0xf);
+    SCALP_SCAN_STEP(0x114, 0xf);
+    SCALP_SCAN_STEP(0x118, 0xf);
+    SCALP_SCAN_STEP(0x142, 0xa);
+    SCALP_SCAN_STEP(0x143, 0xc);
+#undef SCALP_SCAN_STEP
+    return v;
+}
+
+__device__ __forceinline__ double wave_sum_f64(double v) {
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
 // Minimum and maximum over the 64 lanes of a wave (all lanes active), the
 // same value in every lane.
 __device__ __forceinline__ int wave_min_i32(int v) {

@@ -162,24 +162,25 @@ int launch_soft_assign(const SoftGeom& g, const float4* packed, const float* the
 int launch_soft_update(const SoftGeom& g, const float* q, const unsigned short* pmask,
                        const float4* packed, const float* theta_prev, float* theta_next, double* z,
                        hipStream_t st);
-// cand: scratch of 2 * B * K float4 (per-superpixel terms of the update backward);
-// gd receives the nonzero dL/dD only, gmask ([B][N]) which of the 9 slots they are
+// Backward.  cand: 2 * B * K float4, per superpixel the terms of the update
+// backward; pairs: [B][9][N] (pixel, dL/dD) lists, count: their lengths, 9 per
+// (image, cell, slice); gth, gth_prev (dL/dTheta) are FP64; z_prev: masses of
+// the iteration before (null in the first); cap_bytes: LDS tile budget.
+int soft_bwd_slices(int W, int H, int nx, int ny);
+int launch_soft_bwd_start(const SoftGeom& g, const float* grad_theta, const double* z,
+                          const float* theta, double* gth, float4* cand, hipStream_t st);
 int launch_soft_bwd_update(const SoftGeom& g, int first, const float* q,
-                           const unsigned short* pmask, const double* z,
-                           const float* theta, const float4* packed, const double* gth,
-                           const float* gq_in, float* gd, unsigned short* gmask, float4* gf,
-                           float4* cand, hipStream_t st);
-int launch_soft_bwd_pass(const SoftGeom& g, const double* z, const double* gth, double* gth_prev,
-                         hipStream_t st);
-// dL/dTheta (gth, gth_prev, gth0) is FP64; cap_bytes: LDS tile budget of the path pass
+                           const unsigned short* pmask, const float4* packed, const float* gq_in,
+                           const float4* cand, uint2* pairs, int* count, float4* gf,
+                           hipStream_t st);
 int launch_soft_bwd_path(const SoftGeom& g, const float4* packed, const float* theta_prev,
-                         const float* fa, const float* fb, const float* gd,
-                         const unsigned short* gmask, float4* gf, double* gth_prev,
-                         int cap_bytes, hipStream_t st);
+                         const float* fa, const float* fb, const uint2* pairs, const int* count,
+                         const double* z, const double* gth, const double* z_prev,
+                         double* gth_prev, float4* cand, float4* gf, int cap_bytes,
+                         hipStream_t st);
 int launch_soft_bwd_finish(const SoftGeom& g, const float4* gf, const double* gth0,
                            const float* contour, float sigma, float* glab, float* gcon,
                            hipStream_t st);
-int launch_widen_f32(const float* src, double* dst, long long n, hipStream_t st);
 
 // ---- per-pixel maps (scalp_maps.hip)
 int launch_boundary_frequency(int W, int H, int n, const int* labels, float* out, hipStream_t s);

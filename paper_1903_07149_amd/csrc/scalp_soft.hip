@@ -18,14 +18,15 @@
 //                  0 over the 3x3 cell block in a fixed order (FP64 partial
 //                  sums, tree reduction): deterministic, no atomics.
 // Backward, per iteration in reverse:
-//   k_soft_bwd_update  thread per pixel: soft-update and softmax backward,
-//                      giving dL/dD for the 9 slots.
-//   k_soft_bwd_path    workgroup per (image, cell): every (pixel, slot) with a
-//                      nonzero dL/dD re-walks its path (samples are recomputed,
+//   k_soft_bwd_update  workgroup per (image, cell, slice): soft-update and
+//                      softmax backward of its pixels, and, per slot, the list
+//                      of the (pixel, dL/dD) that are not 0.
+//   k_soft_bwd_path    workgroup per (image, superpixel): re-walks the paths of
+//                      the pixels listed under it (samples are recomputed,
 //                      never stored), adding the path's two per-sample weights
-//                      into LDS tiles; a fold over the tiles then forms dL/df,
-//                      dL/dw and the candidates' centre gradients (FP64), which
-//                      leave the workgroup as atomics (not bit-reproducible).
+//                      into LDS tiles; a fold over the tiles then forms dL/df
+//                      and dL/dw (float atomics: not bit-reproducible) and the
+//                      superpixel's centre gradient (FP64).
 #include <algorithm>
 
 #include "scalp_device.h"
@@ -43,6 +44,8 @@ struct SoftImg {
     double temp;
     int prune;   // 1: skip the walks of slots whose softmax weight is provably 0
     int near;    // 32-bit byte offsets reach every texel of an image
+    int bspl;    // slices of a cell in the backward's lists
+    double inv_w;      // 1 / W
     FastDiv dper[2];   // 8 x the two cell heights (see PixelMap)
 };
 
@@ -52,16 +55,6 @@ constexpr double kZMin = 1e-6;
 
 // Softmax weight below which a slot's path terms are left out of the backward.
 constexpr float kQMin = 0x1p-24f;
-
-struct SoftCand {
-    int k;
-    float l, a, b, x, y;
-    int cx, cy;
-};
-
-struct SoftShared {
-    SoftCand cand[9];
-};
 
 // ------------------------------------------------------------------ forward
 
@@ -371,529 +364,470 @@ __global__ __launch_bounds__(WG) void k_soft_update(SoftImg s, const float* __re
 // u = dL/dTheta_k / Z_k (5 values) and v = u . Theta_k, all zero when Z_k is
 // below kZMin (such a superpixel kept its centre and passes no gradient to
 // Q or f).
-__global__ void k_soft_bwd_cand(SoftImg s, const double* __restrict__ z,
-                                const float* __restrict__ theta, const double* __restrict__ gth,
-                                float4* __restrict__ cand) {
+__device__ __forceinline__ void store_cand(double Z, const double (&g)[5],
+                                           const float* __restrict__ theta,
+                                           float4* __restrict__ cand) {
+    float u[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    float v = 0.0f;
+    if (Z >= kZMin) {
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+            u[c] = (float)(g[c] / Z);
+            v += u[c] * theta[c];
+        }
+    }
+    cand[0] = make_float4(u[0], u[1], u[2], u[3]);
+    cand[1] = make_float4(u[4], v, 0.0f, 0.0f);
+}
+
+// dL/dTheta_T from the caller, in FP64, and the terms of the first update.
+__global__ void k_soft_bwd_start(SoftImg s, const float* __restrict__ grad_theta,
+                                 const double* __restrict__ z, const float* __restrict__ theta,
+                                 double* __restrict__ gth, float4* __restrict__ cand) {
     const long long total = (long long)s.B * s.K;
     for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
          i += (long long)gridDim.x * blockDim.x) {
-        float u[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-        float v = 0.0f;
-        const double Zd = z[i];
-        if (Zd >= kZMin) {
-            for (int c = 0; c < 5; ++c) {
-                u[c] = (float)(gth[5 * i + c] / Zd);
-                v += u[c] * theta[5 * i + c];
-            }
+        double g[5];
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+            g[c] = (double)grad_theta[5 * i + c];
+            gth[5 * i + c] = g[c];
         }
-        cand[2 * i] = make_float4(u[0], u[1], u[2], u[3]);
-        cand[2 * i + 1] = make_float4(u[4], v, 0.0f, 0.0f);
+        store_cand(z[i], g, theta + 5 * i, cand + 2 * i);
     }
 }
 
-// Soft-update backward (theta_t = sum Q feat / Z) and softmax backward:
-// gd[j] = dL/dD_pj (0 where Q_pj < kQMin).  gf += dL/df_p through the update.
-// With u, v of k_soft_bwd_cand: dL/dQ_pk += u . feat_p - v and
-// dL/df_p += Q_pk u[0..2].
-__global__ __launch_bounds__(256) void k_soft_bwd_update(SoftImg s, int first,
-                                                         const float* __restrict__ q,
-                                                         const unsigned short* __restrict__ pmask,
-                                                         const float4* __restrict__ cand,
-                                                         const float4* __restrict__ packed,
-                                                         const float* __restrict__ gq_in,
-                                                         float* __restrict__ gd,
-                                                         unsigned short* __restrict__ gmask,
-                                                         float4* __restrict__ gf) {
-    SOFT_FOR_PIXELS(s) {
-        const long long p = (long long)y * s.W + x;
+// Pixels [t0, t1) of slice `slice` of a cell of P pixels in the backward's
+// lists, in whole 64-pixel chunks.
+__device__ __forceinline__ void bwd_slice(const SoftImg& s, int P, int slice, int& t0, int& t1) {
+    const int chunks = (P + 63) >> 6;
+    t0 = 64 * (int)((long long)chunks * slice / s.bspl);
+    t1 = min(P, 64 * (int)((long long)chunks * (slice + 1) / s.bspl));
+}
+
+constexpr int kUpdateWG = 256;
+
+// Soft-update backward (theta_t = sum Q feat / Z) and softmax backward of the
+// pixels of a slice of a cell: dL/dD_pj (0 where Q_pj < kQMin), and gf +=
+// dL/df_p through the update.  With u, v of store_cand: dL/dQ_pk += u . feat_p
+// - v and dL/df_p += Q_pk u[0..2].  The cell's 9 candidates are uniform, so
+// their u, v come through the scalar cache.  The dL/dD that are not 0 (one
+// pixel in ten at low T) are listed per slot as (pixel, value), in no
+// particular order, from entry 9 N b + j N + (pixels of the cells before, in
+// cell order) + t0 on, and counted: the path pass finds what it walks without
+// a search.  first: gf is written, not added to.
+__global__ __launch_bounds__(kUpdateWG) void k_soft_bwd_update(
+    SoftImg s, int first, const float* __restrict__ q, const unsigned short* __restrict__ pmask,
+    const float4* __restrict__ cand, const float4* __restrict__ packed,
+    const float* __restrict__ gq_in, uint2* __restrict__ pairs, int* __restrict__ count,
+    float4* __restrict__ gf) {
+    __shared__ int cnt[9];
+    const int tid = threadIdx.x;
+    const int item = xcd_remap(blockIdx.x, gridDim.x);
+    const int bc = item / s.bspl, slice = item - bc * s.bspl;
+    const int b = bc / s.K, cell = bc - b * s.K;
+    const int W = s.W, H = s.H;
+    const int ci = cell / s.nx, cj = cell - ci * s.nx;
+    const int x0 = cell_lo(cj, W, s.nx), cw = cell_lo(cj + 1, W, s.nx) - x0;
+    const int y0 = cell_lo(ci, H, s.ny), ch = cell_lo(ci + 1, H, s.ny) - y0;
+    int t0, t1;
+    bwd_slice(s, cw * ch, slice, t0, t1);
+    if (tid < 9) cnt[tid] = 0;
+    __syncthreads();
+    const Neighbours nb = neighbours_of(s.nx, s.ny, ci, cj);
+    const ConstF cb = (ConstF)(uintptr_t)(cand + 2LL * s.K * b);
+    const PixelMap pm = pixel_map(s.dper, cw, ch);
+    const long long base = 9LL * s.N * b;
+    uint2* __restrict__ list = pairs + base + ((long long)y0 * W + (long long)x0 * ch + t0);
+    for (int t = t0; t < t1; t += kUpdateWG) {                  // uniform
+        const bool mine = t + tid < t1;
+        int x = 0, y = 0;
+        if (mine) {
+            pixel_at(pm, t + tid, x, y);
+            x += x0;
+            y += y0;
+        }
+        const int p = y * W + x;
         const long long i = (long long)b * s.N + p;
-        const int ci = cell_of(y, s.ny, s.H), cj = cell_of(x, s.nx, s.W);
-        const float4 f = packed[i];
-        const float fx = (float)x, fy = (float)y;
-        const long long qb = 9LL * s.N * b + p;
-        const float4* cb = cand + 2LL * s.K * b;
-        float Q[9], G[9];
-        float gfl = 0.0f, gfa = 0.0f, gfb = 0.0f, dot = 0.0f;
-        const unsigned nz = pmask[i];              // which Q are not 0
-#pragma unroll
-        for (int j = 0; j < 9; ++j)
-            Q[j] = (nz >> j) & 1u ? q[qb + (long long)j * s.N] : 0.0f;
         // a slot with Q_pj = 0 adds nothing to the softmax dot product, to
-        // dL/df or to dL/dD (Q_pj < 2^-24): its dL/dQ and candidate terms
-        // are not loaded
+        // dL/df or to dL/dD (Q_pj < 2^-24): its Q, its dL/dQ and its
+        // candidate's terms are not read
+        const unsigned nz = mine ? pmask[i] : 0u;
+        float Q[9], G[9];
 #pragma unroll
         for (int j = 0; j < 9; ++j) {
-            const int ii = ci + j / 3 - 1, jj = cj + j % 3 - 1;
-            G[j] = 0.0f;
-            if (ii < 0 || ii >= s.ny || jj < 0 || jj >= s.nx || Q[j] == 0.0f) continue;
-            if (first) G[j] = gq_in[qb + (long long)j * s.N];
-            const int k = ii * s.nx + jj;
-            const float4 u = cb[2 * k], u4v = cb[2 * k + 1];
-            G[j] += (((u.x * f.x + u.y * f.y) + (u.z * f.z + u.w * fx)) + u4v.x * fy) - u4v.y;
-            gfl += u.x * Q[j];
-            gfa += u.y * Q[j];
-            gfb += u.z * Q[j];
-            dot += Q[j] * G[j];
+            Q[j] = G[j] = 0.0f;
+            if ((nz >> j) & 1u) {
+                Q[j] = q[base + (long long)j * s.N + p];
+                if (first) G[j] = gq_in[base + (long long)j * s.N + p];
+            }
+        }
+        const float4 f = mine ? packed[i] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        const float fx = (float)x, fy = (float)y;
+        float gfl = 0.0f, gfa = 0.0f, gfb = 0.0f, dot = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 9; ++j) {
+            if (__ballot((nz >> j) & 1u) == 0ULL) continue;     // uniform over the wave
+            const ConstF u = cb + 8LL * __builtin_amdgcn_readfirstlane(nb.row[j / 3] + nb.col[j % 3]);
+            const float u0 = u[0], u1 = u[1], u2 = u[2], u3 = u[3], u4 = u[4], v = u[5];
+            if ((nz >> j) & 1u) {
+                G[j] += (((u0 * f.x + u1 * f.y) + (u2 * f.z + u3 * fx)) + u4 * fy) - v;
+                gfl += u0 * Q[j];
+                gfa += u1 * Q[j];
+                gfb += u2 * Q[j];
+                dot += Q[j] * G[j];
+            }
         }
         // A slot's whole path contribution is proportional to Q_pj; below
         // FP32's unit roundoff (2^-24) it is dropped, and the path pass skips
-        // the slot (at low T most pixels have one slot above it).  Only the
-        // nonzero dL/dD are stored; bit j of the pixel's mask says which.
-        unsigned m = 0;
+        // the slot (at low T most pixels have one slot above it).
 #pragma unroll
         for (int j = 0; j < 9; ++j) {
             const float g = Q[j] < kQMin ? 0.0f : -s.inv_t * Q[j] * (G[j] - dot);
-            if (g != 0.0f) {
-                gd[qb + (long long)j * s.N] = g;
-                m |= 1u << j;
-            }
+            const unsigned long long m = __ballot(g != 0.0f);
+            if (m == 0ULL) continue;                            // uniform over the wave
+            const int at = wave_claim(&cnt[j], m);
+            if (g != 0.0f)
+                list[(long long)j * s.N + at] = make_uint2((unsigned)p, __float_as_uint(g));
         }
-        gmask[i] = (unsigned short)m;
-        float4 o = gf[i];
-        o.x += gfl;
-        o.y += gfa;
-        o.z += gfb;
-        gf[i] = o;
+        if (mine) {
+            float4 o = first ? make_float4(0.0f, 0.0f, 0.0f, 0.0f) : gf[i];
+            o.x += gfl;
+            o.y += gfa;
+            o.z += gfb;
+            gf[i] = o;
+        }
     }
+    __syncthreads();
+    if (tid < 9) count[9LL * item + tid] = cnt[tid];
 }
 
-// dL/dTheta_{t-1} starts as the pass-through of superpixels whose soft mass
-// was zero (they kept their previous centre) and receives the path terms.
-__global__ void k_soft_bwd_pass(SoftImg s, const double* __restrict__ z,
-                                const double* __restrict__ gth, double* __restrict__ gth_prev) {
-    const long long total = 5LL * s.B * s.K;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
-         i += (long long)gridDim.x * blockDim.x)
-        gth_prev[i] = z[i / 5] >= kZMin ? 0.0 : gth[i];
-}
+constexpr int kPathWG = 256;
+// Most lists (9 cells x slices) of a superpixel.
+constexpr int kBwdLists = 252;
+// Texels per thread and trip of the fold, their loads in flight together.
+constexpr int kFold = 4;
 
-// Per wave, a list of (pixel, slot) pairs whose dL/dD is not zero, listed
-// chunk by chunk and slot by slot, walked in whole rounds of 64 whenever the
-// next slot would overflow its kBwdBatch entries (the rest carried over);
-// per slot, seven FP64 sums (the centre gradient's five components, the
-// endpoint's two weights) in kBwdCopies copies.
-constexpr int kBwdBatch = 192;
-constexpr int kBwdCopies = 8;
-// Texels per thread and trip of the fold.
-constexpr int kFold = 2;
-
-// Where the backward path pass of one work item keeps its tiles: per slot,
-// the box [bx0, bx1) x [by0, by1) of the pixels whose path to the slot it
-// walks, grown to contain the slot's endpoint, and the offset (in doubles)
-// of the slot's FP64 weight tile over that box (-1: the slot's paths scatter
-// to global memory instead); one FP32 tile of dL/dw over the union of the
-// staged boxes follows the weight tiles.
-struct BwdLayout {
-    int bx0[9], bx1[9], by0[9], by1[9];
-    int has[9];
-    int soff[9];
-    int ux0, uy0, uw, uh;
-    int woff;      // in floats
-};
-
-// One workgroup per (image, cell).  Every (pixel, slot) whose dL/dD is not
-// zero (at low T about one per pixel) re-walks its path.  Along a path to
-// candidate k every sample q receives the same two weights,
+// One workgroup per (image, superpixel k): every pixel whose dL/dD of the slot
+// that points at k is not zero (listed by k_soft_bwd_update under the 9 cells
+// around k) re-walks its path.  Along a path to k every sample q receives the
+// same two weights,
 //   dL/df_q += cf (f_q - f_k)   with cf = dL/dD * B (1 - lambda) 2 / |P|
 //   dL/dw_q += cw               with cw = dL/dD * A gamma / |P|
-// (and p itself dL/dD * B lambda 2 (f_p - f_k)), so the walk only adds cf
-// into an FP64 tile S_k(q) of the slot (p's lambda term included) and cw
-// into the FP32 tile of dL/dw: two LDS atomics per sample and no texel read.
-// A fold over the union of the slots' boxes then forms, per texel,
-// dL/df_q = sum_k S_k(q) (f_q - f_k) from one texel load, and the centre
-// gradient of each candidate, -sum_q S_k(q) (f_q - f_k), in FP64.  The
-// spatial part of the centre gradient and the endpoint's weights (every path
-// to k ends there) are summed per slot and added once.  A first pass over
-// the slot masks of dL/dD sizes the boxes.  Slots whose tiles do not fit the
-// budget walk their paths from global memory instead, reading the texels and
-// scattering the four gradient floats with float atomics.  The centre
-// gradients are summed in FP64 (no FP32 partial sum longer than one path);
-// dL/dTheta leaves as FP64 atomics, dL/df and dL/dw as float atomics (not
-// bit-reproducible).  At least 4 waves per SIMD (at most 128 VGPRs): two 512-lane
-// workgroups per CU, as the LDS budget allows.
+// (and p itself dL/dD * B lambda 2 (f_p - f_k)), so the walk only adds cf into
+// an FP64 tile S(q) (p's lambda term included) and cw into an FP32 tile of
+// dL/dw, over the box of the pixels and k's endpoint: two LDS atomics per
+// sample and no texel read.  A fold over the box then forms, per texel,
+// dL/df_q = S(q) (f_q - f_k) from one texel load, and k's centre gradient,
+// -sum_q S(q) (f_q - f_k), in FP64.  The spatial part of the centre gradient
+// and the endpoint's weights (every path ends there) are summed per lane.
+// Pairs whose box exceeds the tile budget are taken by fewer lists at a time,
+// and a list by halves (it is in the order of the cell's chunks) down to 64; if
+// those still do not fit, their paths are walked from global memory, reading
+// the texels and scattering the four gradient floats with float atomics.  Every centre
+// gradient is summed here, in FP64 (no FP32 partial sum longer than one path),
+// and stored, with the terms that the update of the iteration before needs.
+//
+// What bounds it: the latency of a superpixel's chain of phases, with the tiles
+// limiting a CU to 4 workgroups.  A workgroup per cell, with a tile for each of
+// its 9 candidates and a fold over all of them, took 298 us per iteration of 16
+// x 512x512 against 300 K to 400 K walked pairs (47 to 64 per superpixel).
 template <int WG>
-__global__ __launch_bounds__(WG, 4) void k_soft_bwd_path(SoftImg s, const float4* __restrict__ packed,
-                                                      const float* __restrict__ theta_prev,
-                                                      const float* __restrict__ fa,
-                                                      const float* __restrict__ fb,
-                                                      const float* __restrict__ gd,
-                                                      const unsigned short* __restrict__ gmask,
-                                                      float4* __restrict__ gf,
-                                                      double* __restrict__ gth_prev, int cap_bytes) {
+__global__ __launch_bounds__(WG) void k_soft_bwd_path(
+    SoftImg s, const float4* __restrict__ packed, const float* __restrict__ theta_prev,
+    const float* __restrict__ fa, const float* __restrict__ fb, const uint2* __restrict__ pairs,
+    const int* __restrict__ count, const double* __restrict__ z, const double* __restrict__ gth,
+    const double* __restrict__ z_prev, double* __restrict__ gth_prev, float4* __restrict__ cand,
+    float4* __restrict__ gf, int cap_bytes) {
     extern __shared__ double bwd_dyn[];
-    __shared__ SoftShared sh;
-    __shared__ BwdLayout bl;
-    __shared__ int wl_t[WG / 64][kBwdBatch];              // pixel (see wl_xy) in the cell
-    __shared__ unsigned char wl_j[WG / 64][kBwdBatch];    // slot
-    __shared__ float wl_g[WG / 64][kBwdBatch];            // dL/dD
-    __shared__ double bins[9][7][kBwdCopies];
-    const int item = xcd_remap(blockIdx.x, gridDim.x);
-    const int b = item / s.K, cell = item - b * s.K;
-    const int tid = threadIdx.x;
+    constexpr int kWaves = WG / 64;
+    __shared__ long long lbase[kBwdLists + 4];    // first entry of each list
+    __shared__ int lpre[kBwdLists + 4];           // pairs in the lists before
+    __shared__ int wtot[kWaves];
+    __shared__ int wbox[4][kWaves];
+    __shared__ float4 turn[kWaves][64];
+    __shared__ double red[5][kWaves];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int W = s.W, H = s.H;
-    const int ci = cell / s.nx, cj = cell - ci * s.nx;
-    const int x0 = cell_lo(cj, W, s.nx), x1 = cell_lo(cj + 1, W, s.nx);
-    const int y0 = cell_lo(ci, H, s.ny), y1 = cell_lo(ci + 1, H, s.ny);
+    const int bk = xcd_remap(blockIdx.x, gridDim.x);
+    const int b = bk / s.K, k = bk - b * s.K;
+    const int ci = k / s.nx, cj = k - ci * s.nx;
     const float4* __restrict__ img = packed + (long long)b * s.N;
     float4* __restrict__ gimg = gf + (long long)b * s.N;
-    // the candidates' centres (this pass needs no endpoint texel) are loaded
-    // here and stored after the first pass, which does not use them; the
-    // slots' boxes start empty and take the endpoint in the layout step
-    float cl = 0.0f, ca = 0.0f, cb = 0.0f, cxf = 0.0f, cyf = 0.0f;
-    int ck = -1;
-    if (tid < 9) {
-        const int ii = ci + tid / 3 - 1, jj = cj + tid % 3 - 1;
-        if (ii >= 0 && ii < s.ny && jj >= 0 && jj < s.nx) {
-            ck = ii * s.nx + jj;
-            const float* c5 = theta_prev + 5LL * s.K * b + 5LL * ck;
-            cl = c5[0]; ca = c5[1]; cb = c5[2]; cxf = c5[3]; cyf = c5[4];
-        }
-        bl.bx0[tid] = INT_MAX;
-        bl.bx1[tid] = INT_MIN;
-        bl.by0[tid] = INT_MAX;
-        bl.by1[tid] = INT_MIN;
-        bl.has[tid] = 0;
-    }
-    for (int t = tid; t < 9 * 7 * kBwdCopies; t += WG) (&bins[0][0][0])[t] = 0.0;
-    __syncthreads();
-    const int cw = x1 - x0, ch = y1 - y0, P = cw * ch;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int cp = lane & (kBwdCopies - 1);
+    const ConstF ck = (ConstF)(uintptr_t)(theta_prev + 5LL * bk);
+    const float cl = ck[0], ca = ck[1], cb = ck[2], cxf = ck[3], cyf = ck[4];
+    const int cx = round_coord(cxf, W - 1), cy = round_coord(cyf, H - 1);
     const long long base = 9LL * s.N * b;
-    // list entries hold the pixel's offsets in the cell as two 16-bit
-    // halves when they fit, else its index in the cell's pixel order
-    const bool wl_xy = cw < 65536 && ch < 65536;
-    // pass 1: the box of each slot's walked pixels (a chunk's box per chunk
-    // with any nonzero dL/dD in the slot)
-    for (int chunk = wave; chunk * 64 < P; chunk += WG / 64) {
-        const int t = chunk * 64 + lane;
-        const bool valid = t < P;
-        int px = 0, py = 0;
-        if (valid) {
-            cell_pixel(t, cw, ch, px, py);
-            px += x0;
-            py += y0;
-        }
-        int mnx = valid ? px : 0x7fffffff, mxx = valid ? px : -1;
-        int mny = valid ? py : 0x7fffffff, mxy = valid ? py : -1;
-        for (int o = 32; o > 0; o >>= 1) {
-            mnx = min(mnx, __shfl_xor(mnx, o, 64));
-            mxx = max(mxx, __shfl_xor(mxx, o, 64));
-            mny = min(mny, __shfl_xor(mny, o, 64));
-            mxy = max(mxy, __shfl_xor(mxy, o, 64));
-        }
-        const unsigned msk = valid ? gmask[(long long)b * s.N + (long long)py * W + px] : 0u;
-#pragma unroll
-        for (int j = 0; j < 9; ++j) {
-            if (__ballot((msk >> j) & 1u) != 0ULL && lane == 0) {
-                atomicMin(&bl.bx0[j], mnx);
-                atomicMax(&bl.bx1[j], mxx + 1);
-                atomicMin(&bl.by0[j], mny);
-                atomicMax(&bl.by1[j], mxy + 1);
-                bl.has[j] = 1;
-            }
+    // the lists of k: cell (ci + di, cj + dj), read under its slot (-di, -dj)
+    const int lists = 9 * s.bspl;
+    int n = 0;
+    if (tid < lists) {
+        const int nbr = tid / s.bspl, slice = tid - nbr * s.bspl;
+        const int ii = ci + nbr / 3 - 1, jj = cj + nbr % 3 - 1;
+        if (ii >= 0 && ii < s.ny && jj >= 0 && jj < s.nx) {
+            const int x0 = cell_lo(jj, W, s.nx), cw = cell_lo(jj + 1, W, s.nx) - x0;
+            const int y0 = cell_lo(ii, H, s.ny), ch = cell_lo(ii + 1, H, s.ny) - y0;
+            int t0, t1;
+            bwd_slice(s, cw * ch, slice, t0, t1);
+            const long long item = ((long long)b * s.K + ii * s.nx + jj) * s.bspl + slice;
+            n = count[9 * item + 8 - nbr];
+            lbase[tid] = base + (long long)(8 - nbr) * s.N +
+                         ((long long)y0 * W + (long long)x0 * ch + t0);
         }
     }
-    if (tid < 9) {
-        SoftCand c;
-        c.k = ck;
-        c.l = cl; c.a = ca; c.b = cb; c.x = cxf; c.y = cyf;
-        c.cx = ck >= 0 ? round_coord(cxf, W - 1) : 0;
-        c.cy = ck >= 0 ? round_coord(cyf, H - 1) : 0;
-        sh.cand[tid] = c;
-    }
+    const int incl = wave_scan_incl(n);
+    if (lane == 63) wtot[wave] = incl;
     __syncthreads();
-    // tile layout: slots in the order own cell, edges, corners, while they fit
-    if (tid == 0) {
-        constexpr unsigned long long kOrder = 0x862075314ULL;
-        int used = 0;                                           // bytes of weight tiles
-        int ux0 = 0x7fffffff, uy0 = 0x7fffffff, ux1 = -1, uy1 = -1;
-        for (int t = 0; t < 9; ++t) {
-            const int j = (int)((kOrder >> (4 * t)) & 15ULL);
-            bl.soff[j] = -1;
-            if (sh.cand[j].k < 0 || !bl.has[j]) continue;
-            // every path of the slot ends at its endpoint
-            bl.bx0[j] = min(bl.bx0[j], sh.cand[j].cx);
-            bl.bx1[j] = max(bl.bx1[j], sh.cand[j].cx + 1);
-            bl.by0[j] = min(bl.by0[j], sh.cand[j].cy);
-            bl.by1[j] = max(bl.by1[j], sh.cand[j].cy + 1);
-            const int bw = bl.bx1[j] - bl.bx0[j], bh = bl.by1[j] - bl.by0[j];
-            const long long sb = 8LL * bw * bh;
-            const int nx0 = min(ux0, bl.bx0[j]), nx1 = max(ux1, bl.bx1[j]);
-            const int ny0 = min(uy0, bl.by0[j]), ny1 = max(uy1, bl.by1[j]);
-            const long long ub = 4LL * (nx1 - nx0) * (ny1 - ny0);
-            if (used + sb + ub <= cap_bytes) {
-                bl.soff[j] = used / 8;
-                used += (int)sb;
-                ux0 = nx0; ux1 = nx1; uy0 = ny0; uy1 = ny1;
-            }
-        }
-        if (ux1 < 0) ux0 = ux1 = uy0 = uy1 = 0;
-        bl.ux0 = ux0; bl.uy0 = uy0; bl.uw = ux1 - ux0; bl.uh = uy1 - uy0;
-        bl.woff = used / 4;
+    int total = 0;
+    for (int v = 0; v < kWaves; ++v) {
+        if (v == wave && tid < lists) lpre[tid] = total + incl - n;
+        total += wtot[v];
     }
+    total = __builtin_amdgcn_readfirstlane(total);
     __syncthreads();
-    float* wtile = reinterpret_cast<float*>(bwd_dyn) + bl.woff;
-    const int ux0 = bl.ux0, uy0 = bl.uy0, uw = bl.uw, uh = bl.uh;
-    {
-        const int words = bl.woff + uw * uh;
-        float* z = reinterpret_cast<float*>(bwd_dyn);
-        for (int e = tid; e < words; e += WG) z[e] = 0.0f;
-    }
-    __syncthreads();
+    double gc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};     // this lane's share of dL/dTheta_k
     const float lambda = s.lambda, oml = 1.0f - lambda;
-    // walks listed pair i of this wave (the lanes of a wave call it together)
-    auto walk_pair = [&](int i) {
-        const int jj = wl_j[wave][i];
-        const float gj = wl_g[wave][i];
-        int x, y;
-        if (wl_xy) {
-            x = wl_t[wave][i] & 0xffff;
-            y = wl_t[wave][i] >> 16;
-        } else {
-            cell_pixel(wl_t[wave][i], cw, ch, x, y);
+    // pairs a0 .. a0 + len - 1, one per lane, spread over the waves
+    const int own = lane * kWaves + wave;
+    int a0 = 0, len = min(total, WG);
+    while (a0 < total) {                          // uniform
+        const bool mine = own < len;
+        int x = cx, y = cy;
+        float gj = 0.0f, A = 0.0f, Bw = 0.0f;
+        if (mine) {
+            int l = 0, h = lists - 1;             // the last list that starts at or before it
+            while (l < h) {
+                const int m = (l + h + 1) >> 1;
+                if (lpre[m] <= a0 + own) l = m; else h = m - 1;
+            }
+            const uint2 e = pairs[lbase[l] + (a0 + own - lpre[l])];
+            const int p = (int)e.x;
+            gj = __uint_as_float(e.y);
+            const long long o = base + (long long)(8 - l / s.bspl) * s.N + p;
+            A = fa[o];
+            Bw = fb[o];
+            y = (int)((double)p * s.inv_w);
+            x = p - y * W;
+            if (x < 0) { --y; x += W; }
+            if (x >= W) { ++y; x -= W; }
         }
-        x += x0;
-        y += y0;
-        const int p = y * W + x;
-        const SoftCand c = sh.cand[jj];
-        const long long o = base + (long long)jj * s.N + p;
-        const float A = fa[o], Bw = fb[o];
-        const int dx = c.cx - x, dy = c.cy - y;
-        const int adx = dx < 0 ? -dx : dx, ady = dy < 0 ? -dy : dy;
-        const int n = adx > ady ? adx : ady;
-        const float inv_np = 1.0f / (float)(n + 1);
-        const float cf = 2.0f * gj * Bw * oml * inv_np;  // per sample, times (f_q - f_k)
-        const float cw_ = gj * A * s.gamma * inv_np;     // per sample: dL/dw_q
-        const float lf = 2.0f * gj * Bw * lambda;        // lambda term of p
-        atomicAdd(&bins[jj][3][cp], (double)(-2.0f * gj * s.spw * ((float)x - c.x)));
-        atomicAdd(&bins[jj][4][cp], (double)(-2.0f * gj * s.spw * ((float)y - c.y)));
-        const bool xmaj = adx >= ady;
-        const int so = bl.soff[jj];
-        if (so >= 0) {                                   // staged
-            // samples i = 0 .. n-1 (p itself first); the endpoint i = n is
-            // added once per slot
-            const int sbx0 = bl.bx0[jj], sby0 = bl.by0[jj], sp = bl.bx1[jj] - sbx0;
-            double* st = bwd_dyn + so;
-            const int stx = dx < 0 ? -1 : 1;
-            const int sys = dy < 0 ? -sp : sp, syw = dy < 0 ? -uw : uw;
-            const int smaj_s = xmaj ? stx : sys, sdiag_s = smaj_s + (xmaj ? sys : stx);
-            const int smaj_w = xmaj ? stx : syw, sdiag_w = smaj_w + (xmaj ? syw : stx);
-            int ls = (y - sby0) * sp + (x - sbx0);
-            int lw = (y - uy0) * uw + (x - ux0);
-            const double cfd = (double)cf;
-            if (n > 0) {
-                atomicAdd(&st[ls], cfd + (double)lf);
-                atomicAdd(&wtile[lw], cw_);
-                const unsigned F = step_increment(xmaj ? ady : adx, n);
-                unsigned acc = 0x80000000u;
-                for (int i = 1; i < n; ++i) {
-                    const bool cr = __builtin_add_overflow(acc, F, &acc);
-                    ls += cr ? sdiag_s : smaj_s;
-                    lw += cr ? sdiag_w : smaj_w;
-                    atomicAdd(&st[ls], cfd);
-                    atomicAdd(&wtile[lw], cw_);
-                }
-            } else {
-                atomicAdd(&st[ls], (double)lf);
+        int mnx = min(x, cx), mxx = max(x, cx), mny = min(y, cy), mxy = max(y, cy);
+        mnx = wave_min_i32(mnx);
+        mxx = wave_max_i32(mxx);
+        mny = wave_min_i32(mny);
+        mxy = wave_max_i32(mxy);
+        if (lane == 0) {
+            wbox[0][wave] = mnx;
+            wbox[1][wave] = mxx;
+            wbox[2][wave] = mny;
+            wbox[3][wave] = mxy;
+        }
+        __syncthreads();
+        for (int v = 0; v < kWaves; ++v) {
+            mnx = min(mnx, wbox[0][v]);
+            mxx = max(mxx, wbox[1][v]);
+            mny = min(mny, wbox[2][v]);
+            mxy = max(mxy, wbox[3][v]);
+        }
+        mnx = __builtin_amdgcn_readfirstlane(mnx);
+        mny = __builtin_amdgcn_readfirstlane(mny);
+        const int bw = __builtin_amdgcn_readfirstlane(mxx - mnx + 1);
+        const int bh = __builtin_amdgcn_readfirstlane(mxy - mny + 1);
+        const bool staged = 12LL * bw * bh <= cap_bytes;                 // uniform
+        if (!staged) {
+            // fewer: the lists that end in the first half, or else the first
+            // list, or else half of it
+            int next = a0 + len, half = a0;
+            for (int l = 0; l < lists; ++l) {
+                const int v = lpre[l];
+                if (v > a0) next = min(next, v);
+                if (v <= a0 + (len >> 1)) half = max(half, v);
             }
-            atomicAdd(&bins[jj][5][cp], cfd);
-            atomicAdd(&bins[jj][6][cp], (double)cw_);
-        } else {                                         // scatter to global memory
-            float gk[3] = {0.0f, 0.0f, 0.0f};
-            const float4 fp = img[p];
-            const float dl = fp.x - c.l, da = fp.y - c.a, db = fp.z - c.b;
-            gk[0] -= lf * dl;
-            gk[1] -= lf * da;
-            gk[2] -= lf * db;
-            const int am = xmaj ? ady : adx;
-            const int two_n = 2 * n, inc = 2 * am;
-            int rem = n;
-            const int stx = dx < 0 ? -1 : 1, sty = dy < 0 ? -W : W;
-            const int smaj = xmaj ? stx : sty;
-            const int sdiag = smaj + (xmaj ? sty : stx);
-            int gi = p;
-            unsafeAtomicAdd(&gimg[gi].x, lf * dl);
-            unsafeAtomicAdd(&gimg[gi].y, lf * da);
-            unsafeAtomicAdd(&gimg[gi].z, lf * db);
-            for (int i = 0; i <= n; ++i) {
-                if (i > 0) {
-                    rem += inc;
-                    const bool st_ = rem >= two_n;
-                    rem -= st_ ? two_n : 0;
-                    gi += st_ ? sdiag : smaj;
-                }
-                const float4 fq = img[gi];
-                const float el = cf * (fq.x - c.l), ea = cf * (fq.y - c.a),
-                            eb = cf * (fq.z - c.b);
-                unsafeAtomicAdd(&gimg[gi].x, el);
-                unsafeAtomicAdd(&gimg[gi].y, ea);
-                unsafeAtomicAdd(&gimg[gi].z, eb);
-                unsafeAtomicAdd(&gimg[gi].w, cw_);
-                gk[0] -= el;
-                gk[1] -= ea;
-                gk[2] -= eb;
+            const int fewer = half > a0 ? half - a0 : next < a0 + len ? next - a0
+                                                    : max(64, (len >> 1) & ~63);
+            if (__builtin_amdgcn_readfirstlane(fewer) < len) {           // uniform
+                len = __builtin_amdgcn_readfirstlane(fewer);
+                __syncthreads();                  // wbox is written again
+                continue;
             }
+        }
+        const int area = staged ? bw * bh : 0;
+        double* __restrict__ st = bwd_dyn;
+        float* __restrict__ wt = reinterpret_cast<float*>(bwd_dyn + area);
+        for (int e = tid; e < area; e += WG) {
+            st[e] = 0.0;
+            wt[e] = 0.0f;
+        }
+        __syncthreads();
+        double vc = 0.0, vw = 0.0;                // the endpoint's weights
+        if (mine) {
+            const int p = y * W + x;
+            const int dx = cx - x, dy = cy - y;
+            const int adx = dx < 0 ? -dx : dx, ady = dy < 0 ? -dy : dy;
+            const int np = max(adx, ady);
+            const float inv_np = 1.0f / (float)(np + 1);
+            const float cf = 2.0f * gj * Bw * oml * inv_np;  // per sample, times (f_q - f_k)
+            const float cw_ = gj * A * s.gamma * inv_np;     // per sample: dL/dw_q
+            const float lf = 2.0f * gj * Bw * lambda;        // lambda term of p
+            gc[3] += (double)(-2.0f * gj * s.spw * ((float)x - cxf));
+            gc[4] += (double)(-2.0f * gj * s.spw * ((float)y - cyf));
+            const bool xmaj = adx >= ady;
+            if (staged) {                                    // uniform
+                // samples i = 0 .. n-1 (p itself first); the endpoint i = n
+                // is added once per superpixel
+                const int stx = dx < 0 ? -1 : 1, sty = dy < 0 ? -bw : bw;
+                const int smaj = xmaj ? stx : sty, sdiag = stx + sty;
+                int ls = (y - mny) * bw + (x - mnx);
+                const double cfd = (double)cf;
+                if (np > 0) {
+                    atomicAdd(&st[ls], cfd + (double)lf);
+                    atomicAdd(&wt[ls], cw_);
+                    const unsigned F = step_increment(xmaj ? ady : adx, np);
+                    unsigned acc = 0x80000000u;
+                    for (int m = 1; m < np; ++m) {
+                        const bool cr = __builtin_add_overflow(acc, F, &acc);
+                        ls += cr ? sdiag : smaj;
+                        atomicAdd(&st[ls], cfd);
+                        atomicAdd(&wt[ls], cw_);
+                    }
+                } else {
+                    atomicAdd(&st[ls], (double)lf);
+                }
+                vc += cfd;
+                vw += (double)cw_;
+            } else {                                         // scatter to global memory
+                float gk[3] = {0.0f, 0.0f, 0.0f};
+                const float4 fp = img[p];
+                const float dl = fp.x - cl, da = fp.y - ca, db = fp.z - cb;
+                gk[0] -= lf * dl;
+                gk[1] -= lf * da;
+                gk[2] -= lf * db;
+                const int am = xmaj ? ady : adx;
+                const int two_n = 2 * np, inc = 2 * am;
+                int rem = np;
+                const int stx = dx < 0 ? -1 : 1, sty = dy < 0 ? -W : W;
+                const int smaj = xmaj ? stx : sty;
+                const int sdiag = stx + sty;
+                int gi = p;
+                unsafeAtomicAdd(&gimg[gi].x, lf * dl);
+                unsafeAtomicAdd(&gimg[gi].y, lf * da);
+                unsafeAtomicAdd(&gimg[gi].z, lf * db);
+                for (int m = 0; m <= np; ++m) {
+                    if (m > 0) {
+                        rem += inc;
+                        const bool step = rem >= two_n;
+                        rem -= step ? two_n : 0;
+                        gi += step ? sdiag : smaj;
+                    }
+                    const float4 fq = img[gi];
+                    const float el = cf * (fq.x - cl), ea = cf * (fq.y - ca),
+                                eb = cf * (fq.z - cb);
+                    unsafeAtomicAdd(&gimg[gi].x, el);
+                    unsafeAtomicAdd(&gimg[gi].y, ea);
+                    unsafeAtomicAdd(&gimg[gi].z, eb);
+                    unsafeAtomicAdd(&gimg[gi].w, cw_);
+                    gk[0] -= el;
+                    gk[1] -= ea;
+                    gk[2] -= eb;
+                }
 #pragma unroll
-            for (int v = 0; v < 3; ++v) atomicAdd(&bins[jj][v][cp], (double)gk[v]);
-        }
-    };
-    // walks pairs [0, upto) of the list, 64 per round; then the list's LDS
-    // may be rewritten (a wave's LDS accesses stay in order; the fences keep
-    // the compiler from moving them across)
-    auto walk_list = [&](int upto) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        for (int i = lane; i - lane < upto; i += 64)            // uniform trip count
-            if (i < upto) walk_pair(i);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
-    // pass 2: list the nonzero pairs and walk them
-    int nb = 0;                        // pairs listed and not walked yet (uniform over the wave)
-    for (int chunk = wave; chunk * 64 < P; chunk += WG / 64) {
-        const int t = chunk * 64 + lane;
-        const bool valid = t < P;
-        int px = 0, py = 0;
-        if (valid) {
-            cell_pixel(t, cw, ch, px, py);
-            px += x0;
-            py += y0;
-        }
-        const unsigned msk = valid ? gmask[(long long)b * s.N + (long long)py * W + px] : 0u;
-        float g[9];
-#pragma unroll
-        for (int j = 0; j < 9; ++j)
-            g[j] = (msk >> j) & 1u ? gd[base + (long long)j * s.N + (long long)py * W + px] : 0.0f;
-        const int tag = wl_xy ? (px - x0) | ((py - y0) << 16) : t;
-#pragma unroll 1
-        for (int jn = 0; jn < 9; ++jn) {                        // uniform
-            float gj = 0.0f;
-#pragma unroll
-            for (int j = 0; j < 9; ++j) gj = j == jn ? g[j] : gj;
-            const unsigned long long m = __ballot(gj != 0.0f);
-            const int cnt = __popcll(m);
-            if (nb + cnt > kBwdBatch) {                         // uniform: make room
-                // walk the whole rounds, move the rest (< 64 pairs) to the front
-                const int full = nb & ~63;
-                walk_list(full);
-                const int left = nb - full;
-                int lt = 0, lj = 0;
-                float lg = 0.0f;
-                if (lane < left) {
-                    lt = wl_t[wave][full + lane];
-                    lj = wl_j[wave][full + lane];
-                    lg = wl_g[wave][full + lane];
-                }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                if (lane < left) {
-                    wl_t[wave][lane] = lt;
-                    wl_j[wave][lane] = (unsigned char)lj;
-                    wl_g[wave][lane] = lg;
-                }
-                nb = left;
+                for (int v = 0; v < 3; ++v) gc[v] += (double)gk[v];
             }
-            if (gj != 0.0f) {
-                const int at = nb + (int)__builtin_amdgcn_mbcnt_hi(
-                                       (unsigned)(m >> 32),
-                                       __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-                wl_t[wave][at] = tag;
-                wl_j[wave][at] = (unsigned char)jn;
-                wl_g[wave][at] = gj;
-            }
-            nb += cnt;
         }
+        if (staged) {                                        // uniform
+            if (wave < len) {                                // uniform: this wave walked
+                vc = wave_sum_f64(vc);
+                vw = wave_sum_f64(vw);
+                const int e = (cy - mny) * bw + (cx - mnx);
+                if (lane == 0) {
+                    atomicAdd(&st[e], vc);
+                    atomicAdd(&wt[e], (float)vw);
+                }
+            }
+            __syncthreads();
+            // the fold
+            const int dr = WG / bw, dc = WG - dr * bw;
+            int r = tid / bw, c = tid - r * bw;
+            for (int e0 = 0; e0 < area; e0 += kFold * WG) {   // uniform: every lane stays
+                double sv[kFold];
+                float wv[kFold];
+                float4 f[kFold];
+                int p[kFold];
+#pragma unroll
+                for (int u = 0; u < kFold; ++u) {
+                    const int e = e0 + tid + u * WG;
+                    sv[u] = e < area ? st[e] : 0.0;
+                    wv[u] = e < area ? wt[e] : 0.0f;
+                    p[u] = (mny + r) * W + mnx + c;
+                    c += dc;
+                    const bool wrap = c >= bw;
+                    c -= wrap ? bw : 0;
+                    r += dr + (wrap ? 1 : 0);
+                }
+#pragma unroll
+                for (int u = 0; u < kFold; ++u)
+                    if (sv[u] != 0.0 || wv[u] != 0.0f) f[u] = img[p[u]];
+#pragma unroll
+                for (int u = 0; u < kFold; ++u) {
+                    if (__ballot(sv[u] != 0.0 || wv[u] != 0.0f) == 0ULL) continue;   // uniform
+                    float4 d = make_float4(0.0f, 0.0f, 0.0f, wv[u]);
+                    if (sv[u] != 0.0) {
+                        const double el = sv[u] * (double)(f[u].x - cl);
+                        const double ea = sv[u] * (double)(f[u].y - ca);
+                        const double eb = sv[u] * (double)(f[u].z - cb);
+                        gc[0] -= el;
+                        gc[1] -= ea;
+                        gc[2] -= eb;
+                        d.x = (float)el;
+                        d.y = (float)ea;
+                        d.z = (float)eb;
+                    }
+                    // through LDS, so that an atomic instruction adds the four
+                    // values of 16 neighbouring texels, 256 bytes in a row,
+                    // and not one value of 64 texels
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    turn[wave][lane] = d;
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int from = 16 * v + (lane >> 2);
+                        const float val = reinterpret_cast<const float*>(&turn[wave][from])[lane & 3];
+                        const int q = __shfl(p[u], from, 64);
+                        if (val != 0.0f)
+                            unsafeAtomicAdd(reinterpret_cast<float*>(gimg + q) + (lane & 3), val);
+                    }
+                }
+            }
+        }
+        a0 += len;
+        len = min(total - a0, WG);
+        __syncthreads();                          // wbox and the tiles are written again
     }
-    walk_list(nb);
-    __syncthreads();
-    // the endpoint's weights, once per staged slot (one writer per weight
-    // tile entry; two candidates may round to the same endpoint pixel, so
-    // the shared dL/dw tile takes an atomic)
-    if (tid < 9 && bl.soff[tid] >= 0) {
-        const SoftCand c = sh.cand[tid];
-        double vc = 0.0, vw = 0.0;
-        for (int k = 0; k < kBwdCopies; ++k) {
-            vc += bins[tid][5][k];
-            vw += bins[tid][6][k];
+    // dL/dTheta_{t-1}: the pass-through of a superpixel whose soft mass was
+    // zero (it kept its previous centre) and the path terms
+    if (total > 0) {                              // uniform
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+            gc[v] = wave_sum_f64(gc[v]);
+            if (lane == 0) red[v][wave] = gc[v];
         }
-        const int sp = bl.bx1[tid] - bl.bx0[tid];
-        bwd_dyn[bl.soff[tid] + (c.cy - bl.by0[tid]) * sp + (c.cx - bl.bx0[tid])] += vc;
-        atomicAdd(&wtile[(c.cy - uy0) * uw + (c.cx - ux0)], (float)vw);
+        __syncthreads();
     }
-    __syncthreads();
-    // fold over the union box, kFold texels per thread and trip with their
-    // texel loads issued first: dL/df_q = sum_k S_k(q) (f_q - f_k) (FP64, one
-    // rounding) and dL/dw_q; the centre gradients -sum_q S_k(q) (f_q - f_k)
-    // go to the FP64 slot sums term by term
-    {
-        const int area = uw * uh;
-        const int dr = uw > 0 ? WG / uw : 0, dc = uw > 0 ? WG - dr * uw : 0;
-        int r = uw > 0 ? tid / uw : 0, c = tid - r * uw;
-        for (int e0 = tid; e0 < area; e0 += kFold * WG) {
-            int xs[kFold], ys[kFold];
-            float4 fs[kFold];
+    if (tid == 0) {
+        const bool kept = !(z[bk] >= kZMin);
+        double g[5];
 #pragma unroll
-            for (int u = 0; u < kFold; ++u) {
-                xs[u] = ux0 + c;
-                ys[u] = uy0 + r;
-                if (e0 + u * WG < area) fs[u] = img[(long long)ys[u] * W + xs[u]];
-                c += dc;
-                const bool wrap = c >= uw;
-                c -= wrap ? uw : 0;
-                r += dr + (wrap ? 1 : 0);
-            }
-#pragma unroll
-            for (int u = 0; u < kFold; ++u) {
-                const int e = e0 + u * WG;
-                if (e >= area) break;
-                const int x = xs[u], y = ys[u];
-                const float4 f = fs[u];
-                const float wv = wtile[e];
-                double ax = 0.0, ay = 0.0, az = 0.0;
-#pragma unroll
-                for (int j = 0; j < 9; ++j) {
-                    const int so = bl.soff[j];
-                    if (so < 0) continue;
-                    if (x < bl.bx0[j] || x >= bl.bx1[j] || y < bl.by0[j] || y >= bl.by1[j])
-                        continue;
-                    const double sv = bwd_dyn[so + (y - bl.by0[j]) * (bl.bx1[j] - bl.bx0[j]) +
-                                              (x - bl.bx0[j])];
-                    if (sv == 0.0) continue;
-                    const double el = sv * (double)(f.x - sh.cand[j].l);
-                    const double ea = sv * (double)(f.y - sh.cand[j].a);
-                    const double eb = sv * (double)(f.z - sh.cand[j].b);
-                    ax += el;
-                    ay += ea;
-                    az += eb;
-                    atomicAdd(&bins[j][0][cp], -el);
-                    atomicAdd(&bins[j][1][cp], -ea);
-                    atomicAdd(&bins[j][2][cp], -eb);
-                }
-                if (ax != 0.0 || ay != 0.0 || az != 0.0 || wv != 0.0f) {
-                    float4* d = &gimg[(long long)y * W + x];
-                    unsafeAtomicAdd(&d->x, (float)ax);
-                    unsafeAtomicAdd(&d->y, (float)ay);
-                    unsafeAtomicAdd(&d->z, (float)az);
-                    unsafeAtomicAdd(&d->w, wv);
-                }
-            }
+        for (int v = 0; v < 5; ++v) {
+            g[v] = kept ? gth[5LL * bk + v] : 0.0;
+            if (total > 0)
+                for (int w = 0; w < kWaves; ++w) g[v] += red[v][w];
+            gth_prev[5LL * bk + v] = g[v];
         }
-    }
-    __syncthreads();
-    // the centre gradients
-    if (tid < 9) {
-        const SoftCand c = sh.cand[tid];
-        if (c.k >= 0) {
-            for (int q = 0; q < 5; ++q) {
-                double a = 0.0;
-                for (int k = 0; k < kBwdCopies; ++k) a += bins[tid][q][k];
-                if (a != 0.0) unsafeAtomicAdd(&gth_prev[5LL * s.K * b + 5LL * c.k + q], a);
-            }
-        }
+        if (z_prev) store_cand(z_prev[bk], g, theta_prev + 5LL * bk, cand + 2LL * bk);
     }
 }
 
@@ -921,19 +855,20 @@ __global__ __launch_bounds__(256) void k_soft_bwd_finish(SoftImg s, const float4
     }
 }
 
-__global__ void k_widen_f32(const float* __restrict__ src, double* __restrict__ dst, long long n) {
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-         i += (long long)gridDim.x * blockDim.x)
-        dst[i] = (double)src[i];
-}
-
 constexpr int kSoftWG = 256;
-constexpr int kSoftBwdWG = 512;
-// Tile budget of the backward path pass in bytes (FP64 weight tiles plus the
-// FP32 dL/dw tile): with its ~18 KiB of static LDS (the waves' pair lists,
-// the slot sums, the layout, the candidates) two 512-lane workgroups still
-// fit in a CU's 160 KiB.  Slots beyond it scatter to global memory instead.
+// Tile budget of the backward path pass in bytes (an FP64 weight and an FP32
+// dL/dw per texel): what the paths of one cell's pixels to a superpixel of the
+// 3x3 block around it mostly span, 1.8 cells by 1.8 cells, at least
+// kBwdLdsLeast (with 8 KiB of static LDS four workgroups fit in a CU's 160
+// KiB; less would split the pairs of small cells) and at most kBwdLdsBytes.
+constexpr int kBwdLdsLeast = 28 * 1024;
 constexpr int kBwdLdsBytes = 60 * 1024;
+
+static int path_lds_bytes(const SoftGeom& g, int cap_bytes) {
+    const double cw = (double)g.W / g.nx, ch = (double)g.H / g.ny;
+    const double want = std::min(12.0 * 1.8 * 1.8 * cw * ch, (double)kBwdLdsBytes);
+    return std::min(cap_bytes, std::max((int)want, kBwdLdsLeast)) & ~15;
+}
 
 unsigned grid_for(long long n) {
     return (unsigned)std::max<long long>(1, std::min<long long>((n + 255) / 256, 65536));
@@ -963,12 +898,18 @@ int soft_slices(int W, int H, int nx, int ny, int wg) {
     return (int)std::max<long long>(1, (chunks + per - 1) / per);
 }
 
+int soft_bwd_slices(int W, int H, int nx, int ny) {
+    return std::min(soft_slices(W, H, nx, ny, 1024), kBwdLists / 9);
+}
+
 static SoftImg to_img(const SoftGeom& g) {
     SoftImg s;
     s.W = g.W; s.H = g.H; s.nx = g.nx; s.ny = g.ny; s.K = g.nx * g.ny; s.B = g.B;
     s.N = (long long)g.W * g.H;
     s.spl = soft_slices(g.W, g.H, g.nx, g.ny, g.wg);
     s.near = s.N < (1LL << 28) && g.W + g.H < 46340;
+    s.bspl = soft_bwd_slices(g.W, g.H, g.nx, g.ny);
+    s.inv_w = 1.0 / (double)g.W;
     for (int i = 0; i < 2; ++i) {
         const long long ch = g.H / g.ny + i, cw = g.W / g.nx + 1;
         s.dper[i] = fast_div(8 * ch, cw * ch);
@@ -981,7 +922,7 @@ static SoftImg to_img(const SoftGeom& g) {
 
 void lift_soft_lds_limits() {
     static_cast<void>(hipFuncSetAttribute(
-        reinterpret_cast<const void*>(k_soft_bwd_path<kSoftBwdWG>),
+        reinterpret_cast<const void*>(k_soft_bwd_path<kPathWG>),
         hipFuncAttributeMaxDynamicSharedMemorySize, kBwdLdsBytes));
     static_cast<void>(hipGetLastError());
 }
@@ -1018,45 +959,35 @@ int launch_soft_update(const SoftGeom& g, const float* q, const unsigned short* 
     return hipGetLastError();
 }
 
+int launch_soft_bwd_start(const SoftGeom& g, const float* grad_theta, const double* z,
+                          const float* theta, double* gth, float4* cand, hipStream_t st) {
+    const SoftImg s = to_img(g);
+    hipLaunchKernelGGL(k_soft_bwd_start, dim3(grid_for((long long)s.B * s.K)), dim3(256), 0, st, s,
+                       grad_theta, z, theta, gth, cand);
+    return hipGetLastError();
+}
+
 int launch_soft_bwd_update(const SoftGeom& g, int first, const float* q,
-                           const unsigned short* pmask, const double* z,
-                           const float* theta, const float4* packed, const double* gth,
-                           const float* gq_in, float* gd, unsigned short* gmask, float4* gf,
-                           float4* cand, hipStream_t st) {
+                           const unsigned short* pmask, const float4* packed, const float* gq_in,
+                           const float4* cand, uint2* pairs, int* count, float4* gf,
+                           hipStream_t st) {
     const SoftImg s = to_img(g);
-    hipLaunchKernelGGL(k_soft_bwd_cand, dim3(grid_for((long long)s.B * s.K)), dim3(256), 0, st, s,
-                       z, theta, gth, cand);
-    hipLaunchKernelGGL(k_soft_bwd_update, pixel_grid(s), dim3(256), 0, st, s, first, q, pmask, cand,
-                       packed, gq_in, gd, gmask, gf);
-    return hipGetLastError();
-}
-
-int launch_soft_bwd_pass(const SoftGeom& g, const double* z, const double* gth, double* gth_prev,
-                         hipStream_t st) {
-    const SoftImg s = to_img(g);
-    hipLaunchKernelGGL(k_soft_bwd_pass, dim3(grid_for(5LL * s.B * s.K)), dim3(256), 0, st, s, z,
-                       gth, gth_prev);
-    return hipGetLastError();
-}
-
-template <int WG>
-static int soft_bwd_path_t(const SoftImg& s, const float4* packed, const float* theta_prev,
-                           const float* fa, const float* fb, const float* gd,
-                           const unsigned short* gmask, float4* gf, double* gth_prev,
-                           int cap_bytes, hipStream_t st) {
-    hipLaunchKernelGGL(k_soft_bwd_path<WG>, dim3(s.B * s.K), dim3(WG), (size_t)cap_bytes, st, s,
-                       packed, theta_prev, fa, fb, gd, gmask, gf, gth_prev, cap_bytes);
+    hipLaunchKernelGGL(k_soft_bwd_update, dim3(s.B * s.K * s.bspl), dim3(kUpdateWG), 0, st, s,
+                       first, q, pmask, cand, packed, gq_in, pairs, count, gf);
     return hipGetLastError();
 }
 
 int launch_soft_bwd_path(const SoftGeom& g, const float4* packed, const float* theta_prev,
-                         const float* fa, const float* fb, const float* gd,
-                         const unsigned short* gmask, float4* gf, double* gth_prev,
-                         int cap_bytes, hipStream_t st) {
-    // one shape for the backward pass whatever the assignment's (512 lanes;
-    // a cell's work is split over its 64-pixel chunks, one wave each)
-    return soft_bwd_path_t<kSoftBwdWG>(to_img(g), packed, theta_prev, fa, fb, gd, gmask, gf,
-                                       gth_prev, std::min(cap_bytes, kBwdLdsBytes) & ~7, st);
+                         const float* fa, const float* fb, const uint2* pairs, const int* count,
+                         const double* z, const double* gth, const double* z_prev,
+                         double* gth_prev, float4* cand, float4* gf, int cap_bytes,
+                         hipStream_t st) {
+    const SoftImg s = to_img(g);
+    const int cap = path_lds_bytes(g, cap_bytes);
+    hipLaunchKernelGGL(k_soft_bwd_path<kPathWG>, dim3(s.B * s.K), dim3(kPathWG), (size_t)cap, st, s,
+                       packed, theta_prev, fa, fb, pairs, count, z, gth, z_prev, gth_prev, cand,
+                       gf, cap);
+    return hipGetLastError();
 }
 
 int launch_soft_bwd_finish(const SoftGeom& g, const float4* gf, const double* gth0,
@@ -1065,11 +996,6 @@ int launch_soft_bwd_finish(const SoftGeom& g, const float4* gf, const double* gt
     const SoftImg s = to_img(g);
     hipLaunchKernelGGL(k_soft_bwd_finish, pixel_grid(s), dim3(256), 0, st, s, gf, gth0,
                        contour, sigma, glab, gcon);
-    return hipGetLastError();
-}
-
-int launch_widen_f32(const float* src, double* dst, long long n, hipStream_t st) {
-    hipLaunchKernelGGL(k_widen_f32, dim3(grid_for(n)), dim3(256), 0, st, src, dst, n);
     return hipGetLastError();
 }
 
