@@ -529,9 +529,14 @@ constexpr int kFold = 4;
 // and stored, with the terms that the update of the iteration before needs.
 //
 // What bounds it: the latency of a superpixel's chain of phases, with the tiles
-// limiting a CU to 4 workgroups.  A workgroup per cell, with a tile for each of
-// its 9 candidates and a fold over all of them, took 298 us per iteration of 16
-// x 512x512 against 300 K to 400 K walked pairs (47 to 64 per superpixel).
+// limiting a CU to 4 workgroups; the walks, the fold and its atomics take about
+// a quarter of the time each.  16 x 512x512, k = 400, T = 0.5 (300 K to 400 K
+// walked pairs, 47 to 64 per superpixel): 152 us per iteration, where a
+// workgroup per cell with a tile for each of its 9 candidates and a fold over
+// all of them took 298.  Atomics of one value of 64 texels instead of rows of
+// 16 texels' four values: 235.  Workgroups of 128 or 512 threads: 175 and 221;
+// a least budget of 20 or 40 KiB: 164 and 149, but at 40 the small grids lose a
+// workgroup per CU.
 template <int WG>
 __global__ __launch_bounds__(WG) void k_soft_bwd_path(
     SoftImg s, const float4* __restrict__ packed, const float* __restrict__ theta_prev,

@@ -265,6 +265,30 @@ def test_soft_large_cells_largest_budget(orc):
     assert_grads(orc, lab, con, k, gq, gth, iters, T, glab, gcon)
 
 
+@pytest.mark.parametrize("W,H,k,T,lds", [
+    (70, 66, 4, 500.0, 0),      # 2 pieces per cell, up to 1155 pairs in a list
+    (70, 66, 4, 500.0, 200),    # the same, most lists beyond the tile budget
+    (33, 1, 5, 100.0, 0),       # one row
+    (1, 40, 4, 100.0, 1),       # one column, no tile fits
+    (400, 150, 2, 3000.0, 0),   # 30000-pixel cells: the most pieces per cell
+])
+def test_soft_backward_item_edges(orc, W, H, k, T, lds):
+    """Superpixels whose pairs fill several batches, span several pieces of a
+    cell, or whose box exceeds the tile and is halved or scattered."""
+    iters = 2
+    lab, con = _batch(1, (W, H), 6, 730)
+    rng = np.random.default_rng(7)
+    K = orc.grid(W, H, k).num_sp
+    gq = rng.normal(0, 1, (1, 9, H, W)).astype(np.float32)
+    gth = rng.normal(0, 1, (1, K, 5)).astype(np.float32)
+    eng = _engine(W, H, k, 1, T, iters, lds_pixels=lds)
+    L, C = dev(lab), dev(con)
+    say("soft backward items", W, H, k, T, lds)
+    c_t, q_t, saved = eng.forward(L, C)
+    glab, gcon = (host(t) for t in eng.backward(L, C, c_t, q_t, saved, dev(gq), dev(gth)))
+    assert_grads(orc, lab, con, k, gq, gth, iters, T, glab, gcon)
+
+
 def test_soft_low_temperature_is_hard(orc):
     """Integer Lab on 4x4-pixel cells: T -> 0 gives one-hot Q at the hard assignment."""
     from paper_1903_07149_amd.scalp import Scalp
