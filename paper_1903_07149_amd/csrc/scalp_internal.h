@@ -20,19 +20,16 @@ constexpr int kAccStride = 8;
 // Control words in the workspace.
 enum Ctrl : int {
     kCtrlProjCount = 0,   // entries in the projection list
-    kCtrlGradMax = 64,    // words 64-1087: kGradSlots partial maxima of the squared
-                          // gradient magnitude (FP64 bits), one per 128-byte line
+    kCtrlGradMax = 64,    // words 64-1087: kGradSlots maxima of the squared gradient
+                          // magnitude (FP64 bits)
     kCtrlQueue = 1088,    // words 1088-1343: the persistent assignment's 8 queue heads
                           // (one per XCD's run of items), one per 128-byte line
     kCtrlWords = 1344
 };
 
-// The gradient maximum is kept in kGradSlots 64-bit slots kGradStride words
-// apart (one per 128-byte cache line; block b of the maximum pass updates
-// slot b mod kGradSlots), so that the atomics of thousands of blocks do not
-// queue on one line; readers take the largest.
-constexpr int kGradSlots = 32, kGradStride = 16;
-constexpr int kGradBytes = kGradSlots * kGradStride * 8;
+// Each block of the gradient's maximum pass has one of kGradSlots 64-bit slots.
+constexpr int kGradSlots = 512;
+constexpr int kGradBytes = kGradSlots * 8;
 
 // Division of numbers below a known limit by an invariant d, as one high
 // multiplication: floor(v / d) = floor(v m / 2^32) with m = ceil(2^32 / d)
@@ -186,7 +183,7 @@ int launch_soft_bwd_finish(const SoftGeom& g, const float4* gf, const double* gt
 int launch_boundary_frequency(int W, int H, int n, const int* labels, float* out, hipStream_t s);
 int launch_contour_from_lab(int W, int H, const float* lab, float* out, void* ws, hipStream_t s);
 // prepare with the contour prior computed from lab (same values as
-// launch_contour_from_lab followed by launch_prepare); mx: 8 bytes of scratch
+// launch_contour_from_lab followed by launch_prepare); mx: kGradBytes of scratch
 int launch_prepare_gradient(int W, int H, const float* lab, float sigma, float4* packed,
                             unsigned long long* mx, hipStream_t s);
 

@@ -43,6 +43,27 @@ def test_contour_from_lab_bit_exact(H, W, seed):
     assert (got == ref).all(), f"{int((got != ref).sum())} values differ"
 
 
+@pytest.mark.parametrize("H,W", [(4, 62), (5, 63), (3, 124), (9, 125), (8, 1), (2, 2), (301, 2500)])
+def test_contour_from_lab_item_edges(H, W):
+    """Remainders of the 62-column, 4-row items; quotients whose FP64 value lies
+    half-way between two FP32 numbers (differences of 25 bits over a power of
+    two), zeros, and quotients below FP32's normal range: all bit exact."""
+    from paper_1903_07149_amd.maps import contour_from_lab
+    rng = np.random.default_rng(H * W)
+    noise = rng.normal(0, 20, (H, W, 3)).astype(np.float32)
+    half = np.zeros((H, W, 3), np.float32)
+    amp = 2.0 ** 24 - rng.integers(0, 1 << 20, W)
+    amp[:3] = 2.0 ** 24
+    half[..., 0] = np.where(np.arange(W) % 4 < 2, 1.0, -1.0) * amp
+    tiny = noise * np.float32(1e-38)
+    tiny[H // 2, W // 2] = 90.0
+    for name, lab in (("noise", noise), ("half", half), ("tiny", tiny)):
+        say("contour edges", H, W, name)
+        got = host(contour_from_lab(dev(lab)))
+        ref = OM.contour_prior(lab)
+        assert (got == ref).all(), f"{name}: {int((got != ref).sum())} values differ"
+
+
 def test_contour_of_constant_image_is_zero():
     from paper_1903_07149_amd.maps import contour_from_lab
     got = host(contour_from_lab(torch.full((20, 30, 3), 7.0, device="cuda")))
