@@ -3,43 +3,42 @@
 // undersegmentation error (Eq. (7)) and compactness (Eq. (8)) of a label map
 // against a ground-truth partition.
 //
-//   k_metric_pixels  one pass over the pixels in blocks of 256 columns by
-//                    a few whole rows, each lane loading its pixel and four
-//                    clamped neighbours of both maps (independent loads, no
-//                    branches; the next row's loads issued before the
-//                    current row is processed): the overlap table
-//                    |S_k n G_i| and the perimeter of every superpixel in
-//                    pixel edges (4-connectivity, image border included),
-//                    gathered per distinct (k, i) pair among a wave's pixels
-//                    into a hash table in LDS and added to global memory once
-//                    per pair and block (device-scope atomics are the
-//                    expensive part here); and two boundary bitmaps, one
-//                    64-bit word per wave and row (bit b = pixel 64 w + b).
-//   k_metric_recall  thread per bitmap word: boundary-recall counts
+//   k_metric_pixels  one pass over the pixels, a wave per 64 columns by 4 rows
+//                    (every row loaded once, all in flight together; left and
+//                    right neighbours from the lanes beside): the overlap
+//                    table |S_k n G_i| and the perimeter of every superpixel
+//                    in pixel edges (4-connectivity, image border included),
+//                    gathered per run of equal (k, i) in a row into a hash
+//                    table in LDS and added to global memory once per pair
+//                    and block; and two boundary bitmaps, one 64-bit word per
+//                    wave and row (bit b = pixel 64 w + b).
+//   k_metric_rest    thread per bitmap word: boundary-recall counts
 //                    (ground-truth boundary pixels, those with a superpixel
 //                    boundary pixel at distance < epsilon, superpixel
 //                    boundary pixels) from the superpixel bitmap dilated
 //                    over the epsilon disc with word shifts; one partial sum
-//                    per workgroup.
-//   k_metric_rows    wave per superpixel: area, largest overlap, UE row sum
-//                    (integers) and the CO term 4 pi A^2 / P^2 (FP64).
+//                    per workgroup;
+//                    and, in the launch's other blocks, wave per superpixel:
+//                    area, largest overlap, UE row sum (integers) and the CO
+//                    term 4 pi A^2 / P^2 (FP64).
 //   k_metric_final   one workgroup: fixed-order sums of the rows and of the
 //                    recall partials, so the result does not depend on the
 //                    order of the atomics.
 #include <algorithm>
 
-#include "scalp_internal.h"
+#include "scalp_device.h"
 
 namespace scalp {
 namespace {
+
+using namespace dev;
 
 constexpr int kMetricWG = 256;
 
 struct MetricGeom {
     int W, H, K, R;
     int Wq;         // bitmap words per row, ceil(W / 64)
-    int rows;       // rows per k_metric_pixels block
-    int nrb;        // k_metric_recall blocks (partial sums)
+    int nrb;        // recall blocks (partial sums)
     int r;          // neighbourhood half-width for boundary recall
     float eps2;     // epsilon^2
 };
@@ -53,122 +52,123 @@ struct PairTable {
     unsigned key[kPairSlots], cnt[kPairSlots], edge[kPairSlots];
 };
 
-// For every distinct (k, i) among the wave's lanes with `ok`: popc(m) pixels
-// and the lanes' edge counts into the workgroup's pair table (a wave covers
-// 64 neighbouring pixels, which mostly share their superpixel and region).
-// e0..e2 are the bit planes of the lanes' edge counts (0..4), so a group's
-// edge sum is three masked popcounts.  A full table sends the pair straight
-// to global memory.
-__device__ __forceinline__ void wave_count(PairTable& pt, unsigned* __restrict__ table,
-                                           unsigned* __restrict__ perim, int R, bool ok, int k,
-                                           int i, unsigned long long e0, unsigned long long e1,
-                                           unsigned long long e2) {
+// One row of a wave: lane `head` begins a run of equal (k, i) (or of lanes with
+// !ok) that ends before the next head.  Every head with ok adds its run's pixels
+// and edge counts to the workgroup's table, all heads at once.  e0..e2 are the
+// bit planes of the lanes' edge counts (0..4), so a run's edge sum is three
+// masked popcounts.  A full table sends the pair straight to global memory.
+__device__ __forceinline__ void row_count(PairTable& pt, unsigned* __restrict__ table,
+                                          unsigned* __restrict__ perim, int R, bool ok, bool head,
+                                          int k, int i, unsigned e) {
     const int lane = threadIdx.x & 63;
-    unsigned long long pending = __ballot(ok);
-    while (pending != 0ULL) {                         // uniform over the wave
-        const int leader = __ffsll((long long)pending) - 1;
-        const int lk = __builtin_amdgcn_readlane(k, leader);
-        const int li = __builtin_amdgcn_readlane(i, leader);
-        const unsigned long long m = __ballot(ok && k == lk && i == li) & pending;
-        if (lane == leader) {
-            const unsigned n = (unsigned)__popcll(m);
-            const unsigned edges = (unsigned)(__popcll(e0 & m) + 2 * __popcll(e1 & m) +
-                                              4 * __popcll(e2 & m));
-            const unsigned key = (unsigned)lk * (unsigned)R + (unsigned)li;
-            unsigned h = (key * 2654435761u) >> (32 - kPairBits);
-            bool done = false;
-            for (int probe = 0; probe < kPairSlots && !done; ++probe) {
-                const unsigned old = atomicCAS(&pt.key[h], kEmpty, key);
-                if (old == kEmpty || old == key) {
-                    atomicAdd(&pt.cnt[h], n);
-                    if (edges) atomicAdd(&pt.edge[h], edges);
-                    done = true;
-                }
-                h = (h + 1) & (kPairSlots - 1);
-            }
-            if (!done) {
-                atomicAdd(&table[key], n);
-                if (edges) atomicAdd(&perim[lk], edges);
-            }
+    const unsigned long long heads = __ballot(head);
+    const unsigned long long e0 = __ballot(e & 1u), e1 = __ballot(e & 2u), e2 = __ballot(e & 4u);
+    if (!head || !ok) return;
+    // bits lane .. the next head (exclusive); without one, to the end
+    const unsigned long long above = heads & ~((2ULL << lane) - 1ULL);
+    const unsigned long long m = ((above & (0ULL - above)) - 1ULL) & ~((1ULL << lane) - 1ULL);
+    const unsigned n = (unsigned)__popcll(m);
+    const unsigned edges = (unsigned)(__popcll(e0 & m) + 2 * __popcll(e1 & m) + 4 * __popcll(e2 & m));
+    const unsigned key = (unsigned)k * (unsigned)R + (unsigned)i;
+    unsigned h = (key * 2654435761u) >> (32 - kPairBits);
+    for (int probe = 0; probe < kPairSlots; ++probe) {
+        unsigned old = *const_cast<volatile unsigned*>(&pt.key[h]);
+        if (old == kEmpty) old = atomicCAS(&pt.key[h], kEmpty, key);
+        if (old == kEmpty || old == key) {
+            atomicAdd(&pt.cnt[h], n);
+            if (edges) atomicAdd(&pt.edge[h], edges);
+            return;
         }
-        pending &= ~m;
+        h = (h + 1) & (kPairSlots - 1);
     }
+    atomicAdd(&table[key], n);
+    if (edges) atomicAdd(&perim[k], edges);
 }
 
-// A lane's pixel and its four clamped neighbours in both maps.
-struct PixRow {
-    int k, i, sl, sr, su, sd, gl, gr, gu, gd;
-};
-
-__device__ __forceinline__ PixRow load_row(const int* __restrict__ S, const int* __restrict__ G,
-                                           const MetricGeom& g, int y, int xc, int xl, int xr) {
-    const long long row = (long long)y * g.W;
-    const long long up = (long long)max(y - 1, 0) * g.W;
-    const long long dn = (long long)min(y + 1, g.H - 1) * g.W;
-    PixRow p;
-    p.k = S[row + xc];
-    p.i = G[row + xc];
-    p.sl = S[row + xl];
-    p.sr = S[row + xr];
-    p.su = S[up + xc];
-    p.sd = S[dn + xc];
-    p.gl = G[row + xl];
-    p.gr = G[row + xr];
-    p.gu = G[up + xc];
-    p.gd = G[dn + xc];
-    return p;
+// The lane below's (DPP wave_shr:1) or above's (wave_shl:1) value; the wave's
+// first or last lane gets `edge`.
+template <int CTRL>
+__device__ __forceinline__ int beside(int v, int edge) {
+    return __builtin_amdgcn_update_dpp(edge, v, CTRL, 0xf, 0xf, false);
 }
 
-// Block (bx, by): columns [256 bx, 256 bx + 256) of rows [by * rows, ...).
-// A pixel is a boundary pixel when a 4-neighbour inside the image has
-// another label; the clamped neighbour of a border pixel is the pixel
-// itself, which never differs.
-__global__ __launch_bounds__(kMetricWG) void k_metric_pixels(MetricGeom g, const int* __restrict__ S,
+constexpr int kTileRows = 4;                                    // of a wave
+constexpr int kBlockRows = kTileRows * (kMetricWG / 64);
+
+// A workgroup takes tiles of 64 columns by kBlockRows rows, `tiles` in all.  A pixel is a boundary pixel when a
+// 4-neighbour inside the image has another label; the clamped neighbour of a
+// border pixel is the pixel itself, which never differs.
+//
+// What bounds it: the latency of a wave's chain (loads, 4 rows of table updates,
+// the block's flush).  8 rows a wave: 12.3 us, 16: 32.  1920x1080, 2000 superpixels, 400
+// regions: 34.4 us with a turn of the table update per distinct pair of a row
+// (24 us of it those turns), 11.3 now.
+__global__ __launch_bounds__(kMetricWG) void k_metric_pixels(MetricGeom g, int tiles,
+                                                             const int* __restrict__ S,
                                                              const int* __restrict__ G,
                                                              unsigned* __restrict__ table,
                                                              unsigned* __restrict__ perim,
                                                              unsigned long long* __restrict__ smap,
                                                              unsigned long long* __restrict__ gmap) {
     __shared__ PairTable pt;
-    for (int t = threadIdx.x; t < kPairSlots; t += kMetricWG) {
-        pt.key[t] = kEmpty;
-        pt.cnt[t] = 0u;
-        pt.edge[t] = 0u;
-    }
-    __syncthreads();
-    const int x = blockIdx.x * kMetricWG + threadIdx.x;
-    const int word = (blockIdx.x * kMetricWG + (threadIdx.x & ~63)) >> 6;
-    const bool store = word < g.Wq && (threadIdx.x & 63) == 0;
-    const bool in = x < g.W;
-    const int xc = min(x, g.W - 1), xl = max(xc - 1, 0), xr = min(xc + 1, g.W - 1);
-    const int y0 = blockIdx.y * g.rows, y1 = min(y0 + g.rows, g.H);
-    PixRow cur = load_row(S, G, g, y0, xc, xl, xr);
-    for (int y = y0; y < y1; ++y) {                   // uniform
-        PixRow nxt = cur;
-        if (y + 1 < y1) nxt = load_row(S, G, g, y + 1, xc, xl, xr);
-        const int k = cur.k, i = cur.i;
-        const bool dl = cur.sl != k, dr = cur.sr != k, du = cur.su != k, dd = cur.sd != k;
-        const bool sb = in && (dl || dr || du || dd);
-        const bool gb = in && (cur.gl != i || cur.gr != i || cur.gu != i || cur.gd != i);
-        const unsigned long long sm = __ballot(sb), gm = __ballot(gb);
-        if (store) {
-            smap[(long long)y * g.Wq + word] = sm;
-            gmap[(long long)y * g.Wq + word] = gm;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    for (int tile = xcd_remap(blockIdx.x, gridDim.x); tile < tiles; tile += gridDim.x) {   // uniform
+        const int by = tile / g.Wq, word = tile - by * g.Wq;
+        const int x = word * 64 + lane, y0 = by * kBlockRows + wave * kTileRows;
+        const bool in = x < g.W;
+        const int xc = min(x, g.W - 1);
+        // column beside the wave, for its first and last lanes
+        const int xe = lane == 0 ? max(x - 1, 0) : min(x + 1, g.W - 1);
+        int s[kTileRows + 2], r[kTileRows + 2], se[kTileRows], re[kTileRows];
+        for (int i = 0; i < kTileRows + 2; ++i) {
+            const long long row = (long long)min(max(y0 + i - 1, 0), g.H - 1) * g.W;
+            s[i] = S[row + xc];
+            r[i] = G[row + xc];
         }
-        const bool ok = in && k >= 0 && k < g.K && i >= 0 && i < g.R;
-        const unsigned e = (unsigned)(dl || x == 0) + (unsigned)(dr || x + 1 >= g.W) +
-                           (unsigned)(du || y == 0) + (unsigned)(dd || y + 1 >= g.H);
-        const unsigned long long e0 = __ballot(ok && (e & 1u)), e1 = __ballot(ok && (e & 2u)),
-                                 e2 = __ballot(ok && (e & 4u));
-        wave_count(pt, table, perim, g.R, ok, k, i, e0, e1, e2);
-        cur = nxt;
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < kPairSlots; t += kMetricWG) {
-        const unsigned key = pt.key[t];
-        if (key == kEmpty) continue;
-        atomicAdd(&table[key], pt.cnt[t]);
-        if (pt.edge[t]) atomicAdd(&perim[key / (unsigned)g.R], pt.edge[t]);
+        for (int i = 0; i < kTileRows; ++i) {
+            se[i] = re[i] = 0;
+            const long long row = (long long)min(y0 + i, g.H - 1) * g.W;
+            if (lane == 0 || lane == 63) {
+                se[i] = S[row + xe];
+                re[i] = G[row + xe];
+            }
+        }
+        for (int t = threadIdx.x; t < kPairSlots; t += kMetricWG) {   // while they come
+            pt.key[t] = kEmpty;
+            pt.cnt[t] = 0u;
+            pt.edge[t] = 0u;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kTileRows; ++i) {
+            const int y = y0 + i;
+            if (y >= g.H) break;                      // uniform over the wave
+            const int k = s[i + 1], reg = r[i + 1];
+            const int kl = beside<0x138>(k, se[i]), kr = beside<0x130>(k, se[i]);
+            const int gl = beside<0x138>(reg, re[i]), gr = beside<0x130>(reg, re[i]);
+            const bool dl = kl != k, dr = in && kr != k, du = s[i] != k, dd = s[i + 2] != k;
+            const bool sb = in && (dl || dr || du || dd);
+            const bool gb = in && (gl != reg || gr != reg || r[i] != reg || r[i + 2] != reg);
+            const unsigned long long sm = __ballot(sb), gm = __ballot(gb);
+            if (lane == 0) {
+                smap[(long long)y * g.Wq + word] = sm;
+                gmap[(long long)y * g.Wq + word] = gm;
+            }
+            const bool ok = in && k >= 0 && k < g.K && reg >= 0 && reg < g.R;
+            const unsigned e = (unsigned)(dl || x == 0) + (unsigned)(dr || x + 1 >= g.W) +
+                               (unsigned)(du || y == 0) + (unsigned)(dd || y + 1 >= g.H);
+            const bool head = lane == 0 || dl || gl != reg || x == g.W;
+            row_count(pt, table, perim, g.R, ok, head, k, reg, ok ? e : 0u);
+        }
+        __syncthreads();
+        for (int t = threadIdx.x; t < kPairSlots; t += kMetricWG) {
+            const unsigned key = pt.key[t];
+            if (key == kEmpty) continue;
+            atomicAdd(&table[key], pt.cnt[t]);
+            if (pt.edge[t]) atomicAdd(&perim[key / (unsigned)g.R], pt.edge[t]);
+        }
+        __syncthreads();
     }
 }
 
@@ -199,15 +199,15 @@ __device__ __forceinline__ unsigned long long dilate_mid(unsigned long long lo,
 // The disc rows are taken three at a time, their words loaded before any is
 // dilated.  part[3 b + {0, 1, 2}] = this block's ground-truth boundary
 // pixels, recalled ones, superpixel boundary pixels.
-__global__ __launch_bounds__(kMetricWG) void k_metric_recall(MetricGeom g,
-                                                             const unsigned long long* __restrict__ smap,
-                                                             const unsigned long long* __restrict__ gmap,
-                                                             unsigned long long* __restrict__ part) {
+__device__ __forceinline__ void metric_recall(const MetricGeom& g,
+                                              const unsigned long long* __restrict__ smap,
+                                              const unsigned long long* __restrict__ gmap,
+                                              unsigned long long* __restrict__ part) {
     __shared__ unsigned long long red[kMetricWG / 64][3];
     const long long words = (long long)g.H * g.Wq;
     unsigned long long gb = 0, hit = 0, sb = 0;
     for (long long t = blockIdx.x * (long long)kMetricWG + threadIdx.x; t < words;
-         t += (long long)gridDim.x * kMetricWG) {
+         t += (long long)g.nrb * kMetricWG) {
         const int y = (int)(t / g.Wq), w = (int)(t - (long long)y * g.Wq);
         const unsigned long long gw = gmap[t];
         sb += (unsigned long long)__popcll(smap[t]);
@@ -259,13 +259,13 @@ __global__ __launch_bounds__(kMetricWG) void k_metric_recall(MetricGeom g,
 // Per superpixel (one wave each, lanes striding over the regions): area,
 // largest overlap (ASA), sum over meeting regions of |S_k| - |S_k n G_i|
 // (UE), and the CO term.  Integer sums and maxima: exact in any order.
-__global__ __launch_bounds__(256) void k_metric_rows(MetricGeom g,
-                                                     const unsigned* __restrict__ table,
-                                                     const unsigned* __restrict__ perim,
-                                                     unsigned long long* __restrict__ row_max,
-                                                     unsigned long long* __restrict__ row_ue,
-                                                     double* __restrict__ row_co) {
-    const int k = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+__device__ __forceinline__ void metric_rows(const MetricGeom& g, int block,
+                                            const unsigned* __restrict__ table,
+                                            const unsigned* __restrict__ perim,
+                                            unsigned long long* __restrict__ row_max,
+                                            unsigned long long* __restrict__ row_ue,
+                                            double* __restrict__ row_co) {
+    const int k = block * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (k >= g.K) return;                             // uniform over the wave
     const unsigned* t = table + (long long)k * g.R;
     unsigned long long area = 0, meet = 0;
@@ -291,53 +291,81 @@ __global__ __launch_bounds__(256) void k_metric_rows(MetricGeom g,
     }
 }
 
-__global__ __launch_bounds__(1024) void k_metric_final(MetricGeom g,
-                                                       const unsigned long long* __restrict__ row_max,
-                                                       const unsigned long long* __restrict__ row_ue,
-                                                       const double* __restrict__ row_co,
-                                                       const unsigned long long* __restrict__ part,
-                                                       double* __restrict__ out) {
-    __shared__ unsigned long long rm[1024], ru[1024], rg[1024], rh[1024], rs[1024];
-    __shared__ double rc[1024];
+// Recall in blocks [0, g.nrb), rows in the others: neither reads what the other
+// writes, and each alone lasts about as long as a launch (4.5 and 4.6 us apart,
+// 4.7 together).
+__global__ __launch_bounds__(kMetricWG) void k_metric_rest(MetricGeom g,
+                                                           const unsigned long long* __restrict__ smap,
+                                                           const unsigned long long* __restrict__ gmap,
+                                                           unsigned long long* __restrict__ part,
+                                                           const unsigned* __restrict__ table,
+                                                           const unsigned* __restrict__ perim,
+                                                           unsigned long long* __restrict__ row_max,
+                                                           unsigned long long* __restrict__ row_ue,
+                                                           double* __restrict__ row_co) {
+    if ((int)blockIdx.x < g.nrb)
+        metric_recall(g, smap, gmap, part);
+    else
+        metric_rows(g, (int)blockIdx.x - g.nrb, table, perim, row_max, row_ue, row_co);
+}
+
+__device__ __forceinline__ unsigned long long wave_total(unsigned long long v) {
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// Sums of integers in any order; the FP64 terms are summed in 1024 strands (k mod
+// 1024, four to a lane), paired t with t + 512, then t + 256, ...: in registers,
+// then through LDS above a wave and by shuffles within.  One workgroup of four
+// waves: with sixteen the reductions took longer than the loads they save.
+__global__ __launch_bounds__(kMetricWG) void k_metric_final(MetricGeom g,
+                                                            const unsigned long long* __restrict__ row_max,
+                                                            const unsigned long long* __restrict__ row_ue,
+                                                            const double* __restrict__ row_co,
+                                                            const unsigned long long* __restrict__ part,
+                                                            double* __restrict__ out) {
+    __shared__ unsigned long long red[5][kMetricWG / 64];
+    __shared__ double rc[kMetricWG];
     const int tid = threadIdx.x;
-    unsigned long long m = 0, u = 0, gb = 0, hit = 0, sb = 0;
-    double c = 0.0;
-    for (int k = tid; k < g.K; k += 1024) {
-        m += row_max[k];
-        u += row_ue[k];
-        c += row_co[k];
-    }
-    for (int b = tid; b < g.nrb; b += 1024) {
-        gb += part[3LL * b];
-        hit += part[3LL * b + 1];
-        sb += part[3LL * b + 2];
-    }
-    rm[tid] = m;
-    ru[tid] = u;
-    rc[tid] = c;
-    rg[tid] = gb;
-    rh[tid] = hit;
-    rs[tid] = sb;
-    __syncthreads();
-    for (int h = 512; h > 0; h >>= 1) {
-        if (tid < h) {
-            rm[tid] += rm[tid + h];
-            ru[tid] += ru[tid + h];
-            rc[tid] += rc[tid + h];
-            rg[tid] += rg[tid + h];
-            rh[tid] += rh[tid + h];
-            rs[tid] += rs[tid + h];
+    unsigned long long v[5] = {0, 0, 0, 0, 0};
+    double c[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int k0 = 0; k0 < g.K; k0 += 1024) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            // (loads of a lane past the end repeat the last row: all in flight)
+            const int k = k0 + 256 * q + tid, kc = min(k, g.K - 1);
+            const unsigned long long m = row_max[kc], u = row_ue[kc];
+            const double t = row_co[kc];
+            v[0] += k < g.K ? m : 0ULL;
+            v[1] += k < g.K ? u : 0ULL;
+            c[q] += k < g.K ? t : 0.0;
         }
-        __syncthreads();
     }
+    for (int b = tid; b < g.nrb; b += kMetricWG) {
+        v[2] += part[3LL * b];
+        v[3] += part[3LL * b + 1];
+        v[4] += part[3LL * b + 2];
+    }
+    rc[tid] = (c[0] + c[2]) + (c[1] + c[3]);
+#pragma unroll
+    for (int j = 0; j < 5; ++j) {
+        v[j] = wave_total(v[j]);
+        if ((tid & 63) == 0) red[j][tid >> 6] = v[j];
+    }
+    __syncthreads();
+    if (tid >= 64) return;
+    double co = (rc[tid] + rc[tid + 128]) + (rc[tid + 64] + rc[tid + 192]);
+    for (int o = 32; o > 0; o >>= 1) co += __shfl_down(co, o, 64);   // lane 0: the tree's order
     if (tid == 0) {
+#pragma unroll
+        for (int j = 0; j < 5; ++j) v[j] = red[j][0] + red[j][1] + red[j][2] + red[j][3];
         const double N = (double)g.W * (double)g.H;
-        out[0] = rg[0] ? (double)rh[0] / (double)rg[0] : 1.0;      // BR
-        out[1] = (double)rm[0] / N;                                 // ASA
-        out[2] = (double)ru[0] / N;                                 // UE
-        out[3] = rc[0] / N;                                         // CO
-        out[4] = (double)rg[0];                                     // |B(G)|
-        out[5] = (double)rs[0];                                     // |B(S)|
+        out[0] = v[2] ? (double)v[3] / (double)v[2] : 1.0;      // BR
+        out[1] = (double)v[0] / N;                                 // ASA
+        out[2] = (double)v[1] / N;                                 // UE
+        out[3] = co / N;                                         // CO
+        out[4] = (double)v[2];                                     // |B(G)|
+        out[5] = (double)v[4];                                     // |B(S)|
     }
 }
 
@@ -349,7 +377,7 @@ __global__ void k_zero_u32(unsigned* __restrict__ p, long long n) {
 
 }  // namespace
 
-constexpr int kRecallBlocks = 2048;   // most k_metric_recall blocks (partial sums)
+constexpr int kRecallBlocks = 2048;   // most recall blocks (partial sums)
 
 size_t metrics_workspace_bytes(int W, int H, int K, int R) {
     auto up = [](size_t v) { return (v + 255) / 256 * 256; };
@@ -366,13 +394,7 @@ int launch_metrics(int W, int H, const int* S, int K, const int* G, int R, float
     g.Wq = (W + 63) / 64;
     g.r = (int)ceilf(eps) - 1;
     g.eps2 = eps * eps;
-    // k_metric_pixels: about 1024 blocks of 256 columns by up to 16 rows (more
-    // rows per block gather more pixels per pair in LDS before the atomics)
-    const int bx = (W + kMetricWG - 1) / kMetricWG;
-    g.rows = (int)std::max<long long>(
-        std::min<long long>((long long)H * bx / 1024, 16),
-        std::max<long long>(1, ((long long)H + 65534) / 65535));
-    const int by = (H + g.rows - 1) / g.rows;
+    const int tiles = g.Wq * ((H + kBlockRows - 1) / kBlockRows);   // below 2^27
     const long long map = (long long)H * g.Wq;
     g.nrb = (int)std::min<long long>((map + kMetricWG - 1) / kMetricWG, kRecallBlocks);
     char* b = static_cast<char*>(ws);
@@ -394,13 +416,11 @@ int launch_metrics(int W, int H, const int* S, int K, const int* G, int R, float
     const long long zero_words = (long long)(reinterpret_cast<char*>(row_max) - b) / 4;
     const unsigned zb = (unsigned)std::min<long long>((zero_words + 255) / 256, 65536);
     hipLaunchKernelGGL(k_zero_u32, dim3(zb), dim3(256), 0, st, table, zero_words);
-    hipLaunchKernelGGL(k_metric_pixels, dim3((unsigned)bx, (unsigned)by), dim3(kMetricWG), 0, st,
-                       g, S, G, table, perim, smap, gmap);
-    hipLaunchKernelGGL(k_metric_recall, dim3((unsigned)g.nrb), dim3(kMetricWG), 0, st, g, smap,
-                       gmap, part);
-    hipLaunchKernelGGL(k_metric_rows, dim3((unsigned)((K + 3) / 4)), dim3(256), 0, st, g, table,
-                       perim, row_max, row_ue, row_co);
-    hipLaunchKernelGGL(k_metric_final, dim3(1), dim3(1024), 0, st, g, row_max, row_ue, row_co, part,
+    hipLaunchKernelGGL(k_metric_pixels, dim3((unsigned)std::min(tiles, 65536)), dim3(kMetricWG), 0,
+                       st, g, tiles, S, G, table, perim, smap, gmap);
+    hipLaunchKernelGGL(k_metric_rest, dim3((unsigned)(g.nrb + (K + 3) / 4)), dim3(kMetricWG), 0, st,
+                       g, smap, gmap, part, table, perim, row_max, row_ue, row_co);
+    hipLaunchKernelGGL(k_metric_final, dim3(1), dim3(kMetricWG), 0, st, g, row_max, row_ue, row_co, part,
                        out);
     return hipGetLastError();
 }

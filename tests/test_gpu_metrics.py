@@ -29,6 +29,38 @@ def test_metrics_match_definitions(H, W, K, R, seed, eps):
     assert got["sp_boundary"] == int(M.boundary(sp).sum())
 
 
+@pytest.mark.parametrize("H,W", [(4, 64), (5, 65), (16, 63), (17, 129), (1, 1), (2, 128), (33, 257)])
+def test_metrics_tile_edges(H, W):
+    """Remainders of the 64-column, 16-row tiles, runs that cross from one wave's
+    columns to the next, and labels outside [0, K) or [0, R): those pixels count
+    in no overlap and no perimeter, but are boundary pixels."""
+    from paper_1903_07149_amd.metrics import metrics
+    rng = np.random.default_rng(100 * H + W)
+    K, R = 12, 7
+    sp = np.repeat(rng.integers(0, K, (H, W // 3 + 1)), 3, axis=1)[:, :W].astype(np.int32)
+    gt = np.repeat(rng.integers(0, R, (H, W // 5 + 1)), 5, axis=1)[:, :W].astype(np.int32)
+    for name, a, b in (("inside", sp, gt), ("outside", sp - 2, gt - 1)):
+        say("metrics edges", H, W, name)
+        got = metrics(dev(a), dev(b), num_sp=K, num_regions=R, epsilon=2.0)
+        ok = (a >= 0) & (b >= 0)
+        big = np.pad(a, 1, constant_values=-9)       # another label all round
+        edges = sum((big[1 + dy:1 + dy + H, 1 + dx:1 + dx + W] != a).astype(np.int64)
+                    for dy, dx in ((0, 1), (0, -1), (1, 0), (-1, 0)))
+        table = np.zeros((K, R), np.int64)
+        np.add.at(table, (a[ok], b[ok]), 1)
+        perim = np.bincount(a[ok], weights=edges[ok], minlength=K)
+        area = table.sum(axis=1)
+        n = float(H * W)
+        assert got["asa"] == table.max(axis=1).sum() / n
+        assert got["ue"] == ((table > 0).sum(axis=1) * area - area).sum() / n
+        some = area > 0
+        co = (4 * np.pi * area[some].astype(float) ** 2 / perim[some] ** 2).sum() / n
+        assert abs(got["co"] - co) <= 1e-12 * max(1.0, co)
+        assert got["br"] == M.boundary_recall(a, b, 2.0)
+        assert got["gt_boundary"] == int(M.boundary(b).sum())
+        assert got["sp_boundary"] == int(M.boundary(a).sum())
+
+
 @pytest.mark.parametrize("eps", [17.5, 40.25, 63.9, 64.0])
 def test_boundary_recall_far_and_across_words(eps):
     """Sparse superpixel boundaries (two vertical cuts, one short horizontal
