@@ -71,20 +71,19 @@ typedef struct {
     int32_t reuse_prepared;  /* 1: the workspace already holds this image's
                                 packed (l, a, b, w) from an earlier call with
                                 the same lab/contour/sigma; skip re-packing  */
-    int32_t lds_pixels;      /* tuning of the window form and of the soft
-                                backward: LDS budget in 16-byte units (the
-                                window form's one table of twice this many
-                                8-byte entries), 0..9728; 0 selects the default
-                                (4800).  The 3x3 form and the soft forward have
-                                no tables.  The results do not depend on it  */
-    int32_t wg_size;         /* tuning: assignment workgroup size, 0 (default:
-                                256, and 1024 for the window form), 256, 512 or
-                                1024                                         */
+    int32_t lds_pixels;      /* tuning of the soft backward: LDS budget of its
+                                tiles in 16-byte units, 0..9728; 0 selects the
+                                default (4800).  The hard assignments and the
+                                soft forward have no tables.  The results do
+                                not depend on it                             */
+    int32_t wg_size;         /* tuning: workgroup size of the 3x3 assignment and
+                                of the soft forward, 0 (default: 256), 256, 512
+                                or 1024 (the window form always takes 256)   */
     int32_t assign_mode;     /* SCALP_ASSIGN_GRID3X3 (default) or
                                 SCALP_ASSIGN_WINDOW, see below               */
     int32_t contour_source;  /* SCALP_CONTOUR_INPUT (default) or
                                 SCALP_CONTOUR_GRADIENT, see below            */
-    int32_t exact_pruning;   /* 1 (default): the 3x3 assignment skips the path
+    int32_t exact_pruning;   /* 1 (default): the assignment skips the path
                                 walk of a candidate whose exact FP32 lower
                                 bound of D (lambda dcp + spatial term of
                                 Eq. (3)) cannot beat the best so far, and the
@@ -137,8 +136,8 @@ int scalp_default_params(scalp_params_t* out);
 int scalp_make_grid(int32_t width, int32_t height, int32_t k, scalp_grid_t* out);
 
 /* Bytes of device workspace the single-image entry points need for grid g:
- * the packed (l, a, b, w) image (16 B per pixel), 8 B per pixel of window
- * minima, 68 B per superpixel (integer accumulators, projection queue) and
+ * the packed (l, a, b, w) image (16 B per pixel), 8 B per pixel for the window
+ * form, 68 B per superpixel (integer accumulators, projection queue) and
  * 5376 B of control words (projection queue length, partial maxima of the
  * computed contour prior, the batched assignment's per-XCD queue heads).
  * 0 if g is invalid. */

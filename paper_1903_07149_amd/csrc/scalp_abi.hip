@@ -26,9 +26,6 @@ namespace {
 constexpr size_t kAlign = 256;
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
-std::once_flag g_init_once;
-void library_init() { std::call_once(g_init_once, [] { lift_lds_limits(); }); }
-
 // r = sqrt(N / k) in FP64 (Sec. II-A), with the requested k.
 double grid_r(int W, int H, int k) { return std::sqrt((double)W * (double)H / (double)k); }
 
@@ -64,22 +61,14 @@ bool pack_inputs_ok(const scalp_params_t* p, const float* lab, const float* cont
     return lab && (contour || p->contour_source == SCALP_CONTOUR_GRADIENT);
 }
 
-// Launch shape of the window form (default: 1024 lanes).
-Tuning tuning_of(const scalp_params_t* p) {
-    Tuning t;
-    t.wg = p->wg_size == 0 ? 1024 : p->wg_size;
-    t.lds_pixels = p->lds_pixels > 0 ? p->lds_pixels : default_lds_pixels();
-    t.blocks_per_cu = p->persistent_blocks;
-    return t;
-}
-
 // Launch shape of the grid form and of the soft forward.  256 lanes by default: an item's waves meet
 // at three barriers, and the more items a CU holds, the less it waits there
 // (10 iterations of 1920x1080, k = 2000: 0.848, 0.864 and 0.897 ms at 256,
 // 512 and 1024 lanes; the 64-image batch: 34.0, 36.0 and 39.2 ms).
-Tuning grid_tuning_of(const scalp_params_t* p) {
-    Tuning t = tuning_of(p);
+Tuning tuning_of(const scalp_params_t* p) {
+    Tuning t;
     t.wg = p->wg_size == 0 ? 256 : p->wg_size;
+    t.blocks_per_cu = p->persistent_blocks;
     return t;
 }
 
@@ -103,7 +92,7 @@ Img img_of(const scalp_grid_t* g, const scalp_params_t* p, long long pix, int sp
     const double r = grid_r(g->width, g->height, g->k_requested);
     im.spw = (float)(((double)p->m * (double)p->m) / (r * r));          // Eq. (3)
     im.gamma = p->gamma < 0.0f ? (float)(2.0 * r) : p->gamma;           // Sec. III-A.3
-    im.spl = slices_of(g, grid_tuning_of(p).wg);
+    im.spl = slices_of(g, tuning_of(p).wg);
     im.rad = (int)std::floor(r + 0.5);
     im.prune = p->exact_pruning;
     // Each XCD (own L2) takes a contiguous run of the cell order; strips of
@@ -116,9 +105,9 @@ Img img_of(const scalp_grid_t* g, const scalp_params_t* p, long long pix, int sp
 }
 
 // Single-image workspace: [packed float4 N][acc int64 8K][ctrl int32 64][plist int32 K]
-// [window minima uint64 N]
+// [the window form's tile lists, 8 N]
 struct Layout {
-    size_t packed, acc, ctrl, plist, keys, total;
+    size_t packed, acc, ctrl, plist, lists, total;
 };
 
 Layout layout_of(long long N, long long K) {
@@ -127,8 +116,8 @@ Layout layout_of(long long N, long long K) {
     L.acc = align_up((size_t)N * 16);
     L.ctrl = L.acc + (size_t)K * kAccStride * 8;   // acc and ctrl are contiguous (cleared together)
     L.plist = align_up(L.ctrl + kCtrlWords * 4);
-    L.keys = align_up(L.plist + (size_t)K * 4);
-    L.total = align_up(L.keys + (size_t)N * 8);
+    L.lists = align_up(L.plist + (size_t)K * 4);
+    L.total = align_up(L.lists + (size_t)N * 8);
     return L;
 }
 
@@ -137,14 +126,14 @@ struct Views {
     long long* acc;
     int* ctrl;
     int* plist;
-    unsigned long long* keys;
+    void* lists;
 };
 
 Views views_of(void* ws, const Layout& L) {
     char* b = static_cast<char*>(ws);
     return Views{reinterpret_cast<float4*>(b + L.packed), reinterpret_cast<long long*>(b + L.acc),
                  reinterpret_cast<int*>(b + L.ctrl), reinterpret_cast<int*>(b + L.plist),
-                 reinterpret_cast<unsigned long long*>(b + L.keys)};
+                 b + L.lists};
 }
 
 // Half-width of Algorithm 1's window: r = sqrt(N/k) rounded to whole pixels.
@@ -202,37 +191,33 @@ int enq_init(const Img& im, const Views& v, float* centers, int* endpoints, int*
     return e;
 }
 
-// One window-form pass and its sums (the update cannot be fused: a pixel's
-// label is known only after every window covering it).  The sums pass takes
-// the labels from the window minima and resets them, so consecutive passes
-// need no fill in between; first: fill the minima and clear the sums first
-// (the keys of a workspace hold all ones only after a window pass or a fill;
-// within a run the finalize step leaves every sum at zero, as the grid form
-// relies on).
+// One window-form pass with its sums; first: clear them, and the counts of the tile
+// lists, before (within a run every sum is left at zero by the finalize step, as the
+// grid form relies on, and every count by the pass; the words between the two are
+// the projection list, which is not in use).
 int enq_window_pass(const Img& im, const scalp_params_t* p, const Views& v, int R,
-                    const float* centers, const int* endpoints, int* labels, long long clear_n,
-                    bool first, hipStream_t s) {
-    int e = first ? launch_fill_keys(im, v.keys, s) : (int)hipSuccess;
-    if (e == hipSuccess && first) e = launch_clear(v.acc, clear_n, s);
-    if (e == hipSuccess)
-        e = launch_assign_window(im, v.packed, centers, endpoints, labels, v.keys, R, p->lambda,
-                                 false, tuning_of(p), s);
-    if (e == hipSuccess)
-        e = launch_accumulate_window(im, v.packed, labels, v.keys, v.ctrl, v.acc, s);
-    return e;
+                    const float* centers, const int* endpoints, int* labels, bool first,
+                    bool listed, hipStream_t s) {
+    const long long words = (static_cast<long long*>(v.lists) - v.acc) + window_count_words(im.W, im.H);
+    const int e = first ? launch_clear(v.acc, words, s) : (int)hipSuccess;
+    if (e != hipSuccess) return e;
+    return launch_assign_window(im, v.packed, centers, endpoints, labels, v.acc, v.ctrl, v.lists, R,
+                                p->lambda, true, listed, s);
 }
 
 int enq_iterations(const Img& im, const scalp_params_t* p, const Views& v, float* centers,
-                   int* endpoints, int* labels, int* counts, hipStream_t s, int R,
-                   long long clear_n) {
-    const Tuning t = grid_tuning_of(p);
+                   int* endpoints, int* labels, int* counts, hipStream_t s, int R) {
+    const Tuning t = tuning_of(p);
+    const bool window = p->assign_mode == SCALP_ASSIGN_WINDOW;
     for (int it = 0; it < p->iterations; ++it) {
-        int e = p->assign_mode == SCALP_ASSIGN_WINDOW
-                    ? enq_window_pass(im, p, v, R, centers, endpoints, labels, clear_n, it == 0, s)
-                    : launch_assign(im, v.packed, centers, endpoints, labels, v.acc, v.ctrl,
-                                    p->lambda, true, t, s);
+        int e = window ? enq_window_pass(im, p, v, R, centers, endpoints, labels, it == 0,
+                                         it > 0 && p->project != 0, s)
+                       : launch_assign(im, v.packed, centers, endpoints, labels, v.acc, v.ctrl,
+                                       p->lambda, true, t, s);
+        void* next = window && it + 1 < p->iterations ? v.lists : nullptr;
         if (e == hipSuccess)
-            e = p->project ? launch_finalize_project(im, centers, endpoints, counts, v.acc, labels, s)
+            e = p->project ? launch_finalize_project(im, centers, endpoints, counts, v.acc, labels,
+                                                     next, R, s)
                            : launch_finalize(im, centers, endpoints, counts, v.acc, labels, v.ctrl,
                                              v.plist, false, s);
         if (e != hipSuccess) return e;
@@ -328,7 +313,6 @@ int scalp_prepare(const scalp_grid_t* g, const scalp_params_t* p, const float* l
     int rc = check_common(g, p, ws, ws_bytes);
     if (rc != SCALP_OK) return rc;
     if (!pack_inputs_ok(p, lab, contour)) return SCALP_ERR_ARG;
-    library_init();
     const Views v = views_of(ws, layout_of((long long)g->width * g->height, g->num_sp));
     CHECK_HIP(enq_prepare(g, p, lab, contour, v, (hipStream_t)stream));
     return SCALP_OK;
@@ -341,7 +325,6 @@ int scalp_init_grid(const scalp_grid_t* g, const scalp_params_t* p, const float*
     if (rc != SCALP_OK) return rc;
     if (!centers || !endpoints || !labels) return SCALP_ERR_ARG;
     if (!p->reuse_prepared && !pack_inputs_ok(p, lab, contour)) return SCALP_ERR_ARG;
-    library_init();
     const hipStream_t s = (hipStream_t)stream;
     const Layout L = layout_of((long long)g->width * g->height, g->num_sp);
     const Views v = views_of(ws, L);
@@ -358,17 +341,18 @@ int scalp_assign(const scalp_grid_t* g, const scalp_params_t* p, const float* la
     if (rc != SCALP_OK) return rc;
     if (!centers || !endpoints || !labels) return SCALP_ERR_ARG;
     if (!p->reuse_prepared && !pack_inputs_ok(p, lab, contour)) return SCALP_ERR_ARG;
-    library_init();
     const hipStream_t s = (hipStream_t)stream;
     const Views v = views_of(ws, layout_of((long long)g->width * g->height, g->num_sp));
     if (!p->reuse_prepared) CHECK_HIP(enq_prepare(g, p, lab, contour, v, s));
-    if (p->assign_mode == SCALP_ASSIGN_WINDOW)
+    if (p->assign_mode == SCALP_ASSIGN_WINDOW) {
+        CHECK_HIP(launch_clear(static_cast<long long*>(v.lists),
+                               window_count_words(g->width, g->height), s));
         CHECK_HIP(launch_assign_window(img_of(g, p, 0, 0), v.packed, centers, endpoints, labels,
-                                       v.keys, window_radius(g), p->lambda, true, tuning_of(p),
-                                       s));
-    else
+                                       v.acc, v.ctrl, v.lists, window_radius(g), p->lambda, false,
+                                       false, s));
+    } else
         CHECK_HIP(launch_assign(img_of(g, p, 0, 0), v.packed, centers, endpoints, labels, v.acc,
-                                v.ctrl, p->lambda, false, grid_tuning_of(p), s));
+                                v.ctrl, p->lambda, false, tuning_of(p), s));
     return SCALP_OK;
 }
 
@@ -378,7 +362,6 @@ int scalp_update(const scalp_grid_t* g, const scalp_params_t* p, const float* la
     int rc = check_common(g, p, ws, ws_bytes);
     if (rc != SCALP_OK) return rc;
     if (!lab || !labels || !centers || !endpoints || !counts) return SCALP_ERR_ARG;
-    library_init();
     const hipStream_t s = (hipStream_t)stream;
     const Layout L = layout_of((long long)g->width * g->height, g->num_sp);
     const Views v = views_of(ws, L);
@@ -398,15 +381,14 @@ int scalp_assign_accumulate(const scalp_grid_t* g, const scalp_params_t* p, cons
     int rc = check_common(g, p, ws, ws_bytes);
     if (rc != SCALP_OK) return rc;
     if (!centers || !endpoints || !labels) return SCALP_ERR_ARG;
-    library_init();
     const Layout L = layout_of((long long)g->width * g->height, g->num_sp);
     const Views v = views_of(ws, L);
     if (p->assign_mode == SCALP_ASSIGN_WINDOW)
         CHECK_HIP(enq_window_pass(img_of(g, p, 0, 0), p, v, window_radius(g), centers, endpoints,
-                                  labels, clear_words(L), true, (hipStream_t)stream));
+                                  labels, true, false, (hipStream_t)stream));
     else
         CHECK_HIP(launch_assign(img_of(g, p, 0, 0), v.packed, centers, endpoints, labels, v.acc,
-                                v.ctrl, p->lambda, true, grid_tuning_of(p), (hipStream_t)stream));
+                                v.ctrl, p->lambda, true, tuning_of(p), (hipStream_t)stream));
     return SCALP_OK;
 }
 
@@ -416,7 +398,6 @@ int scalp_finalize(const scalp_grid_t* g, const scalp_params_t* p, const int32_t
     int rc = check_common(g, p, ws, ws_bytes);
     if (rc != SCALP_OK) return rc;
     if (!labels || !centers || !endpoints || !counts) return SCALP_ERR_ARG;
-    library_init();
     const hipStream_t s = (hipStream_t)stream;
     const Views v = views_of(ws, layout_of((long long)g->width * g->height, g->num_sp));
     const Img im = img_of(g, p, 0, 0);
@@ -434,15 +415,13 @@ int scalp_run(const scalp_grid_t* g, const scalp_params_t* p, const float* lab,
     if (rc != SCALP_OK) return rc;
     if (!centers || !endpoints || !labels || !counts) return SCALP_ERR_ARG;
     if (!p->reuse_prepared && !pack_inputs_ok(p, lab, contour)) return SCALP_ERR_ARG;
-    library_init();
     const hipStream_t s = (hipStream_t)stream;
     const Layout L = layout_of((long long)g->width * g->height, g->num_sp);
     const Views v = views_of(ws, L);
     const Img im = img_of(g, p, 0, 0);
     if (!p->reuse_prepared) CHECK_HIP(enq_prepare(g, p, lab, contour, v, s));
     CHECK_HIP(enq_init(im, v, centers, endpoints, counts, labels, s));
-    CHECK_HIP(enq_iterations(im, p, v, centers, endpoints, labels, counts, s, window_radius(g),
-                             clear_words(L)));
+    CHECK_HIP(enq_iterations(im, p, v, centers, endpoints, labels, counts, s, window_radius(g)));
     return SCALP_OK;
 }
 
@@ -466,15 +445,13 @@ int scalp_graph_create(const scalp_grid_t* g, const scalp_params_t* p, float* ce
     int rc = check_common(g, p, ws, ws_bytes);
     if (rc != SCALP_OK) return rc;
     if (!centers || !endpoints || !labels || !counts || !out) return SCALP_ERR_ARG;
-    library_init();
     const Layout L = layout_of((long long)g->width * g->height, g->num_sp);
     const Views v = views_of(ws, L);
     const Img im = img_of(g, p, 0, 0);
     const scalp_params_t pc = *p;
     const int R = window_radius(g);
-    const long long cw = clear_words(L);
     return capture(out, [&](hipStream_t s) {
-        return enq_iterations(im, &pc, v, centers, endpoints, labels, counts, s, R, cw);
+        return enq_iterations(im, &pc, v, centers, endpoints, labels, counts, s, R);
     });
 }
 
@@ -573,7 +550,7 @@ int enq_batched(const scalp_batch_desc_t* d, int n, const scalp_params_t* p, con
     if (e == hipSuccess)
         e = launch_finalize_batched(imgs, starts, n, (int)BL.K, centers, endpoints, counts, v.acc,
                                     labels, v.ctrl, v.plist, false, s);
-    const Tuning t = grid_tuning_of(p);
+    const Tuning t = tuning_of(p);
     long long max_block = 0;
     for (int i = 0; i < n; ++i)
         max_block = std::max(max_block, block_pixels(d[i].grid.width, d[i].grid.height,
@@ -610,8 +587,7 @@ int scalp_run_batched(const scalp_batch_desc_t* descs, int32_t n, const scalp_pa
     if (!centers || !endpoints || !labels || !counts) return SCALP_ERR_ARG;
     if (!p->reuse_prepared && !pack_inputs_ok(p, lab, contour)) return SCALP_ERR_ARG;
     if (!ws || ws_bytes < BL.total) return SCALP_ERR_WORKSPACE;
-    library_init();
-    const int grid = persistent_grid(grid_tuning_of(p));
+    const int grid = persistent_grid(tuning_of(p));
     if (grid < 1) return SCALP_ERR_HIP;
     CHECK_HIP(enq_batched(descs, n, p, lab, contour, centers, endpoints, labels, counts, ws, BL,
                           grid, (hipStream_t)stream));
@@ -628,9 +604,8 @@ int scalp_batched_graph_create(const scalp_batch_desc_t* descs, int32_t n, const
     if (!centers || !endpoints || !labels || !counts || !out) return SCALP_ERR_ARG;
     if (!p->reuse_prepared && !pack_inputs_ok(p, lab, contour)) return SCALP_ERR_ARG;
     if (!ws || ws_bytes < BL.total) return SCALP_ERR_WORKSPACE;
-    library_init();
     // the occupancy query runs before the capture
-    const int grid = persistent_grid(grid_tuning_of(p));
+    const int grid = persistent_grid(tuning_of(p));
     if (grid < 1) return SCALP_ERR_HIP;
     return capture(out, [&](hipStream_t s) {
         return enq_batched(descs, n, p, lab, contour, centers, endpoints, labels, counts, ws, BL,
@@ -697,7 +672,7 @@ bool soft_args_ok(const scalp_grid_t* g, const scalp_params_t* p, float temperat
 }
 
 int soft_cap_bytes(const scalp_params_t* p) {
-    return (p->lds_pixels > 0 ? p->lds_pixels : default_lds_pixels()) * 16;
+    return (p->lds_pixels > 0 ? p->lds_pixels : kDefaultLdsPixels) * 16;
 }
 
 std::once_flag g_soft_once;
@@ -725,14 +700,13 @@ int scalp_soft_forward(const scalp_grid_t* g, const scalp_params_t* p, float tem
     if (!p->reuse_prepared && !pack_inputs_ok(p, lab, contour)) return SCALP_ERR_ARG;
     const SoftWs W = soft_ws_layout(g, batch);
     if (!ws || ws_bytes < W.total) return SCALP_ERR_WORKSPACE;
-    library_init();
     std::call_once(g_soft_once, [] { lift_soft_lds_limits(); });
     const hipStream_t s = (hipStream_t)stream;
     const long long N = (long long)g->width * g->height, K = g->num_sp, B = batch;
     const int T = p->iterations;
     const Img im = img_of(g, p, 0, 0);
     const SoftGeom geo = soft_geom(g->width, g->height, g->nx, g->ny, batch, im.spw, im.gamma,
-                                   p->lambda, temperature, grid_tuning_of(p).wg,
+                                   p->lambda, temperature, tuning_of(p).wg,
                                    p->exact_pruning);
     const SoftSaved S = soft_saved_layout(g, B, T);
     char* wb = static_cast<char*>(ws);
@@ -769,14 +743,13 @@ int scalp_soft_backward(const scalp_grid_t* g, const scalp_params_t* p, float te
     if (!p->reuse_prepared && !lab) return SCALP_ERR_ARG;
     const SoftWs W = soft_ws_layout(g, batch);
     if (!ws || ws_bytes < W.total) return SCALP_ERR_WORKSPACE;
-    library_init();
     std::call_once(g_soft_once, [] { lift_soft_lds_limits(); });
     const hipStream_t s = (hipStream_t)stream;
     const long long N = (long long)g->width * g->height, K = g->num_sp, B = batch;
     const int T = p->iterations;
     const Img im = img_of(g, p, 0, 0);
     const SoftGeom geo = soft_geom(g->width, g->height, g->nx, g->ny, batch, im.spw, im.gamma,
-                                   p->lambda, temperature, grid_tuning_of(p).wg,
+                                   p->lambda, temperature, tuning_of(p).wg,
                                    p->exact_pruning);
     const SoftSaved S = soft_saved_layout(g, B, T);
     char* wb = static_cast<char*>(ws);

@@ -49,11 +49,10 @@ __device__ __forceinline__ long long to_fixed(float v) {
 // Accumulates the samples i = 1 .. n-1 of the path from the pixel at linear
 // index `idx` toward (dx, dy): on major-axis step i the minor offset is
 // floor((2 i |d_minor| + n) / (2 n)).  stepx / stepy are the index strides
-// of one pixel in x / y.  Global-memory variant, used when a candidate's
-// path rectangle exceeds the LDS tables; samples are accumulated in path
-// order, with up to three texel loads in flight.  Paths of up to 46340
+// of one pixel in x / y.  For paths of any length, by 64-bit indexes (walk_near
+// takes the others); samples are accumulated in path order, with up to three texel loads in flight.  Paths of up to 46340
 // steps count the minor steps as the carries of a 32-bit accumulator (exact
-// there, see walk_table); longer ones (cells over ~15000 pixels wide, or
+// there, see step_increment); longer ones (cells over ~15000 pixels wide, or
 // caller-supplied endpoints far across a wide image) keep the remainder
 // exactly.
 __device__ __forceinline__ unsigned step_increment(int am, int n);
@@ -145,9 +144,16 @@ __device__ __forceinline__ void walk_path(const float4* __restrict__ base, int i
 #undef SCALP_GACC
 }
 
-// Increment of the carry-counting line stepper below for minor extent am and
-// major extent n (0 <= am <= n).  Any F with 0 <= F - 2^32 am/n < 2^32/(2 n^2)
-// steps exactly (see walk_table).  For n < 1023 a reciprocal good to one ulp
+// Stepping along a discrete line: the minor-axis offset after i major steps,
+// floor(i s + 1/2) with s = |d_minor| / n, is the number of carries out of a
+// 32-bit accumulator that starts at 2^31 and adds F = ceil(2^32 s) per step (2^32
+// - 1 when s = 1).  The accumulated excess i (F - 2^32 s) < i stays below the gap
+// 2^32 / (2n) between i s + 1/2 and the next integer whenever 2 n^2 < 2^32, i.e.
+// n < 46340, and an exact tie is never undershot since F rounds up: one add with
+// carry-out, one select and one address add per sample.
+//
+// Increment F for minor extent am and major extent n (0 <= am <= n).  Any F with
+// 0 <= F - 2^32 am/n < 2^32/(2 n^2) steps exactly.  For n < 1023 a reciprocal good to one ulp
 // gives 2^32 am/n within 769, and adding 1025 lands in (256, 1794]: inside
 // the window for every n up to 1094.  Longer paths take the correctly
 // rounded double quotient, rounded up.
@@ -160,76 +166,8 @@ __device__ __forceinline__ unsigned step_increment(int am, int n) {
     return (unsigned)ceil((double)am * 4294967296.0 / (double)n);
 }
 
-// Fills an LDS table with (d_c(q), w_q) for the texels of a rectangle of
-// the packed image: entry e = r * tw + c holds texel (min(tx0 + c, W - 1),
-// ty0 + r), for e < area (entries past the rectangle's width only pad the
-// row pitch and are never read by a path).  Lanes step by WG entries, i.e.
-// by (WG / tw rows, WG mod tw columns), with no division per entry, and
-// take two entries per trip with both loads issued before either is used.
-template <int WG>
-__device__ __forceinline__ void fill_table(float2* tab, const float4* __restrict__ img, int W,
-                                           int tx0, int ty0, int tw, int area, float l, float a,
-                                           float b) {
-    const int tid = threadIdx.x;
-    const int dr = WG / tw, dc = WG - dr * tw;
-    int r = tid / tw, c = tid - r * tw;
-    const float4* row = img + (long long)(ty0 + r) * W;
-    int e = tid;
-    for (; e + WG < area; e += 2 * WG) {
-        const float4 f0 = row[min(tx0 + c, W - 1)];
-        c += dc;
-        bool wrap = c >= tw;
-        c -= wrap ? tw : 0;
-        row += (long long)(dr + (wrap ? 1 : 0)) * W;
-        const float4 f1 = row[min(tx0 + c, W - 1)];
-        c += dc;
-        wrap = c >= tw;
-        c -= wrap ? tw : 0;
-        row += (long long)(dr + (wrap ? 1 : 0)) * W;
-        tab[e] = make_float2(colour_dist(f0, l, a, b), f0.w);
-        tab[e + WG] = make_float2(colour_dist(f1, l, a, b), f1.w);
-    }
-    if (e < area) {
-        const float4 f = row[min(tx0 + c, W - 1)];
-        tab[e] = make_float2(colour_dist(f, l, a, b), f.w);
-    }
-}
-
-// The same table, filled column by column: with R = WG / tw >= 1 rows per
-// pass, lane tid < R tw keeps column c = tid mod tw of rows r0 = tid / tw,
-// r0 + R, r0 + 2R, ... (entry e = r tw + c, starting at e = tid), so an
-// entry costs one texel load, its colour distance and two index adds.
-// r0 = floor(tid m / 2^24) with m = ceil(2^24 / tw): exact for tid < 2^10
-// and tw < 2^14, since m tw - 2^24 < tw and tid (m tw - 2^24) < 2^24.  rows:
-// the rectangle's rows; the caller supplies R and m (computed once per
-// table) and takes fill_table when tw > WG.
-template <int WG>
-__device__ __forceinline__ void fill_table_cols(float2* tab, const float4* __restrict__ img,
-                                                int W, int tx0, int ty0, int tw, int rows, int R,
-                                                unsigned m, float l, float a, float b) {
-    const int tid = threadIdx.x;
-    const int r0 = (int)__umulhi((unsigned)tid << 8, m);
-    if (r0 >= R) return;                           // lanes past R tw
-    const int c = tid - r0 * tw;
-    int p = (ty0 + r0) * W + min(tx0 + c, W - 1);  // < W H < 2^31
-    const int dp = R * W, de = R * tw;
-    int e = tid, r = r0;
-    for (; r + R < rows; r += 2 * R) {
-        const float4 f0 = img[p];
-        const float4 f1 = img[p + dp];
-        tab[e] = make_float2(colour_dist(f0, l, a, b), f0.w);
-        tab[e + de] = make_float2(colour_dist(f1, l, a, b), f1.w);
-        p += 2 * dp;
-        e += 2 * de;
-    }
-    if (r < rows) {
-        const float4 f = img[p];
-        tab[e] = make_float2(colour_dist(f, l, a, b), f.w);
-    }
-}
-
 // The steps of a path from (dx, dy): major and diagonal index strides and the
-// carry-counting increment (see walk_table), for strides sx, sy of one pixel.
+// carry-counting increment (see step_increment), for strides sx, sy of one pixel.
 struct PathStep {
     int n, smaj, sdiag;
     unsigned F;
@@ -321,94 +259,6 @@ __device__ __forceinline__ void walk_near(const float4* __restrict__ img, unsign
 }
 #undef SCALP_STEP
 #undef SCALP_ACC
-
-// The walk over a per-candidate LDS table of (colour distance, w) pairs: the
-// colour distance of a texel to the candidate does not depend on the pixel
-// the path starts from, so it is computed once per texel (same FP32
-// operations, same order) and every path sample costs two adds.
-//
-// Stepping: the minor-axis offset after i major steps, floor(i s + 1/2) with
-// s = |d_minor| / n, is the number of carries out of a 32-bit accumulator
-// that starts at 2^31 and adds F = ceil(2^32 s) per step (2^32 - 1 when
-// s = 1).  The accumulated excess i (F - 2^32 s) < i stays below the gap
-// 2^32 / (2n) between i s + 1/2 and the next integer whenever 2 n^2 < 2^32,
-// i.e. n < 46340 (tables never exceed 2 x 9728 entries, so every path over a
-// table qualifies), and an exact tie is never undershot since F rounds up.
-// One add with carry-out, one select and one address add per sample; four
-// samples per loop trip with the loads issued ahead of the adds.  The trip
-// counter is decremented with a borrow-out that is itself the exit test, and
-// the accumulator passes through an empty asm statement once per trip so
-// that the compiler keeps the chain of adds instead of re-deriving acc from
-// a separate induction variable (one instruction less per trip each).
-__device__ __forceinline__ void walk_table(const float2* tab, int idx, int tw, int dx, int dy,
-                                           float& sc, float& sw) {
-    const int adx = dx < 0 ? -dx : dx;
-    const int ady = dy < 0 ? -dy : dy;
-    const bool xmaj = adx >= ady;
-    const int n = xmaj ? adx : ady;
-    if (n < 2) return;
-    const int am = xmaj ? ady : adx;
-    const unsigned F = step_increment(am, n);
-    const int sx = dx < 0 ? -8 : 8;
-    const int sy = dy < 0 ? -8 * tw : 8 * tw;
-    const int smaj = xmaj ? sx : sy;
-    const int sdiag = smaj + (xmaj ? sy : sx);
-    unsigned acc = 0x80000000u;
-    const char* q = reinterpret_cast<const char*>(tab + idx);
-#define SCALP_STEP()                                              \
-    do {                                                          \
-        const bool c_ = __builtin_add_overflow(acc, F, &acc);     \
-        q += c_ ? sdiag : smaj;                                   \
-    } while (0)
-#define SCALP_LOAD() (*reinterpret_cast<const float2*>(q))
-#define SCALP_ACC(v)                                              \
-    do {                                                          \
-        sc = sc + (v).x;                                          \
-        sw = sw + (v).y;                                          \
-    } while (0)
-    // samples 1 .. n-1 (sample 0 and the endpoint are added by the caller)
-    SCALP_STEP();
-    float2 fa = SCALP_LOAD();
-    unsigned trips = (unsigned)(n - 2) >> 2;
-    while (!__builtin_sub_overflow(trips, 1u, &trips)) {
-        SCALP_STEP();
-        const float2 fb = SCALP_LOAD();
-        SCALP_STEP();
-        const float2 fc = SCALP_LOAD();
-        SCALP_ACC(fa);
-        SCALP_STEP();
-        const float2 fd = SCALP_LOAD();
-        SCALP_ACC(fb);
-        SCALP_STEP();
-        fa = SCALP_LOAD();
-        SCALP_ACC(fc);
-        SCALP_ACC(fd);
-        asm volatile("" : "+v"(acc));
-    }
-    const int rem = (n - 2) & 3;
-    if (rem > 0) {
-        SCALP_STEP();
-        const float2 fb = SCALP_LOAD();
-        SCALP_ACC(fa);
-        fa = fb;
-    }
-    if (rem > 1) {
-        SCALP_STEP();
-        const float2 fb = SCALP_LOAD();
-        SCALP_ACC(fa);
-        fa = fb;
-    }
-    if (rem > 2) {
-        SCALP_STEP();
-        const float2 fb = SCALP_LOAD();
-        SCALP_ACC(fa);
-        fa = fb;
-    }
-    SCALP_ACC(fa);
-#undef SCALP_STEP
-#undef SCALP_LOAD
-#undef SCALP_ACC
-}
 
 // Correctly rounded FP64 reciprocals 1/1 .. 1/1024, built at compile time.
 struct RecipTable {
@@ -610,12 +460,6 @@ __device__ __forceinline__ void pixel_at(const PixelMap& p, int t, int& x, int& 
     y = (s & 1) ? (p.ch - 1 - row) : row;
 }
 
-// Strip (8-column band) of cell pixel t, in the order of cell_pixel.
-__device__ __forceinline__ int strip_of(int t, int cw, int ch) {
-    const int fullpx = (cw >> 3) * 8 * ch;
-    return t < fullpx ? t / (8 * ch) : (cw >> 3);
-}
-
 // The candidates' centres as the bounds read them: the item's 9 superpixels
 // are uniform over the workgroup, so their values come through the scalar
 // cache into scalar registers (nothing writes centres or endpoints while an
@@ -712,31 +556,10 @@ __device__ __forceinline__ int wave_claim(int* count, unsigned long long m) {
 
 __device__ __forceinline__ float key_bound(unsigned key) { return __uint_as_float(key & ~15u); }
 
-// x of lane i - CTRL's shift, 0 where that lane is outside the row or the
-// row is not in ROW_MASK (DPP: gfx9 row_shr / row_bcast controls).
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ float dpp_or_zero(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROW_MASK, 0xf,
-                                                      false));
-}
-
-// Sum over the 64 lanes of a wave in six DPP steps (no LDS traffic): row
-// prefix sums by shifts of 1, 2, 4 and 8 lanes, then the last lane of each
-// row is broadcast into the next row (row_bcast:15) and lane 31 into rows 2
-// and 3 (row_bcast:31).  Only lane 63 holds the total.  All lanes must be
-// active.
-__device__ __forceinline__ float wave_sum_last(float v) {
-    v += dpp_or_zero<0x111, 0xf>(v);
-    v += dpp_or_zero<0x112, 0xf>(v);
-    v += dpp_or_zero<0x114, 0xf>(v);
-    v += dpp_or_zero<0x118, 0xf>(v);
-    v += dpp_or_zero<0x142, 0xa>(v);
-    v += dpp_or_zero<0x143, 0xc>(v);
-    return v;
-}
-
-// Sum over the lanes up to and including this one, in six DPP steps (see
-// wave_sum_last).  All lanes must be active.
+// Sum over the lanes up to and including this one, in six DPP steps (no LDS
+// traffic): row prefix sums by shifts of 1, 2, 4 and 8 lanes, then the last lane
+// of each row is added to the next row (row_bcast:15) and lane 31 to rows 2 and 3
+// (row_bcast:31).  All lanes must be active.
 __device__ __forceinline__ int wave_scan_incl(int v) {
 #define SCALP_SCAN_STEP(ctrl, rows) \
     v += __builtin_amdgcn_update_dpp(0, v, ctrl, rows, 0xf, false)
@@ -765,11 +588,6 @@ __device__ __forceinline__ int wave_min_i32(int v) {
 __device__ __forceinline__ int wave_max_i32(int v) {
     for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
     return __builtin_amdgcn_readfirstlane(v);
-}
-
-__device__ __forceinline__ float wave_sum(float v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
 }
 
 }  // namespace dev

@@ -73,19 +73,14 @@ constexpr int kMinAssignWG = 256;
 
 struct Tuning {
     int wg;           // workgroup size of the assignment kernel (256, 512 or 1024)
-    int lds_pixels;   // LDS table budget in 16-byte units (window form)
     int blocks_per_cu = 0;   // persistent launch: workgroups per CU (0: as many as fit)
 };
 
-int default_lds_pixels();
-// LDS budget of the table-walking kernels in 16-byte units (the window form's
-// one table of twice as many 8-byte entries; the soft forward's two tables):
-// 152 KiB of the 160 KiB of a gfx950 CU.
+// LDS budget of the soft backward's tiles in 16-byte units: the default, and the
+// largest (152 KiB of the 160 KiB of a gfx950 CU).
+constexpr int kDefaultLdsPixels = 4800;
 constexpr int kMaxLdsPixels = 9728;
 
-// Raises the per-kernel dynamic LDS limit of the assignment kernels (once per
-// process, before any launch or capture).
-void lift_lds_limits();
 int launch_write_bytes(void* dst, const void* src, size_t n, hipStream_t s);
 
 // Launchers (return hipError_t as int).  All enqueue on `s`.
@@ -99,18 +94,16 @@ int launch_assign(const Img& im, const float4* packed, const float* centres,
                   bool accumulate, const Tuning& t, hipStream_t s);
 int launch_accumulate(const Img& im, const float* lab, const int* labels, long long* acc,
                       hipStream_t s);
-// Window form of the assignment (candidate rule of Algorithm 1).  keys: one
-// 64-bit minimum per pixel.  labels_out: fill the keys, then write the labels
-// (labels in/out); else the keys must hold all ones on entry and keep the
-// pass's minima for launch_accumulate_window.
+// Window form of the assignment (candidate rule of Algorithm 1; labels in/out).
+// lists: max(8 W H, 256) bytes of scratch, the first window_count_words 64-bit
+// words of them zero before the first pass (every pass leaves them zero).
+// listed: the lists are made already (launch_finalize_project of the pass before).
+// accumulate: add the update's sums to acc and empty the projection queue, as the
+// grid form does.
+long long window_count_words(int W, int H);
 int launch_assign_window(const Img& im, const float4* packed, const float* centres,
-                         const int* endpoints, int* labels, unsigned long long* keys, int R,
-                         float lambda, bool labels_out, const Tuning& t, hipStream_t s);
-int launch_fill_keys(const Img& im, unsigned long long* keys, hipStream_t s);
-// The update sums of a window pass: labels from the keys where a window
-// covered the pixel, keys reset to all ones, the projection queue emptied.
-int launch_accumulate_window(const Img& im, const float4* packed, int* labels,
-                             unsigned long long* keys, int* ctrl, long long* acc, hipStream_t s);
+                         const int* endpoints, int* labels, long long* acc, int* ctrl, void* lists,
+                         int R, float lambda, bool accumulate, bool listed, hipStream_t s);
 int launch_finalize(const Img& im, float* centres, int* endpoints, int* counts,
                     long long* acc, const int* labels, int* ctrl, int* plist, bool project,
                     hipStream_t s);
@@ -121,8 +114,9 @@ int launch_finalize_project_batched(const Img* imgs, const int* sp_start, int n_
                                     int* endpoints, int* counts, long long* acc, const int* labels,
                                     int* ctrl, hipStream_t s);
 long long block_pixels(int W, int H, int nx, int ny);
+// lists (or null) and R: make the tile lists of the window form's next pass, too
 int launch_finalize_project(const Img& im, float* centres, int* endpoints, int* counts,
-                            long long* acc, const int* labels, hipStream_t s);
+                            long long* acc, const int* labels, void* lists, int R, hipStream_t s);
 int launch_project(const Img& im, const float* centres, const int* counts, const int* labels,
                    int* endpoints, const int* ctrl, const int* plist, hipStream_t s);
 

@@ -322,97 +322,290 @@ void k_assign_persistent(const Img* __restrict__ imgs,
 // Window candidate rule of Algorithm 1: a pixel's candidates are the
 // clusters whose window (half-width R around the rounded barycenter)
 // contains it, and it takes the smallest D of Eq. (3), the smallest k among
-// equal distances.  One workgroup per cluster k scans k's window, computes D
-// for every pixel of it along the path to k's endpoint, and offers (D, k) to
-// the pixel with a 64-bit atomic minimum of (FP32 bits of D, k): D >= 0, so
-// the minimum is the smallest D and, among equal D, the smallest k.
-template <int WG>
-__global__ __launch_bounds__(WG) void k_assign_window(Img im, const float4* __restrict__ packed,
-                                                      const float* __restrict__ centres,
-                                                      const int* __restrict__ endpoints,
-                                                      unsigned long long* __restrict__ keys,
-                                                      int R, float lambda, int cap) {
-    extern __shared__ float2 win_tab[];
+// equal distances: the smallest (FP32 bits of D, k) as a 64-bit number (D >= 0;
+// an infinite or NaN D loses to every finite one).  A pixel that no window
+// contains keeps its label.  Single images only (im.pix and im.sp are 0).
+
+constexpr int kWinTile = 16;     // a workgroup's tile is kWinTile x kWinTile pixels
+constexpr int kWinWG = kWinTile * kWinTile;
+constexpr int kWinBatch = 12;    // candidates that a tile evaluates at a time (at most 15)
+constexpr int kWinIds = 512;     // candidates that a tile lists at a time
+
+// The tiles' candidates: count[tile] (cleared before the first pass; every tile
+// clears its own again) and the first `cap` of them in list[tile * cap ...], in
+// any order.
+struct WinLists {
+    int* count;
+    int* list;
+    int cap, tx, tiles;   // tiles of a row, in all
+};
+
+// Adds cluster k with barycenter (x, y) to the tiles that its window meets.  The
+// lanes of one wave call.
+__device__ __forceinline__ void add_to_tiles(const Img& im, int k, float x, float y, int R,
+                                             const WinLists& wl) {
+    const int wx = round_coord(x, im.W - 1), wy = round_coord(y, im.H - 1);
+    const int tx0 = max(wx - R, 0) / kWinTile, tx1 = min(wx + R, im.W - 1) / kWinTile;
+    const int ty0 = max(wy - R, 0) / kWinTile, ty1 = min(wy + R, im.H - 1) / kWinTile;
+    const int nx = tx1 - tx0 + 1, n = nx * (ty1 - ty0 + 1);
+    for (int i = threadIdx.x & 63; i < n; i += 64) {
+        const int r = i / nx;
+        const int tile = (ty0 + r) * wl.tx + tx0 + (i - r * nx);
+        const int at = atomicAdd(&wl.count[tile], 1);
+        if (at < wl.cap) wl.list[(long long)tile * wl.cap + at] = k;
+    }
+}
+
+// The lists of all clusters, a wave per cluster (before the first pass of a run;
+// k_finalize_project makes those of the next one).
+__global__ __launch_bounds__(256) void k_window_lists(Img im, const float* __restrict__ centres, int R,
+                                                      WinLists wl) {
+    const int k = blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+    if (k >= im.nx * im.ny) return;
+    add_to_tiles(im, k, centres[5LL * k + 3], centres[5LL * k + 4], R, wl);
+}
+
+// Candidates are numbered by their place in ids, which is in ascending k; win is,
+// by pixel, the smallest (FP32 bits of D) << 32 | number + 1, with 0 as the number
+// of a cluster of an earlier list (its k is smaller; its label is stored).
+struct WinShared {
+    unsigned long long bins[kWinBatch * 6][kBinCopies];   // the update's sums, [slot * 6 + sum]
+    unsigned long long win[kWinWG];
+    float4 cand[kWinBatch][2];                            // (l, a, b, x), (y, endpoint)
+    int4 box[kWinBatch];                                  // k, the window's corner
+    int ids[kWinIds], unsorted[kWinIds];
+    unsigned short list[(kWinBatch - 1) * kWinWG];        // pixel | slot << 8
+    int pairs, count;
+};
+
+__device__ __forceinline__ unsigned med3(unsigned a, unsigned b, unsigned c) {
+    return max(min(a, b), min(max(a, b), c));
+}
+
+// What a bound must exceed for its candidate to lose to `win`; nothing does
+// while that is no finite D.
+__device__ __forceinline__ float win_threshold(unsigned long long win) {
+    const float best = __uint_as_float((unsigned)(win >> 32));
+    return best < INFINITY ? threshold(best) : INFINITY;
+}
+
+// A workgroup takes a tile of kWinTile x kWinTile pixels, one pixel per lane, a
+// wave an 8x8 block.  It evaluates the tile's candidates as the grid form does its
+// 9: the candidate with the smallest lower bound of D first, then by full waves the
+// (pixel, candidate) pairs whose bound does not exceed that D.  More than kWinBatch
+// candidates are taken in batches against the smallest D so far; a tile whose list
+// overflowed tests all clusters, kWinIds at a time.  With ACCUM the update's sums go
+// through bins per candidate of the tile (to global memory directly for pixels that
+// no window contains).
+//
+// What bounds it: VALU issue, as in the grid form (31 M wave instructions per
+// launch at 1920x1080, k = 2000, R = 32).  69 us with the sums.  A workgroup per
+// cluster that walked its whole window over a table in LDS (4.1 walks per pixel,
+// each result through a 64-bit minimum in global memory) took 78, and the sums
+// another 17.  One kernel for NEAR and not took 77 (the walks by 64-bit indexes made
+// it spill), all keys of a batch in registers instead of the four smallest 95, and
+// 72 at 7 waves per SIMD.
+template <bool ACCUM, bool NEAR>
+__global__ __launch_bounds__(kWinWG) __attribute__((amdgpu_waves_per_eu(8))) void k_assign_window(
+    Img im, const float4* __restrict__ packed, const float* __restrict__ centres,
+    const int* __restrict__ endpoints, int* __restrict__ labels, long long* __restrict__ acc,
+    int* __restrict__ ctrl, WinLists wl, int R, float lambda, int tile0) {
+    __shared__ WinShared sh;
     const int tid = threadIdx.x;
-    const int k = xcd_remap(blockIdx.x, gridDim.x);
-    const int W = im.W, H = im.H;
-    const float4* __restrict__ img = packed + im.pix;
-    const float* ck = centres + 5LL * (im.sp + k);
-    const float l = ck[0], a = ck[1], b = ck[2], xk = ck[3], yk = ck[4];
-    const int wx = round_coord(xk, W - 1), wy = round_coord(yk, H - 1);
-    const int cx = min(max(endpoints[2LL * (im.sp + k)], 0), W - 1);
-    const int cy = min(max(endpoints[2LL * (im.sp + k) + 1], 0), H - 1);
-    const int x0 = max(wx - R, 0), x1 = min(wx + R, W - 1) + 1;
-    const int y0 = max(wy - R, 0), y1 = min(wy + R, H - 1) + 1;
-    // the paths of the window end at (cx, cy): over bbox(window, endpoint)
-    // the table holds (d_c(q, k), w_q), two 8-byte entries per 16-byte unit
-    const int rx0 = min(x0, cx), rx1 = max(x1, cx + 1);
-    const int ry0 = min(y0, cy), ry1 = max(y1, cy + 1);
-    const bool staged = (long long)(rx1 - rx0) * (ry1 - ry0) <= 2LL * cap;
-    const int rw = rx1 - rx0;
-    if (staged) {
-        if (rw <= WG)                                // uniform
-            fill_table_cols<WG>(win_tab, img, W, rx0, ry0, rw, ry1 - ry0, WG / rw,
-                                (0x1000000u + (unsigned)rw - 1u) / (unsigned)rw, l, a, b);
-        else
-            fill_table<WG>(win_tab, img, W, rx0, ry0, rw, rw * (ry1 - ry0), l, a, b);
+    if (ACCUM && tile0 == 0 && blockIdx.x == 0 && tid == 0) ctrl[kCtrlProjCount] = 0;
+    const int W = im.W, H = im.H, K = im.nx * im.ny;
+    Eqs eqs;
+    eqs.img = packed;
+    eqs.W = W;
+    eqs.near = NEAR;
+    eqs.lambda = lambda;
+    eqs.oml = 1.0f - lambda;
+    eqs.gamma = im.gamma;
+    eqs.spw = im.spw;
+    const bool prune = im.prune != 0;
+    const bool cut = prune && im.gamma <= 0x1p40f;
+    const unsigned span = 2u * (unsigned)R;
+    const ConstF ccen = (ConstF)(uintptr_t)centres;
+    // candidate k into slot j
+    auto stage = [&](int j, int k) {
+        const float* c = centres + 5LL * k;
+        sh.cand[j][0] = make_float4(c[0], c[1], c[2], c[3]);
+        sh.cand[j][1] = make_float4(c[4], __int_as_float(min(max(endpoints[2LL * k], 0), W - 1)),
+                                    __int_as_float(min(max(endpoints[2LL * k + 1], 0), H - 1)), 0.0f);
+        sh.box[j] = make_int4(k, round_coord(c[3], W - 1) - R, round_coord(c[4], H - 1) - R, 0);
+    };
+    // pixel `id` of the tile, relative to its corner
+    auto pixel_x = [](int id) { return (id & 7) + ((id >> 3) & 8); };
+    auto pixel_y = [](int id) { return ((id >> 3) & 7) + ((id >> 4) & 8); };
+
+    const int tile = tile0 + xcd_remap(blockIdx.x, gridDim.x);
+    const int ty = tile / wl.tx;
+    const int x0 = (tile - ty * wl.tx) * kWinTile, y0 = ty * kWinTile;
+    const int x1 = min(x0 + kWinTile, W) - 1, y1 = min(y0 + kWinTile, H) - 1;
+    const int px = x0 + pixel_x(tid), py = y0 + pixel_y(tid);
+    const bool mine = px < W && py < H;
+
+    auto distance = [&](int j, float4 f, int qx, int qy, bool on, float thr) -> float {
+        const float4 c0 = sh.cand[j][0], c1 = sh.cand[j][1];
+        const float ck[5] = {c0.x, c0.y, c0.z, c0.w, c1.x};
+        float A, B;
+        return path_distance(eqs, ck, f, __float_as_int(c1.y), __float_as_int(c1.z), qx, qy, on,
+                             thr, A, B);
+    };
+    // key of slot j: the upper 28 bits of the bound of D (see bound_keys) with the slot
+    // below, kNoKey where the window does not contain the lane's pixel
+    auto key_of = [&](int j, float4 fp) -> unsigned {
+        const int4 box = sh.box[j];
+        const ConstF c = ccen + 5LL * __builtin_amdgcn_readfirstlane(box.x);
+        const float dl = fp.x - c[0], da = fp.y - c[1], db = fp.z - c[2];
+        const float ex = (float)px - c[3], ey = (float)py - c[4];
+        const float dcp = __builtin_fmaf(db, db, __builtin_fmaf(da, da, dl * dl));
+        const float lb = __builtin_fmaf(ex * ex + ey * ey, im.spw, lambda * dcp);
+        const bool in = (unsigned)(px - box.y) <= span && (unsigned)(py - box.z) <= span;
+        // (without the sign that a NaN may have)
+        return in ? (__float_as_uint(lb) & 0x7ffffff0u) | (unsigned)j : kNoKey;
+    };
+    sh.win[tid] = ~0ULL;
+    const int all = __builtin_amdgcn_readfirstlane(*const_cast<volatile int*>(&wl.count[tile]));
+    const bool scan = all > wl.cap;
+    if (ACCUM)
+        for (int t = tid; t < kWinBatch * 6 * kBinCopies; t += kWinWG) (&sh.bins[0][0])[t] = 0ULL;
+    int listed = all;
+    if (!scan) {
+        const int* list = wl.list + (long long)tile * wl.cap;
+        for (int t = tid; t < listed; t += kWinWG) sh.unsorted[t] = list[t];
     }
-    __syncthreads();
-    const float4 fc = img[(long long)cy * W + cx];
-    const float dcc = colour_dist(fc, l, a, b), wc = fc.w;
-    const int cw = x1 - x0, ch = y1 - y0, P = cw * ch;
-    const int lane = tid & 63, wave = tid >> 6;
-    const float oml = 1.0f - lambda;
-    for (int chunk = wave; chunk * 64 < P; chunk += WG / 64) {
-        const int t = chunk * 64 + lane;
-        if (t >= P) continue;
-        int x, y;
-        cell_pixel(t, cw, ch, x, y);
-        x += x0;
-        y += y0;
-        const int p = y * W + x;
-        const float4 fp = img[p];
-        const int dx = cx - x, dy = cy - y;
-        const int adx = dx < 0 ? -dx : dx, ady = dy < 0 ? -dy : dy;
-        const int n = adx > ady ? adx : ady;
-        const double inv = path_recip(n);
-        const float dcp = colour_dist(fp, l, a, b);
-        float sc = dcp, sw = fp.w;
-        if (staged)
-            walk_table(win_tab, (y - ry0) * rw + (x - rx0), rw, dx, dy, sc, sw);
-        else
-            walk_path(img, p, 1, W, dx, dy, l, a, b, sc, sw);
-        if (n > 0) {
-            sc = sc + dcc;
-            sw = sw + wc;
+    // one turn, or one per kWinIds clusters (the same control in all waves)
+    for (int k0 = 0;; k0 += kWinIds) {
+        if (scan) {
+            if (tid == 0) sh.count = 0;
+            __syncthreads();
+            for (int k = k0 + tid; k < min(k0 + kWinIds, K); k += kWinWG) {
+                const float* c = centres + 5LL * k;
+                const int wx = round_coord(c[3], W - 1), wy = round_coord(c[4], H - 1);
+                const bool in = wx - R <= x1 && wx + R >= x0 && wy - R <= y1 && wy + R >= y0;
+                if (in) sh.unsorted[atomicAdd(&sh.count, 1)] = k;
+            }
+            __syncthreads();
+            listed = __builtin_amdgcn_readfirstlane(sh.count);
+        } else {
+            __syncthreads();
+            if (tid == 0) wl.count[tile] = 0;              // all waves have read it
         }
-        float qc, qw;
-        div_path_len(sc, sw, n, inv, qc, qw);
-        const float A = lambda * dcp + oml * qc;
-        const float B = 1.0f + im.gamma * qw;
-        const float ex = (float)x - xk, ey = (float)y - yk;
-        const float D = A * B + (ex * ex + ey * ey) * im.spw;
-        const unsigned long long key = ((unsigned long long)__float_as_uint(D) << 32) | (unsigned)k;
-        // keys only ever decrease: a stored key at or below this one (even
-        // read stale) means the atomic would change nothing
-        unsigned long long* kp = &keys[im.pix + p];
-        if (key < *reinterpret_cast<volatile unsigned long long*>(kp)) atomicMin(kp, key);
+        const bool last = !scan || k0 + kWinIds >= K;
+        for (int t = tid; t < listed; t += kWinWG) {
+            const int k = sh.unsorted[t];
+            int rank = 0;
+            for (int u = 0; u < listed; ++u) rank += sh.unsorted[u] < k ? 1 : 0;
+            sh.ids[rank] = k;
+            if (rank < kWinBatch) stage(rank, k);
+        }
+        __syncthreads();
+        for (int b0 = 0; b0 < listed; b0 += kWinBatch) {
+            const int n = min(listed - b0, kWinBatch);
+            if (b0 > 0 && tid < n) stage(tid, sh.ids[b0 + tid]);
+            if (tid == 0) sh.pairs = 0;
+            __syncthreads();
+            if (mine) {
+                const float4 fp = packed[py * W + px];
+                unsigned long long win = sh.win[tid];
+                // the four smallest keys, k1 < k2 < k3 < k4
+                unsigned k1 = kNoKey, k2 = kNoKey, k3 = kNoKey, k4 = kNoKey;
+                for (int j = 0; j < n; ++j) {
+                    const unsigned key = key_of(j, fp);
+                    k4 = med3(k3, k4, key);
+                    k3 = med3(k2, k3, key);
+                    k2 = med3(k1, k2, key);
+                    k1 = min(k1, key);
+                }
+                if (k1 != kNoKey && !(prune && key_bound(k1) > win_threshold(win))) {
+                    const int j = (int)(k1 & 15u);
+                    const float D = distance(j, fp, px, py, false, 0.0f);
+                    const unsigned long long found =
+                        ((unsigned long long)__float_as_uint(D) << 32) | (unsigned)(b0 + j + 1);
+                    if (found < win) sh.win[tid] = win = found;
+                }
+                const float thr = win_threshold(win);
+                auto list = [&](unsigned key) {            // whether any lane's is
+                    const bool more = key != kNoKey && !(prune && key_bound(key) > thr);
+                    const unsigned long long m = __ballot(more);
+                    if (m == 0ULL) return false;
+                    const int at = wave_claim(&sh.pairs, m);
+                    if (more) sh.list[at] = (unsigned short)(tid | ((key & 15u) << 8));
+                    return true;
+                };
+                if (list(k2) && list(k3) && list(k4)) {
+                    for (int j = 0; j < n; ++j) {
+                        const unsigned key = key_of(j, fp);
+                        list(key > k4 ? key : kNoKey);
+                    }
+                }
+            }
+            __syncthreads();
+            const int pairs = __builtin_amdgcn_readfirstlane(sh.pairs);
+            for (int i = tid; i < pairs; i += kWinWG) {
+                const unsigned e = sh.list[i];
+                const int id = (int)(e & 255u), j = (int)(e >> 8);
+                const int qx = x0 + pixel_x(id), qy = y0 + pixel_y(id);
+                const float D = distance(j, packed[qy * W + qx], qx, qy, cut, win_threshold(sh.win[id]));
+                atomicMin(&sh.win[id], ((unsigned long long)__float_as_uint(D) << 32) |
+                                           (unsigned)(b0 + j + 1));
+            }
+            __syncthreads();
+        }
+        if (last) break;
+        const unsigned long long win = sh.win[tid];
+        if (mine && win != ~0ULL && (unsigned)win != 0u) {
+            labels[py * W + px] = sh.ids[(unsigned)win - 1u];
+            sh.win[tid] = win & ~0xffffffffULL;
+        }
+        __syncthreads();
     }
-}
+    if (scan && tid == 0) wl.count[tile] = 0;
 
-__global__ void k_fill_u64(unsigned long long* __restrict__ p, long long n, unsigned long long v) {
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-         i += (long long)gridDim.x * blockDim.x)
-        p[i] = v;
-}
-
-// Labels from the window minima; pixels no window covered keep their label.
-__global__ void k_window_labels(const unsigned long long* __restrict__ keys, int* __restrict__ labels,
-                                long long n) {
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-         i += (long long)gridDim.x * blockDim.x) {
-        const unsigned long long key = keys[i];
-        if (key != ~0ULL) labels[i] = (int)(unsigned)(key & 0xffffffffULL);
+    const unsigned long long win = sh.win[tid];
+    const int slot = mine && win != ~0ULL ? (int)(unsigned)win - 1 : -1;
+    const int p = py * W + px;
+    if (slot >= 0) labels[p] = sh.ids[slot];
+    if (!ACCUM) return;
+    unsigned long long v[6] = {1ULL, (unsigned long long)px, (unsigned long long)py, 0ULL, 0ULL, 0ULL};
+    if (mine) {
+        const float4 f = packed[py * W + px];
+        v[3] = (unsigned long long)to_fixed(f.x);
+        v[4] = (unsigned long long)to_fixed(f.y);
+        v[5] = (unsigned long long)to_fixed(f.z);
+        if (slot < 0) {
+            const int k = labels[p];
+            if (k >= 0 && k < K)
+                for (int c = 0; c < 6; ++c)
+                    atomicAdd((unsigned long long*)(acc + kAccStride * (long long)k + c),
+                              v[c]);
+        }
+    }
+    // the bins hold kWinBatch candidates at a time
+    const int cp = (tid ^ (tid >> 3)) & (kBinCopies - 1);
+    for (int s0 = 0; s0 < listed; s0 += kWinBatch) {
+        if (slot >= s0 && slot < s0 + kWinBatch) {
+#pragma unroll
+            for (int c = 0; c < 6; ++c) atomicAdd(&sh.bins[6 * (slot - s0) + c][cp], v[c]);
+        }
+        __syncthreads();
+        const int j = tid / 6;
+        if (j < min(listed - s0, kWinBatch)) {
+            unsigned long long n = 0, sum = 0;
+            for (int c = 0; c < kBinCopies; ++c) {
+                n += sh.bins[6 * j][c];
+                sum += sh.bins[tid][c];
+            }
+            if (n != 0ULL)
+                atomicAdd((unsigned long long*)(acc + kAccStride * (long long)sh.ids[s0 + j] +
+                                                (tid - 6 * j)),
+                          sum);
+        }
+        if (s0 + kWinBatch >= listed) break;
+        __syncthreads();
+        for (int t = tid; t < kWinBatch * 6 * kBinCopies; t += kWinWG) (&sh.bins[0][0])[t] = 0ULL;
+        __syncthreads();
     }
 }
 
@@ -486,45 +679,24 @@ __global__ __launch_bounds__(WG) void k_init_cells_batched(const Img* __restrict
 
 // ---------------------------------------------------------------- update from labels
 
-// Colour source of the update: the caller's lab array, or the packed texels.
-struct LabSource {
-    const float* lab;
-    const float4* packed;
-    __device__ __forceinline__ float3 operator()(long long p) const {
-        if (packed) {
-            const float4 f = packed[p];
-            return make_float3(f.x, f.y, f.z);
-        }
-        return make_float3(lab[3 * p], lab[3 * p + 1], lab[3 * p + 2]);
-    }
-};
-
-// Integer sums of the update for labels that need not be grid neighbours
-// (window form, caller-supplied labels).  One workgroup per grid cell
+// Integer sums of the update for caller-supplied labels, which need not be grid
+// neighbours.  One workgroup per grid cell
 // accumulates into a small LDS table keyed by label (open addressing, key
 // claimed with a compare-and-swap); a label that finds no free slot goes
 // straight to the global sums.  The sums are integers, so the result does
 // not depend on the order of the atomics.
 constexpr int kAccSlots = 32;
 
-// wkeys (window form, else null): the pass's window minima; a pixel whose
-// key is set takes its label from it (the others keep theirs), and every key
-// is reset to the all-ones "no window" value for the next pass; the pass
-// also empties the projection queue that the finalize step after it fills
-// (ctrl, as the fused grid-form pass does).
 template <int WG>
-__global__ __launch_bounds__(WG) void k_accumulate(Img im, LabSource src,
-                                                   int* __restrict__ labels,
-                                                   unsigned long long* __restrict__ wkeys,
-                                                   int* __restrict__ ctrl,
+__global__ __launch_bounds__(WG) void k_accumulate(Img im, const float* __restrict__ lab,
+                                                   const int* __restrict__ labels,
                                                    long long* __restrict__ acc) {
     __shared__ int keys[kAccSlots];
     // [slot * 6 + sum][copy]: the lanes of a wave mostly carry one label, so
-    // each adds to copy (t ^ t >> 3) mod kBinCopies (see CellShared)
+    // each adds to copy (t ^ t >> 3) mod kBinCopies (see ItemShared)
     __shared__ unsigned long long bins[kAccSlots * 6][kBinCopies];
     const int tid = threadIdx.x;
     const int cell = blockIdx.x;
-    if (ctrl && cell == 0 && tid == 0) ctrl[kCtrlProjCount] = 0;
     const int ci = cell / im.nx, cj = cell - ci * im.nx;
     const int x0 = cell_lo(cj, im.W, im.nx), x1 = cell_lo(cj + 1, im.W, im.nx);
     const int y0 = cell_lo(ci, im.H, im.ny), y1 = cell_lo(ci + 1, im.H, im.ny);
@@ -538,21 +710,9 @@ __global__ __launch_bounds__(WG) void k_accumulate(Img im, LabSource src,
         const int r = t / cw;
         const int x = x0 + (t - r * cw), y = y0 + r;
         const long long p = (long long)y * im.W + x;
-        int k;
-        if (wkeys) {
-            const unsigned long long key = wkeys[p];
-            if (key != ~0ULL) {
-                k = (int)(unsigned)(key & 0xffffffffULL);
-                labels[p] = k;
-            } else {
-                k = labels[p];
-            }
-            wkeys[p] = ~0ULL;
-        } else {
-            k = labels[p];
-        }
+        const int k = labels[p];
         if (k < 0 || k >= K) continue;
-        const float3 f = src(p);
+        const float3 f = make_float3(lab[3 * p], lab[3 * p + 1], lab[3 * p + 2]);
         const unsigned long long v[6] = {1ULL, (unsigned long long)x, (unsigned long long)y,
                                          (unsigned long long)to_fixed(f.x),
                                          (unsigned long long)to_fixed(f.y),
@@ -784,7 +944,7 @@ __device__ void project_one(const Img& im, int k, const float* __restrict__ cent
 template <int WG>
 __global__ __launch_bounds__(WG) void k_finalize_project(Img im, float* centres, int* endpoints,
                                                          int* counts, long long* acc,
-                                                         const int* labels) {
+                                                         const int* labels, int R, WinLists wl) {
     __shared__ float sx, sy;
     __shared__ int scnt, smove;
     const int k = blockIdx.x;
@@ -793,11 +953,16 @@ __global__ __launch_bounds__(WG) void k_finalize_project(Img im, float* centres,
         int cnt = 0;
         smove = finalize_core(im, k, centres, endpoints, counts, acc, labels, true, xk, yk, cnt)
                     ? 1 : 0;
+        if (wl.count && cnt == 0) {                // an empty cluster stays where it was
+            xk = centres[5LL * (im.sp + k) + 3];
+            yk = centres[5LL * (im.sp + k) + 4];
+        }
         sx = xk;
         sy = yk;
         scnt = cnt;
     }
     __syncthreads();
+    if (wl.count && threadIdx.x < 64) add_to_tiles(im, k, sx, sy, R, wl);
     if (smove) project_at<WG>(im, k, sx, sy, scnt, labels, endpoints);   // uniform
 }
 
@@ -866,17 +1031,6 @@ constexpr int kFinProjectWG = 256;
 constexpr int kWideProjectWG = 1024;
 constexpr long long kWideProjectPixels = 32768;
 
-size_t dyn_lds(const Tuning& t) { return (size_t)t.lds_pixels * sizeof(float4); }
-
-template <typename K>
-void allow_lds(K kernel, size_t bytes) {
-    // Lift the dynamic-LDS limit to what the launch needs (gfx950: 160 KiB per CU).
-    static_cast<void>(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                          hipFuncAttributeMaxDynamicSharedMemorySize,
-                                          (int)bytes));
-    static_cast<void>(hipGetLastError());
-}
-
 }  // namespace
 
 void finish_img(Img& im) {
@@ -895,10 +1049,6 @@ void finish_img(Img& im) {
     }
 }
 
-// 4800 x 16 B of tables (75 KiB) fit twice in 160 KiB: two 1024-thread
-// workgroups per CU.
-int default_lds_pixels() { return 4800; }
-
 int launch_write_bytes(void* dst, const void* src, size_t n, hipStream_t s) {
     const unsigned char* in = static_cast<const unsigned char*>(src);
     unsigned char* out = static_cast<unsigned char*>(dst);
@@ -911,13 +1061,6 @@ int launch_write_bytes(void* dst, const void* src, size_t n, hipStream_t s) {
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
-}
-
-void lift_lds_limits() {
-    const size_t cap = 152 * 1024;
-    allow_lds(k_assign_window<256>, cap);
-    allow_lds(k_assign_window<512>, cap);
-    allow_lds(k_assign_window<1024>, cap);
 }
 
 int launch_prepare(long long n, const float* lab, const float* contour, float sigma,
@@ -1024,55 +1167,46 @@ int persistent_grid(const Tuning& t) {
     return cus * per;
 }
 
-template <int WG>
-static int launch_window_t(const Img& im, const float4* packed, const float* centres,
-                           const int* endpoints, unsigned long long* keys, int R, float lambda,
-                           const Tuning& t, hipStream_t s) {
-    hipLaunchKernelGGL(k_assign_window<WG>, dim3(im.nx * im.ny), dim3(WG), dyn_lds(t), s, im,
-                       packed, centres, endpoints, keys, R, lambda, t.lds_pixels);
-    return hipGetLastError();
+// 8 W H bytes, but at least 256, hold the counts and a list of at least 16 ids per
+// tile: tiles / (W H) is at most 2/17 (W = 17, H = 1) unless there is one tile.
+static WinLists win_lists(const Img& im, void* mem) {
+    WinLists wl;
+    wl.tx = (im.W + kWinTile - 1) / kWinTile;
+    wl.tiles = wl.tx * ((im.H + kWinTile - 1) / kWinTile);
+    const long long words = std::max(2LL * im.W * im.H, 64LL);
+    wl.cap = (int)std::min<long long>(words / wl.tiles - 1, kWinIds);
+    wl.count = static_cast<int*>(mem);
+    wl.list = wl.count + wl.tiles;
+    return wl;
 }
 
-int launch_fill_keys(const Img& im, unsigned long long* keys, hipStream_t s) {
-    const long long n = (long long)im.W * im.H;
-    const unsigned blocks = (unsigned)std::min<long long>((n + 255) / 256, 65536);
-    hipLaunchKernelGGL(k_fill_u64, dim3(blocks), dim3(256), 0, s, keys + im.pix, n, ~0ULL);
-    return hipGetLastError();
+long long window_count_words(int W, int H) {
+    return ((long long)((W + kWinTile - 1) / kWinTile) * ((H + kWinTile - 1) / kWinTile) + 1) / 2;
 }
 
 int launch_assign_window(const Img& im, const float4* packed, const float* centres,
-                         const int* endpoints, int* labels, unsigned long long* keys, int R,
-                         float lambda, bool labels_out, const Tuning& t, hipStream_t s) {
-    const long long n = (long long)im.W * im.H;
-    const unsigned blocks = (unsigned)std::min<long long>((n + 255) / 256, 65536);
-    if (labels_out) {
-        const int e = launch_fill_keys(im, keys, s);
-        if (e != hipSuccess) return e;
+                         const int* endpoints, int* labels, long long* acc, int* ctrl, void* lists,
+                         int R, float lambda, bool accumulate, bool listed, hipStream_t s) {
+    const WinLists wl = win_lists(im, lists);
+    const int K = im.nx * im.ny, tiles = wl.tiles;
+    const bool near = !im.far && im.W + im.H < 46340;
+    if (!listed)
+        hipLaunchKernelGGL(k_window_lists, dim3((K + 3) / 4), dim3(256), 0, s, im, centres, R, wl);
+    // at most 2^22 workgroups a launch (an image one pixel high may have 2^27 tiles)
+    for (int t0 = 0; t0 < tiles; t0 += 1 << 22) {
+        const dim3 grid((unsigned)std::min(tiles - t0, 1 << 22));
+        const auto kernel = accumulate ? near ? k_assign_window<true, true> : k_assign_window<true, false>
+                            : near ? k_assign_window<false, true> : k_assign_window<false, false>;
+        hipLaunchKernelGGL(kernel, grid, dim3(kWinWG), 0, s, im, packed, centres, endpoints, labels,
+                           acc, ctrl, wl, R, lambda, t0);
     }
-    int r;
-    if (t.wg == 1024) r = launch_window_t<1024>(im, packed, centres, endpoints, keys, R, lambda, t, s);
-    else if (t.wg == 512) r = launch_window_t<512>(im, packed, centres, endpoints, keys, R, lambda, t, s);
-    else r = launch_window_t<256>(im, packed, centres, endpoints, keys, R, lambda, t, s);
-    if (r != hipSuccess || !labels_out) return r;
-    hipLaunchKernelGGL(k_window_labels, dim3(blocks), dim3(256), 0, s, keys + im.pix,
-                       labels + im.pix, n);
     return hipGetLastError();
 }
 
 int launch_accumulate(const Img& im, const float* lab, const int* labels, long long* acc,
                       hipStream_t s) {
-    const LabSource src{lab, nullptr};
-    hipLaunchKernelGGL(k_accumulate<kSmallWG>, dim3(im.nx * im.ny), dim3(kSmallWG), 0, s, im, src,
-                       const_cast<int*>(labels), static_cast<unsigned long long*>(nullptr),
-                       static_cast<int*>(nullptr), acc);
-    return hipGetLastError();
-}
-
-int launch_accumulate_window(const Img& im, const float4* packed, int* labels,
-                             unsigned long long* keys, int* ctrl, long long* acc, hipStream_t s) {
-    const LabSource src{nullptr, packed};
-    hipLaunchKernelGGL(k_accumulate<kSmallWG>, dim3(im.nx * im.ny), dim3(kSmallWG), 0, s, im, src,
-                       labels, keys + im.pix, ctrl, acc);
+    hipLaunchKernelGGL(k_accumulate<kSmallWG>, dim3(im.nx * im.ny), dim3(kSmallWG), 0, s, im, lab,
+                       labels, acc);
     return hipGetLastError();
 }
 
@@ -1099,13 +1233,16 @@ long long block_pixels(int W, int H, int nx, int ny) {
 }
 
 int launch_finalize_project(const Img& im, float* centres, int* endpoints, int* counts,
-                            long long* acc, const int* labels, hipStream_t s) {
+                            long long* acc, const int* labels, void* lists, int R, hipStream_t s) {
+    const WinLists wl = lists ? win_lists(im, lists) : WinLists{};
     if (block_pixels(im.W, im.H, im.nx, im.ny) > kWideProjectPixels)
         hipLaunchKernelGGL(k_finalize_project<kWideProjectWG>, dim3(im.nx * im.ny),
-                           dim3(kWideProjectWG), 0, s, im, centres, endpoints, counts, acc, labels);
+                           dim3(kWideProjectWG), 0, s, im, centres, endpoints, counts, acc, labels, R,
+                           wl);
     else
         hipLaunchKernelGGL(k_finalize_project<kFinProjectWG>, dim3(im.nx * im.ny),
-                           dim3(kFinProjectWG), 0, s, im, centres, endpoints, counts, acc, labels);
+                           dim3(kFinProjectWG), 0, s, im, centres, endpoints, counts, acc, labels, R,
+                           wl);
     return hipGetLastError();
 }
 

@@ -43,6 +43,81 @@ def test_window_assign_bit_exact(orc, W, H, k, tune):
     assert (lbl == ol).all(), f"{int((lbl != ol).sum())} labels differ"
 
 
+def _clumped(g, lab, rng, spread):
+    """Every barycenter within `spread` pixels of one point, endpoints anywhere."""
+    K = g.num_sp
+    c = np.empty((K, 5), np.float32)
+    ys, xs = rng.integers(0, g.height, K), rng.integers(0, g.width, K)
+    c[:, :3] = lab[ys, xs]
+    c[:, 3] = np.clip(0.6 * g.width + rng.uniform(-spread, spread, K), 0, g.width - 1)
+    c[:, 4] = np.clip(0.4 * g.height + rng.uniform(-spread, spread, K), 0, g.height - 1)
+    e = np.stack([rng.integers(0, g.width, K), rng.integers(0, g.height, K)], 1).astype(np.int32)
+    return c, e
+
+
+@pytest.mark.parametrize("prune", [1, 0])
+@pytest.mark.parametrize("W,H,k,spread", [
+    (16, 16, 4, 30.0), (17, 33, 6, 30.0), (95, 15, 13, 60.0),   # whole, one over, one short of tiles
+    (96, 80, 14, 4.0),      # 12 candidates and more: the last that fit and those beyond
+    (96, 80, 200, 2.0),     # 200 candidates in few tiles: many batches
+    (96, 80, 800, 1.5),     # lists overflow: all clusters are tested, in turns
+])
+def test_window_tiles_and_lists(orc, W, H, k, spread, prune):
+    img = synth.make_image(W, H, 5, 10.0, 17)
+    g = orc.grid(W, H, k)
+    rng = np.random.default_rng(W + H + k)
+    c, e = _clumped(g, img.lab, rng, spread)
+    prev = rng.integers(0, g.num_sp, (H, W)).astype(np.int32)
+    s = _scalp(W, H, k, exact_pruning=prune)
+    say("window lists", W, H, k, spread, prune)
+    lab, con = dev(img.lab), dev(img.contour)
+    ol, _ = orc.assign_window(g, img.lab, orc.wmap(img.contour), c, e, prev)
+    for rep in range(2):                     # the second pass meets counts left at zero
+        lbl = host(s.assign(lab, con, dev(c), dev(e), labels=dev(prev)))
+        assert (lbl == ol).all(), f"{rep}: {int((lbl != ol).sum())} labels differ"
+
+
+@pytest.mark.parametrize("W,H,k,spread", [(96, 80, 14, 4.0), (96, 80, 200, 2.0), (96, 80, 800, 1.5)])
+def test_window_sums_of_long_lists(orc, W, H, k, spread):
+    """A stepped pass with the update's sums: several batches of bins, overflowed
+    lists, and pixels that no window contains (their sums go to their old label)."""
+    img = synth.make_image(W, H, 5, 10.0, 18)
+    g = orc.grid(W, H, k)
+    rng = np.random.default_rng(W + H + k)
+    c, e = _clumped(g, img.lab, rng, spread)
+    prev = rng.integers(0, g.num_sp, (H, W)).astype(np.int32)
+    ol, _ = orc.assign_window(g, img.lab, orc.wmap(img.contour), c, e, prev)
+    oc, on = orc.update(g, img.lab, ol, c, mode=orc.MEAN_FIXED)
+    s = _scalp(W, H, k)
+    say("window sums", W, H, k, spread)
+    lab, con = dev(img.lab), dev(img.contour)
+    C, E, L = dev(c), dev(e), dev(prev)
+    N = torch.zeros(g.num_sp, dtype=torch.int32, device="cuda")
+    s.prepare(lab, con)
+    s.assign_accumulate(C, E, L)
+    s.finalize(L, C, E, N)
+    assert (host(L) == ol).all()
+    assert (host(C) == oc).all() and (host(N) == on).all()
+
+
+def test_window_paths_beyond_carry_range(orc):
+    """W + H beyond 46340: the walks with 64-bit indexes."""
+    W, H, k = 46400, 2, 8
+    rng = np.random.default_rng(5)
+    lab = rng.normal(0, 20, (H, W, 3)).astype(np.float32)
+    con = rng.random((H, W)).astype(np.float32)
+    g = orc.grid(W, H, k)
+    c, e = _clumped(g, lab, rng, 500.0)
+    e[:, 0] = np.clip(c[:, 3] + rng.integers(-3000, 3000, g.num_sp), 0, W - 1)
+    e[0, 0] = 0
+    prev = np.zeros((H, W), np.int32)
+    s = _scalp(W, H, k)
+    say("window wide", W, H, k)
+    lbl = host(s.assign(dev(lab), dev(con), dev(c), dev(e), labels=dev(prev)))
+    ol, _ = orc.assign_window(g, lab, orc.wmap(con), c, e, prev)
+    assert (lbl == ol).all()
+
+
 def _compare(orc, img, k, iters):
     H, W = img.contour.shape
     s = _scalp(W, H, k)
