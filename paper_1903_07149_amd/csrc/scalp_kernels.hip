@@ -897,29 +897,49 @@ __device__ void scan_region(const int* __restrict__ lb, int W, int k, int X0, in
     block_min_sum<WG>(best, found);
 }
 
-// Eq. (4) for one queued cluster: the argmin over all its members, found by
-// scanning regions of growing size until every member (counts) was seen:
+// Eq. (4) for one queued cluster: the argmin over all its members.  First the
+// square of half-width kNearHalf around the rounded barycenter: a member there
+// whose squared distance is below kNearHalf^2 is the nearest, as every pixel
+// outside is at least kNearHalf + 1/2 - ulp away (coordinates up to 2^22, ulp
+// 1/4).  Else regions of growing size until every member (counts) was seen:
 // the 3x3 cell block around its grid cell (where the grid form's labels
-// lie), then the square of half-width 2R + 2 around its rounded barycenter
+// lie), then the square of half-width 2R + 2 around the rounded barycenter
 // (the window form: members lie within R of the previous barycenter, which
 // lies within R of the new one), then the whole image (any labels).
+//
+// What bounds it: the latency of the label loads.  1920x1080, k = 2000, per
+// launch of k_finalize_project: 9.1 us with the 9400-pixel block always scanned
+// and 15.5 in the window form, whose members leave it; 6.1 and 6.2 now (the latter
+// with the next pass's lists); the 64-image batch: 135 to 95 us.  With a half-width
+// of 16 some clusters of nearly every launch still scan the block: 7.5.
+constexpr int kNearHalf = 22;   // 45 x 45 pixels: one trip of 256 lanes' 8 loads
+
 template <int WG>
 __device__ void project_at(const Img& im, int k, float xk, float yk, int count,
                            const int* __restrict__ labels, int* __restrict__ endpoints) {
     const int W = im.W, H = im.H;
     const int* lb = labels + im.pix;
-    const int ci = k / im.nx, cj = k - ci * im.nx;
-    unsigned long long best;
-    int found;
-    scan_region<WG>(lb, W, k, cell_lo(max(cj - 1, 0), W, im.nx), cell_lo(min(cj + 2, im.nx), W, im.nx),
-                    cell_lo(max(ci - 1, 0), H, im.ny), cell_lo(min(ci + 2, im.ny), H, im.ny), xk, yk,
-                    best, found);
-    if (found < count) {                           // uniform: reduced over the workgroup
-        const int h = 2 * im.rad + 2;
-        const int cx = round_coord(xk, W - 1), cy = round_coord(yk, H - 1);
-        scan_region<WG>(lb, W, k, max(cx - h, 0), min(cx + h + 1, W), max(cy - h, 0),
-                        min(cy + h + 1, H), xk, yk, best, found);
-        if (found < count) scan_region<WG>(lb, W, k, 0, W, 0, H, xk, yk, best, found);
+    const int cx = round_coord(xk, W - 1), cy = round_coord(yk, H - 1);
+    unsigned long long best = ~0ULL;
+    int found = 0;
+    bool done = false;
+    if (max(W, H) <= 1 << 22) {
+        scan_region<WG>(lb, W, k, max(cx - kNearHalf, 0), min(cx + kNearHalf + 1, W),
+                        max(cy - kNearHalf, 0), min(cy + kNearHalf + 1, H), xk, yk, best, found);
+        done = found == count ||
+               (found > 0 && __uint_as_float((unsigned)(best >> 32)) < (float)(kNearHalf * kNearHalf));
+    }
+    if (!done) {                                   // uniform: reduced over the workgroup
+        const int ci = k / im.nx, cj = k - ci * im.nx;
+        scan_region<WG>(lb, W, k, cell_lo(max(cj - 1, 0), W, im.nx), cell_lo(min(cj + 2, im.nx), W, im.nx),
+                        cell_lo(max(ci - 1, 0), H, im.ny), cell_lo(min(ci + 2, im.ny), H, im.ny), xk, yk,
+                        best, found);
+        if (found < count) {
+            const int h = 2 * im.rad + 2;
+            scan_region<WG>(lb, W, k, max(cx - h, 0), min(cx + h + 1, W), max(cy - h, 0),
+                            min(cy + h + 1, H), xk, yk, best, found);
+            if (found < count) scan_region<WG>(lb, W, k, 0, W, 0, H, xk, yk, best, found);
+        }
     }
     if (threadIdx.x == 0 && best != ~0ULL) {
         const unsigned idx = (unsigned)(best & 0xffffffffULL);

@@ -287,6 +287,35 @@ def test_update_arbitrary_labels(orc):
     assert (cnt == ocnt).all() and (nc == oc).all() and (ne == oe).all()
 
 
+@pytest.mark.parametrize("inner", [3.0, 21.9, 22.0, 22.5, 23.0, 45.0])
+@pytest.mark.parametrize("x,y", [(100, 70), (20, 15), (188, 128)])
+def test_projection_of_rings(orc, inner, x, y):
+    """Clusters that are rings around their barycenter (cut off by the image near
+    its corners), with the nearest member inside, at the edge of and outside the
+    square around the barycenter that is scanned first; beside them one cluster
+    of two far parts and one of a single pixel."""
+    W, H, k = 200, 140, 12
+    g = orc.grid(W, H, k)
+    yy, xx = np.mgrid[0:H, 0:W]
+    d = np.hypot(xx - x, yy - y)
+    labels = np.zeros((H, W), np.int32)
+    labels[(d >= inner) & (d < inner + 1.5)] = 5
+    labels[:, 40:43] = 7
+    labels[:, 155:158] = 7
+    labels[0, 0] = 9
+    rng = np.random.default_rng(3)
+    lab = rng.normal(0, 20, (H, W, 3)).astype(np.float32)
+    c = np.zeros((g.num_sp, 5), np.float32)
+    e = np.zeros((g.num_sp, 2), np.int32)
+    from paper_1903_07149_amd.scalp import Scalp
+    say("projection of rings", inner, x, y)
+    gc, ge, gn = (host(t) for t in Scalp(W, H, k).update(dev(lab), dev(labels), dev(c), dev(e)))
+    oc, on = orc.update(g, lab, labels, c, mode=orc.MEAN_FIXED)
+    oe, moved = orc.project(g, labels, oc, on, e)
+    assert moved > 0
+    assert (gc == oc).all() and (gn == on).all() and (ge == oe).all()
+
+
 def test_update_many_labels_per_cell(orc):
     """Random labels over 64 superpixels on a 64x64 image: each 8x8 cell holds
     more distinct labels than the update's per-cell LDS table (32 slots), so
