@@ -65,6 +65,8 @@ struct Img {
 };
 // Fills the derived fields above from W, H, nx, ny, spl and strips.
 void finish_img(Img& im);
+// Whether 32-bit indexes and step counters serve every path of the image.
+bool near_image(const Img& im);
 
 // An assignment work item has at most as many pixels as its workgroup has
 // lanes (one pixel per lane): cells larger than that are split into several
@@ -123,10 +125,11 @@ int launch_project(const Img& im, const float* centres, const int* counts, const
 // Batched variants: imgs/cell_start/sp_start are device arrays in the workspace.
 int launch_init_cells_batched(const Img* imgs, const int* cell_start, int n_img, int total_cells,
                               const float4* packed, int* labels, long long* acc, hipStream_t s);
+// (near: near_image of every image)
 int launch_assign_persistent(const Img* imgs, const int* item_start, int n_img, int total_items,
                              const float4* packed, const float* centres, const int* endpoints,
                              int* labels, long long* acc, int* ctrl, float lambda,
-                             const Tuning& t, int grid, hipStream_t s);
+                             const Tuning& t, bool near, int grid, hipStream_t s);
 int launch_finalize_batched(const Img* imgs, const int* sp_start, int n_img, int total_sp,
                             float* centres, int* endpoints, int* counts, long long* acc,
                             const int* labels, int* ctrl, int* plist, bool project,

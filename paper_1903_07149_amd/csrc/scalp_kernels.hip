@@ -91,6 +91,10 @@ __device__ __forceinline__ int slice_chunk(int chunks, int i, const Img& im) {
 // minimum per pixel.  A walk of that second pass stops as soon as its partial
 // sums prove that D exceeds the pixel's first one (Cut).
 //
+// NEAR (near_image): the walks by 32-bit indexes.  A kernel with both needs 10
+// registers more (62 instead of 52; the persistent one spilled) and took 1 to 2 %
+// longer.
+//
 // What bounds it: VALU issue.  33.4 M wave instructions per launch at
 // 1920x1080, k = 2000 (the bounds 180 of a wave's 1023, the first walk 300,
 // its evaluation 150, the second pass 200), 0.93 issued per CU-clock; 0.070
@@ -103,7 +107,7 @@ __device__ __forceinline__ int slice_chunk(int chunks, int i, const Img& im) {
 // CU and was slower (0.132 ms against 0.105 with the rest equal), as was a
 // counting sort of the first walks by length (18 instead of 23 slots per
 // pixel, but 100 more instructions and two more barriers).
-template <int WG, bool ACCUM>
+template <int WG, bool ACCUM, bool NEAR>
 __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int slice,
                                              const float4* __restrict__ packed,
                                              const float* __restrict__ centres,
@@ -132,7 +136,7 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
     Eqs eqs;
     eqs.img = img;
     eqs.W = W;
-    eqs.near = !im.far && W + H < 46340;
+    eqs.near = NEAR;
     eqs.lambda = lambda;
     eqs.oml = 1.0f - lambda;
     eqs.gamma = im.gamma;
@@ -252,7 +256,7 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
     }
 }
 
-template <int WG, bool ACCUM>
+template <int WG, bool ACCUM, bool NEAR>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_assign(Img im, const float4* __restrict__ packed,
                                                const float* __restrict__ centres,
                                                const int* __restrict__ endpoints,
@@ -265,12 +269,12 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_
     const int pos = fdiv(item, im.dspl);
     int ci, cj;
     cell_in_strips(pos, im, ci, cj);
-    process_cell<WG, ACCUM>(im, ci, cj, item - pos * im.spl, packed, centres, endpoints, labels,
+    process_cell<WG, ACCUM, NEAR>(im, ci, cj, item - pos * im.spl, packed, centres, endpoints, labels,
                             acc, lambda, sh);
 }
 
 // At most 64 VGPRs (8 waves per SIMD): two 1024-thread workgroups per CU.
-template <int WG>
+template <int WG, bool NEAR>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8)))
 void k_assign_persistent(const Img* __restrict__ imgs,
                                                           const int* __restrict__ item_start,
@@ -311,7 +315,7 @@ void k_assign_persistent(const Img* __restrict__ imgs,
         const int pos = fdiv(local, im.dspl);
         int ci, cj;
         cell_in_strips(pos, im, ci, cj);
-        process_cell<WG, true>(im, ci, cj, local - pos * im.spl, packed, centres, endpoints,
+        process_cell<WG, true, NEAR>(im, ci, cj, local - pos * im.spl, packed, centres, endpoints,
                                labels, acc, lambda, sh);
         __syncthreads();   // shared state is reused by the next item
     }
@@ -1053,6 +1057,8 @@ constexpr long long kWideProjectPixels = 32768;
 
 }  // namespace
 
+bool near_image(const Img& im) { return !im.far && im.W + im.H < 46340; }
+
 void finish_img(Img& im) {
     const long long W = im.W, H = im.H, nx = im.nx, ny = im.ny, K = nx * ny;
     im.far = W * H >= (1LL << 28);
@@ -1116,62 +1122,46 @@ int launch_init_cells_batched(const Img* imgs, const int* cell_start, int n_img,
 template <int WG, bool ACCUM>
 static int launch_assign_t(const Img& im, const float4* packed, const float* centres,
                            const int* endpoints, int* labels, long long* acc, int* ctrl,
-                           float lambda, const Tuning& t, hipStream_t s) {
-    hipLaunchKernelGGL((k_assign<WG, ACCUM>), dim3(im.nx * im.ny * im.spl), dim3(WG), 0, s, im,
-                       packed, centres, endpoints, labels, acc, ctrl, lambda);
+                           float lambda, hipStream_t s) {
+    const auto kernel = near_image(im) ? k_assign<WG, ACCUM, true> : k_assign<WG, ACCUM, false>;
+    hipLaunchKernelGGL(kernel, dim3(im.nx * im.ny * im.spl), dim3(WG), 0, s, im, packed, centres,
+                       endpoints, labels, acc, ctrl, lambda);
     return hipGetLastError();
 }
 
 template <int WG>
 static int launch_assign_wg(const Img& im, const float4* packed, const float* centres,
                             const int* endpoints, int* labels, long long* acc, int* ctrl,
-                            float lambda, bool accumulate, const Tuning& t, hipStream_t s) {
+                            float lambda, bool accumulate, hipStream_t s) {
     return accumulate ? launch_assign_t<WG, true>(im, packed, centres, endpoints, labels, acc,
-                                                  ctrl, lambda, t, s)
+                                                  ctrl, lambda, s)
                       : launch_assign_t<WG, false>(im, packed, centres, endpoints, labels, acc,
-                                                   ctrl, lambda, t, s);
+                                                   ctrl, lambda, s);
 }
 
 int launch_assign(const Img& im, const float4* packed, const float* centres,
                   const int* endpoints, int* labels, long long* acc, int* ctrl, float lambda,
                   bool accumulate, const Tuning& t, hipStream_t s) {
-    if (t.wg == 1024)
-        return launch_assign_wg<1024>(im, packed, centres, endpoints, labels, acc, ctrl, lambda,
-                                      accumulate, t, s);
-    if (t.wg == 512)
-        return launch_assign_wg<512>(im, packed, centres, endpoints, labels, acc, ctrl, lambda,
-                                     accumulate, t, s);
-    return launch_assign_wg<256>(im, packed, centres, endpoints, labels, acc, ctrl, lambda,
-                                 accumulate, t, s);
+    const auto launch = t.wg == 1024 ? launch_assign_wg<1024>
+                        : t.wg == 512 ? launch_assign_wg<512> : launch_assign_wg<256>;
+    return launch(im, packed, centres, endpoints, labels, acc, ctrl, lambda, accumulate, s);
 }
 
-template <int WG>
-static int launch_persistent_t(const Img* imgs, const int* item_start, int n_img, int total,
-                               const float4* packed, const float* centres, const int* endpoints,
-                               int* labels, long long* acc, int* ctrl, float lambda,
-                               const Tuning& t, int grid, hipStream_t s) {
-    hipLaunchKernelGGL(k_assign_persistent<WG>, dim3(grid), dim3(WG), 0, s, imgs, item_start,
-                       n_img, total, packed, centres, endpoints, labels, acc, ctrl, lambda);
-    return hipGetLastError();
+// The persistent assignment's kernel for a workgroup size, and for images that
+// are all near or not.
+static decltype(&k_assign_persistent<256, true>) persistent_kernel(int wg, bool near) {
+    if (wg == 1024) return near ? k_assign_persistent<1024, true> : k_assign_persistent<1024, false>;
+    if (wg == 512) return near ? k_assign_persistent<512, true> : k_assign_persistent<512, false>;
+    return near ? k_assign_persistent<256, true> : k_assign_persistent<256, false>;
 }
 
 int launch_assign_persistent(const Img* imgs, const int* item_start, int n_img, int total_items,
                              const float4* packed, const float* centres, const int* endpoints,
                              int* labels, long long* acc, int* ctrl, float lambda,
-                             const Tuning& t, int grid, hipStream_t s) {
-    if (t.wg == 1024)
-        return launch_persistent_t<1024>(imgs, item_start, n_img, total_items, packed, centres,
-                                         endpoints, labels, acc, ctrl, lambda, t, grid, s);
-    if (t.wg == 512)
-        return launch_persistent_t<512>(imgs, item_start, n_img, total_items, packed, centres,
-                                        endpoints, labels, acc, ctrl, lambda, t, grid, s);
-    return launch_persistent_t<256>(imgs, item_start, n_img, total_items, packed, centres,
-                                    endpoints, labels, acc, ctrl, lambda, t, grid, s);
-}
-
-template <int WG>
-static int persistent_occupancy(int* per) {
-    return (int)hipOccupancyMaxActiveBlocksPerMultiprocessor(per, k_assign_persistent<WG>, WG, 0);
+                             const Tuning& t, bool near, int grid, hipStream_t s) {
+    hipLaunchKernelGGL(persistent_kernel(t.wg, near), dim3(grid), dim3(t.wg), 0, s, imgs, item_start,
+                       n_img, total_items, packed, centres, endpoints, labels, acc, ctrl, lambda);
+    return hipGetLastError();
 }
 
 int persistent_grid(const Tuning& t) {
@@ -1179,9 +1169,9 @@ int persistent_grid(const Tuning& t) {
     if (hipGetDevice(&dev) != hipSuccess) return -1;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return -1;
-    const int e = t.wg == 1024 ? persistent_occupancy<1024>(&per)
-                  : t.wg == 512 ? persistent_occupancy<512>(&per)
-                                : persistent_occupancy<256>(&per);
+    // (both kernels of a size are held to 64 registers: one occupancy)
+    const int e = (int)hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &per, reinterpret_cast<const void*>(persistent_kernel(t.wg, true)), t.wg, 0);
     if (e != (int)hipSuccess || per < 1) per = 1;
     if (t.blocks_per_cu > 0 && t.blocks_per_cu < per) per = t.blocks_per_cu;
     return cus * per;
@@ -1209,7 +1199,7 @@ int launch_assign_window(const Img& im, const float4* packed, const float* centr
                          int R, float lambda, bool accumulate, bool listed, hipStream_t s) {
     const WinLists wl = win_lists(im, lists);
     const int K = im.nx * im.ny, tiles = wl.tiles;
-    const bool near = !im.far && im.W + im.H < 46340;
+    const bool near = near_image(im);
     if (!listed)
         hipLaunchKernelGGL(k_window_lists, dim3((K + 3) / 4), dim3(256), 0, s, im, centres, R, wl);
     // at most 2^22 workgroups a launch (an image one pixel high may have 2^27 tiles)
