@@ -97,8 +97,10 @@ __device__ __forceinline__ int slice_chunk(int chunks, int i, const Img& im) {
 //
 // What bounds it: VALU issue.  33.4 M wave instructions per launch at
 // 1920x1080, k = 2000 (the bounds 180 of a wave's 1023, the first walk 300,
-// its evaluation 150, the second pass 200), 0.93 issued per CU-clock; 0.070
-// ms per launch.  Tables of (d_c, w) per candidate in LDS, all nine taken in
+// its evaluation 150, the second pass 200), 0.93 issued per CU-clock; 0.069
+// ms per launch.  (The settling is one piece of code for all pixels: settled in
+// the first pass where nothing was listed, it ran twice in most waves, 1.6 % of
+// this launch and 3 % of the 64-image batch.)  Tables of (d_c, w) per candidate in LDS, all nine taken in
 // turn by the whole workgroup behind a barrier each, made a sample cost 5
 // instructions instead of 13 but walked 85 samples per pixel in 64-lane slots
 // instead of 33, filled 20 table entries per pixel and waited at the barriers:
@@ -219,8 +221,6 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
         if (again) {
             sh.xy[tid] = make_int2(px, py);
             sh.win[tid] = ((unsigned long long)__float_as_uint(best) << 32) | (unsigned)bestj;
-        } else {
-            settle(px, py, bestj);
         }
     }
     __syncthreads();
@@ -237,7 +237,7 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
             atomicMin(&sh.win[id], ((unsigned long long)__float_as_uint(D) << 32) | (unsigned)j);
     }
     __syncthreads();
-    if (again) settle(px, py, (int)(unsigned)sh.win[tid]);
+    if (mine) settle(px, py, again ? (int)(unsigned)sh.win[tid] : bestj);
     __syncthreads();
 
     if (ACCUM) {
@@ -332,8 +332,8 @@ void k_assign_persistent(const Img* __restrict__ imgs,
 
 constexpr int kWinTile = 16;     // a workgroup's tile is kWinTile x kWinTile pixels
 constexpr int kWinWG = kWinTile * kWinTile;
-constexpr int kWinBatch = 12;    // candidates that a tile evaluates at a time (at most 15)
-constexpr int kWinIds = 512;     // candidates that a tile lists at a time
+constexpr int kWinBatch = 15;    // candidates that a tile evaluates at a time (4-bit slots)
+constexpr int kWinIds = 512;     // longest list of a tile
 
 // The tiles' candidates: count[tile] (cleared before the first pass; every tile
 // clears its own again) and the first `cap` of them in list[tile * cap ...], in
@@ -376,10 +376,10 @@ struct WinShared {
     unsigned long long bins[kWinBatch * 6][kBinCopies];   // the update's sums, [slot * 6 + sum]
     unsigned long long win[kWinWG];
     float4 cand[kWinBatch][2];                            // (l, a, b, x), (y, endpoint)
-    int4 box[kWinBatch];                                  // k, the window's corner
+    int2 box[kWinBatch];                                  // the window's corner
     int ids[kWinIds], unsorted[kWinIds];
     unsigned short list[(kWinBatch - 1) * kWinWG];        // pixel | slot << 8
-    int pairs, count;
+    int pairs, count[kWinWG / 64];
 };
 
 __device__ __forceinline__ unsigned med3(unsigned a, unsigned b, unsigned c) {
@@ -398,9 +398,10 @@ __device__ __forceinline__ float win_threshold(unsigned long long win) {
 // 9: the candidate with the smallest lower bound of D first, then by full waves the
 // (pixel, candidate) pairs whose bound does not exceed that D.  More than kWinBatch
 // candidates are taken in batches against the smallest D so far; a tile whose list
-// overflowed tests all clusters, kWinIds at a time.  With ACCUM the update's sums go
-// through bins per candidate of the tile (to global memory directly for pixels that
-// no window contains).
+// overflowed, and every tile without lists, tests all clusters, kWinWG at a time.
+// With ACCUM the update's sums go through bins per candidate of the tile (to global
+// memory directly for pixels that no window contains, and for winners of an earlier
+// turn of an overflowed list).
 //
 // What bounds it: VALU issue, as in the grid form (31 M wave instructions per
 // launch at 1920x1080, k = 2000, R = 32).  69 us with the sums.  A workgroup per
@@ -429,14 +430,25 @@ __global__ __launch_bounds__(kWinWG) __attribute__((amdgpu_waves_per_eu(8))) voi
     const bool prune = im.prune != 0;
     const bool cut = prune && im.gamma <= 0x1p40f;
     const unsigned span = 2u * (unsigned)R;
-    const ConstF ccen = (ConstF)(uintptr_t)centres;
-    // candidate k into slot j
-    auto stage = [&](int j, int k) {
+    // a cluster's centre, endpoint and the corner of its window
+    struct Cluster {
+        float l, a, b, x, y;
+        int ex, ey, wx, wy;
+    };
+    auto cluster = [&](int k) {
         const float* c = centres + 5LL * k;
-        sh.cand[j][0] = make_float4(c[0], c[1], c[2], c[3]);
-        sh.cand[j][1] = make_float4(c[4], __int_as_float(min(max(endpoints[2LL * k], 0), W - 1)),
-                                    __int_as_float(min(max(endpoints[2LL * k + 1], 0), H - 1)), 0.0f);
-        sh.box[j] = make_int4(k, round_coord(c[3], W - 1) - R, round_coord(c[4], H - 1) - R, 0);
+        const int* e = endpoints + 2LL * k;
+        Cluster v = {c[0], c[1], c[2], c[3], c[4], e[0], e[1], 0, 0};
+        v.ex = min(max(v.ex, 0), W - 1);
+        v.ey = min(max(v.ey, 0), H - 1);
+        v.wx = round_coord(v.x, W - 1) - R;
+        v.wy = round_coord(v.y, H - 1) - R;
+        return v;
+    };
+    auto stage = [&](int j, const Cluster& v) {
+        sh.cand[j][0] = make_float4(v.l, v.a, v.b, v.x);
+        sh.cand[j][1] = make_float4(v.y, __int_as_float(v.ex), __int_as_float(v.ey), 0.0f);
+        sh.box[j] = make_int2(v.wx, v.wy);
     };
     // pixel `id` of the tile, relative to its corner
     auto pixel_x = [](int id) { return (id & 7) + ((id >> 3) & 8); };
@@ -459,55 +471,63 @@ __global__ __launch_bounds__(kWinWG) __attribute__((amdgpu_waves_per_eu(8))) voi
     // key of slot j: the upper 28 bits of the bound of D (see bound_keys) with the slot
     // below, kNoKey where the window does not contain the lane's pixel
     auto key_of = [&](int j, float4 fp) -> unsigned {
-        const int4 box = sh.box[j];
-        const ConstF c = ccen + 5LL * __builtin_amdgcn_readfirstlane(box.x);
-        const float dl = fp.x - c[0], da = fp.y - c[1], db = fp.z - c[2];
-        const float ex = (float)px - c[3], ey = (float)py - c[4];
+        const float4 c0 = sh.cand[j][0], c1 = sh.cand[j][1];
+        const float dl = fp.x - c0.x, da = fp.y - c0.y, db = fp.z - c0.z;
+        const float ex = (float)px - c0.w, ey = (float)py - c1.x;
         const float dcp = __builtin_fmaf(db, db, __builtin_fmaf(da, da, dl * dl));
         const float lb = __builtin_fmaf(ex * ex + ey * ey, im.spw, lambda * dcp);
-        const bool in = (unsigned)(px - box.y) <= span && (unsigned)(py - box.z) <= span;
+        const int2 box = sh.box[j];
+        const bool in = (unsigned)(px - box.x) <= span && (unsigned)(py - box.y) <= span;
         // (without the sign that a NaN may have)
         return in ? (__float_as_uint(lb) & 0x7ffffff0u) | (unsigned)j : kNoKey;
     };
     sh.win[tid] = ~0ULL;
-    const int all = __builtin_amdgcn_readfirstlane(*const_cast<volatile int*>(&wl.count[tile]));
-    const bool scan = all > wl.cap;
+    const int all = wl.count
+        ? __builtin_amdgcn_readfirstlane(*const_cast<volatile int*>(&wl.count[tile])) : 0;
+    const bool scan = !wl.count || all > wl.cap;
     if (ACCUM)
         for (int t = tid; t < kWinBatch * 6 * kBinCopies; t += kWinWG) (&sh.bins[0][0])[t] = 0ULL;
     int listed = all;
-    if (!scan) {
-        const int* list = wl.list + (long long)tile * wl.cap;
-        for (int t = tid; t < listed; t += kWinWG) sh.unsorted[t] = list[t];
-    }
-    // one turn, or one per kWinIds clusters (the same control in all waves)
-    for (int k0 = 0;; k0 += kWinIds) {
+    // one turn, or one per kWinWG clusters (the same control in all waves)
+    for (int k0 = 0;; k0 += kWinWG) {
+        const bool last = !scan || k0 + kWinWG >= K;
+        int k = k0 + tid, rank = 0;
         if (scan) {
-            if (tid == 0) sh.count = 0;
+            // the candidates among the lanes' clusters, in the order of the lanes
+            const bool own = k < K;
+            const Cluster v = cluster(own ? k : K - 1);
+            const bool in = own && v.wx <= x1 && v.wx + 2 * R >= x0 && v.wy <= y1 && v.wy + 2 * R >= y0;
+            const unsigned long long m = __ballot(in);
+            if ((tid & 63) == 0) sh.count[tid >> 6] = __popcll(m);
             __syncthreads();
-            for (int k = k0 + tid; k < min(k0 + kWinIds, K); k += kWinWG) {
-                const float* c = centres + 5LL * k;
-                const int wx = round_coord(c[3], W - 1), wy = round_coord(c[4], H - 1);
-                const bool in = wx - R <= x1 && wx + R >= x0 && wy - R <= y1 && wy + R >= y0;
-                if (in) sh.unsorted[atomicAdd(&sh.count, 1)] = k;
+            rank = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                  __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+            listed = 0;
+            for (int w = 0; w < kWinWG / 64; ++w) {
+                if (w == tid >> 6) rank += listed;
+                listed += __builtin_amdgcn_readfirstlane(sh.count[w]);
             }
-            __syncthreads();
-            listed = __builtin_amdgcn_readfirstlane(sh.count);
+            if (in) {
+                sh.ids[rank] = k;
+                if (rank < kWinBatch) stage(rank, v);
+            }
         } else {
+            const int* list = wl.list + (long long)tile * wl.cap;
+            for (int t = tid; t < listed; t += kWinWG) sh.unsorted[t] = list[t];
             __syncthreads();
             if (tid == 0) wl.count[tile] = 0;              // all waves have read it
-        }
-        const bool last = !scan || k0 + kWinIds >= K;
-        for (int t = tid; t < listed; t += kWinWG) {
-            const int k = sh.unsorted[t];
-            int rank = 0;
-            for (int u = 0; u < listed; ++u) rank += sh.unsorted[u] < k ? 1 : 0;
-            sh.ids[rank] = k;
-            if (rank < kWinBatch) stage(rank, k);
+            for (int t = tid; t < listed; t += kWinWG) {
+                k = sh.unsorted[t];
+                rank = 0;
+                for (int u = 0; u < listed; ++u) rank += sh.unsorted[u] < k ? 1 : 0;
+                sh.ids[rank] = k;
+                if (rank < kWinBatch) stage(rank, cluster(k));
+            }
         }
         __syncthreads();
         for (int b0 = 0; b0 < listed; b0 += kWinBatch) {
             const int n = min(listed - b0, kWinBatch);
-            if (b0 > 0 && tid < n) stage(tid, sh.ids[b0 + tid]);
+            if (b0 > 0 && tid < n) stage(tid, cluster(sh.ids[b0 + tid]));
             if (tid == 0) sh.pairs = 0;
             __syncthreads();
             if (mine) {
@@ -565,7 +585,7 @@ __global__ __launch_bounds__(kWinWG) __attribute__((amdgpu_waves_per_eu(8))) voi
         }
         __syncthreads();
     }
-    if (scan && tid == 0) wl.count[tile] = 0;
+    if (scan && wl.count && tid == 0) wl.count[tile] = 0;
 
     const unsigned long long win = sh.win[tid];
     const int slot = mine && win != ~0ULL ? (int)(unsigned)win - 1 : -1;
@@ -1179,11 +1199,16 @@ int persistent_grid(const Tuning& t) {
 
 // 8 W H bytes, but at least 256, hold the counts and a list of at least 16 ids per
 // tile: tiles / (W H) is at most 2/17 (W = 17, H = 1) unless there is one tile.
+//
+// No lists (count null) for up to kWinWG clusters: every tile tests them all in one
+// turn, which takes no longer than reading a list does, and nothing has to make them
+// (97x61, 30 clusters: 165 us for 10 iterations, with lists 172).
 static WinLists win_lists(const Img& im, void* mem) {
-    WinLists wl;
+    WinLists wl = {};
     wl.tx = (im.W + kWinTile - 1) / kWinTile;
     wl.tiles = wl.tx * ((im.H + kWinTile - 1) / kWinTile);
     const long long words = std::max(2LL * im.W * im.H, 64LL);
+    if (!mem || im.nx * im.ny <= kWinWG) return wl;
     wl.cap = (int)std::min<long long>(words / wl.tiles - 1, kWinIds);
     wl.count = static_cast<int*>(mem);
     wl.list = wl.count + wl.tiles;
@@ -1200,7 +1225,7 @@ int launch_assign_window(const Img& im, const float4* packed, const float* centr
     const WinLists wl = win_lists(im, lists);
     const int K = im.nx * im.ny, tiles = wl.tiles;
     const bool near = near_image(im);
-    if (!listed)
+    if (wl.count && !listed)
         hipLaunchKernelGGL(k_window_lists, dim3((K + 3) / 4), dim3(256), 0, s, im, centres, R, wl);
     // at most 2^22 workgroups a launch (an image one pixel high may have 2^27 tiles)
     for (int t0 = 0; t0 < tiles; t0 += 1 << 22) {
@@ -1244,7 +1269,7 @@ long long block_pixels(int W, int H, int nx, int ny) {
 
 int launch_finalize_project(const Img& im, float* centres, int* endpoints, int* counts,
                             long long* acc, const int* labels, void* lists, int R, hipStream_t s) {
-    const WinLists wl = lists ? win_lists(im, lists) : WinLists{};
+    const WinLists wl = win_lists(im, lists);
     if (block_pixels(im.W, im.H, im.nx, im.ny) > kWideProjectPixels)
         hipLaunchKernelGGL(k_finalize_project<kWideProjectWG>, dim3(im.nx * im.ny),
                            dim3(kWideProjectWG), 0, s, im, centres, endpoints, counts, acc, labels, R,
