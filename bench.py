@@ -21,7 +21,7 @@ Also reported on the same JSON line:
                 average launch time and that roofline fraction;
   cpu_baseline  the plain C oracle timed on this host's cores on the same
                 workload;
-  extensions    the ragged 64-image batch in one persistent launch per
+  extensions    the ragged 64-image batch in one assignment launch per
                 iteration (hipGraph), against the same images run one by one
                 through the single-image path, and soft SCALP forward+backward.
 
@@ -97,7 +97,7 @@ def parse():
                          "autotuning")
     ap.add_argument("--batch-launch", default=None,
                     help="WG,LDS_PIXELS,BLOCKS_PER_CU[,TABLE_MODE]: fixed launch shape of the "
-                         "batched persistent kernel instead of autotuning it on the batch")
+                         "batched kernel instead of autotuning it on the batch")
     return ap.parse_args()
 
 
@@ -397,7 +397,7 @@ def bench_batched(torch, args, tuned):
     shapes = [(w.width, w.height, w.k) for w in wls]
     lab = torch.cat([torch.from_numpy(i.lab.reshape(-1, 3)) for i in imgs]).cuda()
     con = torch.cat([torch.from_numpy(i.contour.reshape(-1)) for i in imgs]).cuda()
-    # launch shape of the persistent kernel, tuned on this batch
+    # launch shape of the batched kernel, tuned on this batch
     if args.batch_launch:
         tuned_b = batch_launch(args.batch_launch)
     else:
@@ -444,7 +444,7 @@ def bench_batched(torch, args, tuned):
     for (s0, s1), g in zip(b0.sp_slices(), b0.grids):
         flops += counts.pass_work(g.width, g.height, g.nx, g.ny, e0[s0:s1])["flops"]
     roof = alu_roofline(flops, ms * 1e-3 / 10,
-                        "batched run / 10 (pack, init, then per iteration the persistent "
+                        "batched run / 10 (pack, init, then per iteration the batched "
                         "assignment, finalize and projection); work at the initial grid")
     return {"workload": f"{len(wls)} ragged Voronoi images, H,W in [240,2160], k = HW/1000, 10 it",
             "roofline": roof,
@@ -521,7 +521,7 @@ def bench_multiscale(torch, args, tuned):
     ks = scales()
     lab_b, con_b = MultiScale.stack_of(len(ks), torch.from_numpy(img.lab).cuda(),
                                        torch.from_numpy(img.contour).cuda())
-    # launch shape of the persistent kernel, tuned on this batch of 12 scales
+    # launch shape of the batched kernel, tuned on this batch of 12 scales
     if args.batch_launch:
         tuned_ms = batch_launch(args.batch_launch)
     else:
@@ -687,7 +687,7 @@ def bench_soft(torch, args):
     h1.record()
     torch.cuda.synchronize()
     hard = h0.elapsed_time(h1) / reps
-    # ... and as one ragged batch (persistent launch, shape tuned on it)
+    # ... and as one ragged batch (shape tuned on it)
     from paper_1903_07149_amd import autotune
     from paper_1903_07149_amd.scalp import ScalpBatch
     shapes = [(W, H, k)] * B

@@ -77,8 +77,9 @@ typedef struct {
                                 soft forward have no tables.  The results do
                                 not depend on it                             */
     int32_t wg_size;         /* tuning: workgroup size of the 3x3 assignment and
-                                of the soft forward, 0 (default: 256), 256, 512
-                                or 1024 (the window form always takes 256)   */
+                                of the soft forward, 0 (default: 256, or 512
+                                for small batches), 256, 512 or 1024 (the window
+                                form always takes 256)                       */
     int32_t assign_mode;     /* SCALP_ASSIGN_GRID3X3 (default) or
                                 SCALP_ASSIGN_WINDOW, see below               */
     int32_t contour_source;  /* SCALP_CONTOUR_INPUT (default) or
@@ -92,10 +93,10 @@ typedef struct {
                                 every candidate is walked.  The results are
                                 the same either way; 0 or 1, else
                                 SCALP_ERR_ARG                                */
-    int32_t persistent_blocks; /* tuning: workgroups per compute unit of the
-                                batched persistent launch, 0 (default: as many
-                                as fit) or 1..16 (capped at what fits); the
-                                results do not depend on it                  */
+    int32_t persistent_blocks; /* 0 (default) to 16, else SCALP_ERR_ARG.  Bounded
+                                the workgroups per compute unit of the batched
+                                assignment when they were persistent: kept for
+                                callers that set it, without effect          */
     int32_t table_mode;      /* 0 (default) or 1, else SCALP_ERR_ARG.  Chose
                                 between two table schedules of the 3x3
                                 assignment, which has no tables any more: kept
@@ -139,7 +140,7 @@ int scalp_make_grid(int32_t width, int32_t height, int32_t k, scalp_grid_t* out)
  * the packed (l, a, b, w) image (16 B per pixel), 8 B per pixel for the window
  * form, 68 B per superpixel (integer accumulators, projection queue) and
  * 5376 B of control words (projection queue length, partial maxima of the
- * computed contour prior, the batched assignment's per-XCD queue heads).
+ * computed contour prior).
  * 0 if g is invalid. */
 size_t scalp_workspace_bytes(const scalp_grid_t* g);
 
@@ -253,9 +254,8 @@ size_t scalp_batch_workspace_bytes(const scalp_batch_desc_t* descs, int32_t n_im
 
 /* Algorithm 1 on every image of the batch: prepare, init and
  * p->iterations x (assign + update, projection), each iteration one
- * persistent launch over a work queue of (image, cell, slice) items (a
- * cell larger than the workgroup is cut into slices of whole 64-pixel
- * chunks).  Results are identical to scalp_run on each image alone.
+ * launch over the (image, cell, slice) items (a cell larger than a workgroup is
+ * cut into slices of whole 64-pixel chunks).  Results are identical to scalp_run on each image alone.
  * descs: host array; all other arrays are device arrays concatenated as
  * described above.  gamma < 0 selects 2r per image. */
 int scalp_run_batched(const scalp_batch_desc_t* descs, int32_t n_images, const scalp_params_t* p,

@@ -2,13 +2,12 @@
 
 Knobs that change speed but never results (every configuration is checked
 bit-exact against the oracle by the GPU tests): the workgroup size (lanes of
-one work item, one pixel each) and, for a ragged batch, the number of
-persistent workgroups per CU.
+one work item, one pixel each).
 
 tune() times one fused assignment pass (`scalp_assign_accumulate`) per
 configuration with HIP events on the workload's own image and superpixel
 state; tune_batch() times whole batched runs (`scalp_run_batched`: packing,
-grid initialisation and two persistent iterations) on the batch itself.
+grid initialisation and two iterations) on the batch itself.
 Winners are cached in a JSON file keyed by device architecture and workload
 shape (for a batch: the histogram of its images' sizes and cell sides).
 """
@@ -24,8 +23,7 @@ import torch
 from .scalp import Scalp, ScalpBatch
 
 CANDIDATES = [dict(wg_size=w) for w in (256, 512, 1024)]
-BATCH_CANDIDATES = [dict(wg_size=w, persistent_blocks=b) for w in (256, 512, 1024)
-                    for b in (0, 1, 2, 4)]
+BATCH_CANDIDATES = CANDIDATES
 CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuning_cache.json")
 
 
@@ -96,7 +94,7 @@ def batch_key(shapes) -> str:
 
 def time_batch_config(shapes, lab, contour, cfg: dict, reps: int = 2, iterations: int = 2) -> float:
     """Average milliseconds of one batched run (pack, init, `iterations`
-    persistent iterations) with `cfg`."""
+    iterations) with `cfg`."""
     b = ScalpBatch(shapes, iterations=iterations, **cfg)
     out = b.new_state()
     b.run(lab, contour, out=out)                  # warm-up of this shape

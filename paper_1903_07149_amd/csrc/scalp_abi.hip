@@ -68,20 +68,17 @@ bool pack_inputs_ok(const scalp_params_t* p, const float* lab, const float* cont
 Tuning tuning_of(const scalp_params_t* p) {
     Tuning t;
     t.wg = p->wg_size == 0 ? 256 : p->wg_size;
-    t.blocks_per_cu = p->persistent_blocks;
     return t;
 }
 
-// Assignment work items per cell for workgroups of wg lanes: the largest cell
-// is ceil(W / nx) x ceil(H / ny) pixels, in ceil(. / 64) chunks of 64, split
-// evenly so that no item has more than wg / 64 chunks.
-int slices_of(const scalp_grid_t* g, int wg) {
-    const long long cw = (g->width + g->nx - 1) / g->nx, ch = (g->height + g->ny - 1) / g->ny;
-    const long long chunks = (cw * ch + 63) / 64, per = wg / 64;
-    return (int)std::max<long long>(1, (chunks + per - 1) / per);
+// Work items per cell of a single image's launch.
+int slices_of(const scalp_grid_t* g, const scalp_params_t* p) {
+    return assign_slices(g->width, g->height, g->nx, g->ny,
+                         item_pixels(g->width, g->height, g->num_sp, tuning_of(p).wg),
+                         fill_slices(g->num_sp));
 }
 
-Img img_of(const scalp_grid_t* g, const scalp_params_t* p, long long pix, int sp) {
+Img img_of(const scalp_grid_t* g, const scalp_params_t* p, long long pix, int sp, int spl) {
     Img im;
     im.W = g->width;
     im.H = g->height;
@@ -92,7 +89,7 @@ Img img_of(const scalp_grid_t* g, const scalp_params_t* p, long long pix, int sp
     const double r = grid_r(g->width, g->height, g->k_requested);
     im.spw = (float)(((double)p->m * (double)p->m) / (r * r));          // Eq. (3)
     im.gamma = p->gamma < 0.0f ? (float)(2.0 * r) : p->gamma;           // Sec. III-A.3
-    im.spl = slices_of(g, tuning_of(p).wg);
+    im.spl = spl;
     im.rad = (int)std::floor(r + 0.5);
     im.prune = p->exact_pruning;
     // Each XCD (own L2) takes a contiguous run of the cell order; strips of
@@ -330,7 +327,7 @@ int scalp_init_grid(const scalp_grid_t* g, const scalp_params_t* p, const float*
     const Views v = views_of(ws, L);
     if (!p->reuse_prepared) CHECK_HIP(enq_prepare(g, p, lab, contour, v, s));
     // counts are not an output of this call: the projection list area holds them
-    CHECK_HIP(enq_init(img_of(g, p, 0, 0), v, centers, endpoints, v.plist, labels, s));
+    CHECK_HIP(enq_init(img_of(g, p, 0, 0, slices_of(g, p)), v, centers, endpoints, v.plist, labels, s));
     return SCALP_OK;
 }
 
@@ -347,11 +344,11 @@ int scalp_assign(const scalp_grid_t* g, const scalp_params_t* p, const float* la
     if (p->assign_mode == SCALP_ASSIGN_WINDOW) {
         CHECK_HIP(launch_clear(static_cast<long long*>(v.lists),
                                window_count_words(g->width, g->height), s));
-        CHECK_HIP(launch_assign_window(img_of(g, p, 0, 0), v.packed, centers, endpoints, labels,
+        CHECK_HIP(launch_assign_window(img_of(g, p, 0, 0, slices_of(g, p)), v.packed, centers, endpoints, labels,
                                        v.acc, v.ctrl, v.lists, window_radius(g), p->lambda, false,
                                        false, s));
     } else
-        CHECK_HIP(launch_assign(img_of(g, p, 0, 0), v.packed, centers, endpoints, labels, v.acc,
+        CHECK_HIP(launch_assign(img_of(g, p, 0, 0, slices_of(g, p)), v.packed, centers, endpoints, labels, v.acc,
                                 v.ctrl, p->lambda, false, tuning_of(p), s));
     return SCALP_OK;
 }
@@ -365,7 +362,7 @@ int scalp_update(const scalp_grid_t* g, const scalp_params_t* p, const float* la
     const hipStream_t s = (hipStream_t)stream;
     const Layout L = layout_of((long long)g->width * g->height, g->num_sp);
     const Views v = views_of(ws, L);
-    const Img im = img_of(g, p, 0, 0);
+    const Img im = img_of(g, p, 0, 0, slices_of(g, p));
     CHECK_HIP(launch_clear(v.acc, clear_words(L), s));
     CHECK_HIP(launch_accumulate(im, lab, labels, v.acc, s));
     CHECK_HIP(launch_finalize(im, centers, endpoints, counts, v.acc, labels, v.ctrl, v.plist,
@@ -384,10 +381,10 @@ int scalp_assign_accumulate(const scalp_grid_t* g, const scalp_params_t* p, cons
     const Layout L = layout_of((long long)g->width * g->height, g->num_sp);
     const Views v = views_of(ws, L);
     if (p->assign_mode == SCALP_ASSIGN_WINDOW)
-        CHECK_HIP(enq_window_pass(img_of(g, p, 0, 0), p, v, window_radius(g), centers, endpoints,
+        CHECK_HIP(enq_window_pass(img_of(g, p, 0, 0, slices_of(g, p)), p, v, window_radius(g), centers, endpoints,
                                   labels, true, false, (hipStream_t)stream));
     else
-        CHECK_HIP(launch_assign(img_of(g, p, 0, 0), v.packed, centers, endpoints, labels, v.acc,
+        CHECK_HIP(launch_assign(img_of(g, p, 0, 0, slices_of(g, p)), v.packed, centers, endpoints, labels, v.acc,
                                 v.ctrl, p->lambda, true, tuning_of(p), (hipStream_t)stream));
     return SCALP_OK;
 }
@@ -400,7 +397,7 @@ int scalp_finalize(const scalp_grid_t* g, const scalp_params_t* p, const int32_t
     if (!labels || !centers || !endpoints || !counts) return SCALP_ERR_ARG;
     const hipStream_t s = (hipStream_t)stream;
     const Views v = views_of(ws, layout_of((long long)g->width * g->height, g->num_sp));
-    const Img im = img_of(g, p, 0, 0);
+    const Img im = img_of(g, p, 0, 0, slices_of(g, p));
     CHECK_HIP(launch_finalize(im, centers, endpoints, counts, v.acc, labels, v.ctrl, v.plist,
                               p->project != 0, s));
     if (p->project)
@@ -418,7 +415,7 @@ int scalp_run(const scalp_grid_t* g, const scalp_params_t* p, const float* lab,
     const hipStream_t s = (hipStream_t)stream;
     const Layout L = layout_of((long long)g->width * g->height, g->num_sp);
     const Views v = views_of(ws, L);
-    const Img im = img_of(g, p, 0, 0);
+    const Img im = img_of(g, p, 0, 0, slices_of(g, p));
     if (!p->reuse_prepared) CHECK_HIP(enq_prepare(g, p, lab, contour, v, s));
     CHECK_HIP(enq_init(im, v, centers, endpoints, counts, labels, s));
     CHECK_HIP(enq_iterations(im, p, v, centers, endpoints, labels, counts, s, window_radius(g)));
@@ -447,7 +444,7 @@ int scalp_graph_create(const scalp_grid_t* g, const scalp_params_t* p, float* ce
     if (!centers || !endpoints || !labels || !counts || !out) return SCALP_ERR_ARG;
     const Layout L = layout_of((long long)g->width * g->height, g->num_sp);
     const Views v = views_of(ws, L);
-    const Img im = img_of(g, p, 0, 0);
+    const Img im = img_of(g, p, 0, 0, slices_of(g, p));
     const scalp_params_t pc = *p;
     const int R = window_radius(g);
     return capture(out, [&](hipStream_t s) {
@@ -489,7 +486,8 @@ bool batch_layout(const scalp_batch_desc_t* d, int n, BatchLayout* out) {
         if (d[i].pix_offset != N || d[i].sp_offset != K) return false;
         N += (long long)d[i].grid.width * d[i].grid.height;
         K += d[i].grid.num_sp;
-        I += (long long)d[i].grid.num_sp * slices_of(&d[i].grid, kMinAssignWG);   // most items
+        I += (long long)d[i].grid.num_sp * assign_slices(d[i].grid.width, d[i].grid.height, d[i].grid.nx,
+                                                         d[i].grid.ny, kMinAssignWG, 1);
         if (N >= (1LL << 40) || K >= (1LL << 31) || I >= (1LL << 31)) return false;
     }
     out->items_total = I;
@@ -505,7 +503,9 @@ bool batch_layout(const scalp_batch_desc_t* d, int n, BatchLayout* out) {
 
 int enq_batched(const scalp_batch_desc_t* d, int n, const scalp_params_t* p, const float* lab,
                 const float* contour, float* centers, int* endpoints, int* labels, int* counts,
-                void* ws, const BatchLayout& BL, int grid, hipStream_t s) {
+                void* ws, const BatchLayout& BL, hipStream_t s) {
+    const Tuning t = tuning_of(p);
+    const bool few = BL.N < kFewPixels;
     const Views v = views_of(ws, BL.base);
     char* b = static_cast<char*>(ws);
     Img* imgs = reinterpret_cast<Img*>(b + BL.imgs);
@@ -515,14 +515,20 @@ int enq_batched(const scalp_batch_desc_t* d, int n, const scalp_params_t* p, con
     std::vector<int> hstart((size_t)n + 1), hitem(9 * ((size_t)n + 1));
     long long total_items = 0;
     for (int i = 0; i < n; ++i) {
-        himg[(size_t)i] = img_of(&d[i].grid, p, d[i].pix_offset, d[i].sp_offset);
+        const scalp_grid_t& g = d[i].grid;
+        // (items_total is below 2^31; smaller items only where they cannot pass it)
+        const int pixels = few ? 64 : BL.items_total < 1LL << 29
+                                     ? item_pixels(g.width, g.height, g.num_sp, t.wg) : t.wg;
+        himg[(size_t)i] = img_of(&g, p, d[i].pix_offset, d[i].sp_offset,
+                                 assign_slices(g.width, g.height, g.nx, g.ny, pixels, 1));
         hstart[(size_t)i] = d[i].sp_offset;
         hitem[(size_t)i] = (int)total_items;
-        total_items += (long long)d[i].grid.num_sp * himg[(size_t)i].spl;   // < 2^31: batch_layout
+        total_items += (long long)g.num_sp * himg[(size_t)i].spl;
     }
     hstart[(size_t)n] = (int)BL.K;
     hitem[(size_t)n] = (int)total_items;
-    // the persistent assignment's run of XCD x: the x-th eighth of each image's items
+    // the assignment's run of XCD x: the x-th eighth of each image's items
+    int longest_run = 0;
     for (int x = 0; x < 8; ++x) {
         int* run = hitem.data() + ((size_t)n + 1) * (size_t)(1 + x);
         run[0] = 0;
@@ -530,6 +536,7 @@ int enq_batched(const scalp_batch_desc_t* d, int n, const scalp_params_t* p, con
             const long long ni = (long long)hitem[(size_t)i + 1] - hitem[(size_t)i];
             run[i + 1] = run[i] + (int)((ni * (x + 1) >> 3) - (ni * x >> 3));
         }
+        longest_run = std::max(longest_run, run[n]);
     }
     int e = launch_write_bytes(imgs, himg.data(), sizeof(Img) * (size_t)n, s);
     if (e == hipSuccess) e = launch_write_bytes(starts, hstart.data(), sizeof(int) * (size_t)(n + 1), s);
@@ -550,7 +557,6 @@ int enq_batched(const scalp_batch_desc_t* d, int n, const scalp_params_t* p, con
     if (e == hipSuccess)
         e = launch_finalize_batched(imgs, starts, n, (int)BL.K, centers, endpoints, counts, v.acc,
                                     labels, v.ctrl, v.plist, false, s);
-    const Tuning t = tuning_of(p);
     bool near = true;
     for (const Img& im : himg) near = near && near_image(im);
     long long max_block = 0;
@@ -558,12 +564,12 @@ int enq_batched(const scalp_batch_desc_t* d, int n, const scalp_params_t* p, con
         max_block = std::max(max_block, block_pixels(d[i].grid.width, d[i].grid.height,
                                                      d[i].grid.nx, d[i].grid.ny));
     for (int it = 0; e == hipSuccess && it < p->iterations; ++it) {
-        e = launch_assign_persistent(imgs, items, n, (int)total_items, v.packed, centers, endpoints,
-                                     labels, v.acc, v.ctrl, p->lambda, t, near, grid, s);
+        e = launch_assign_batched(imgs, items, n, longest_run, v.packed, centers, endpoints, labels,
+                                  v.acc, v.ctrl, p->lambda, t, near, s);
         if (e == hipSuccess)
             e = p->project ? launch_finalize_project_batched(imgs, starts, n, (int)BL.K, max_block,
                                                              centers, endpoints, counts, v.acc,
-                                                             labels, v.ctrl, s)
+                                                             labels, s)
                            : launch_finalize_batched(imgs, starts, n, (int)BL.K, centers,
                                                      endpoints, counts, v.acc, labels, v.ctrl,
                                                      v.plist, false, s);
@@ -589,10 +595,8 @@ int scalp_run_batched(const scalp_batch_desc_t* descs, int32_t n, const scalp_pa
     if (!centers || !endpoints || !labels || !counts) return SCALP_ERR_ARG;
     if (!p->reuse_prepared && !pack_inputs_ok(p, lab, contour)) return SCALP_ERR_ARG;
     if (!ws || ws_bytes < BL.total) return SCALP_ERR_WORKSPACE;
-    const int grid = persistent_grid(tuning_of(p));
-    if (grid < 1) return SCALP_ERR_HIP;
     CHECK_HIP(enq_batched(descs, n, p, lab, contour, centers, endpoints, labels, counts, ws, BL,
-                          grid, (hipStream_t)stream));
+                          (hipStream_t)stream));
     return SCALP_OK;
 }
 
@@ -606,12 +610,9 @@ int scalp_batched_graph_create(const scalp_batch_desc_t* descs, int32_t n, const
     if (!centers || !endpoints || !labels || !counts || !out) return SCALP_ERR_ARG;
     if (!p->reuse_prepared && !pack_inputs_ok(p, lab, contour)) return SCALP_ERR_ARG;
     if (!ws || ws_bytes < BL.total) return SCALP_ERR_WORKSPACE;
-    // the occupancy query runs before the capture
-    const int grid = persistent_grid(tuning_of(p));
-    if (grid < 1) return SCALP_ERR_HIP;
     return capture(out, [&](hipStream_t s) {
         return enq_batched(descs, n, p, lab, contour, centers, endpoints, labels, counts, ws, BL,
-                           grid, s);
+                           s);
     });
 }
 
@@ -620,6 +621,13 @@ int scalp_batched_graph_create(const scalp_batch_desc_t* descs, int32_t n, const
 }  // extern "C"
 
 namespace {
+
+// 512 lanes where there are no more cells than compute units (2 x 97x61, T = 5: 14.4
+// us per assignment at 256, 13.3 at 512, 13.9 at 1024; 2 x 256x256, k = 128: 34, 31,
+// 40).
+int soft_wg(const scalp_grid_t* g, const scalp_params_t* p, long long batch) {
+    return p->wg_size == 0 && batch * g->num_sp <= kCUs ? 512 : tuning_of(p).wg;
+}
 
 // saved: [A: T][B][9][N] float, [Bf: T][B][9][N] float, [Z: T][B][K] double,
 // [masks of the Q that are not 0: T][B][N] uint16
@@ -669,7 +677,7 @@ bool soft_args_ok(const scalp_grid_t* g, const scalp_params_t* p, float temperat
     if ((long long)batch * N >= (1LL << 40)) return false;
     // one workgroup per (image, cell, slice) must fit a 32-bit grid
     const long long items = (long long)batch * g->num_sp *
-                            soft_slices(g->width, g->height, g->nx, g->ny, kMinAssignWG);
+                            assign_slices(g->width, g->height, g->nx, g->ny, kMinAssignWG, 1);
     return items <= 0x7fffffffLL;
 }
 
@@ -706,9 +714,9 @@ int scalp_soft_forward(const scalp_grid_t* g, const scalp_params_t* p, float tem
     const hipStream_t s = (hipStream_t)stream;
     const long long N = (long long)g->width * g->height, K = g->num_sp, B = batch;
     const int T = p->iterations;
-    const Img im = img_of(g, p, 0, 0);
+    const Img im = img_of(g, p, 0, 0, slices_of(g, p));
     const SoftGeom geo = soft_geom(g->width, g->height, g->nx, g->ny, batch, im.spw, im.gamma,
-                                   p->lambda, temperature, tuning_of(p).wg,
+                                   p->lambda, temperature, soft_wg(g, p, batch),
                                    p->exact_pruning);
     const SoftSaved S = soft_saved_layout(g, B, T);
     char* wb = static_cast<char*>(ws);
@@ -749,9 +757,9 @@ int scalp_soft_backward(const scalp_grid_t* g, const scalp_params_t* p, float te
     const hipStream_t s = (hipStream_t)stream;
     const long long N = (long long)g->width * g->height, K = g->num_sp, B = batch;
     const int T = p->iterations;
-    const Img im = img_of(g, p, 0, 0);
+    const Img im = img_of(g, p, 0, 0, slices_of(g, p));
     const SoftGeom geo = soft_geom(g->width, g->height, g->nx, g->ny, batch, im.spw, im.gamma,
-                                   p->lambda, temperature, tuning_of(p).wg,
+                                   p->lambda, temperature, soft_wg(g, p, batch),
                                    p->exact_pruning);
     const SoftSaved S = soft_saved_layout(g, B, T);
     char* wb = static_cast<char*>(ws);

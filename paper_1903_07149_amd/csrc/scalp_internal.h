@@ -2,6 +2,8 @@
 // layer of libscalp.so (not part of the public interface).
 #pragma once
 
+#include <algorithm>
+
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -22,9 +24,7 @@ enum Ctrl : int {
     kCtrlProjCount = 0,   // entries in the projection list
     kCtrlGradMax = 64,    // words 64-1087: kGradSlots maxima of the squared gradient
                           // magnitude (FP64 bits)
-    kCtrlQueue = 1088,    // words 1088-1343: the persistent assignment's 8 queue heads
-                          // (one per XCD's run of items), one per 128-byte line
-    kCtrlWords = 1344
+    kCtrlWords = 1344     // (the rest is unused: callers' buffers are sized by it)
 };
 
 // Each block of the gradient's maximum pass has one of kGradSlots 64-bit slots.
@@ -73,9 +73,41 @@ bool near_image(const Img& im);
 // items, which also spreads images with few, large superpixels over the chip.
 constexpr int kMinAssignWG = 256;
 
+constexpr int kCUs = 256;
+
+// Pixels of a work item of a hard assignment by workgroups of wg lanes.  Where
+// paths are long (cells above 48 x 48 pixels) a pixel has several pairs in the
+// second pass: items of half a workgroup's pixels halve its rounds, and end more
+// evenly.  12 scales of 481x321 (k = 6 to 600): 199 us per iteration, 234 with 256
+// pixels in all items, 213 with 64 in cells above 96 x 96.  (Beyond 2^30 pixels a
+// launch of a workgroup per item would have too many lanes.)
+inline int item_pixels(long long W, long long H, long long K, int wg) {
+    return W * H > 2304 * K && W * H <= 1LL << 30 ? std::min(wg, 128) : wg;
+}
+
+// Items per cell: so many that no item has more than `pixels` pixels, and at least
+// `fill` of them, down to one 64-pixel chunk each.
+inline int assign_slices(int W, int H, int nx, int ny, int pixels, long long fill) {
+    const long long cw = (W + nx - 1) / nx, ch = (H + ny - 1) / ny;
+    const long long chunks = (cw * ch + 63) / 64, per = pixels / 64;
+    return (int)std::max((chunks + per - 1) / per, std::min(chunks, fill));
+}
+
+// `fill` of a launch over `cells` cells: where a workgroup each would not reach all
+// compute units, as many as do (the lanes without a pixel walk the second pass's
+// pairs).  97x61, 30 cells, one item per cell: 11.2 us instead of 10.6; two such
+// images soft at T = 5: 20.5 instead of 13.7.  More items than kCUs gain nothing
+// (481x321, 250 cells in 3 items: 14.0 us, in 4: 14.6).
+inline long long fill_slices(long long cells) { return kCUs / cells; }
+
+// A batch of fewer pixels than this, half the lanes that the chip holds, takes 64
+// pixels an item: 7 scales of 189x117 (0.15 M pixels) 32 us per iteration with 128
+// or 256, 26 with 64; 3 images of up to 480 pixels a side, 250 pixels a superpixel,
+// 22.8 and 21.5.  (12 scales of 481x321, 1.9 M: 207 us as they are, 256 with 64.)
+constexpr long long kFewPixels = 1 << 18;
+
 struct Tuning {
     int wg;           // workgroup size of the assignment kernel (256, 512 or 1024)
-    int blocks_per_cu = 0;   // persistent launch: workgroups per CU (0: as many as fit)
 };
 
 // LDS budget of the soft backward's tiles in 16-byte units: the default, and the
@@ -114,7 +146,7 @@ int launch_finalize(const Img& im, float* centres, int* endpoints, int* counts,
 int launch_finalize_project_batched(const Img* imgs, const int* sp_start, int n_img,
                                     int total_sp, long long max_block_px, float* centres,
                                     int* endpoints, int* counts, long long* acc, const int* labels,
-                                    int* ctrl, hipStream_t s);
+                                    hipStream_t s);
 long long block_pixels(int W, int H, int nx, int ny);
 // lists (or null) and R: make the tile lists of the window form's next pass, too
 int launch_finalize_project(const Img& im, float* centres, int* endpoints, int* counts,
@@ -125,16 +157,16 @@ int launch_project(const Img& im, const float* centres, const int* counts, const
 // Batched variants: imgs/cell_start/sp_start are device arrays in the workspace.
 int launch_init_cells_batched(const Img* imgs, const int* cell_start, int n_img, int total_cells,
                               const float4* packed, int* labels, long long* acc, hipStream_t s);
-// (near: near_image of every image)
-int launch_assign_persistent(const Img* imgs, const int* item_start, int n_img, int total_items,
-                             const float4* packed, const float* centres, const int* endpoints,
-                             int* labels, long long* acc, int* ctrl, float lambda,
-                             const Tuning& t, bool near, int grid, hipStream_t s);
+// longest_run: items of the longest of the 8 XCDs' runs; near: near_image of every
+// image
+int launch_assign_batched(const Img* imgs, const int* item_start, int n_img, int longest_run,
+                          const float4* packed, const float* centres, const int* endpoints,
+                          int* labels, long long* acc, int* ctrl, float lambda, const Tuning& t,
+                          bool near, hipStream_t s);
 int launch_finalize_batched(const Img* imgs, const int* sp_start, int n_img, int total_sp,
                             float* centres, int* endpoints, int* counts, long long* acc,
                             const int* labels, int* ctrl, int* plist, bool project,
                             hipStream_t s);
-int persistent_grid(const Tuning& t);
 
 // ---- soft SCALP (scalp_soft.hip)
 struct SoftGeom {
@@ -148,7 +180,6 @@ SoftGeom soft_geom(int W, int H, int nx, int ny, int B, float spw, float gamma, 
 void lift_soft_lds_limits();
 // Work items per cell of the soft assignment at workgroup size wg: a cell
 // is cut into slices of whole 64-pixel chunks, at most wg pixels each.
-int soft_slices(int W, int H, int nx, int ny, int wg);
 int launch_soft_init(const SoftGeom& g, const float4* packed, float* theta0, hipStream_t st);
 // pmask [B][N]: bit j of a pixel: its Q of slot j is not 0
 int launch_soft_assign(const SoftGeom& g, const float4* packed, const float* theta_prev, float* q,

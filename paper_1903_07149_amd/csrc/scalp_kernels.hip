@@ -92,7 +92,7 @@ __device__ __forceinline__ int slice_chunk(int chunks, int i, const Img& im) {
 // sums prove that D exceeds the pixel's first one (Cut).
 //
 // NEAR (near_image): the walks by 32-bit indexes.  A kernel with both needs 10
-// registers more (62 instead of 52; the persistent one spilled) and took 1 to 2 %
+// registers more (62 instead of 52; with the batch's tables it spilled) and took 1 to 2 %
 // longer.
 //
 // What bounds it: VALU issue.  33.4 M wave instructions per launch at
@@ -273,52 +273,43 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_
                             acc, lambda, sh);
 }
 
-// At most 64 VGPRs (8 waves per SIMD): two 1024-thread workgroups per CU.
+// The assignment over a ragged batch, a workgroup per (image, cell, slice) item,
+// dispatched by the hardware as workgroups end.
+//
+// XCD x (workgroup b runs on XCD b mod 8) has its own run of items: the x-th
+// eighth of every image's items, in the cell order of cell_in_strips, so its
+// cells form a block and share its L2, and every XCD starts on every image
+// (images of few, large cells walk long paths).  run x = item_start + (n_img +
+// 1) (1 + x) holds where each image's share starts in the run.
+//
+// Workgroups that stayed and took items from eight queues spent their time at
+// the queues: an atomic and two barriers per item, and eight failed atomics of
+// every workgroup on eight words at the end: 40 us per iteration instead of 26 for 7
+// scales of 189x117, 36 instead of 22 for 3 small images; 64 images of up to 2160
+// pixels a side 2.95 ms instead of 2.93, and 12 scales of 481x321, where taking over
+// another XCD's items helped, 202 instead of 207.
 template <int WG, bool NEAR>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8)))
-void k_assign_persistent(const Img* __restrict__ imgs,
-                                                          const int* __restrict__ item_start,
-                                                          int n_img, int total,
-                                                          const float4* __restrict__ packed,
-                                                          const float* __restrict__ centres,
-                                                          const int* __restrict__ endpoints,
-                                                          int* __restrict__ labels,
-                                                          long long* __restrict__ acc, int* ctrl,
-                                                          float lambda) {
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_assign_batched(
+    const Img* __restrict__ imgs, const int* __restrict__ item_start, int n_img,
+    const float4* __restrict__ packed, const float* __restrict__ centres,
+    const int* __restrict__ endpoints, int* __restrict__ labels, long long* __restrict__ acc, int* ctrl,
+    float lambda, int h0) {
     __shared__ ItemShared<WG> sh;
-    __shared__ int item;
     if (blockIdx.x == 0 && threadIdx.x == 0) ctrl[kCtrlProjCount] = 0;
-    // XCD x (workgroup b runs on XCD b mod 8) has its own run of items and
-    // queue head: the x-th eighth of every image's items, in the cell order
-    // of cell_in_strips, so its cells form a block and share its L2, and
-    // every XCD starts on every image (images of few, large cells walk long
-    // paths).  run x = item_start + (n_img + 1) (1 + x) holds where each
-    // image's share starts in the run.  A workgroup takes the items of its
-    // XCD's run, then those left in the other runs, in turn.
     // (the tables are constant during the launch: scalar loads)
     const ConstI starts = (ConstI)(uintptr_t)item_start;
-    for (int q = 0; q < 8;) {
-        const int x = (int)((blockIdx.x + q) & 7u);
-        const ConstI run = starts + (n_img + 1) * (1 + x);
-        if (threadIdx.x == 0) item = atomicAdd(&ctrl[kCtrlQueue + 32 * x], 1);
-        __syncthreads();
-        const int h = __builtin_amdgcn_readfirstlane(item);   // uniform: kept in SGPRs
-        __syncthreads();
-        if (h >= run[n_img]) {
-            ++q;
-            continue;
-        }
-        const int i = find_image(run, n_img, h);
-        const Img im = load_const(imgs + i);
-        const int ni = starts[i + 1] - starts[i];
-        const int local = __builtin_amdgcn_readfirstlane((int)((long long)ni * x >> 3) + (h - run[i]));
-        const int pos = fdiv(local, im.dspl);
-        int ci, cj;
-        cell_in_strips(pos, im, ci, cj);
-        process_cell<WG, true, NEAR>(im, ci, cj, local - pos * im.spl, packed, centres, endpoints,
-                               labels, acc, lambda, sh);
-        __syncthreads();   // shared state is reused by the next item
-    }
+    const int x = (int)(blockIdx.x & 7u), h = h0 + (int)(blockIdx.x >> 3);
+    const ConstI run = starts + (n_img + 1) * (1 + x);
+    if (h >= run[n_img]) return;                   // the shorter runs
+    const int i = find_image(run, n_img, h);
+    const Img im = load_const(imgs + i);
+    const int ni = starts[i + 1] - starts[i];
+    const int local = __builtin_amdgcn_readfirstlane((int)((long long)ni * x >> 3) + (h - run[i]));
+    const int pos = fdiv(local, im.dspl);
+    int ci, cj;
+    cell_in_strips(pos, im, ci, cj);
+    process_cell<WG, true, NEAR>(im, ci, cj, local - pos * im.spl, packed, centres, endpoints, labels,
+                                 acc, lambda, sh);
 }
 
 // ---------------------------------------------------------------- window form
@@ -837,7 +828,6 @@ __global__ void k_finalize_batched(const Img* __restrict__ imgs, const int* __re
                                    int* counts, long long* acc, const int* labels, int* ctrl,
                                    int* plist, int project) {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g < 8) ctrl[kCtrlQueue + 32 * g] = 0;   // the next persistent assignment starts afresh
     if (g >= total) return;
     const int i = find_image(sp_start, n_img, g);
     const Img im = imgs[i];
@@ -1010,21 +1000,17 @@ __global__ __launch_bounds__(WG) void k_finalize_project(Img im, float* centres,
     if (smove) project_at<WG>(im, k, sx, sy, scnt, labels, endpoints);   // uniform
 }
 
-// The same over a ragged batch, a workgroup per superpixel of the batch;
-// like k_finalize_batched it resets the persistent assignment's queue heads.
+// The same over a ragged batch, a workgroup per superpixel of the batch.
 template <int WG>
 __global__ __launch_bounds__(WG) void k_finalize_project_batched(const Img* __restrict__ imgs,
                                                                  const int* __restrict__ sp_start,
                                                                  int n_img, float* centres,
                                                                  int* endpoints, int* counts,
-                                                                 long long* acc, const int* labels,
-                                                                 int* ctrl) {
+                                                                 long long* acc,
+                                                                 const int* labels) {
     __shared__ float sx, sy;
     __shared__ int scnt, smove, simg;
     const int g = blockIdx.x;
-    // the next persistent assignment starts afresh (block 0 clears all 8
-    // heads: a batch may have fewer than 8 superpixels)
-    if (g == 0 && threadIdx.x < 8) ctrl[kCtrlQueue + 32 * threadIdx.x] = 0;
     if (threadIdx.x == 0) {
         const int i = find_image(sp_start, n_img, g);
         float xk = 0.0f, yk = 0.0f;
@@ -1167,34 +1153,20 @@ int launch_assign(const Img& im, const float4* packed, const float* centres,
     return launch(im, packed, centres, endpoints, labels, acc, ctrl, lambda, accumulate, s);
 }
 
-// The persistent assignment's kernel for a workgroup size, and for images that
-// are all near or not.
-static decltype(&k_assign_persistent<256, true>) persistent_kernel(int wg, bool near) {
-    if (wg == 1024) return near ? k_assign_persistent<1024, true> : k_assign_persistent<1024, false>;
-    if (wg == 512) return near ? k_assign_persistent<512, true> : k_assign_persistent<512, false>;
-    return near ? k_assign_persistent<256, true> : k_assign_persistent<256, false>;
-}
-
-int launch_assign_persistent(const Img* imgs, const int* item_start, int n_img, int total_items,
-                             const float4* packed, const float* centres, const int* endpoints,
-                             int* labels, long long* acc, int* ctrl, float lambda,
-                             const Tuning& t, bool near, int grid, hipStream_t s) {
-    hipLaunchKernelGGL(persistent_kernel(t.wg, near), dim3(grid), dim3(t.wg), 0, s, imgs, item_start,
-                       n_img, total_items, packed, centres, endpoints, labels, acc, ctrl, lambda);
+int launch_assign_batched(const Img* imgs, const int* item_start, int n_img, int longest_run,
+                          const float4* packed, const float* centres, const int* endpoints,
+                          int* labels, long long* acc, int* ctrl, float lambda, const Tuning& t,
+                          bool near, hipStream_t s) {
+    const auto kernel = t.wg == 1024  ? near ? k_assign_batched<1024, true> : k_assign_batched<1024, false>
+                        : t.wg == 512 ? near ? k_assign_batched<512, true> : k_assign_batched<512, false>
+                                      : near ? k_assign_batched<256, true> : k_assign_batched<256, false>;
+    // (a launch holds below 2^32 lanes)
+    for (int h0 = 0; h0 < longest_run; h0 += 1 << 18) {
+        const unsigned n = (unsigned)std::min(longest_run - h0, 1 << 18);
+        hipLaunchKernelGGL(kernel, dim3(8u * n), dim3(t.wg), 0, s, imgs, item_start, n_img, packed,
+                           centres, endpoints, labels, acc, ctrl, lambda, h0);
+    }
     return hipGetLastError();
-}
-
-int persistent_grid(const Tuning& t) {
-    int dev = 0, cus = 0, per = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return -1;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return -1;
-    // (both kernels of a size are held to 64 registers: one occupancy)
-    const int e = (int)hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &per, reinterpret_cast<const void*>(persistent_kernel(t.wg, true)), t.wg, 0);
-    if (e != (int)hipSuccess || per < 1) per = 1;
-    if (t.blocks_per_cu > 0 && t.blocks_per_cu < per) per = t.blocks_per_cu;
-    return cus * per;
 }
 
 // 8 W H bytes, but at least 256, hold the counts and a list of at least 16 ids per
@@ -1284,15 +1256,15 @@ int launch_finalize_project(const Img& im, float* centres, int* endpoints, int* 
 int launch_finalize_project_batched(const Img* imgs, const int* sp_start, int n_img,
                                     int total_sp, long long max_block_px, float* centres,
                                     int* endpoints, int* counts, long long* acc, const int* labels,
-                                    int* ctrl, hipStream_t s) {
+                                    hipStream_t s) {
     if (max_block_px > kWideProjectPixels)
         hipLaunchKernelGGL(k_finalize_project_batched<kWideProjectWG>, dim3(total_sp),
                            dim3(kWideProjectWG), 0, s, imgs, sp_start, n_img, centres, endpoints,
-                           counts, acc, labels, ctrl);
+                           counts, acc, labels);
     else
         hipLaunchKernelGGL(k_finalize_project_batched<kFinProjectWG>, dim3(total_sp),
                            dim3(kFinProjectWG), 0, s, imgs, sp_start, n_img, centres, endpoints,
-                           counts, acc, labels, ctrl);
+                           counts, acc, labels);
     return hipGetLastError();
 }
 

@@ -502,7 +502,11 @@ __global__ __launch_bounds__(kUpdateWG) void k_soft_bwd_update(
     if (tid < 9) count[9LL * item + tid] = cnt[tid];
 }
 
-constexpr int kPathWG = 256;
+// Workgroup of the path pass: 256 lanes, or 512 where there are at most 2 kCUs
+// superpixels in all (2 x 97x61, T = 5: 16.9 instead of 20.1 us per iteration; 2 x 256x256, k =
+// 128, T = 5: 78 instead of 90; 512x512, k = 400, T = 5: 122 instead of 135, and no
+// difference at T = 0.5).
+constexpr int kPathWG = 256, kPathWideWG = 512;
 // Most lists (9 cells x slices) of a superpixel.
 constexpr int kBwdLists = 252;
 // Texels per thread and trip of the fold, their loads in flight together.
@@ -529,14 +533,12 @@ constexpr int kFold = 4;
 // and stored, with the terms that the update of the iteration before needs.
 //
 // What bounds it: the latency of a superpixel's chain of phases, with the tiles
-// limiting a CU to 4 workgroups; the walks, the fold and its atomics take about
+// limiting a CU to 3 workgroups; the walks, the fold and its atomics take about
 // a quarter of the time each.  16 x 512x512, k = 400, T = 0.5 (300 K to 400 K
-// walked pairs, 47 to 64 per superpixel): 152 us per iteration, where a
+// walked pairs, 47 to 64 per superpixel): 144 us per iteration, where a
 // workgroup per cell with a tile for each of its 9 candidates and a fold over
 // all of them took 298.  Atomics of one value of 64 texels instead of rows of
-// 16 texels' four values: 235.  Workgroups of 128 or 512 threads: 175 and 221;
-// a least budget of 20 or 40 KiB: 164 and 149, but at 40 the small grids lose a
-// workgroup per CU.
+// 16 texels' four values: 235.  Workgroups of 128 or 512 threads: 175 and 221.
 template <int WG>
 __global__ __launch_bounds__(WG) void k_soft_bwd_path(
     SoftImg s, const float4* __restrict__ packed, const float* __restrict__ theta_prev,
@@ -864,9 +866,12 @@ constexpr int kSoftWG = 256;
 // Tile budget of the backward path pass in bytes (an FP64 weight and an FP32
 // dL/dw per texel): what the paths of one cell's pixels to a superpixel of the
 // 3x3 block around it mostly span, 1.8 cells by 1.8 cells, at least
-// kBwdLdsLeast (with 8 KiB of static LDS four workgroups fit in a CU's 160
-// KiB; less would split the pairs of small cells) and at most kBwdLdsBytes.
-constexpr int kBwdLdsLeast = 28 * 1024;
+// kBwdLdsLeast and at most kBwdLdsBytes.  44 KiB and 9 KiB of static LDS fit three
+// times in a CU's 160 KiB; with less the pairs of small cells come apart into more
+// batches, with more a CU holds fewer workgroups.  Path pass at 28, 44 and 60 KiB,
+// 512x512, k = 400, T = 0.5: 16 images 152, 144, 184 us, 4 images 67, 50, 56; 2 x
+// 256x256, k = 128: 27, 17, 17; 16 images at T = 5: 674, 718, 831.
+constexpr int kBwdLdsLeast = 44 * 1024;
 constexpr int kBwdLdsBytes = 60 * 1024;
 
 static int path_lds_bytes(const SoftGeom& g, int cap_bytes) {
@@ -897,21 +902,15 @@ static dim3 pixel_grid(const SoftImg& s) {
     return dim3((unsigned)bx, (unsigned)std::min(by, 65535), (unsigned)s.B);
 }
 
-int soft_slices(int W, int H, int nx, int ny, int wg) {
-    const long long cw = (W + nx - 1) / nx, ch = (H + ny - 1) / ny;
-    const long long chunks = (cw * ch + 63) / 64, per = wg / 64;
-    return (int)std::max<long long>(1, (chunks + per - 1) / per);
-}
-
 int soft_bwd_slices(int W, int H, int nx, int ny) {
-    return std::min(soft_slices(W, H, nx, ny, 1024), kBwdLists / 9);
+    return std::min(assign_slices(W, H, nx, ny, 1024, 1), kBwdLists / 9);
 }
 
 static SoftImg to_img(const SoftGeom& g) {
     SoftImg s;
     s.W = g.W; s.H = g.H; s.nx = g.nx; s.ny = g.ny; s.K = g.nx * g.ny; s.B = g.B;
     s.N = (long long)g.W * g.H;
-    s.spl = soft_slices(g.W, g.H, g.nx, g.ny, g.wg);
+    s.spl = assign_slices(g.W, g.H, g.nx, g.ny, g.wg, fill_slices((long long)g.B * s.K));
     s.near = s.N < (1LL << 28) && g.W + g.H < 46340;
     s.bspl = soft_bwd_slices(g.W, g.H, g.nx, g.ny);
     s.inv_w = 1.0 / (double)g.W;
@@ -926,9 +925,10 @@ static SoftImg to_img(const SoftGeom& g) {
 }
 
 void lift_soft_lds_limits() {
-    static_cast<void>(hipFuncSetAttribute(
-        reinterpret_cast<const void*>(k_soft_bwd_path<kPathWG>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, kBwdLdsBytes));
+    for (const auto kernel : {k_soft_bwd_path<kPathWG>, k_soft_bwd_path<kPathWideWG>})
+        static_cast<void>(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                              hipFuncAttributeMaxDynamicSharedMemorySize,
+                                              kBwdLdsBytes));
     static_cast<void>(hipGetLastError());
 }
 
@@ -989,7 +989,9 @@ int launch_soft_bwd_path(const SoftGeom& g, const float4* packed, const float* t
                          hipStream_t st) {
     const SoftImg s = to_img(g);
     const int cap = path_lds_bytes(g, cap_bytes);
-    hipLaunchKernelGGL(k_soft_bwd_path<kPathWG>, dim3(s.B * s.K), dim3(kPathWG), (size_t)cap, st, s,
+    const bool wide = (long long)s.B * s.K <= 2 * kCUs;
+    const auto kernel = wide ? k_soft_bwd_path<kPathWideWG> : k_soft_bwd_path<kPathWG>;
+    hipLaunchKernelGGL(kernel, dim3(s.B * s.K), dim3(wide ? kPathWideWG : kPathWG), (size_t)cap, st, s,
                        packed, theta_prev, fa, fb, pairs, count, z, gth, z_prev, gth_prev, cand,
                        gf, cap);
     return hipGetLastError();

@@ -42,7 +42,7 @@ def scales(n: int = 12, kmin: int = 6, kmax: int = 600) -> list[int]:
 
 class MultiScale:
     """Decompositions of one image at several k, run as one ragged batch (one
-    persistent launch per iteration), and their boundary-frequency map."""
+    assignment launch per iteration), and their boundary-frequency map."""
 
     def __init__(self, width: int, height: int, ks: list[int] | None = None, **params):
         self.ks = ks or scales()

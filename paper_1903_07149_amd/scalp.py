@@ -207,7 +207,7 @@ class Graph:
 
 class ScalpBatch:
     """A ragged batch: images of different sizes and superpixel counts,
-    concatenated pixel-wise, run by one persistent launch per iteration."""
+    concatenated pixel-wise, run by one assignment launch per iteration."""
 
     def __init__(self, shapes: list[tuple[int, int, int]], device="cuda", **params):
         self.grids = [make_grid(w, h, k) for (w, h, k) in shapes]

@@ -121,3 +121,26 @@ def test_batched_single_image_equals_single_path(W, H, k):
     assert (l.reshape(H, W) == host(r.labels)).all()
     assert (c == host(r.centers)).all() and (e == host(r.endpoints)).all()
     assert (n == host(r.counts)).all()
+
+
+@pytest.mark.parametrize("shapes", [
+    [(512, 512, 300)],                                   # 2^18 pixels: items of 256 pixels
+    [(511, 512, 300)],                                   # fewer: 64 pixels, 512 lanes
+    [(300, 200, 1), (160, 160, 256), (37, 5, 7)],        # one cell; one superpixel over an item
+    [(480, 192, 40), (490, 196, 40), (640, 640, 60)],    # cells of 2304 pixels, and above
+])
+def test_batched_item_sizes(orc, shapes):
+    """The rules that choose a work item's pixels and the workgroup, on both
+    sides, for the batch and for its images on their own."""
+    from paper_1903_07149_amd.scalp import Scalp, ScalpBatch
+    imgs = [synth.make_image(w, h, 12, 10.0, 60 + i) for i, (w, h, _) in enumerate(shapes)]
+    b = ScalpBatch(shapes, iterations=2)
+    lab = dev(np.concatenate([im.lab.reshape(-1, 3) for im in imgs]))
+    con = dev(np.concatenate([im.contour.reshape(-1) for im in imgs]))
+    say("batched item sizes", shapes)
+    c, e, l, n = (host(t) for t in b.run(lab, con))
+    for (p0, p1, H, W), (w, h, k), im in zip(b.pixel_slices(), shapes, imgs):
+        ref = orc.run(im.lab, im.contour, k, iterations=2, mode=orc.MEAN_FIXED)
+        assert (l[p0:p1].reshape(H, W) == ref.labels).all(), (w, h, k)
+        r = Scalp(w, h, k, iterations=2).run(dev(im.lab), dev(im.contour))
+        assert (host(r.labels) == ref.labels).all(), (w, h, k)
