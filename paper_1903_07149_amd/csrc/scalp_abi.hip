@@ -101,6 +101,11 @@ Img img_of(const scalp_grid_t* g, const scalp_params_t* p, long long pix, int sp
     return im;
 }
 
+// A single image, in a launch of its own.
+Img image_of(const scalp_grid_t* g, const scalp_params_t* p) {
+    return img_of(g, p, 0, 0, slices_of(g, p));
+}
+
 // Single-image workspace: [packed float4 N][acc int64 8K][ctrl int32 64][plist int32 K]
 // [the window form's tile lists, 8 N]
 struct Layout {
@@ -327,7 +332,7 @@ int scalp_init_grid(const scalp_grid_t* g, const scalp_params_t* p, const float*
     const Views v = views_of(ws, L);
     if (!p->reuse_prepared) CHECK_HIP(enq_prepare(g, p, lab, contour, v, s));
     // counts are not an output of this call: the projection list area holds them
-    CHECK_HIP(enq_init(img_of(g, p, 0, 0, slices_of(g, p)), v, centers, endpoints, v.plist, labels, s));
+    CHECK_HIP(enq_init(image_of(g, p), v, centers, endpoints, v.plist, labels, s));
     return SCALP_OK;
 }
 
@@ -344,11 +349,11 @@ int scalp_assign(const scalp_grid_t* g, const scalp_params_t* p, const float* la
     if (p->assign_mode == SCALP_ASSIGN_WINDOW) {
         CHECK_HIP(launch_clear(static_cast<long long*>(v.lists),
                                window_count_words(g->width, g->height), s));
-        CHECK_HIP(launch_assign_window(img_of(g, p, 0, 0, slices_of(g, p)), v.packed, centers, endpoints, labels,
+        CHECK_HIP(launch_assign_window(image_of(g, p), v.packed, centers, endpoints, labels,
                                        v.acc, v.ctrl, v.lists, window_radius(g), p->lambda, false,
                                        false, s));
     } else
-        CHECK_HIP(launch_assign(img_of(g, p, 0, 0, slices_of(g, p)), v.packed, centers, endpoints, labels, v.acc,
+        CHECK_HIP(launch_assign(image_of(g, p), v.packed, centers, endpoints, labels, v.acc,
                                 v.ctrl, p->lambda, false, tuning_of(p), s));
     return SCALP_OK;
 }
@@ -362,7 +367,7 @@ int scalp_update(const scalp_grid_t* g, const scalp_params_t* p, const float* la
     const hipStream_t s = (hipStream_t)stream;
     const Layout L = layout_of((long long)g->width * g->height, g->num_sp);
     const Views v = views_of(ws, L);
-    const Img im = img_of(g, p, 0, 0, slices_of(g, p));
+    const Img im = image_of(g, p);
     CHECK_HIP(launch_clear(v.acc, clear_words(L), s));
     CHECK_HIP(launch_accumulate(im, lab, labels, v.acc, s));
     CHECK_HIP(launch_finalize(im, centers, endpoints, counts, v.acc, labels, v.ctrl, v.plist,
@@ -381,10 +386,10 @@ int scalp_assign_accumulate(const scalp_grid_t* g, const scalp_params_t* p, cons
     const Layout L = layout_of((long long)g->width * g->height, g->num_sp);
     const Views v = views_of(ws, L);
     if (p->assign_mode == SCALP_ASSIGN_WINDOW)
-        CHECK_HIP(enq_window_pass(img_of(g, p, 0, 0, slices_of(g, p)), p, v, window_radius(g), centers, endpoints,
+        CHECK_HIP(enq_window_pass(image_of(g, p), p, v, window_radius(g), centers, endpoints,
                                   labels, true, false, (hipStream_t)stream));
     else
-        CHECK_HIP(launch_assign(img_of(g, p, 0, 0, slices_of(g, p)), v.packed, centers, endpoints, labels, v.acc,
+        CHECK_HIP(launch_assign(image_of(g, p), v.packed, centers, endpoints, labels, v.acc,
                                 v.ctrl, p->lambda, true, tuning_of(p), (hipStream_t)stream));
     return SCALP_OK;
 }
@@ -397,7 +402,7 @@ int scalp_finalize(const scalp_grid_t* g, const scalp_params_t* p, const int32_t
     if (!labels || !centers || !endpoints || !counts) return SCALP_ERR_ARG;
     const hipStream_t s = (hipStream_t)stream;
     const Views v = views_of(ws, layout_of((long long)g->width * g->height, g->num_sp));
-    const Img im = img_of(g, p, 0, 0, slices_of(g, p));
+    const Img im = image_of(g, p);
     CHECK_HIP(launch_finalize(im, centers, endpoints, counts, v.acc, labels, v.ctrl, v.plist,
                               p->project != 0, s));
     if (p->project)
@@ -415,7 +420,7 @@ int scalp_run(const scalp_grid_t* g, const scalp_params_t* p, const float* lab,
     const hipStream_t s = (hipStream_t)stream;
     const Layout L = layout_of((long long)g->width * g->height, g->num_sp);
     const Views v = views_of(ws, L);
-    const Img im = img_of(g, p, 0, 0, slices_of(g, p));
+    const Img im = image_of(g, p);
     if (!p->reuse_prepared) CHECK_HIP(enq_prepare(g, p, lab, contour, v, s));
     CHECK_HIP(enq_init(im, v, centers, endpoints, counts, labels, s));
     CHECK_HIP(enq_iterations(im, p, v, centers, endpoints, labels, counts, s, window_radius(g)));
@@ -444,7 +449,7 @@ int scalp_graph_create(const scalp_grid_t* g, const scalp_params_t* p, float* ce
     if (!centers || !endpoints || !labels || !counts || !out) return SCALP_ERR_ARG;
     const Layout L = layout_of((long long)g->width * g->height, g->num_sp);
     const Views v = views_of(ws, L);
-    const Img im = img_of(g, p, 0, 0, slices_of(g, p));
+    const Img im = image_of(g, p);
     const scalp_params_t pc = *p;
     const int R = window_radius(g);
     return capture(out, [&](hipStream_t s) {
@@ -553,7 +558,8 @@ int enq_batched(const scalp_batch_desc_t* d, int n, const scalp_params_t* p, con
             e = launch_prepare(BL.N, lab, contour, p->sigma, v.packed, s);
         }
     }
-    if (e == hipSuccess) e = launch_init_cells_batched(imgs, starts, n, (int)BL.K, v.packed, labels, v.acc, s);
+    if (e == hipSuccess)
+        e = launch_init_cells_batched(imgs, starts, n, (int)BL.K, v.packed, labels, v.acc, s);
     if (e == hipSuccess)
         e = launch_finalize_batched(imgs, starts, n, (int)BL.K, centers, endpoints, counts, v.acc,
                                     labels, v.ctrl, v.plist, false, s);
@@ -714,7 +720,7 @@ int scalp_soft_forward(const scalp_grid_t* g, const scalp_params_t* p, float tem
     const hipStream_t s = (hipStream_t)stream;
     const long long N = (long long)g->width * g->height, K = g->num_sp, B = batch;
     const int T = p->iterations;
-    const Img im = img_of(g, p, 0, 0, slices_of(g, p));
+    const Img im = image_of(g, p);
     const SoftGeom geo = soft_geom(g->width, g->height, g->nx, g->ny, batch, im.spw, im.gamma,
                                    p->lambda, temperature, soft_wg(g, p, batch),
                                    p->exact_pruning);
@@ -757,7 +763,7 @@ int scalp_soft_backward(const scalp_grid_t* g, const scalp_params_t* p, float te
     const hipStream_t s = (hipStream_t)stream;
     const long long N = (long long)g->width * g->height, K = g->num_sp, B = batch;
     const int T = p->iterations;
-    const Img im = img_of(g, p, 0, 0, slices_of(g, p));
+    const Img im = image_of(g, p);
     const SoftGeom geo = soft_geom(g->width, g->height, g->nx, g->ny, batch, im.spw, im.gamma,
                                    p->lambda, temperature, soft_wg(g, p, batch),
                                    p->exact_pruning);

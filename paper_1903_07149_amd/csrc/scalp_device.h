@@ -50,11 +50,11 @@ __device__ __forceinline__ long long to_fixed(float v) {
 // index `idx` toward (dx, dy): on major-axis step i the minor offset is
 // floor((2 i |d_minor| + n) / (2 n)).  stepx / stepy are the index strides
 // of one pixel in x / y.  For paths of any length, by 64-bit indexes (walk_near
-// takes the others); samples are accumulated in path order, with up to three texel loads in flight.  Paths of up to 46340
-// steps count the minor steps as the carries of a 32-bit accumulator (exact
-// there, see step_increment); longer ones (cells over ~15000 pixels wide, or
-// caller-supplied endpoints far across a wide image) keep the remainder
-// exactly.
+// takes the others); samples are accumulated in path order, with up to three
+// texel loads in flight.  Paths of up to 46340 steps count the minor steps as the
+// carries of a 32-bit accumulator (exact there, see step_increment); longer ones
+// (cells over ~15000 pixels wide, or caller-supplied endpoints far across a wide
+// image) keep the remainder exactly.
 __device__ __forceinline__ unsigned step_increment(int am, int n);
 
 __device__ __forceinline__ void walk_path(const float4* __restrict__ base, int idx, int stepx,
@@ -359,7 +359,7 @@ __device__ __forceinline__ int round_coord(float v, int hi) {
 
 // Workgroup index -> work item.  Workgroups are dispatched round-robin over
 // the 8 XCDs; give each XCD a contiguous run of items so that neighbouring
-// cells, which read overlapping table rectangles, share an L2.
+// cells, whose paths overlap, share an L2.
 __device__ __forceinline__ int xcd_remap(int b, int G) {
     const int q = G >> 3, rem = G & 7;
     const int x = b & 7, slot = b >> 3;

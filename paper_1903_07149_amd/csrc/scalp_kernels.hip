@@ -100,9 +100,9 @@ __device__ __forceinline__ int slice_chunk(int chunks, int i, const Img& im) {
 // its evaluation 150, the second pass 200), 0.93 issued per CU-clock; 0.069
 // ms per launch.  (The settling is one piece of code for all pixels: settled in
 // the first pass where nothing was listed, it ran twice in most waves, 1.6 % of
-// this launch and 3 % of the 64-image batch.)  Tables of (d_c, w) per candidate in LDS, all nine taken in
-// turn by the whole workgroup behind a barrier each, made a sample cost 5
-// instructions instead of 13 but walked 85 samples per pixel in 64-lane slots
+// this launch and 3 % of the 64-image batch.)  Tables of (d_c, w) per candidate in
+// LDS, all nine taken in turn by the whole workgroup behind a barrier each, made a
+// sample cost 5 instructions instead of 13 but walked 85 samples per pixel in 64-lane slots
 // instead of 33, filled 20 table entries per pixel and waited at the barriers:
 // 51.5 M instructions, 0.72 per CU-clock, 0.117 ms.  The texels are read
 // through L1 and L2: a box of them staged in LDS per item left two items per
@@ -257,12 +257,10 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
 }
 
 template <int WG, bool ACCUM, bool NEAR>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_assign(Img im, const float4* __restrict__ packed,
-                                               const float* __restrict__ centres,
-                                               const int* __restrict__ endpoints,
-                                               int* __restrict__ labels,
-                                               long long* __restrict__ acc, int* ctrl,
-                                               float lambda) {
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_assign(
+    Img im, const float4* __restrict__ packed, const float* __restrict__ centres,
+    const int* __restrict__ endpoints, int* __restrict__ labels, long long* __restrict__ acc, int* ctrl,
+    float lambda) {
     __shared__ ItemShared<WG> sh;
     if (ACCUM && blockIdx.x == 0 && threadIdx.x == 0) ctrl[kCtrlProjCount] = 0;
     const int item = xcd_remap(blockIdx.x, gridDim.x);
@@ -945,9 +943,9 @@ __device__ void project_at(const Img& im, int k, float xk, float yk, int count,
     }
     if (!done) {                                   // uniform: reduced over the workgroup
         const int ci = k / im.nx, cj = k - ci * im.nx;
-        scan_region<WG>(lb, W, k, cell_lo(max(cj - 1, 0), W, im.nx), cell_lo(min(cj + 2, im.nx), W, im.nx),
-                        cell_lo(max(ci - 1, 0), H, im.ny), cell_lo(min(ci + 2, im.ny), H, im.ny), xk, yk,
-                        best, found);
+        scan_region<WG>(lb, W, k, cell_lo(max(cj - 1, 0), W, im.nx),
+                        cell_lo(min(cj + 2, im.nx), W, im.nx), cell_lo(max(ci - 1, 0), H, im.ny),
+                        cell_lo(min(ci + 2, im.ny), H, im.ny), xk, yk, best, found);
         if (found < count) {
             const int h = 2 * im.rad + 2;
             scan_region<WG>(lb, W, k, max(cx - h, 0), min(cx + h + 1, W), max(cy - h, 0),
@@ -1157,9 +1155,10 @@ int launch_assign_batched(const Img* imgs, const int* item_start, int n_img, int
                           const float4* packed, const float* centres, const int* endpoints,
                           int* labels, long long* acc, int* ctrl, float lambda, const Tuning& t,
                           bool near, hipStream_t s) {
-    const auto kernel = t.wg == 1024  ? near ? k_assign_batched<1024, true> : k_assign_batched<1024, false>
-                        : t.wg == 512 ? near ? k_assign_batched<512, true> : k_assign_batched<512, false>
-                                      : near ? k_assign_batched<256, true> : k_assign_batched<256, false>;
+    const auto kernel =
+        t.wg == 1024  ? near ? k_assign_batched<1024, true> : k_assign_batched<1024, false>
+        : t.wg == 512 ? near ? k_assign_batched<512, true> : k_assign_batched<512, false>
+                      : near ? k_assign_batched<256, true> : k_assign_batched<256, false>;
     // (a launch holds below 2^32 lanes)
     for (int h0 = 0; h0 < longest_run; h0 += 1 << 18) {
         const unsigned n = (unsigned)std::min(longest_run - h0, 1 << 18);
