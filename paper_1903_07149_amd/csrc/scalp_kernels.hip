@@ -95,20 +95,21 @@ __device__ __forceinline__ int slice_chunk(int chunks, int i, const Img& im) {
 // registers more (62 instead of 52; with the batch's tables it spilled) and took 1 to 2 %
 // longer.
 //
-// What bounds it: VALU issue.  33.4 M wave instructions per launch at
-// 1920x1080, k = 2000 (the bounds 180 of a wave's 1023, the first walk 300,
-// its evaluation 150, the second pass 200), 0.93 issued per CU-clock; 0.069
-// ms per launch.  (The settling is one piece of code for all pixels: settled in
-// the first pass where nothing was listed, it ran twice in most waves, 1.6 % of
+// What bounds it: VALU issue.  32.3 M wave instructions per launch at
+// 1920x1080, k = 2000 (the bounds 180 of a wave's 990, the first walk 300,
+// its evaluation 150, the second pass 200), 0.93 issued per clock in which a CU has
+// work and 0.71 per CU-clock of the whole launch, its start and end included;
+// 0.069 ms per launch.  (The settling is one piece of code for all pixels: settled
+// in the first pass where nothing was listed, it ran twice in most waves, 1.6 % of
 // this launch and 3 % of the 64-image batch.)  Tables of (d_c, w) per candidate in
 // LDS, all nine taken in turn by the whole workgroup behind a barrier each, made a
-// sample cost 5 instructions instead of 13 but walked 85 samples per pixel in 64-lane slots
-// instead of 33, filled 20 table entries per pixel and waited at the barriers:
-// 51.5 M instructions, 0.72 per CU-clock, 0.117 ms.  The texels are read
-// through L1 and L2: a box of them staged in LDS per item left two items per
-// CU and was slower (0.132 ms against 0.105 with the rest equal), as was a
-// counting sort of the first walks by length (18 instead of 23 slots per
-// pixel, but 100 more instructions and two more barriers).
+// sample cost 5 instructions instead of 13 but walked 85 samples per pixel in
+// 64-lane slots instead of 33, filled 20 table entries per pixel and waited at the
+// barriers: 51.5 M instructions, 0.72 per CU-clock of the launch, 0.117 ms.  The
+// texels are read through L1 and L2: a box of them staged in LDS per item left two
+// items per CU and was slower (0.132 ms against 0.105 with the rest equal), as was a
+// counting sort of the first walks by length (18 instead of 23 slots per pixel, but
+// 100 more instructions and two more barriers).
 template <int WG, bool ACCUM, bool NEAR>
 __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int slice,
                                              const float4* __restrict__ packed,
