@@ -389,6 +389,10 @@ __device__ __forceinline__ float win_threshold(unsigned long long win) {
 // (pixel, candidate) pairs whose bound does not exceed that D.  More than kWinBatch
 // candidates are taken in batches against the smallest D so far; a tile whose list
 // overflowed, and every tile without lists, tests all clusters, kWinWG at a time.
+// TILE is kWinTile, or 8 for the smallest images, where a tile of 16 would leave
+// most of the chip without work (the lanes without a pixel test clusters and walk
+// pairs): 97x61, k = 30, 10
+// iterations 159 us with tiles of 16, 145 with 8.
 // With ACCUM the update's sums go through bins per candidate of the tile (to global
 // memory directly for pixels that no window contains, and for winners of an earlier
 // turn of an overflowed list).
@@ -400,7 +404,7 @@ __device__ __forceinline__ float win_threshold(unsigned long long win) {
 // another 17.  One kernel for NEAR and not took 77 (the walks by 64-bit indexes made
 // it spill), all keys of a batch in registers instead of the four smallest 95, and
 // 72 at 7 waves per SIMD.
-template <bool ACCUM, bool NEAR>
+template <bool ACCUM, bool NEAR, int TILE>
 __global__ __launch_bounds__(kWinWG) __attribute__((amdgpu_waves_per_eu(8))) void k_assign_window(
     Img im, const float4* __restrict__ packed, const float* __restrict__ centres,
     const int* __restrict__ endpoints, int* __restrict__ labels, long long* __restrict__ acc,
@@ -446,10 +450,10 @@ __global__ __launch_bounds__(kWinWG) __attribute__((amdgpu_waves_per_eu(8))) voi
 
     const int tile = tile0 + xcd_remap(blockIdx.x, gridDim.x);
     const int ty = tile / wl.tx;
-    const int x0 = (tile - ty * wl.tx) * kWinTile, y0 = ty * kWinTile;
-    const int x1 = min(x0 + kWinTile, W) - 1, y1 = min(y0 + kWinTile, H) - 1;
+    const int x0 = (tile - ty * wl.tx) * TILE, y0 = ty * TILE;
+    const int x1 = min(x0 + TILE, W) - 1, y1 = min(y0 + TILE, H) - 1;
     const int px = x0 + pixel_x(tid), py = y0 + pixel_y(tid);
-    const bool mine = px < W && py < H;
+    const bool mine = tid < TILE * TILE && px < W && py < H;
 
     auto distance = [&](int j, float4 f, int qx, int qy, bool on, float thr) -> float {
         const float4 c0 = sh.cand[j][0], c1 = sh.cand[j][1];
@@ -1174,7 +1178,7 @@ int launch_assign_batched(const Img* imgs, const int* item_start, int n_img, int
 //
 // No lists (count null) for up to kWinWG clusters: every tile tests them all in one
 // turn, which takes no longer than reading a list does, and nothing has to make them
-// (97x61, 30 clusters: 165 us for 10 iterations, with lists 172).
+// (97x61, 30 clusters, 10 iterations: 172 us with lists, 165 without).
 static WinLists win_lists(const Img& im, void* mem) {
     WinLists wl = {};
     wl.tx = (im.W + kWinTile - 1) / kWinTile;
@@ -1194,16 +1198,27 @@ long long window_count_words(int W, int H) {
 int launch_assign_window(const Img& im, const float4* packed, const float* centres,
                          const int* endpoints, int* labels, long long* acc, int* ctrl, void* lists,
                          int R, float lambda, bool accumulate, bool listed, hipStream_t s) {
-    const WinLists wl = win_lists(im, lists);
-    const int K = im.nx * im.ny, tiles = wl.tiles;
+    WinLists wl = win_lists(im, lists);
+    const int K = im.nx * im.ny;
     const bool near = near_image(im);
     if (wl.count && !listed)
         hipLaunchKernelGGL(k_window_lists, dim3((K + 3) / 4), dim3(256), 0, s, im, centres, R, wl);
+    // tiles of 8 x 8 where they still number no more than the compute units
+    const bool small = !wl.count && 4 * wl.tiles <= kCUs;
+    if (small) {
+        wl.tx = (im.W + 7) / 8;
+        wl.tiles = wl.tx * ((im.H + 7) / 8);
+    }
+    const int tiles = wl.tiles;
     // at most 2^22 workgroups a launch (an image one pixel high may have 2^27 tiles)
     for (int t0 = 0; t0 < tiles; t0 += 1 << 22) {
         const dim3 grid((unsigned)std::min(tiles - t0, 1 << 22));
-        const auto kernel = accumulate ? near ? k_assign_window<true, true> : k_assign_window<true, false>
-                            : near ? k_assign_window<false, true> : k_assign_window<false, false>;
+        const auto kernel =
+            small        ? accumulate ? near ? k_assign_window<true, true, 8> : k_assign_window<true, false, 8>
+                           : near ? k_assign_window<false, true, 8> : k_assign_window<false, false, 8>
+            : accumulate ? near ? k_assign_window<true, true, kWinTile> : k_assign_window<true, false, kWinTile>
+                         : near ? k_assign_window<false, true, kWinTile>
+                                : k_assign_window<false, false, kWinTile>;
         hipLaunchKernelGGL(kernel, grid, dim3(kWinWG), 0, s, im, packed, centres, endpoints, labels,
                            acc, ctrl, wl, R, lambda, t0);
     }
