@@ -78,11 +78,12 @@ constexpr int kCUs = 256;
 // Pixels of a work item of a hard assignment by workgroups of wg lanes.  Where
 // paths are long (cells above 48 x 48 pixels) a pixel has several pairs in the
 // second pass: items of half a workgroup's pixels halve its rounds, and end more
-// evenly.  12 scales of 481x321 (k = 6 to 600): 199 us per iteration, 234 with 256
-// pixels in all items, 213 with 64 in cells above 96 x 96.  (Beyond 2^30 pixels a
-// launch of a workgroup per item would have too many lanes.)
+// evenly.  12 scales of 481x321 (k = 6 to 600), 256 lanes: 199 us per iteration, 234
+// with 256 pixels in all items, 213 with 64 in cells above 96 x 96.  Such a launch has
+// about 2 W H lanes, whatever wg is, and a launch holds below 2^32: beyond 2^30
+// pixels the items are not shortened.
 inline int item_pixels(long long W, long long H, long long K, int wg) {
-    return W * H > 2304 * K && W * H <= 1LL << 30 ? std::min(wg, 128) : wg;
+    return W * H > 2304 * K && W * H <= 1LL << 30 ? wg / 2 : wg;
 }
 
 // Items per cell: so many that no item has more than `pixels` pixels, and at least
