@@ -510,7 +510,6 @@ int enq_batched(const scalp_batch_desc_t* d, int n, const scalp_params_t* p, con
                 const float* contour, float* centers, int* endpoints, int* labels, int* counts,
                 void* ws, const BatchLayout& BL, hipStream_t s) {
     const Tuning t = tuning_of(p);
-    const bool few = BL.N < kFewPixels;
     const Views v = views_of(ws, BL.base);
     char* b = static_cast<char*>(ws);
     Img* imgs = reinterpret_cast<Img*>(b + BL.imgs);
@@ -522,8 +521,8 @@ int enq_batched(const scalp_batch_desc_t* d, int n, const scalp_params_t* p, con
     for (int i = 0; i < n; ++i) {
         const scalp_grid_t& g = d[i].grid;
         // (items_total is below 2^31; smaller items only where they cannot pass it)
-        const int pixels = few ? 64 : BL.items_total < 1LL << 29
-                                     ? item_pixels(g.width, g.height, g.num_sp, t.wg) : t.wg;
+        const int pixels = BL.items_total < 1LL << 29
+                               ? batch_item_pixels(BL.N, g.width, g.height, g.num_sp, t.wg) : t.wg;
         himg[(size_t)i] = img_of(&g, p, d[i].pix_offset, d[i].sp_offset,
                                  assign_slices(g.width, g.height, g.nx, g.ny, pixels, 1));
         hstart[(size_t)i] = d[i].sp_offset;

@@ -101,11 +101,18 @@ inline int assign_slices(int W, int H, int nx, int ny, int pixels, long long fil
 // (481x321, 250 cells in 3 items: 14.0 us, in 4: 14.6).
 inline long long fill_slices(long long cells) { return kCUs / cells; }
 
-// A batch of fewer pixels than this, half the lanes that the chip holds, takes 64
-// pixels an item: 7 scales of 189x117 (0.15 M pixels) 32 us per iteration with 128
-// or 256, 26 with 64; 3 images of up to 480 pixels a side, 250 pixels a superpixel,
-// 22.8 and 21.5.  (12 scales of 481x321, 1.9 M: 207 us as they are, 256 with 64.)
+// Pixels of a work item of a batch of N pixels, for its image of W x H pixels and K
+// cells.  A batch of fewer pixels than half the lanes that the chip holds takes a
+// quarter of a workgroup's: 7 scales of 189x117 (0.15 M pixels) 32 us per iteration
+// with 128 or 256 of 256 lanes, 26 with 64; 3 images of up to 480 pixels a side, 250
+// pixels a superpixel, 22.8 and 21.5.  (12 scales of 481x321, 1.9 M: 207 us as they
+// are, 256 with 64.)  Workgroups of 1024 lanes with 64 pixels each left 15 lanes of
+// 16 idle: the same 3 images 52.3 us per iteration at 1024 lanes, 34.4 with 256 pixels.
 constexpr long long kFewPixels = 1 << 18;
+
+inline int batch_item_pixels(long long N, long long W, long long H, long long K, int wg) {
+    return N < kFewPixels ? wg / 4 : item_pixels(W, H, K, wg);
+}
 
 struct Tuning {
     int wg;           // workgroup size of the assignment kernel (256, 512 or 1024)

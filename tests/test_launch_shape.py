@@ -19,8 +19,10 @@ int main() {
     int wg;
     while (scanf("%lld %lld %lld %lld %d", &W, &H, &nx, &ny, &wg) == 5) {
         const int px = item_pixels(W, H, nx * ny, wg);
-        printf("%d %d\n", px, assign_slices((int)W, (int)H, (int)nx, (int)ny, px,
-                                            fill_slices(nx * ny)));
+        const int bpx = batch_item_pixels(W * H, W, H, nx * ny, wg);
+        printf("%d %d %d %d\n", px, assign_slices((int)W, (int)H, (int)nx, (int)ny, px,
+                                                  fill_slices(nx * ny)),
+               bpx, assign_slices((int)W, (int)H, (int)nx, (int)ny, bpx, 1));
     }
 }
 """
@@ -62,7 +64,7 @@ def test_large_cells_stay_below_a_launch(shapes, wg):
             if W * H > 2304 * nx * ny:
                 rows.append((W, H, nx, ny, wg))
     assert len(rows) > 30
-    for (W, H, nx, ny, _), (px, spl) in zip(rows, shapes(rows)):
+    for (W, H, nx, ny, _), (px, spl, *_) in zip(rows, shapes(rows)):
         assert nx * ny * spl * wg < 1 << 32, (W, H, nx, ny, px, spl)
 
 
@@ -74,9 +76,24 @@ def test_items_cover_their_cells(shapes, wg):
         W, H = (int(np.exp(v)) for v in rng.uniform(0, np.log(9000), 2))
         rows.append((W, H, *_grid(W, H, int(rng.integers(1, W * H + 1))), wg))
         rows.append((W, H, *_grid(W, H, max(1, int(W * H / rng.uniform(1, 20000)))), wg))
-    for (W, H, nx, ny, _), (px, spl) in zip(rows, shapes(rows)):
+    for (W, H, nx, ny, _), (px, spl, *_) in zip(rows, shapes(rows)):
         assert 64 <= px <= wg and px % 64 == 0
         chunks = -(-(-(-W // nx) * -(-H // ny)) // 64)      # of the largest cell
         assert 1 <= spl <= chunks
         # chunks split evenly over the slices: none has more than px pixels, nor than the lanes
         assert -(-chunks // spl) * 64 <= px, (W, H, nx, ny, px, spl)
+
+
+@pytest.mark.parametrize("wg", [256, 512, 1024])
+def test_items_of_small_batches_grow_with_the_workgroup(shapes, wg):
+    """At least a quarter of a workgroup's lanes have a pixel where the cells have
+    that many, and no item has more pixels than lanes."""
+    rng = np.random.default_rng(wg)
+    rows = []
+    for _ in range(300):
+        W, H = (int(v) for v in rng.integers(16, 900, 2))
+        rows.append((W, H, *_grid(W, H, max(1, int(W * H / rng.uniform(1, 20000)))), wg))
+    for (W, H, nx, ny, _), (_, _, px, spl) in zip(rows, shapes(rows)):
+        assert wg // 4 <= px <= wg, (W, H, nx, ny, px)
+        chunks = -(-(-(-W // nx) * -(-H // ny)) // 64)
+        assert -(-chunks // spl) * 64 <= px
