@@ -212,8 +212,8 @@ __device__ __forceinline__ bool cut_now(const Cut& c, float sc, float sw) {
 }
 
 // Samples i = 1 .. n (the endpoint) of the path s over the packed image, at
-// 32-bit byte offsets from a uniform base (images of up to 2^28 pixels, paths
-// of up to 46340 steps), from the texel at `off`: 13 VALU instructions per
+// 32-bit byte offsets from a uniform base (Eqs.near_img; paths of up to 46340
+// steps), from the texel at `off`: 13 VALU instructions per
 // sample, of which 8 are the colour distance.  Four samples per trip, their
 // loads in flight together.  A walk that is cut returns an infinite sc.
 __device__ __forceinline__ void walk_near(const float4* __restrict__ img, unsigned off,
@@ -302,10 +302,42 @@ __device__ __forceinline__ void div_path_len(float a, float b, int n, double inv
 struct Eqs {
     const float4* img;     // packed texels
     int W;
-    bool near;             // 32-bit byte offsets reach every texel, and every path is below
-                           // 46340 steps
+    bool near;             // 32-bit byte offsets from near_img reach every texel of a path,
+                           // and every path is below 46340 steps
+    const float4* near_img;   // the texel of pixel (near_x, near_y)
+    int near_x, near_y;
     float lambda, oml, gamma, spw;
 };
+
+// The near walk's fields for an image that it serves as a whole.
+__device__ __forceinline__ void near_all(Eqs& q) {
+    q.near = true;
+    q.near_img = q.img;
+    q.near_x = q.near_y = 0;
+}
+
+// The box of a work item's pixels and path endpoints, which holds its paths, too.
+struct Box {
+    int x0, y0, x1, y1;    // inclusive
+    __device__ __forceinline__ void add(int x, int y) {
+        x0 = min(x0, x);
+        y0 = min(y0, y);
+        x1 = max(x1, x);
+        y1 = max(y1, y);
+    }
+};
+
+// Whether the near walk serves the paths of a box (uniform), from its corner: in an
+// image of 2^28 pixels and more, or of W + H >= 46340, nearly every item's.  10
+// iterations of 60000x400, k = 24000: 18.3 ms, 40.6 by walk_path alone; 18.0 of
+// 40000x600, which is near as a whole.
+__device__ __forceinline__ void near_box(Eqs& q, const Box& b) {
+    const int w = b.x1 - b.x0, h = b.y1 - b.y0;
+    q.near = w < 46340 && h < 46340 && (long long)h * q.W + w < 1LL << 28;
+    q.near_img = q.img + ((long long)b.y0 * q.W + b.x0);
+    q.near_x = b.x0;
+    q.near_y = b.y0;
+}
 
 // D of Eq. (3) of pixel (px, py), whose texel is fp, to the cluster at ck =
 // (l, a, b, x, y) with endpoint (cx, cy), and its factors A, B of Eqs.
@@ -317,7 +349,6 @@ __device__ __forceinline__ float path_distance(const Eqs& q, const float (&ck)[5
                                                float thr, float& A, float& B) {
     const float l = ck[0], a = ck[1], b = ck[2];
     const float ax = (float)px - ck[3], ay = (float)py - ck[4];
-    const int p = py * q.W + px;
     const int dx = cx - px, dy = cy - py;
     const int n = max(abs(dx), abs(dy));
     const double inv = path_recip(n);
@@ -335,9 +366,11 @@ __device__ __forceinline__ float path_distance(const Eqs& q, const float (&ck)[5
             cut.dsp = dsp;
             cut.thr = thr;
         }
-        walk_near(q.img, 16u * (unsigned)p, path_step(dx, dy, 16, 16 * q.W), l, a, b, cut, sc, sw);
+        const unsigned row = 16u * (unsigned)q.W;
+        walk_near(q.near_img, row * (unsigned)(py - q.near_y) + 16u * (unsigned)(px - q.near_x),
+                  path_step(dx, dy, 16, (int)row), l, a, b, cut, sc, sw);
     } else {
-        walk_path(q.img, p, 1, q.W, dx, dy, l, a, b, sc, sw);
+        walk_path(q.img, py * q.W + px, 1, q.W, dx, dy, l, a, b, sc, sw);
         if (n > 0) {                               // sample i = n is the endpoint
             const float4 fc = q.img[(long long)cy * q.W + cx];
             sc = sc + colour_dist(fc, l, a, b);

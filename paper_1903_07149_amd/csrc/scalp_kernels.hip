@@ -91,8 +91,8 @@ __device__ __forceinline__ int slice_chunk(int chunks, int i, const Img& im) {
 // minimum per pixel.  A walk of that second pass stops as soon as its partial
 // sums prove that D exceeds the pixel's first one (Cut).
 //
-// NEAR (near_image): the walks by 32-bit indexes.  A kernel with both needs 10
-// registers more (62 instead of 52; with the batch's tables it spilled) and took 1 to 2 %
+// NEAR (near_image): the walks by 32-bit indexes alone.  The other kernels choose per
+// item (near_box); both walks in one kernel need 10 registers more and took 1 to 2 %
 // longer.
 //
 // What bounds it: VALU issue.  32.3 M wave instructions per launch at
@@ -139,7 +139,17 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
     Eqs eqs;
     eqs.img = img;
     eqs.W = W;
-    eqs.near = NEAR;
+    near_all(eqs);
+    if (!NEAR) {
+        // (of the whole cell; endpoints outside the image are clamped into it)
+        Box box = {x0, y0, x1 - 1, y1 - 1};
+        const ConstI ce = (ConstI)(uintptr_t)end;
+        for (int j = 0; j < 9; ++j) {
+            const int k = nb.row[j / 3] + nb.col[j % 3];
+            box.add(min(max(ce[2 * k], 0), W - 1), min(max(ce[2 * k + 1], 0), H - 1));
+        }
+        near_box(eqs, box);
+    }
     eqs.lambda = lambda;
     eqs.oml = 1.0f - lambda;
     eqs.gamma = im.gamma;
@@ -416,7 +426,7 @@ __global__ __launch_bounds__(kWinWG) __attribute__((amdgpu_waves_per_eu(8))) voi
     Eqs eqs;
     eqs.img = packed;
     eqs.W = W;
-    eqs.near = NEAR;
+    near_all(eqs);
     eqs.lambda = lambda;
     eqs.oml = 1.0f - lambda;
     eqs.gamma = im.gamma;
@@ -524,6 +534,13 @@ __global__ __launch_bounds__(kWinWG) __attribute__((amdgpu_waves_per_eu(8))) voi
             if (b0 > 0 && tid < n) stage(tid, cluster(sh.ids[b0 + tid]));
             if (tid == 0) sh.pairs = 0;
             __syncthreads();
+            if (!NEAR) {
+                Box box = {x0, y0, x1, y1};
+                for (int j = 0; j < n; ++j)
+                    box.add(__builtin_amdgcn_readfirstlane(__float_as_int(sh.cand[j][1].y)),
+                            __builtin_amdgcn_readfirstlane(__float_as_int(sh.cand[j][1].z)));
+                near_box(eqs, box);
+            }
             if (mine) {
                 const float4 fp = packed[py * W + px];
                 unsigned long long win = sh.win[tid];

@@ -142,7 +142,15 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_
     Eqs eqs;
     eqs.img = img;
     eqs.W = W;
-    eqs.near = s.near != 0;
+    near_all(eqs);
+    if (!s.near) {                                              // uniform
+        Box box = {x0, y0, x1 - 1, y1 - 1};
+        for (int j = 0; j < 9; ++j) {
+            const ConstF c = (ConstF)(uintptr_t)cen + 5LL * (nb.row[j / 3] + nb.col[j % 3]);
+            box.add(round_coord(c[3], W - 1), round_coord(c[4], H - 1));
+        }
+        near_box(eqs, box);
+    }
     eqs.lambda = s.lambda;
     eqs.oml = 1.0f - s.lambda;
     eqs.gamma = s.gamma;

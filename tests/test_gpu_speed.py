@@ -1,0 +1,51 @@
+"""Calls whose time must keep up with that of a like call: images that differ only
+in a property that should cost little.  The limits leave about half as much again
+for noise as a correct build needs; what they guard against was far outside."""
+import numpy as np
+import pytest
+
+from gpu_util import needs_gpu, say, torch
+
+pytestmark = [pytest.mark.gpu, needs_gpu]
+
+
+def _image(W, H, seed=1):
+    """Blocks of colour with noise, and a contour map that is nowhere quite 0."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    lo = torch.rand((H // 40 + 1, W // 40 + 1, 3), generator=g, device="cuda") * 60
+    lab = lo.repeat_interleave(40, 0).repeat_interleave(40, 1)[:H, :W]
+    lab = (lab + 4 * torch.randn((H, W, 3), generator=g, device="cuda")).contiguous()
+    return lab, torch.rand((H, W), generator=g, device="cuda") ** 4
+
+
+def _time(fn, target=30.0):
+    """Least of five averages, in ms."""
+    def once(n):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(n):
+            fn()
+        b.record()
+        torch.cuda.synchronize()
+        return a.elapsed_time(b) / n
+    once(2)
+    n = max(2, int(target / once(2)))
+    return min(once(n) for _ in range(5))
+
+
+def _run(W, H, k, data=None, **params):
+    from paper_1903_07149_amd.scalp import Scalp
+    lab, con = data if data is not None else _image(W, H)
+    s = Scalp(W, H, k, **params)
+    out = s.new_state()
+    return _time(lambda: s.run(lab, con, out=out))
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+def test_far_images_keep_up_with_near_ones(mode):
+    """60000x80 against 30000x160, the same pixels and cells."""
+    say("far against near", mode)
+    far = _run(60000, 80, 4800, iterations=5, assign_mode=mode)
+    near = _run(30000, 160, 4800, iterations=5, assign_mode=mode)
+    print(f"far {far:.3f} ms, near {near:.3f} ms")
+    assert far < 1.5 * near
