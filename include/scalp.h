@@ -73,13 +73,12 @@ typedef struct {
                                 the same lab/contour/sigma; skip re-packing  */
     int32_t lds_pixels;      /* tuning of the soft backward: LDS budget of its
                                 tiles in 16-byte units, 0..9728; 0 selects the
-                                default (4800).  The hard assignments and the
-                                soft forward have no tables.  The results do
-                                not depend on it                             */
+                                default (4800).  It bounds no other kernel's
+                                LDS.  The results do not depend on it        */
     int32_t wg_size;         /* tuning: workgroup size of the 3x3 assignment and
-                                of the soft forward, 0 (default: 256, or 512
-                                for small batches), 256, 512 or 1024 (the window
-                                form always takes 256)                       */
+                                of the soft forward, 0 (default: chosen by the
+                                image, 256 for most), 256, 512 or 1024 (the
+                                window form always takes 256)                */
     int32_t assign_mode;     /* SCALP_ASSIGN_GRID3X3 (default) or
                                 SCALP_ASSIGN_WINDOW, see below               */
     int32_t contour_source;  /* SCALP_CONTOUR_INPUT (default) or

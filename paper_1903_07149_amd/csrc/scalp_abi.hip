@@ -61,20 +61,33 @@ bool pack_inputs_ok(const scalp_params_t* p, const float* lab, const float* cont
     return lab && (contour || p->contour_source == SCALP_CONTOUR_GRADIENT);
 }
 
-// Launch shape of the grid form and of the soft forward.  256 lanes by default: an item's waves meet
-// at three barriers, and the more items a CU holds, the less it waits there
-// (10 iterations of 1920x1080, k = 2000: 0.848, 0.864 and 0.897 ms at 256,
-// 512 and 1024 lanes; the 64-image batch: 34.0, 36.0 and 39.2 ms).
-Tuning tuning_of(const scalp_params_t* p) {
+// Launch shape of the grid form over N pixels in K cells.  256 lanes by default: an
+// item's waves meet at three barriers, and the more items a CU holds, the less it waits
+// there (10 iterations of 1920x1080, k = 2000: 0.848, 0.864 and 0.897 ms at 256, 512 and
+// 1024 lanes; the 64-image batch: 34.0, 36.0 and 39.2 ms).  Where every candidate is
+// walked, the more pixels share a table, the fewer entries each has to fill: 1024
+// lanes, or 512 (two pixels a lane) where a cell has no more pixels than a table's item
+// and the cells are many (that image 2.26, 1.63 and 1.74 ms; 481x321, k = 250: 552,
+// 393 and 311 us; 1920x1080, k = 700: 6.58, 4.44 and 3.10 ms).
+Tuning tuning_of(const scalp_params_t* p, long long N, long long K, bool all) {
     Tuning t;
-    t.wg = p->wg_size == 0 ? 256 : p->wg_size;
+    t.wg = p->wg_size != 0 ? p->wg_size
+           : !all          ? 256
+           : K >= 4 * kCUs && N <= kTablePixels * K ? 512 : 1024;
     return t;
+}
+
+Tuning tuning_of(const scalp_grid_t* g, const scalp_params_t* p) {
+    const long long N = (long long)g->width * g->height;
+    return tuning_of(p, N, g->num_sp, walk_all(p->exact_pruning, N, g->num_sp));
 }
 
 // Work items per cell of a single image's launch.
 int slices_of(const scalp_grid_t* g, const scalp_params_t* p) {
+    if (walk_all(p->exact_pruning, (long long)g->width * g->height, g->num_sp))
+        return assign_slices(g->width, g->height, g->nx, g->ny, kTablePixels, 1);
     return assign_slices(g->width, g->height, g->nx, g->ny,
-                         item_pixels(g->width, g->height, g->num_sp, tuning_of(p).wg),
+                         item_pixels(g->width, g->height, g->num_sp, tuning_of(g, p).wg),
                          fill_slices(g->num_sp));
 }
 
@@ -207,9 +220,9 @@ int enq_window_pass(const Img& im, const scalp_params_t* p, const Views& v, int 
                                 p->lambda, true, listed, s);
 }
 
-int enq_iterations(const Img& im, const scalp_params_t* p, const Views& v, float* centers,
+int enq_iterations(const scalp_grid_t* g, const Img& im, const scalp_params_t* p, const Views& v, float* centers,
                    int* endpoints, int* labels, int* counts, hipStream_t s, int R) {
-    const Tuning t = tuning_of(p);
+    const Tuning t = tuning_of(g, p);
     const bool window = p->assign_mode == SCALP_ASSIGN_WINDOW;
     for (int it = 0; it < p->iterations; ++it) {
         int e = window ? enq_window_pass(im, p, v, R, centers, endpoints, labels, it == 0,
@@ -354,7 +367,7 @@ int scalp_assign(const scalp_grid_t* g, const scalp_params_t* p, const float* la
                                        false, s));
     } else
         CHECK_HIP(launch_assign(image_of(g, p), v.packed, centers, endpoints, labels, v.acc,
-                                v.ctrl, p->lambda, false, tuning_of(p), s));
+                                v.ctrl, p->lambda, false, tuning_of(g, p), s));
     return SCALP_OK;
 }
 
@@ -390,7 +403,7 @@ int scalp_assign_accumulate(const scalp_grid_t* g, const scalp_params_t* p, cons
                                   labels, true, false, (hipStream_t)stream));
     else
         CHECK_HIP(launch_assign(image_of(g, p), v.packed, centers, endpoints, labels, v.acc,
-                                v.ctrl, p->lambda, true, tuning_of(p), (hipStream_t)stream));
+                                v.ctrl, p->lambda, true, tuning_of(g, p), (hipStream_t)stream));
     return SCALP_OK;
 }
 
@@ -423,7 +436,7 @@ int scalp_run(const scalp_grid_t* g, const scalp_params_t* p, const float* lab,
     const Img im = image_of(g, p);
     if (!p->reuse_prepared) CHECK_HIP(enq_prepare(g, p, lab, contour, v, s));
     CHECK_HIP(enq_init(im, v, centers, endpoints, counts, labels, s));
-    CHECK_HIP(enq_iterations(im, p, v, centers, endpoints, labels, counts, s, window_radius(g)));
+    CHECK_HIP(enq_iterations(g, im, p, v, centers, endpoints, labels, counts, s, window_radius(g)));
     return SCALP_OK;
 }
 
@@ -453,7 +466,7 @@ int scalp_graph_create(const scalp_grid_t* g, const scalp_params_t* p, float* ce
     const scalp_params_t pc = *p;
     const int R = window_radius(g);
     return capture(out, [&](hipStream_t s) {
-        return enq_iterations(im, &pc, v, centers, endpoints, labels, counts, s, R);
+        return enq_iterations(g, im, &pc, v, centers, endpoints, labels, counts, s, R);
     });
 }
 
@@ -509,7 +522,9 @@ bool batch_layout(const scalp_batch_desc_t* d, int n, BatchLayout* out) {
 int enq_batched(const scalp_batch_desc_t* d, int n, const scalp_params_t* p, const float* lab,
                 const float* contour, float* centers, int* endpoints, int* labels, int* counts,
                 void* ws, const BatchLayout& BL, hipStream_t s) {
-    const Tuning t = tuning_of(p);
+    // (a small batch by pairs: 7 scales of 189x117, 10 iterations, 482 us, 600 over tables)
+    const bool all = walk_all(p->exact_pruning, BL.N, BL.K) && BL.N >= kFewPixels;
+    const Tuning t = tuning_of(p, BL.N, BL.K, all);
     const Views v = views_of(ws, BL.base);
     char* b = static_cast<char*>(ws);
     Img* imgs = reinterpret_cast<Img*>(b + BL.imgs);
@@ -521,7 +536,7 @@ int enq_batched(const scalp_batch_desc_t* d, int n, const scalp_params_t* p, con
     for (int i = 0; i < n; ++i) {
         const scalp_grid_t& g = d[i].grid;
         // (items_total is below 2^31; smaller items only where they cannot pass it)
-        const int pixels = BL.items_total < 1LL << 29
+        const int pixels = all ? kTablePixels : BL.items_total < 1LL << 29
                                ? batch_item_pixels(BL.N, g.width, g.height, g.num_sp, t.wg) : t.wg;
         himg[(size_t)i] = img_of(&g, p, d[i].pix_offset, d[i].sp_offset,
                                  assign_slices(g.width, g.height, g.nx, g.ny, pixels, 1));
@@ -570,7 +585,7 @@ int enq_batched(const scalp_batch_desc_t* d, int n, const scalp_params_t* p, con
                                                      d[i].grid.nx, d[i].grid.ny));
     for (int it = 0; e == hipSuccess && it < p->iterations; ++it) {
         e = launch_assign_batched(imgs, items, n, longest_run, v.packed, centers, endpoints, labels,
-                                  v.acc, v.ctrl, p->lambda, t, near, s);
+                                  v.acc, v.ctrl, p->lambda, t, near, all, s);
         if (e == hipSuccess)
             e = p->project ? launch_finalize_project_batched(imgs, starts, n, (int)BL.K, max_block,
                                                              centers, endpoints, counts, v.acc,
@@ -631,7 +646,7 @@ namespace {
 // us per assignment at 256, 13.3 at 512, 13.9 at 1024; 2 x 256x256, k = 128: 34, 31,
 // 40).
 int soft_wg(const scalp_grid_t* g, const scalp_params_t* p, long long batch) {
-    return p->wg_size == 0 && batch * g->num_sp <= kCUs ? 512 : tuning_of(p).wg;
+    return p->wg_size != 0 ? p->wg_size : batch * g->num_sp <= kCUs ? 512 : 256;
 }
 
 // saved: [A: T][B][9][N] float, [Bf: T][B][9][N] float, [Z: T][B][K] double,

@@ -257,6 +257,38 @@ __device__ __forceinline__ void walk_near(const float4* __restrict__ img, unsign
     }
 #undef SCALP_LOAD
 }
+
+// The same over an LDS table of (colour distance to the candidate, w) of the texels
+// around the paths, from byte offset `off`: 5 VALU instructions and an 8-byte LDS
+// read per sample.  The colour distances are those that walk_near forms, added in
+// the same order: the same sums.
+__device__ __forceinline__ void walk_table(const float2* table, unsigned off, const PathStep& s,
+                                           float& sc, float& sw) {
+    unsigned acc = 0x80000000u;
+    const char* q = reinterpret_cast<const char*>(table);
+#define SCALP_LOAD() (*reinterpret_cast<const float2*>(q + off))
+    unsigned trips = (unsigned)s.n >> 2;
+    while (!__builtin_sub_overflow(trips, 1u, &trips)) {
+        SCALP_STEP(off);
+        const float2 fa = SCALP_LOAD();
+        SCALP_STEP(off);
+        const float2 fb = SCALP_LOAD();
+        SCALP_STEP(off);
+        const float2 fc = SCALP_LOAD();
+        SCALP_STEP(off);
+        const float2 fd = SCALP_LOAD();
+        sc = ((sc + fa.x) + fb.x) + fc.x + fd.x;
+        sw = ((sw + fa.y) + fb.y) + fc.y + fd.y;
+        asm volatile("" : "+v"(acc));
+    }
+    for (int i = s.n & 3; i > 0; --i) {
+        SCALP_STEP(off);
+        const float2 fa = SCALP_LOAD();
+        sc = sc + fa.x;
+        sw = sw + fa.y;
+    }
+#undef SCALP_LOAD
+}
 #undef SCALP_STEP
 #undef SCALP_ACC
 
@@ -339,6 +371,37 @@ __device__ __forceinline__ void near_box(Eqs& q, const Box& b) {
     q.near_y = b.y0;
 }
 
+// A path from pixel (px, py) to the endpoint (cx, cy) of the cluster at ck = (l, a, b,
+// x, y): its steps, 1 / (n + 1) and the spatial term of Eq. (3).
+struct Path {
+    int dx, dy, n;
+    double inv;
+    float dsp;
+};
+
+__device__ __forceinline__ Path path_of(const Eqs& q, const float (&ck)[5], int cx, int cy, int px,
+                                        int py) {
+    Path p;
+    const float ax = (float)px - ck[3], ay = (float)py - ck[4];
+    p.dx = cx - px;
+    p.dy = cy - py;
+    p.n = max(abs(p.dx), abs(p.dy));
+    p.inv = path_recip(p.n);
+    p.dsp = (ax * ax + ay * ay) * q.spw;
+    return p;
+}
+
+// D of Eq. (3) from the colour distance of the path's first pixel and the sums over
+// all its samples, and the factors A, B of Eqs. (1)-(2).
+__device__ __forceinline__ float path_value(const Eqs& q, const Path& p, float dcp, float sc, float sw,
+                                            float& A, float& B) {
+    float qc, qw;                                  // sc / |P|, sw / |P|
+    div_path_len(sc, sw, p.n, p.inv, qc, qw);
+    A = q.lambda * dcp + q.oml * qc;               // Eq. (1)
+    B = 1.0f + q.gamma * qw;                       // Eq. (2)
+    return A * B + p.dsp;                          // Eq. (3)
+}
+
 // D of Eq. (3) of pixel (px, py), whose texel is fp, to the cluster at ck =
 // (l, a, b, x, y) with endpoint (cx, cy), and its factors A, B of Eqs.
 // (1)-(2); FP32, operation by operation.  cut: an infinite D may be returned
@@ -348,40 +411,108 @@ __device__ __forceinline__ float path_distance(const Eqs& q, const float (&ck)[5
                                                int cx, int cy, int px, int py, bool cut_on,
                                                float thr, float& A, float& B) {
     const float l = ck[0], a = ck[1], b = ck[2];
-    const float ax = (float)px - ck[3], ay = (float)py - ck[4];
-    const int dx = cx - px, dy = cy - py;
-    const int n = max(abs(dx), abs(dy));
-    const double inv = path_recip(n);
-    const float dsp = (ax * ax + ay * ay) * q.spw;
+    const Path p = path_of(q, ck, cx, cy, px, py);
     const float dcp = colour_dist(fp, l, a, b);
     float sc = dcp, sw = fp.w;                     // sample i = 0 is p itself
     if (q.near) {                                  // uniform
         Cut cut;
         cut.on = cut_on;
         if (cut_on) {
-            const float rnp = __builtin_amdgcn_rcpf((float)(n + 1));
+            const float rnp = __builtin_amdgcn_rcpf((float)(p.n + 1));
             cut.a0 = q.lambda * dcp;
             cut.f = q.oml * rnp;
             cut.g = q.gamma * rnp;
-            cut.dsp = dsp;
+            cut.dsp = p.dsp;
             cut.thr = thr;
         }
         const unsigned row = 16u * (unsigned)q.W;
         walk_near(q.near_img, row * (unsigned)(py - q.near_y) + 16u * (unsigned)(px - q.near_x),
-                  path_step(dx, dy, 16, (int)row), l, a, b, cut, sc, sw);
+                  path_step(p.dx, p.dy, 16, (int)row), l, a, b, cut, sc, sw);
     } else {
-        walk_path(q.img, py * q.W + px, 1, q.W, dx, dy, l, a, b, sc, sw);
-        if (n > 0) {                               // sample i = n is the endpoint
+        walk_path(q.img, py * q.W + px, 1, q.W, p.dx, p.dy, l, a, b, sc, sw);
+        if (p.n > 0) {                             // sample i = n is the endpoint
             const float4 fc = q.img[(long long)cy * q.W + cx];
             sc = sc + colour_dist(fc, l, a, b);
             sw = sw + fc.w;
         }
     }
-    float qc, qw;                                  // sc / |P|, sw / |P|
-    div_path_len(sc, sw, n, inv, qc, qw);
-    A = q.lambda * dcp + q.oml * qc;               // Eq. (1)
-    B = 1.0f + q.gamma * qw;                       // Eq. (2)
-    return A * B + dsp;                            // Eq. (3)
+    return path_value(q, p, dcp, sc, sw, A, B);
+}
+
+// An LDS table over a box of texels, row-major.  The row pitch is 4 (mod 8) entries
+// where that fits: the 8 rows of a wave's 8x8 block of pixels then lie evenly over the
+// LDS banks.
+struct Table {
+    int x0, y0, pitch, rows;
+    bool fits;             // in `cap` entries, and a row in the workgroup's lanes
+};
+
+__device__ __forceinline__ Table table_of(const Box& b, int cap, int lanes) {
+    Table t;
+    const int w = b.x1 - b.x0 + 1;
+    t.x0 = b.x0;
+    t.y0 = b.y0;
+    t.rows = b.y1 - b.y0 + 1;
+    t.pitch = w + ((12 - w % 8) % 8);
+    if (t.pitch > lanes || (long long)t.pitch * t.rows > cap) t.pitch = w;
+    t.fits = t.pitch <= lanes && (long long)t.pitch * t.rows <= cap;
+    return t;
+}
+
+// Fills it with (d_c(q), w_q), column by column: lane tid keeps one column, c = tid
+// mod pitch, of rows tid / pitch, tid / pitch + R, ... (R = WG / pitch, both as high
+// multiplications by ceil(2^24 / pitch)), so that an entry costs one load, its colour
+// distance and two index adds; four rows' loads in flight.  Entries past the box's
+// width only pad the pitch.
+template <int WG>
+__device__ __forceinline__ void fill_table(float2* table, const Table& t,
+                                           const float4* __restrict__ img, int W, float l, float a,
+                                           float b) {
+    const int tid = threadIdx.x;
+    const unsigned m = (0x1000000u + (unsigned)t.pitch - 1u) / (unsigned)t.pitch;
+    const int R = (int)__umulhi((unsigned)WG << 8, m);
+    const int r0 = (int)__umulhi((unsigned)tid << 8, m);
+    if (r0 >= R) return;                           // lanes past R pitch
+    const int c = tid - r0 * t.pitch;
+    const float4* p = img + ((long long)(t.y0 + r0) * W + min(t.x0 + c, W - 1));
+    const long long dp = (long long)R * W;
+    const int de = R * t.pitch;
+    int e = tid, r = r0;
+#define SCALP_ENTRY(f) make_float2(colour_dist(f, l, a, b), (f).w)
+    for (; r + 3 * R < t.rows; r += 4 * R) {
+        const float4 f0 = p[0], f1 = p[dp], f2 = p[2 * dp], f3 = p[3 * dp];
+        table[e] = SCALP_ENTRY(f0);
+        table[e + de] = SCALP_ENTRY(f1);
+        table[e + 2 * de] = SCALP_ENTRY(f2);
+        table[e + 3 * de] = SCALP_ENTRY(f3);
+        p += 4 * dp;
+        e += 4 * de;
+    }
+    if (r + R < t.rows) {
+        const float4 f0 = p[0], f1 = p[dp];
+        table[e] = SCALP_ENTRY(f0);
+        table[e + de] = SCALP_ENTRY(f1);
+        p += 2 * dp;
+        e += 2 * de;
+        r += 2 * R;
+    }
+    if (r < t.rows) {
+        const float4 f = p[0];
+        table[e] = SCALP_ENTRY(f);
+    }
+#undef SCALP_ENTRY
+}
+
+// path_distance over a table that holds the path.
+__device__ __forceinline__ float table_distance(const Eqs& q, const float (&ck)[5], const Table& t,
+                                                const float2* table, int cx, int cy, int px, int py,
+                                                float& A, float& B) {
+    const Path p = path_of(q, ck, cx, cy, px, py);
+    const int at = (py - t.y0) * t.pitch + (px - t.x0);
+    const float2 f = table[at];
+    float sc = f.x, sw = f.y;                      // sample i = 0 is the pixel itself
+    walk_table(table, 8u * (unsigned)at, path_step(p.dx, p.dy, 8, 8 * t.pitch), sc, sw);
+    return path_value(q, p, f.x, sc, sw, A, B);
 }
 
 __device__ __forceinline__ int round_coord(float v, int hi) {

@@ -86,6 +86,19 @@ inline int item_pixels(long long W, long long H, long long K, int wg) {
     return W * H > 2304 * K && W * H <= 1LL << 30 ? wg / 2 : wg;
 }
 
+// Without exact pruning every pixel walks every candidate: over LDS tables that a
+// workgroup makes of each, up to kTablePixels pixels an item whatever the workgroup.
+// In a launch of few cells the chain of nine tables takes longer than lists of pairs,
+// whose items can be smaller, and in small cells a table has more entries than its
+// paths samples.  10 iterations over tables and by pairs: 97x61, 30 cells, 228 and 170
+// us; 160x120, 70, 248 and 225; 300x200, 130, 276 and 365; 1920x1080 with 41 pixels a
+// cell 9.48 and 3.16 ms, with 207 2.39 and 2.91, with 20 cells 28.5 and 37.7.
+constexpr int kTablePixels = 1024;
+
+inline bool walk_all(int prune, long long N, long long K) {
+    return !prune && N >= 128 * K && std::max(K, N / kTablePixels) > 96;
+}
+
 // Items per cell: so many that no item has more than `pixels` pixels, and at least
 // `fill` of them, down to one 64-pixel chunk each.
 inline int assign_slices(int W, int H, int nx, int ny, int pixels, long long fill) {
@@ -166,11 +179,11 @@ int launch_project(const Img& im, const float* centres, const int* counts, const
 int launch_init_cells_batched(const Img* imgs, const int* cell_start, int n_img, int total_cells,
                               const float4* packed, int* labels, long long* acc, hipStream_t s);
 // longest_run: items of the longest of the 8 XCDs' runs; near: near_image of every
-// image
+// image; all: walk_all of the batch
 int launch_assign_batched(const Img* imgs, const int* item_start, int n_img, int longest_run,
                           const float4* packed, const float* centres, const int* endpoints,
                           int* labels, long long* acc, int* ctrl, float lambda, const Tuning& t,
-                          bool near, hipStream_t s);
+                          bool near, bool all, hipStream_t s);
 int launch_finalize_batched(const Img* imgs, const int* sp_start, int n_img, int total_sp,
                             float* centres, int* endpoints, int* counts, long long* acc,
                             const int* labels, int* ctrl, int* plist, bool project,

@@ -27,6 +27,7 @@
 // compiled with -ffp-contract=off, so it matches the plain CPU definition
 // bit for bit.
 #include <algorithm>
+#include <climits>
 
 #include "scalp_device.h"
 
@@ -54,6 +55,19 @@ struct ItemShared {
     int pairs;
 };
 
+// Per work item of assign_all: a candidate's table, or two of half the size; then the
+// update bins.  72 bytes a lane: the LDS of as many workgroups as the registers let a
+// CU hold.
+template <int WG>
+struct TableShared {
+    static constexpr int kEntries = 9 * WG - 8;
+    union {
+        unsigned long long bins[9 * 6][kBinCopies];
+        float2 table[kEntries];
+    };
+    int box[4];            // of the pixels
+};
+
 // A descriptor read through the scalar cache, word by word (p uniform).
 __device__ __forceinline__ Img load_const(const Img* p) {
     static_assert(sizeof(Img) % 4 == 0, "words");
@@ -71,6 +85,246 @@ __device__ __forceinline__ Img load_const(const Img* p) {
 __device__ __forceinline__ int slice_chunk(int chunks, int i, const Img& im) {
     const long long v = (long long)chunks * i;
     return v < (1LL << 31) ? fdiv((int)v, im.dspl) : (int)(v / im.spl);
+}
+
+// The update's bins, [slot * 6 + sum][copy].
+typedef unsigned long long Bins[9 * 6][kBinCopies];
+
+template <int WG>
+__device__ __forceinline__ void clear_bins(Bins& bins) {
+    for (int t = threadIdx.x; t < 54 * kBinCopies; t += WG) (&bins[0][0])[t] = 0ULL;
+}
+
+// The label of pixel (px, py) and its share of the update's sums: superpixel k, slot j.
+template <bool ACCUM>
+__device__ __forceinline__ void settle(const Img& im, const float4* __restrict__ img, int px, int py,
+                                       int j, int k, int* __restrict__ labels, Bins& bins) {
+    const long long p = (long long)py * im.W + px;
+    labels[im.pix + p] = k;
+    if (ACCUM) {
+        const float4 f = img[p];
+        const int tid = threadIdx.x, cp = (tid ^ (tid >> 3)) & (kBinCopies - 1);
+        unsigned long long(*bin)[kBinCopies] = bins + 6 * j;
+        atomicAdd(&bin[0][cp], 1ULL);
+        atomicAdd(&bin[1][cp], (unsigned long long)px);
+        atomicAdd(&bin[2][cp], (unsigned long long)py);
+        atomicAdd(&bin[3][cp], (unsigned long long)to_fixed(f.x));
+        atomicAdd(&bin[4][cp], (unsigned long long)to_fixed(f.y));
+        atomicAdd(&bin[5][cp], (unsigned long long)to_fixed(f.z));
+    }
+}
+
+// The bins to the sums of superpixels k0, k0 + 1, ... (first of the cell's 3 rows).
+__device__ __forceinline__ void flush_bins(const Img& im, int k0, Bins& bins,
+                                           long long* __restrict__ acc) {
+    const int tid = threadIdx.x;
+    if (tid < 54) {
+        const int j = tid / 6, di = j / 3;
+        unsigned long long n = 0, v = 0;
+        for (int c = 0; c < kBinCopies; ++c) {
+            n += bins[6 * j][c];
+            v += bins[tid][c];
+        }
+        if (n != 0ULL)
+            atomicAdd((unsigned long long*)(acc + kAccStride * (long long)(im.sp + k0 + di * im.nx +
+                                                                           (j - 3 * di)) +
+                                            (tid - 6 * j)),
+                      v);
+    }
+}
+
+// A work item: pixels [t0, t1) in cell_pixel order of the cell of row ci and column cj.
+struct Item {
+    int ci, cj, x0, y0, cw, ch, t0, t1;
+};
+
+__device__ __forceinline__ Item item_of(const Img& im, int ci, int cj, int slice) {
+    Item it;
+    it.ci = ci;
+    it.cj = cj;
+    it.x0 = cell_lo(cj, im.W, im.nx, im.dnx);
+    it.y0 = cell_lo(ci, im.H, im.ny, im.dny);
+    it.cw = cell_lo(cj + 1, im.W, im.nx, im.dnx) - it.x0;
+    it.ch = cell_lo(ci + 1, im.H, im.ny, im.dny) - it.y0;
+    const int P = it.cw * it.ch;
+    it.t0 = 0;
+    it.t1 = P;
+    if (im.spl > 1) {                              // uniform
+        const int chunks = (P + 63) >> 6;
+        it.t0 = 64 * slice_chunk(chunks, slice, im);
+        it.t1 = min(P, 64 * slice_chunk(chunks, slice + 1, im));
+    }
+    return it;
+}
+
+template <bool NEAR>
+__device__ __forceinline__ Eqs item_eqs(const Img& im, const Item& it, const Neighbours& nb,
+                                        const float4* __restrict__ img, const int* __restrict__ end,
+                                        float lambda) {
+    Eqs eqs;
+    eqs.img = img;
+    eqs.W = im.W;
+    near_all(eqs);
+    if (!NEAR) {
+        // (of the whole cell; endpoints outside the image are clamped into it)
+        Box box = {it.x0, it.y0, it.x0 + it.cw - 1, it.y0 + it.ch - 1};
+        const ConstI ce = (ConstI)(uintptr_t)end;
+        for (int j = 0; j < 9; ++j) {
+            const int k = nb.row[j / 3] + nb.col[j % 3];
+            box.add(min(max(ce[2 * k], 0), im.W - 1), min(max(ce[2 * k + 1], 0), im.H - 1));
+        }
+        near_box(eqs, box);
+    }
+    eqs.lambda = lambda;
+    eqs.oml = 1.0f - lambda;
+    eqs.gamma = im.gamma;
+    eqs.spw = im.spw;
+    return eqs;
+}
+
+// Without exact pruning every pixel of a work item walks every candidate: candidate by
+// candidate the workgroup writes (d_c, w) over the box of the pixels and the
+// candidate's endpoint, which holds every path to it, into an LDS table, and the paths
+// are walked there; over global memory where the box exceeds the LDS.  The winner is
+// the smallest (D, slot).  A lane has up to kTablePixels / WG pixels, one at a time in
+// best[0] and at[0] (x and y within the box, slot), which rotate.  Where two tables
+// fit, they alternate: one barrier a candidate.
+//
+// What bounds it: VALU issue; a sample costs 5 instructions and an 8-byte LDS read.  10
+// iterations of 1920x1080, k = 2000: 1.63 ms; 4.68 by the pairs of process_cell, whose
+// samples cost 13 instructions and 16 bytes through L1.
+template <int WG, bool ACCUM, bool NEAR>
+__device__ __forceinline__ void assign_all(const Img& im, int ci, int cj, int slice,
+                                           const float4* __restrict__ packed,
+                                           const float* __restrict__ centres,
+                                           const int* __restrict__ endpoints,
+                                           int* __restrict__ labels, long long* __restrict__ acc,
+                                           float lambda, TableShared<WG>& sh) {
+    constexpr int kRounds = kTablePixels / WG;
+    const int tid = threadIdx.x, W = im.W, H = im.H;
+    const Item it = item_of(im, ci, cj, slice);
+    if (it.t1 <= it.t0) return;                    // an empty slice
+    const float4* __restrict__ img = packed + im.pix;
+    const float* __restrict__ cen = centres + 5LL * im.sp;
+    const int* __restrict__ end = endpoints + 2LL * im.sp;
+    const Neighbours nb = neighbours_of(im.nx, im.ny, ci, cj);
+    const Eqs eqs = item_eqs<NEAR>(im, it, nb, img, end, lambda);
+    const int k0 = (ci - 1) * im.nx + cj - 1;
+    if (tid == 0) {
+        sh.box[0] = sh.box[1] = INT_MAX;
+        sh.box[2] = sh.box[3] = 0;
+    }
+    __syncthreads();
+    float best[kRounds];
+    unsigned at[kRounds];
+    Box own;
+    {
+        const PixelMap map = pixel_map(im.dper, it.cw, it.ch);
+        int x[kRounds], y[kRounds];
+        int lx = INT_MAX, ly = INT_MAX, hx = 0, hy = 0;
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            x[r] = y[r] = -1;
+            const int t = it.t0 + r * WG + tid;
+            if (t < it.t1) {
+                pixel_at(map, t, x[r], y[r]);
+                x[r] += it.x0;
+                y[r] += it.y0;
+                lx = min(lx, x[r]);
+                ly = min(ly, y[r]);
+                hx = max(hx, x[r]);
+                hy = max(hy, y[r]);
+            }
+        }
+        lx = wave_min_i32(lx);
+        ly = wave_min_i32(ly);
+        hx = wave_max_i32(hx);
+        hy = wave_max_i32(hy);
+        if ((tid & 63) == 0) {
+            atomicMin(&sh.box[0], lx);
+            atomicMin(&sh.box[1], ly);
+            atomicMax(&sh.box[2], hx);
+            atomicMax(&sh.box[3], hy);
+        }
+        __syncthreads();
+        own.x0 = __builtin_amdgcn_readfirstlane(sh.box[0]);
+        own.y0 = __builtin_amdgcn_readfirstlane(sh.box[1]);
+        own.x1 = __builtin_amdgcn_readfirstlane(sh.box[2]);
+        own.y1 = __builtin_amdgcn_readfirstlane(sh.box[3]);
+        // (kTablePixels pixels of 8-wide strips span fewer than 4096 rows and columns)
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            best[r] = INFINITY;
+            at[r] = y[r] < 0 ? ~0u
+                             : (unsigned)(x[r] - own.x0) | ((unsigned)(y[r] - own.y0) << 12) | (15u << 24);
+        }
+    }
+    bool half = false, was_full = false;           // uniform
+#pragma unroll 1
+    for (int j = 0; j < 9; ++j) {
+        if (!((nb.inside >> j) & 1u)) continue;    // uniform
+        const int di = (j * 11) >> 5, kk = k0 + di * im.nx + (j - 3 * di);
+        const ConstF cp = (ConstF)(uintptr_t)cen + 5 * kk;
+        const ConstI ep = (ConstI)(uintptr_t)end + 2 * kk;
+        const float ck[5] = {cp[0], cp[1], cp[2], cp[3], cp[4]};
+        const int cx = min(max(ep[0], 0), W - 1), cy = min(max(ep[1], 0), H - 1);
+        Box box = own;
+        box.add(cx, cy);
+        const Table t = table_of(box, TableShared<WG>::kEntries, WG);
+        const bool full = t.pitch * t.rows > TableShared<WG>::kEntries / 2;
+        if (t.fits) {
+            if (full || was_full) __syncthreads(); // the table before was read
+            half = !half && !full;
+            was_full = full;
+        }
+        float2* table = sh.table + (half ? TableShared<WG>::kEntries / 2 : 0);
+        if (t.fits) {
+            fill_table<WG>(table, t, img, W, ck[0], ck[1], ck[2]);
+            __syncthreads();
+        }
+#pragma unroll 1
+        for (int r = 0; r < kRounds; ++r) {
+            if (at[0] != ~0u) {
+                const int px = own.x0 + (int)(at[0] & 4095u), py = own.y0 + (int)((at[0] >> 12) & 4095u);
+                float A, B, D;
+                if (t.fits)                        // uniform
+                    D = table_distance(eqs, ck, t, table, cx, cy, px, py, A, B);
+                else
+                    D = path_distance(eqs, ck, img[py * W + px], cx, cy, px, py, false, 0.0f, A, B);
+                if (D < best[0]) {                 // in ascending slot
+                    best[0] = D;
+                    at[0] = (at[0] & 0xffffffu) | ((unsigned)j << 24);
+                }
+            }
+            const float b0 = best[0];
+            const unsigned a0 = at[0];
+#pragma unroll
+            for (int q = 0; q + 1 < kRounds; ++q) {
+                best[q] = best[q + 1];
+                at[q] = at[q + 1];
+            }
+            best[kRounds - 1] = b0;
+            at[kRounds - 1] = a0;
+        }
+    }
+    __syncthreads();
+    if (ACCUM) {
+        clear_bins<WG>(sh.bins);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        if (at[r] == ~0u) continue;
+        const int slot = (int)(at[r] >> 24);
+        const int j = slot == 15 ? 4 : slot;       // no slot only with non-finite input
+        const int di = (j * 11) >> 5;
+        settle<ACCUM>(im, img, own.x0 + (int)(at[r] & 4095u), own.y0 + (int)((at[r] >> 12) & 4095u),
+                      j, k0 + di * im.nx + (j - 3 * di), labels, sh.bins);
+    }
+    if (ACCUM) {
+        __syncthreads();
+        flush_bins(im, k0, sh.bins, acc);
+    }
 }
 
 // Work item (cell, slice): pixels [t0, t1) of the cell in cell_pixel order,
@@ -120,40 +374,14 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
                                              ItemShared<WG>& sh) {
     const int tid = threadIdx.x;
     const int W = im.W, H = im.H;
-    const int x0 = cell_lo(cj, W, im.nx, im.dnx), x1 = cell_lo(cj + 1, W, im.nx, im.dnx);
-    const int y0 = cell_lo(ci, H, im.ny, im.dny), y1 = cell_lo(ci + 1, H, im.ny, im.dny);
-    const int cw = x1 - x0, ch = y1 - y0;
-    const int P = cw * ch;
-    int t0 = 0, t1 = P;
-    if (im.spl > 1) {                              // uniform
-        const int chunks = (P + 63) >> 6;
-        t0 = 64 * slice_chunk(chunks, slice, im);
-        t1 = min(P, 64 * slice_chunk(chunks, slice + 1, im));
-        if (t1 <= t0) return;                      // an empty slice
-    }
+    const Item it = item_of(im, ci, cj, slice);
+    if (it.t1 <= it.t0) return;                    // an empty slice
     const float4* __restrict__ img = packed + im.pix;
     const int sp = __builtin_amdgcn_readfirstlane(im.sp);
     const float* __restrict__ cen = centres + 5LL * sp;
     const int* __restrict__ end = endpoints + 2LL * sp;
     const Neighbours nb = neighbours_of(im.nx, im.ny, ci, cj);
-    Eqs eqs;
-    eqs.img = img;
-    eqs.W = W;
-    near_all(eqs);
-    if (!NEAR) {
-        // (of the whole cell; endpoints outside the image are clamped into it)
-        Box box = {x0, y0, x1 - 1, y1 - 1};
-        const ConstI ce = (ConstI)(uintptr_t)end;
-        for (int j = 0; j < 9; ++j) {
-            const int k = nb.row[j / 3] + nb.col[j % 3];
-            box.add(min(max(ce[2 * k], 0), W - 1), min(max(ce[2 * k + 1], 0), H - 1));
-        }
-        near_box(eqs, box);
-    }
-    eqs.lambda = lambda;
-    eqs.oml = 1.0f - lambda;
-    eqs.gamma = im.gamma;
-    eqs.spw = im.spw;
+    const Eqs eqs = item_eqs<NEAR>(im, it, nb, img, end, lambda);
     // candidate slot j -> superpixel
     const int k0 = (ci - 1) * im.nx + cj - 1;
     auto superpixel = [&](int j) -> int {
@@ -171,40 +399,21 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
         return path_distance(eqs, ck, fp, min(max(ep.x, 0), W - 1), min(max(ep.y, 0), H - 1), px,
                              py, cut, thr, A, B);
     };
-    // the label of pixel (px, py) and its share of the update's sums
-    auto settle = [&](int px, int py, int bestj) {
-        const int j = bestj < 0 ? 4 : bestj;       // no slot only with non-finite input
-        const long long p = (long long)py * W + px;
-        labels[im.pix + p] = superpixel(j);
-        if (ACCUM) {
-            const float4 f = img[p];
-            const int cp = (tid ^ (tid >> 3)) & (kBinCopies - 1);
-            unsigned long long(*bin)[kBinCopies] = sh.bins + 6 * j;
-            atomicAdd(&bin[0][cp], 1ULL);
-            atomicAdd(&bin[1][cp], (unsigned long long)px);
-            atomicAdd(&bin[2][cp], (unsigned long long)py);
-            atomicAdd(&bin[3][cp], (unsigned long long)to_fixed(f.x));
-            atomicAdd(&bin[4][cp], (unsigned long long)to_fixed(f.y));
-            atomicAdd(&bin[5][cp], (unsigned long long)to_fixed(f.z));
-        }
-    };
 
     if (tid == 0) sh.pairs = 0;
-    if (ACCUM) {
-        for (int t = tid; t < 54 * kBinCopies; t += WG) (&sh.bins[0][0])[t] = 0ULL;
-    }
+    if (ACCUM) clear_bins<WG>(sh.bins);
     __syncthreads();
 
     // first pass: the candidate with the smallest bound; then every other one
     // whose bound does not exceed that D is listed
     const bool prune = im.prune != 0;
-    const bool mine = tid < t1 - t0;
+    const bool mine = tid < it.t1 - it.t0;
     bool again = false;
     int px = 0, py = 0, bestj = -1;
     if (mine) {
-        pixel_at(pixel_map(im.dper, cw, ch), t0 + tid, px, py);
-        px += x0;
-        py += y0;
+        pixel_at(pixel_map(im.dper, it.cw, it.ch), it.t0 + tid, px, py);
+        px += it.x0;
+        py += it.y0;
         unsigned key[9];
         const float4 fp = img[py * W + px];
         bound_keys(nb, (ConstF)(uintptr_t)cen, im.spw, fp, px, py, lambda, key);
@@ -248,38 +457,47 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
             atomicMin(&sh.win[id], ((unsigned long long)__float_as_uint(D) << 32) | (unsigned)j);
     }
     __syncthreads();
-    if (mine) settle(px, py, again ? (int)(unsigned)sh.win[tid] : bestj);
-    __syncthreads();
-
+    if (mine) {
+        if (again) bestj = (int)(unsigned)sh.win[tid];
+        const int j = bestj < 0 ? 4 : bestj;       // no slot only with non-finite input
+        settle<ACCUM>(im, img, px, py, j, superpixel(j), labels, sh.bins);
+    }
     if (ACCUM) {
-        if (tid < 54) {
-            const int j = tid / 6;
-            unsigned long long n = 0, v = 0;
-            for (int c = 0; c < kBinCopies; ++c) {
-                n += sh.bins[6 * j][c];
-                v += sh.bins[tid][c];
-            }
-            if (n != 0ULL)
-                atomicAdd((unsigned long long*)(acc + kAccStride * (long long)(sp + superpixel(j)) +
-                                                (tid - 6 * j)),
-                          v);
-        }
+        __syncthreads();
+        flush_bins(im, k0, sh.bins, acc);
     }
 }
 
-template <int WG, bool ACCUM, bool NEAR>
+// ALL (see walk_all): every candidate is walked, over tables.
+template <int WG, bool ACCUM, bool NEAR, bool ALL>
+__device__ __forceinline__ void assign_item(const Img& im, int item, const float4* __restrict__ packed,
+                                            const float* __restrict__ centres,
+                                            const int* __restrict__ endpoints,
+                                            int* __restrict__ labels, long long* __restrict__ acc,
+                                            float lambda) {
+    const int pos = fdiv(item, im.dspl);
+    int ci, cj;
+    cell_in_strips(pos, im, ci, cj);
+    const int slice = item - pos * im.spl;
+    if constexpr (ALL) {
+        __shared__ TableShared<WG> sh;
+        assign_all<WG, ACCUM, NEAR>(im, ci, cj, slice, packed, centres, endpoints, labels, acc, lambda,
+                                    sh);
+    } else {
+        __shared__ ItemShared<WG> sh;
+        process_cell<WG, ACCUM, NEAR>(im, ci, cj, slice, packed, centres, endpoints, labels, acc,
+                                      lambda, sh);
+    }
+}
+
+template <int WG, bool ACCUM, bool NEAR, bool ALL>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_assign(
     Img im, const float4* __restrict__ packed, const float* __restrict__ centres,
     const int* __restrict__ endpoints, int* __restrict__ labels, long long* __restrict__ acc, int* ctrl,
     float lambda) {
-    __shared__ ItemShared<WG> sh;
     if (ACCUM && blockIdx.x == 0 && threadIdx.x == 0) ctrl[kCtrlProjCount] = 0;
-    const int item = xcd_remap(blockIdx.x, gridDim.x);
-    const int pos = fdiv(item, im.dspl);
-    int ci, cj;
-    cell_in_strips(pos, im, ci, cj);
-    process_cell<WG, ACCUM, NEAR>(im, ci, cj, item - pos * im.spl, packed, centres, endpoints, labels,
-                            acc, lambda, sh);
+    assign_item<WG, ACCUM, NEAR, ALL>(im, xcd_remap(blockIdx.x, gridDim.x), packed, centres, endpoints,
+                                      labels, acc, lambda);
 }
 
 // The assignment over a ragged batch, a workgroup per (image, cell, slice) item,
@@ -297,13 +515,12 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_
 // scales of 189x117, 36 instead of 22 for 3 small images; 64 images of up to 2160
 // pixels a side 2.95 ms instead of 2.93, and 12 scales of 481x321, where taking over
 // another XCD's items helped, 202 instead of 207.
-template <int WG, bool NEAR>
+template <int WG, bool NEAR, bool ALL>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_assign_batched(
     const Img* __restrict__ imgs, const int* __restrict__ item_start, int n_img,
     const float4* __restrict__ packed, const float* __restrict__ centres,
     const int* __restrict__ endpoints, int* __restrict__ labels, long long* __restrict__ acc, int* ctrl,
     float lambda, int h0) {
-    __shared__ ItemShared<WG> sh;
     if (blockIdx.x == 0 && threadIdx.x == 0) ctrl[kCtrlProjCount] = 0;
     // (the tables are constant during the launch: scalar loads)
     const ConstI starts = (ConstI)(uintptr_t)item_start;
@@ -314,11 +531,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_
     const Img im = load_const(imgs + i);
     const int ni = starts[i + 1] - starts[i];
     const int local = __builtin_amdgcn_readfirstlane((int)((long long)ni * x >> 3) + (h - run[i]));
-    const int pos = fdiv(local, im.dspl);
-    int ci, cj;
-    cell_in_strips(pos, im, ci, cj);
-    process_cell<WG, true, NEAR>(im, ci, cj, local - pos * im.spl, packed, centres, endpoints, labels,
-                                 acc, lambda, sh);
+    assign_item<WG, true, NEAR, ALL>(im, local, packed, centres, endpoints, labels, acc, lambda);
 }
 
 // ---------------------------------------------------------------- window form
@@ -1145,11 +1358,11 @@ int launch_init_cells_batched(const Img* imgs, const int* cell_start, int n_img,
     return hipGetLastError();
 }
 
-template <int WG, bool ACCUM>
+template <int WG, bool ACCUM, bool ALL>
 static int launch_assign_t(const Img& im, const float4* packed, const float* centres,
                            const int* endpoints, int* labels, long long* acc, int* ctrl,
                            float lambda, hipStream_t s) {
-    const auto kernel = near_image(im) ? k_assign<WG, ACCUM, true> : k_assign<WG, ACCUM, false>;
+    const auto kernel = near_image(im) ? k_assign<WG, ACCUM, true, ALL> : k_assign<WG, ACCUM, false, ALL>;
     hipLaunchKernelGGL(kernel, dim3(im.nx * im.ny * im.spl), dim3(WG), 0, s, im, packed, centres,
                        endpoints, labels, acc, ctrl, lambda);
     return hipGetLastError();
@@ -1159,10 +1372,10 @@ template <int WG>
 static int launch_assign_wg(const Img& im, const float4* packed, const float* centres,
                             const int* endpoints, int* labels, long long* acc, int* ctrl,
                             float lambda, bool accumulate, hipStream_t s) {
-    return accumulate ? launch_assign_t<WG, true>(im, packed, centres, endpoints, labels, acc,
-                                                  ctrl, lambda, s)
-                      : launch_assign_t<WG, false>(im, packed, centres, endpoints, labels, acc,
-                                                   ctrl, lambda, s);
+    const bool all = walk_all(im.prune, (long long)im.W * im.H, im.nx * im.ny);
+    const auto launch = all ? accumulate ? launch_assign_t<WG, true, true> : launch_assign_t<WG, false, true>
+                        : accumulate ? launch_assign_t<WG, true, false> : launch_assign_t<WG, false, false>;
+    return launch(im, packed, centres, endpoints, labels, acc, ctrl, lambda, s);
 }
 
 int launch_assign(const Img& im, const float4* packed, const float* centres,
@@ -1173,21 +1386,30 @@ int launch_assign(const Img& im, const float4* packed, const float* centres,
     return launch(im, packed, centres, endpoints, labels, acc, ctrl, lambda, accumulate, s);
 }
 
-int launch_assign_batched(const Img* imgs, const int* item_start, int n_img, int longest_run,
-                          const float4* packed, const float* centres, const int* endpoints,
-                          int* labels, long long* acc, int* ctrl, float lambda, const Tuning& t,
-                          bool near, hipStream_t s) {
-    const auto kernel =
-        t.wg == 1024  ? near ? k_assign_batched<1024, true> : k_assign_batched<1024, false>
-        : t.wg == 512 ? near ? k_assign_batched<512, true> : k_assign_batched<512, false>
-                      : near ? k_assign_batched<256, true> : k_assign_batched<256, false>;
+template <int WG>
+static int launch_assign_batched_wg(const Img* imgs, const int* item_start, int n_img, int longest_run,
+                                    const float4* packed, const float* centres, const int* endpoints,
+                                    int* labels, long long* acc, int* ctrl, float lambda, bool near,
+                                    bool all, hipStream_t s) {
+    const auto kernel = all ? near ? k_assign_batched<WG, true, true> : k_assign_batched<WG, false, true>
+                        : near ? k_assign_batched<WG, true, false> : k_assign_batched<WG, false, false>;
     // (a launch holds below 2^32 lanes)
     for (int h0 = 0; h0 < longest_run; h0 += 1 << 18) {
         const unsigned n = (unsigned)std::min(longest_run - h0, 1 << 18);
-        hipLaunchKernelGGL(kernel, dim3(8u * n), dim3(t.wg), 0, s, imgs, item_start, n_img, packed,
+        hipLaunchKernelGGL(kernel, dim3(8u * n), dim3(WG), 0, s, imgs, item_start, n_img, packed,
                            centres, endpoints, labels, acc, ctrl, lambda, h0);
     }
     return hipGetLastError();
+}
+
+int launch_assign_batched(const Img* imgs, const int* item_start, int n_img, int longest_run,
+                          const float4* packed, const float* centres, const int* endpoints,
+                          int* labels, long long* acc, int* ctrl, float lambda, const Tuning& t,
+                          bool near, bool all, hipStream_t s) {
+    const auto launch = t.wg == 1024 ? launch_assign_batched_wg<1024>
+                        : t.wg == 512 ? launch_assign_batched_wg<512> : launch_assign_batched_wg<256>;
+    return launch(imgs, item_start, n_img, longest_run, packed, centres, endpoints, labels, acc, ctrl,
+                  lambda, near, all, s);
 }
 
 // 8 W H bytes, but at least 256, hold the counts and a list of at least 16 ids per

@@ -421,3 +421,77 @@ def test_run_repeatable_and_resumable(orc):
     g3.launch()
     assert (host(l) == host(a.labels)).all() and (host(c) == host(a.centers)).all()
     g3.close()
+
+
+ALL_SIZES = [
+    (320, 320, 100),      # cells of 1024 pixels: the most of an item
+    (330, 330, 100),      # one row and column more
+    (9, 9000, 90),        # narrow cells, a last strip of one column
+    (9000, 12, 100),      # one row of cells
+    (400, 400, 1250),     # the smallest cells that take tables
+    (700, 500, 70),       # boxes beyond the LDS beside some that fit
+    (1200, 90, 4),        # wider than a workgroup
+]
+
+
+@pytest.mark.parametrize("wg", [0, 256, 512, 1024])
+@pytest.mark.parametrize("W,H,k", ALL_SIZES)
+def test_every_candidate_walked_over_tables(orc, W, H, k, wg):
+    """Without exact pruning: tables of one and both halves, paths outside them, every
+    fourth endpoint far off, and the sums."""
+    img = _image(W, H, 14)
+    g = orc.grid(W, H, k)
+    assert W * H >= 128 * g.num_sp and max(g.num_sp, W * H // 1024) > 96   # go to tables
+    c, e = perturbed_state(orc, g, img.lab, seed=W + H, jitter=0.4 * g.r + 1)
+    e = e.copy()
+    e[::4] = np.random.default_rng(1).integers(-9, (W + 9, H + 9), e[::4].shape)
+    s = _scalp(W, H, k, exact_pruning=0, wg_size=wg)
+    say("all candidates", W, H, k, wg)
+    C, E = dev(c), dev(e)
+    L = torch.full((H, W), -7, dtype=torch.int32, device="cuda")
+    N = torch.zeros(g.num_sp, dtype=torch.int32, device="cuda")
+    s.init_grid(dev(img.lab), dev(img.contour))          # packs; the sums are left at zero
+    s.assign_accumulate(C, E, L)
+    s.finalize(L, C, E, N, project=0)
+    ol, _, _ = orc.assign(g, img.lab, orc.wmap(img.contour), c,
+                          np.clip(e, 0, (W - 1, H - 1)).astype(np.int32))
+    assert (host(L) == ol).all(), f"{int((host(L) != ol).sum())} labels differ"
+    oc, on = orc.update(g, img.lab, ol, c, mode=orc.MEAN_FIXED)
+    assert (host(C) == oc).all() and (host(N) == on).all()
+
+
+def test_every_candidate_walked_ties_and_non_finite(orc):
+    """Ties go to the lowest slot, NaN never wins, over tables, too."""
+    W, H, k = 320, 240, 130
+    g = orc.grid(W, H, k)
+    lab = np.full((H, W, 3), 50.0, np.float32)
+    lab[120:, 160:] = 20.0
+    con = np.zeros((H, W), np.float32)
+    c, e = perturbed_state(orc, g, lab, seed=8, jitter=0.0, colour=0.0)
+    for nan in (False, True):
+        if nan:
+            lab = lab.copy()
+            lab[::17, ::13, 1] = np.nan
+        ol, _, _ = orc.assign(g, lab, orc.wmap(con), c, e, spw=orc.spatial_weight(g, 0.0))
+        s = _scalp(W, H, k, exact_pruning=0, m=0.0)
+        say("all candidates, ties", nan)
+        lbl = host(s.assign(dev(lab), dev(con), dev(c), dev(e)))
+        assert (lbl == ol).all(), f"{int((lbl != ol).sum())} labels differ"
+
+
+def test_every_candidate_walked_in_runs_and_batches(orc):
+    from paper_1903_07149_amd.scalp import ScalpBatch
+    shapes = [(200, 150, 60), (97, 61, 30), (520, 500, 250)]
+    imgs = [_image(w, h, 40 + i) for i, (w, h, _) in enumerate(shapes)]
+    refs = [orc.run(i.lab, i.contour, k, iterations=3, mode=orc.MEAN_FIXED)
+            for i, (_, _, k) in zip(imgs, shapes)]
+    for wg in (0, 256, 512, 1024):
+        say("all candidates, batch", wg)
+        b = ScalpBatch(shapes, iterations=3, exact_pruning=0, wg_size=wg)
+        l = host(b.run(dev(np.concatenate([i.lab.reshape(-1, 3) for i in imgs])),
+                       dev(np.concatenate([i.contour.reshape(-1) for i in imgs])))[2])
+        for (p0, p1, H, W), ref in zip(b.pixel_slices(), refs):
+            assert (l[p0:p1].reshape(H, W) == ref.labels).all(), (wg, W, H)
+        for (w, h, k), i, ref in zip(shapes, imgs, refs):
+            r = _scalp(w, h, k, iterations=3, exact_pruning=0, wg_size=wg).run(dev(i.lab), dev(i.contour))
+            assert (host(r.labels) == ref.labels).all() and (host(r.centers) == ref.centres).all()

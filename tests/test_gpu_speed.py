@@ -49,3 +49,14 @@ def test_far_images_keep_up_with_near_ones(mode):
     near = _run(30000, 160, 4800, iterations=5, assign_mode=mode)
     print(f"far {far:.3f} ms, near {near:.3f} ms")
     assert far < 1.5 * near
+
+
+def test_every_candidate_walked_keeps_up():
+    """exact_pruning = 0 walks nine times as many paths, in about 2.3 times the time."""
+    lab, _ = _image(1920, 1080)
+    data = lab, torch.zeros(lab.shape[:2], device="cuda")
+    say("every candidate against the pruned walks")
+    full = _run(1920, 1080, 2000, data, iterations=5, exact_pruning=0)
+    pruned = _run(1920, 1080, 2000, data, iterations=5)
+    print(f"all {full:.3f} ms, pruned {pruned:.3f} ms")
+    assert full < 4.0 * pruned
