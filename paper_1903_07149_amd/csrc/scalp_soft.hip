@@ -519,6 +519,8 @@ constexpr int kPathWG = 256, kPathWideWG = 512;
 constexpr int kBwdLists = 252;
 // Texels per thread and trip of the fold, their loads in flight together.
 constexpr int kFold = 4;
+// Fewest pairs of a run of lists that pay for a tile of their own.
+constexpr int kTilePairs = 128;
 
 // One workgroup per (image, superpixel k): every pixel whose dL/dD of the slot
 // that points at k is not zero (listed by k_soft_bwd_update under the 9 cells
@@ -528,17 +530,23 @@ constexpr int kFold = 4;
 //   dL/dw_q += cw               with cw = dL/dD * A gamma / |P|
 // (and p itself dL/dD * B lambda 2 (f_p - f_k)), so the walk only adds cf into
 // an FP64 tile S(q) (p's lambda term included) and cw into an FP32 tile of
-// dL/dw, over the box of the pixels and k's endpoint: two LDS atomics per
+// dL/dw, over a box that holds the pixels and k's endpoint: two LDS atomics per
 // sample and no texel read.  A fold over the box then forms, per texel,
 // dL/df_q = S(q) (f_q - f_k) from one texel load, and k's centre gradient,
 // -sum_q S(q) (f_q - f_k), in FP64.  The spatial part of the centre gradient
 // and the endpoint's weights (every path ends there) are summed per lane.
-// Pairs whose box exceeds the tile budget are taken by fewer lists at a time,
-// and a list by halves (it is in the order of the cell's chunks) down to 64; if
-// those still do not fit, their paths are walked from global memory, reading
-// the texels and scattering the four gradient floats with float atomics.  Every centre
-// gradient is summed here, in FP64 (no FP32 partial sum longer than one path),
-// and stored, with the terms that the update of the iteration before needs.
+//
+// Pairs whose box exceeds the tile are taken by fewer lists at a time, and a list by
+// halves (it is in the order of the cell's chunks) down to 64.  LARGE, for cells so
+// large that those seldom fit: runs of lists take a tile each, folded once however
+// many pairs it takes, as long as the box of their slices of cells fits and they have
+// pairs enough to pay for it; the lists left share one.  What does not fit either way
+// takes a tile around the endpoint, where the paths meet, and the samples before a path
+// enters it are added to global memory one by one (paths only approach the endpoint,
+// so they do not leave it again), as are all of a path too long for the
+// carry-counting steps.  Every centre gradient is summed here, in FP64 (no FP32 partial
+// sum longer than one path), and stored, with the terms that the update of the
+// iteration before needs.
 //
 // What bounds it: the latency of a superpixel's chain of phases, with the tiles
 // limiting a CU to 3 workgroups; the walks, the fold and its atomics take about
@@ -547,7 +555,9 @@ constexpr int kFold = 4;
 // workgroup per cell with a tile for each of its 9 candidates and a fold over
 // all of them took 298.  Atomics of one value of 64 texels instead of rows of
 // 16 texels' four values: 235.  Workgroups of 128 or 512 threads: 175 and 221.
-template <int WG>
+// Cells of 128x128 pixels (512x512, k = 16), 5 iterations at T = 0.5 and 5: 0.90 and
+// 1.84 ms, 4.23 and 21.1 by halves alone.
+template <int WG, bool LARGE>
 __global__ __launch_bounds__(WG) void k_soft_bwd_path(
     SoftImg s, const float4* __restrict__ packed, const float* __restrict__ theta_prev,
     const float* __restrict__ fa, const float* __restrict__ fb, const uint2* __restrict__ pairs,
@@ -558,6 +568,7 @@ __global__ __launch_bounds__(WG) void k_soft_bwd_path(
     constexpr int kWaves = WG / 64;
     __shared__ long long lbase[kBwdLists + 4];    // first entry of each list
     __shared__ int lpre[kBwdLists + 4];           // pairs in the lists before
+    __shared__ unsigned char left[kBwdLists + 4]; // the list is one of those left
     __shared__ int wtot[kWaves];
     __shared__ int wbox[4][kWaves];
     __shared__ float4 turn[kWaves][64];
@@ -574,6 +585,7 @@ __global__ __launch_bounds__(WG) void k_soft_bwd_path(
     const float cl = ck[0], ca = ck[1], cb = ck[2], cxf = ck[3], cyf = ck[4];
     const int cx = round_coord(cxf, W - 1), cy = round_coord(cyf, H - 1);
     const long long base = 9LL * s.N * b;
+    const int entries = cap_bytes / 12;
     // the lists of k: cell (ci + di, cj + dj), read under its slot (-di, -dj)
     const int lists = 9 * s.bspl;
     int n = 0;
@@ -591,83 +603,166 @@ __global__ __launch_bounds__(WG) void k_soft_bwd_path(
                          ((long long)y0 * W + (long long)x0 * ch + t0);
         }
     }
-    const int incl = wave_scan_incl(n);
-    if (lane == 63) wtot[wave] = incl;
-    __syncthreads();
-    int total = 0;
-    for (int v = 0; v < kWaves; ++v) {
-        if (v == wave && tid < lists) lpre[tid] = total + incl - n;
-        total += wtot[v];
-    }
-    total = __builtin_amdgcn_readfirstlane(total);
-    __syncthreads();
-    double gc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};     // this lane's share of dL/dTheta_k
-    const float lambda = s.lambda, oml = 1.0f - lambda;
-    // pairs a0 .. a0 + len - 1, one per lane, spread over the waves
-    const int own = lane * kWaves + wave;
-    int a0 = 0, len = min(total, WG);
-    while (a0 < total) {                          // uniform
-        const bool mine = own < len;
-        int x = cx, y = cy;
-        float gj = 0.0f, A = 0.0f, Bw = 0.0f;
-        if (mine) {
-            int l = 0, h = lists - 1;             // the last list that starts at or before it
-            while (l < h) {
-                const int m = (l + h + 1) >> 1;
-                if (lpre[m] <= a0 + own) l = m; else h = m - 1;
-            }
-            const uint2 e = pairs[lbase[l] + (a0 + own - lpre[l])];
-            const int p = (int)e.x;
-            gj = __uint_as_float(e.y);
-            const long long o = base + (long long)(8 - l / s.bspl) * s.N + p;
-            A = fa[o];
-            Bw = fb[o];
-            y = (int)((double)p * s.inv_w);
-            x = p - y * W;
-            if (x < 0) { --y; x += W; }
-            if (x >= W) { ++y; x -= W; }
-        }
-        int mnx = min(x, cx), mxx = max(x, cx), mny = min(y, cy), mxy = max(y, cy);
-        mnx = wave_min_i32(mnx);
-        mxx = wave_max_i32(mxx);
-        mny = wave_min_i32(mny);
-        mxy = wave_max_i32(mxy);
-        if (lane == 0) {
-            wbox[0][wave] = mnx;
-            wbox[1][wave] = mxx;
-            wbox[2][wave] = mny;
-            wbox[3][wave] = mxy;
+    // lpre from the lists' lengths: the number of pairs (all lanes call)
+    auto scan = [&](int len) -> int {
+        const int incl = wave_scan_incl(len);
+        if (lane == 63) wtot[wave] = incl;
+        __syncthreads();
+        int total = 0;
+        for (int v = 0; v < kWaves; ++v) {
+            if (v == wave && tid <= lists) lpre[tid] = total + incl - len;
+            total += wtot[v];
         }
         __syncthreads();
-        for (int v = 0; v < kWaves; ++v) {
-            mnx = min(mnx, wbox[0][v]);
-            mxx = max(mxx, wbox[1][v]);
-            mny = min(mny, wbox[2][v]);
-            mxy = max(mxy, wbox[3][v]);
+        return __builtin_amdgcn_readfirstlane(total);
+    };
+    const int total = scan(n);
+    // pair a: its pixel, dL/dD and the factors of its path
+    struct Pair {
+        int x, y;
+        float g, A, B;
+    };
+    auto pair_at = [&](int a) {
+        Pair q;
+        int l = 0, h = lists - 1;                 // the last list that starts at or before it
+        while (l < h) {
+            const int m = (l + h + 1) >> 1;
+            if (lpre[m] <= a) l = m; else h = m - 1;
         }
-        mnx = __builtin_amdgcn_readfirstlane(mnx);
-        mny = __builtin_amdgcn_readfirstlane(mny);
-        const int bw = __builtin_amdgcn_readfirstlane(mxx - mnx + 1);
-        const int bh = __builtin_amdgcn_readfirstlane(mxy - mny + 1);
-        const bool staged = 12LL * bw * bh <= cap_bytes;                 // uniform
-        if (!staged) {
-            // fewer: the lists that end in the first half, or else the first
-            // list, or else half of it
-            int next = a0 + len, half = a0;
-            for (int l = 0; l < lists; ++l) {
-                const int v = lpre[l];
-                if (v > a0) next = min(next, v);
-                if (v <= a0 + (len >> 1)) half = max(half, v);
+        const uint2 e = pairs[lbase[l] + (a - lpre[l])];
+        const int p = (int)e.x;
+        const long long o = base + (long long)(8 - l / s.bspl) * s.N + p;
+        q.g = __uint_as_float(e.y);
+        q.A = fa[o];
+        q.B = fb[o];
+        q.y = (int)((double)p * s.inv_w);
+        q.x = p - q.y * W;
+        if (q.x < 0) { --q.y; q.x += W; }
+        if (q.x >= W) { ++q.y; q.x -= W; }
+        return q;
+    };
+    // the box of list l's part of its cell (uniform)
+    auto list_box = [&](int l) {
+        const int nbr = l / s.bspl, slice = l - nbr * s.bspl;
+        const int jj = cj + nbr % 3 - 1, ii = ci + nbr / 3 - 1;
+        Box r;
+        r.x0 = cell_lo(jj, W, s.nx);
+        r.x1 = cell_lo(jj + 1, W, s.nx) - 1;
+        r.y0 = cell_lo(ii, H, s.ny);
+        r.y1 = cell_lo(ii + 1, H, s.ny) - 1;
+        if (s.bspl > 1) {                         // its 8-column strips
+            const int ch = r.y1 - r.y0 + 1;
+            int t0, t1;
+            bwd_slice(s, (r.x1 - r.x0 + 1) * ch, slice, t0, t1);
+            r.x1 = min(r.x1, r.x0 + 8 * ((t1 - 1) / (8 * ch)) + 7);
+            r.x0 += 8 * (t0 / (8 * ch));
+        }
+        return r;
+    };
+    auto fits = [&](const Box& r) {
+        return (long long)(r.x1 - r.x0 + 1) * (r.y1 - r.y0 + 1) <= entries;
+    };
+    double gc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};     // this lane's share of dL/dTheta_k
+    const float lambda = s.lambda, oml = 1.0f - lambda;
+    // the most square box of a tile within `box` around the endpoint
+    auto clip = [&](Box& box) {
+        const int bw = box.x1 - box.x0 + 1, bh = box.y1 - box.y0 + 1;
+        int w = min(bw, (int)sqrtf((float)entries));
+        const int h = min(bh, entries / w);
+        w = min(bw, entries / h);
+        box.x0 = min(max(cx - w / 2, box.x0), box.x1 - w + 1);
+        box.y0 = min(max(cy - h / 2, box.y0), box.y1 - h + 1);
+        box.x1 = box.x0 + w - 1;
+        box.y1 = box.y0 + h - 1;
+    };
+    const int own = lane * kWaves + wave;         // one pair per lane, spread over the waves
+    int a0 = 0, a1 = min(total, WG);              // the pairs of a tile
+    int next = 0, rest = 0;                       // LARGE: next list; pairs of the lists left
+    bool last = false;
+    while (LARGE ? !last : a0 < total) {          // uniform
+        Box box = {cx, cy, cx, cy};
+        Pair q = {cx, cy, 0.0f, 0.0f, 0.0f};
+        if constexpr (!LARGE) {
+            if (a0 + own < a1) q = pair_at(a0 + own);
+            box.add(q.x, q.y);
+            box = {wave_min_i32(box.x0), wave_min_i32(box.y0), wave_max_i32(box.x1),
+                   wave_max_i32(box.y1)};
+            if (lane == 0) {
+                wbox[0][wave] = box.x0;
+                wbox[1][wave] = box.y0;
+                wbox[2][wave] = box.x1;
+                wbox[3][wave] = box.y1;
             }
-            const int fewer = half > a0 ? half - a0 : next < a0 + len ? next - a0
-                                                    : max(64, (len >> 1) & ~63);
-            if (__builtin_amdgcn_readfirstlane(fewer) < len) {           // uniform
-                len = __builtin_amdgcn_readfirstlane(fewer);
-                __syncthreads();                  // wbox is written again
+            __syncthreads();
+            for (int v = 0; v < kWaves; ++v) {
+                box.add(wbox[0][v], wbox[1][v]);
+                box.add(wbox[2][v], wbox[3][v]);
+            }
+            box = {__builtin_amdgcn_readfirstlane(box.x0), __builtin_amdgcn_readfirstlane(box.y0),
+                   __builtin_amdgcn_readfirstlane(box.x1), __builtin_amdgcn_readfirstlane(box.y1)};
+            if (!fits(box)) {
+                // fewer: the lists that end in the first half, or else the first
+                // list, or else half of it
+                const int len = a1 - a0;
+                int first = a1, half = a0;
+                for (int l = 0; l < lists; ++l) {
+                    const int v = lpre[l];
+                    if (v > a0) first = min(first, v);
+                    if (v <= a0 + (len >> 1)) half = max(half, v);
+                }
+                const int fewer = __builtin_amdgcn_readfirstlane(
+                    half > a0 ? half - a0 : first < a1 ? first - a0 : max(64, (len >> 1) & ~63));
+                if (fewer < len) {                // uniform
+                    a1 = a0 + fewer;
+                    __syncthreads();              // wbox is written again
+                    continue;
+                }
+                clip(box);
+            }
+        } else if (next < lists) {
+            int l1 = next;
+            a0 = a1 = __builtin_amdgcn_readfirstlane(lpre[next]);
+            for (; l1 < lists; ++l1) {
+                const int end = __builtin_amdgcn_readfirstlane(lpre[l1 + 1]);
+                if (end == a1) continue;          // an empty list
+                Box r = list_box(l1);
+                r.add(box.x0, box.y0);
+                r.add(box.x1, box.y1);
+                if (!fits(r)) {
+                    if (a1 > a0) break;
+                    ++l1;                         // not even alone: left
+                    a1 = end;
+                    box.x1 = -1;
+                    break;
+                }
+                box = r;
+                a1 = end;
+            }
+            const bool taken = box.x1 >= 0 && a1 - a0 >= kTilePairs;
+            if (tid >= next && tid < l1) left[tid] = taken ? 0 : 1;
+            next = l1;
+            if (!taken) {
+                rest += a1 - a0;
                 continue;
             }
+        } else {
+            if (rest == 0) break;
+            __syncthreads();
+            const bool mine = tid < lists && n > 0 && left[tid];
+            a0 = 0;
+            a1 = scan(mine ? n : 0);
+            for (int l = 0; l < lists; ++l) {
+                if (__builtin_amdgcn_readfirstlane(lpre[l + 1]) == __builtin_amdgcn_readfirstlane(lpre[l]))
+                    continue;
+                const Box r = list_box(l);
+                box.add(r.x0, r.y0);
+                box.add(r.x1, r.y1);
+            }
+            if (!fits(box)) clip(box);
+            last = true;
         }
-        const int area = staged ? bw * bh : 0;
+        const int mnx = box.x0, mny = box.y0;
+        const int bw = box.x1 - mnx + 1, area = bw * (box.y1 - mny + 1);
         double* __restrict__ st = bwd_dyn;
         float* __restrict__ wt = reinterpret_cast<float*>(bwd_dyn + area);
         for (int e = tid; e < area; e += WG) {
@@ -676,150 +771,141 @@ __global__ __launch_bounds__(WG) void k_soft_bwd_path(
         }
         __syncthreads();
         double vc = 0.0, vw = 0.0;                // the endpoint's weights
-        if (mine) {
-            const int p = y * W + x;
+        // samples i = 0 .. n-1 of a pair's path (p itself first); the endpoint i = n is
+        // added once
+        auto walk = [&](const Pair& q) {
+            int x = q.x, y = q.y;
             const int dx = cx - x, dy = cy - y;
             const int adx = dx < 0 ? -dx : dx, ady = dy < 0 ? -dy : dy;
             const int np = max(adx, ady);
             const float inv_np = 1.0f / (float)(np + 1);
-            const float cf = 2.0f * gj * Bw * oml * inv_np;  // per sample, times (f_q - f_k)
-            const float cw_ = gj * A * s.gamma * inv_np;     // per sample: dL/dw_q
-            const float lf = 2.0f * gj * Bw * lambda;        // lambda term of p
-            gc[3] += (double)(-2.0f * gj * s.spw * ((float)x - cxf));
-            gc[4] += (double)(-2.0f * gj * s.spw * ((float)y - cyf));
+            const float cf = 2.0f * q.g * q.B * oml * inv_np;  // per sample, times (f_q - f_k)
+            const float cw_ = q.g * q.A * s.gamma * inv_np;    // per sample: dL/dw_q
+            const float lf = 2.0f * q.g * q.B * lambda;        // lambda term of p
+            gc[3] += (double)(-2.0f * q.g * s.spw * ((float)x - cxf));
+            gc[4] += (double)(-2.0f * q.g * s.spw * ((float)y - cyf));
             const bool xmaj = adx >= ady;
-            if (staged) {                                    // uniform
-                // samples i = 0 .. n-1 (p itself first); the endpoint i = n
-                // is added once per superpixel
-                const int stx = dx < 0 ? -1 : 1, sty = dy < 0 ? -bw : bw;
-                const int smaj = xmaj ? stx : sty, sdiag = stx + sty;
-                int ls = (y - mny) * bw + (x - mnx);
-                const double cfd = (double)cf;
-                if (np > 0) {
-                    atomicAdd(&st[ls], cfd + (double)lf);
+            const int am = xmaj ? ady : adx;
+            const double cfd = (double)cf;
+            double first = cfd + (double)lf;
+            int m = 0;
+            int rem = np;
+            while (m < np && (x < box.x0 || x > box.x1 || y < box.y0 || y > box.y1 || np >= 46340)) {
+                const int g = y * W + x;
+                const float4 fq = img[g];
+                const double el = first * (double)(fq.x - cl), ea = first * (double)(fq.y - ca),
+                             eb = first * (double)(fq.z - cb);
+                unsafeAtomicAdd(&gimg[g].x, (float)el);
+                unsafeAtomicAdd(&gimg[g].y, (float)ea);
+                unsafeAtomicAdd(&gimg[g].z, (float)eb);
+                unsafeAtomicAdd(&gimg[g].w, cw_);
+                gc[0] -= el;
+                gc[1] -= ea;
+                gc[2] -= eb;
+                first = cfd;
+                ++m;
+                rem += 2 * am;
+                const bool step = rem >= 2 * np;
+                rem -= step ? 2 * np : 0;
+                x += xmaj || step ? (dx < 0 ? -1 : 1) : 0;
+                y += !xmaj || step ? (dy < 0 ? -1 : 1) : 0;
+            }
+            const int stx = dx < 0 ? -1 : 1, sty = dy < 0 ? -bw : bw;
+            const int smaj = xmaj ? stx : sty, sdiag = stx + sty;
+            int ls = (y - mny) * bw + (x - mnx);
+            if (m < np) {
+                atomicAdd(&st[ls], first);
+                atomicAdd(&wt[ls], cw_);
+                const unsigned F = step_increment(am, np);
+                // (after m steps; modulo 2^32, as the steps before would have left it)
+                unsigned acc = 0x80000000u + (unsigned)m * F;
+                for (++m; m < np; ++m) {
+                    const bool cr = __builtin_add_overflow(acc, F, &acc);
+                    ls += cr ? sdiag : smaj;
+                    atomicAdd(&st[ls], cfd);
                     atomicAdd(&wt[ls], cw_);
-                    const unsigned F = step_increment(xmaj ? ady : adx, np);
-                    unsigned acc = 0x80000000u;
-                    for (int m = 1; m < np; ++m) {
-                        const bool cr = __builtin_add_overflow(acc, F, &acc);
-                        ls += cr ? sdiag : smaj;
-                        atomicAdd(&st[ls], cfd);
-                        atomicAdd(&wt[ls], cw_);
-                    }
-                } else {
-                    atomicAdd(&st[ls], (double)lf);
                 }
-                vc += cfd;
-                vw += (double)cw_;
-            } else {                                         // scatter to global memory
-                float gk[3] = {0.0f, 0.0f, 0.0f};
-                const float4 fp = img[p];
-                const float dl = fp.x - cl, da = fp.y - ca, db = fp.z - cb;
-                gk[0] -= lf * dl;
-                gk[1] -= lf * da;
-                gk[2] -= lf * db;
-                const int am = xmaj ? ady : adx;
-                const int two_n = 2 * np, inc = 2 * am;
-                int rem = np;
-                const int stx = dx < 0 ? -1 : 1, sty = dy < 0 ? -W : W;
-                const int smaj = xmaj ? stx : sty;
-                const int sdiag = stx + sty;
-                int gi = p;
-                unsafeAtomicAdd(&gimg[gi].x, lf * dl);
-                unsafeAtomicAdd(&gimg[gi].y, lf * da);
-                unsafeAtomicAdd(&gimg[gi].z, lf * db);
-                for (int m = 0; m <= np; ++m) {
-                    if (m > 0) {
-                        rem += inc;
-                        const bool step = rem >= two_n;
-                        rem -= step ? two_n : 0;
-                        gi += step ? sdiag : smaj;
-                    }
-                    const float4 fq = img[gi];
-                    const float el = cf * (fq.x - cl), ea = cf * (fq.y - ca),
-                                eb = cf * (fq.z - cb);
-                    unsafeAtomicAdd(&gimg[gi].x, el);
-                    unsafeAtomicAdd(&gimg[gi].y, ea);
-                    unsafeAtomicAdd(&gimg[gi].z, eb);
-                    unsafeAtomicAdd(&gimg[gi].w, cw_);
-                    gk[0] -= el;
-                    gk[1] -= ea;
-                    gk[2] -= eb;
-                }
-#pragma unroll
-                for (int v = 0; v < 3; ++v) gc[v] += (double)gk[v];
+            } else if (np == 0) {
+                atomicAdd(&st[ls], (double)lf);
+            }
+            vc += cfd;
+            vw += (double)cw_;
+        };
+        if constexpr (LARGE) {
+            for (int a = a0 + own; a < a1; a += WG) walk(pair_at(a));
+        } else if (a0 + own < a1) {
+            walk(q);
+        }
+        if (a0 + wave < a1) {                                // uniform: this wave walked
+            vc = wave_sum_f64(vc);
+            vw = wave_sum_f64(vw);
+            const int e = (cy - mny) * bw + (cx - mnx);
+            if (lane == 0) {
+                atomicAdd(&st[e], vc);
+                atomicAdd(&wt[e], (float)vw);
             }
         }
-        if (staged) {                                        // uniform
-            if (wave < len) {                                // uniform: this wave walked
-                vc = wave_sum_f64(vc);
-                vw = wave_sum_f64(vw);
-                const int e = (cy - mny) * bw + (cx - mnx);
-                if (lane == 0) {
-                    atomicAdd(&st[e], vc);
-                    atomicAdd(&wt[e], (float)vw);
-                }
+        __syncthreads();
+        // the fold
+        const int dr = WG / bw, dc = WG - dr * bw;
+        int r = tid / bw, c = tid - r * bw;
+        for (int e0 = 0; e0 < area; e0 += kFold * WG) {      // uniform: every lane stays
+            double sv[kFold];
+            float wv[kFold];
+            float4 f[kFold];
+            int p[kFold];
+#pragma unroll
+            for (int u = 0; u < kFold; ++u) {
+                const int e = e0 + tid + u * WG;
+                sv[u] = e < area ? st[e] : 0.0;
+                wv[u] = e < area ? wt[e] : 0.0f;
+                p[u] = (mny + r) * W + mnx + c;
+                c += dc;
+                const bool wrap = c >= bw;
+                c -= wrap ? bw : 0;
+                r += dr + (wrap ? 1 : 0);
             }
-            __syncthreads();
-            // the fold
-            const int dr = WG / bw, dc = WG - dr * bw;
-            int r = tid / bw, c = tid - r * bw;
-            for (int e0 = 0; e0 < area; e0 += kFold * WG) {   // uniform: every lane stays
-                double sv[kFold];
-                float wv[kFold];
-                float4 f[kFold];
-                int p[kFold];
 #pragma unroll
-                for (int u = 0; u < kFold; ++u) {
-                    const int e = e0 + tid + u * WG;
-                    sv[u] = e < area ? st[e] : 0.0;
-                    wv[u] = e < area ? wt[e] : 0.0f;
-                    p[u] = (mny + r) * W + mnx + c;
-                    c += dc;
-                    const bool wrap = c >= bw;
-                    c -= wrap ? bw : 0;
-                    r += dr + (wrap ? 1 : 0);
+            for (int u = 0; u < kFold; ++u)
+                if (sv[u] != 0.0 || wv[u] != 0.0f) f[u] = img[p[u]];
+#pragma unroll
+            for (int u = 0; u < kFold; ++u) {
+                if (__ballot(sv[u] != 0.0 || wv[u] != 0.0f) == 0ULL) continue;   // uniform
+                float4 d = make_float4(0.0f, 0.0f, 0.0f, wv[u]);
+                if (sv[u] != 0.0) {
+                    const double el = sv[u] * (double)(f[u].x - cl);
+                    const double ea = sv[u] * (double)(f[u].y - ca);
+                    const double eb = sv[u] * (double)(f[u].z - cb);
+                    gc[0] -= el;
+                    gc[1] -= ea;
+                    gc[2] -= eb;
+                    d.x = (float)el;
+                    d.y = (float)ea;
+                    d.z = (float)eb;
                 }
+                // through LDS, so that an atomic instruction adds the four
+                // values of 16 neighbouring texels, 256 bytes in a row,
+                // and not one value of 64 texels
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                turn[wave][lane] = d;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-                for (int u = 0; u < kFold; ++u)
-                    if (sv[u] != 0.0 || wv[u] != 0.0f) f[u] = img[p[u]];
-#pragma unroll
-                for (int u = 0; u < kFold; ++u) {
-                    if (__ballot(sv[u] != 0.0 || wv[u] != 0.0f) == 0ULL) continue;   // uniform
-                    float4 d = make_float4(0.0f, 0.0f, 0.0f, wv[u]);
-                    if (sv[u] != 0.0) {
-                        const double el = sv[u] * (double)(f[u].x - cl);
-                        const double ea = sv[u] * (double)(f[u].y - ca);
-                        const double eb = sv[u] * (double)(f[u].z - cb);
-                        gc[0] -= el;
-                        gc[1] -= ea;
-                        gc[2] -= eb;
-                        d.x = (float)el;
-                        d.y = (float)ea;
-                        d.z = (float)eb;
-                    }
-                    // through LDS, so that an atomic instruction adds the four
-                    // values of 16 neighbouring texels, 256 bytes in a row,
-                    // and not one value of 64 texels
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    turn[wave][lane] = d;
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int from = 16 * v + (lane >> 2);
-                        const float val = reinterpret_cast<const float*>(&turn[wave][from])[lane & 3];
-                        const int q = __shfl(p[u], from, 64);
-                        if (val != 0.0f)
-                            unsafeAtomicAdd(reinterpret_cast<float*>(gimg + q) + (lane & 3), val);
-                    }
+                for (int v = 0; v < 4; ++v) {
+                    const int from = 16 * v + (lane >> 2);
+                    const float val = reinterpret_cast<const float*>(&turn[wave][from])[lane & 3];
+                    const int q = __shfl(p[u], from, 64);
+                    if (val != 0.0f)
+                        unsafeAtomicAdd(reinterpret_cast<float*>(gimg + q) + (lane & 3), val);
                 }
             }
         }
-        a0 += len;
-        len = min(total - a0, WG);
+        if constexpr (!LARGE) {
+            a0 = a1;
+            a1 = min(total, a0 + WG);
+        }
         __syncthreads();                          // wbox and the tiles are written again
     }
     // dL/dTheta_{t-1}: the pass-through of a superpixel whose soft mass was
@@ -933,7 +1019,8 @@ static SoftImg to_img(const SoftGeom& g) {
 }
 
 void lift_soft_lds_limits() {
-    for (const auto kernel : {k_soft_bwd_path<kPathWG>, k_soft_bwd_path<kPathWideWG>})
+    for (const auto kernel : {k_soft_bwd_path<kPathWG, false>, k_soft_bwd_path<kPathWideWG, false>,
+                              k_soft_bwd_path<kPathWG, true>, k_soft_bwd_path<kPathWideWG, true>})
         static_cast<void>(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                               hipFuncAttributeMaxDynamicSharedMemorySize,
                                               kBwdLdsBytes));
@@ -998,7 +1085,12 @@ int launch_soft_bwd_path(const SoftGeom& g, const float4* packed, const float* t
     const SoftImg s = to_img(g);
     const int cap = path_lds_bytes(g, cap_bytes);
     const bool wide = (long long)s.B * s.K <= 2 * kCUs;
-    const auto kernel = wide ? k_soft_bwd_path<kPathWideWG> : k_soft_bwd_path<kPathWG>;
+    // (512x512 pixels in cells of 51x51, 5 iterations at T = 0.5 and 5: 0.35 and 1.22 ms
+    // LARGE, 0.36 and 1.29 else; four 256x256 in cells of 57x57 0.45 and 0.87, 0.70 and
+    // 1.46; 512x512 in cells of 26x26 0.23 and 0.67, 0.20 and 0.66)
+    const bool large = 1.75 * g.W / g.nx * g.H / g.ny > cap / 12;
+    const auto kernel = large ? wide ? k_soft_bwd_path<kPathWideWG, true> : k_soft_bwd_path<kPathWG, true>
+                        : wide ? k_soft_bwd_path<kPathWideWG, false> : k_soft_bwd_path<kPathWG, false>;
     hipLaunchKernelGGL(kernel, dim3(s.B * s.K), dim3(wide ? kPathWideWG : kPathWG), (size_t)cap, st, s,
                        packed, theta_prev, fa, fb, pairs, count, z, gth, z_prev, gth_prev, cand,
                        gf, cap);

@@ -338,3 +338,25 @@ def test_soft_full_size_workload(orc):
     assert compare_forward(c_t[:, i:i + 1], q_t[:, i:i + 1], th_o, q_o, 512, 512) == 5
     assert_grads(orc, lab[i:i + 1], con[i:i + 1], 400, gq[i:i + 1], gth[i:i + 1], 5, 0.5,
                  glab[i:i + 1], gcon[i:i + 1])
+
+
+@pytest.mark.parametrize("W,H,k,T,lds", [
+    (240, 240, 9, 0.5, 0),      # 80x80-pixel cells: few pairs, most of them far from the endpoint
+    (240, 240, 9, 50.0, 0),     # many pairs: lists with tiles of their own, and the rest
+    (300, 60, 2, 50.0, 0),      # a tile cut off by the image
+    (60, 60, 25, 500.0, 200),   # small cells: halves of 64 pairs that still do not fit
+])
+def test_soft_backward_tiles_around_the_endpoint(orc, W, H, k, T, lds):
+    """Paths that are longer than any tile: their outer samples go to global memory."""
+    iters = 2
+    lab, con = _batch(1, (W, H), 6, 740)
+    rng = np.random.default_rng(8)
+    K = orc.grid(W, H, k).num_sp
+    gq = rng.normal(0, 1, (1, 9, H, W)).astype(np.float32)
+    gth = rng.normal(0, 1, (1, K, 5)).astype(np.float32)
+    eng = _engine(W, H, k, 1, T, iters, lds_pixels=lds)
+    L, C = dev(lab), dev(con)
+    say("soft backward around the endpoint", W, H, k, T, lds)
+    c_t, q_t, saved = eng.forward(L, C)
+    glab, gcon = (host(t) for t in eng.backward(L, C, c_t, q_t, saved, dev(gq), dev(gth)))
+    assert_grads(orc, lab, con, k, gq, gth, iters, T, glab, gcon)

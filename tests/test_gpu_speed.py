@@ -60,3 +60,18 @@ def test_every_candidate_walked_keeps_up():
     pruned = _run(1920, 1080, 2000, data, iterations=5)
     print(f"all {full:.3f} ms, pruned {pruned:.3f} ms")
     assert full < 4.0 * pruned
+
+
+def test_soft_backward_of_large_cells_keeps_up():
+    """512x512 in 16 cells at T = 5: the backward takes about as long as the forward."""
+    from paper_1903_07149_amd.soft import SoftScalp
+    lab, con = (a[None].contiguous() for a in _image(512, 512))
+    e = SoftScalp(512, 512, 16, 1, temperature=5.0, iterations=2)
+    gq, gt = torch.ones((1, 9, 512, 512), device="cuda"), torch.ones((1, e.K, 5), device="cuda")
+    gq[:, 4] = -1.0
+    say("soft large cells, time")
+    ct, q, saved = e.forward(lab, con)
+    fwd = _time(lambda: e.forward(lab, con))
+    bwd = _time(lambda: e.backward(lab, con, ct, q, saved, gq, gt))
+    print(f"forward {fwd:.3f} ms, backward {bwd:.3f} ms")
+    assert bwd < 4.0 * fwd
