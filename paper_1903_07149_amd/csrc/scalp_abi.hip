@@ -642,13 +642,6 @@ int scalp_batched_graph_create(const scalp_batch_desc_t* descs, int32_t n, const
 
 namespace {
 
-// 512 lanes where there are no more cells than compute units (2 x 97x61, T = 5: 14.4
-// us per assignment at 256, 13.3 at 512, 13.9 at 1024; 2 x 256x256, k = 128: 34, 31,
-// 40).
-int soft_wg(const scalp_grid_t* g, const scalp_params_t* p, long long batch) {
-    return p->wg_size != 0 ? p->wg_size : batch * g->num_sp <= kCUs ? 512 : 256;
-}
-
 // saved: [A: T][B][9][N] float, [Bf: T][B][9][N] float, [Z: T][B][K] double,
 // [masks of the Q that are not 0: T][B][N] uint16
 struct SoftSaved {
@@ -736,8 +729,7 @@ int scalp_soft_forward(const scalp_grid_t* g, const scalp_params_t* p, float tem
     const int T = p->iterations;
     const Img im = image_of(g, p);
     const SoftGeom geo = soft_geom(g->width, g->height, g->nx, g->ny, batch, im.spw, im.gamma,
-                                   p->lambda, temperature, soft_wg(g, p, batch),
-                                   p->exact_pruning);
+                                   p->lambda, temperature, p->wg_size, p->exact_pruning);
     const SoftSaved S = soft_saved_layout(g, B, T);
     char* wb = static_cast<char*>(ws);
     char* sb = static_cast<char*>(saved);
@@ -779,8 +771,7 @@ int scalp_soft_backward(const scalp_grid_t* g, const scalp_params_t* p, float te
     const int T = p->iterations;
     const Img im = image_of(g, p);
     const SoftGeom geo = soft_geom(g->width, g->height, g->nx, g->ny, batch, im.spw, im.gamma,
-                                   p->lambda, temperature, soft_wg(g, p, batch),
-                                   p->exact_pruning);
+                                   p->lambda, temperature, p->wg_size, p->exact_pruning);
     const SoftSaved S = soft_saved_layout(g, B, T);
     char* wb = static_cast<char*>(ws);
     const char* sb = static_cast<const char*>(saved);

@@ -192,7 +192,7 @@ int launch_finalize_batched(const Img* imgs, const int* sp_start, int n_img, int
 // ---- soft SCALP (scalp_soft.hip)
 struct SoftGeom {
     int W, H, nx, ny, B;
-    int wg;   // workgroup size of the path kernels (256, 512 or 1024)
+    int wg;   // workgroup size of the forward's assignment (0: chosen, 256, 512 or 1024)
     float spw, gamma, lambda, temperature;
     int prune;  // 1: skip the walks of slots whose softmax weight is provably 0
 };

@@ -28,6 +28,7 @@
 //                      and dL/dw (float atomics: not bit-reproducible) and the
 //                      superpixel's centre gradient (FP64).
 #include <algorithm>
+#include <climits>
 
 #include "scalp_device.h"
 
@@ -38,7 +39,7 @@ using namespace dev;
 
 struct SoftImg {
     int W, H, nx, ny, K, B;
-    int spl;    // work items (slices) per cell of the path kernels
+    int spl;    // work items (slices) per cell of the assignment
     long long N;
     float spw, gamma, lambda, inv_t;
     double temp;
@@ -99,6 +100,80 @@ struct SoftItem {
     int pairs, multis;
 };
 
+// Q_pj = softmax_j(-D_pj / T) in FP64, rounded once to FP32 (the FP32 distances differ
+// by far more than FP32's exponent range allows at small T).  A slot with (D - Dmin) /
+// T > 110 has exp < 2^-158: added to the sum (at least 1, the minimum's term) it
+// changes nothing in FP64, and its Q rounds to 0 in FP32, so neither the exponential
+// nor the quotient is computed (same results, most slots at low T).
+__device__ __forceinline__ void softmax(float (&v)[9], double temp) {
+    float dmin = INFINITY;
+#pragma unroll
+    for (int j = 0; j < 9; ++j) dmin = fminf(dmin, v[j]);
+    double e[9], sum = 0.0;
+#pragma unroll
+    for (int j = 0; j < 9; ++j) {
+        e[j] = 0.0;
+        if (v[j] < INFINITY) {
+            const double t = ((double)v[j] - (double)dmin) / temp;
+            if (t <= 110.0) e[j] = exp(-t);
+        }
+        sum += e[j];
+    }
+#pragma unroll
+    for (int j = 0; j < 9; ++j) v[j] = e[j] == 0.0 ? 0.0f : (float)(e[j] / sum);
+}
+
+// What a slot's bound must exceed to prove that its Q is 0, where the pixel has a
+// candidate with D = best (see k_soft_assign).
+__device__ __forceinline__ float soft_limit(float best, double temp) {
+    return fmaxf((best + 111.0f * (float)temp) * (1.0f + 0x1p-15f), 0x1p-70f);
+}
+
+// A work item: pixels [t0, t1) of a cell of image b.
+struct SoftCell {
+    int b, ci, cj, x0, y0, cw, ch, t0, t1;
+};
+
+__device__ __forceinline__ SoftCell soft_cell(const SoftImg& s, int item) {
+    SoftCell c;
+    const int bc = item / s.spl, slice = item - bc * s.spl;
+    c.b = bc / s.K;
+    const int cell = bc - c.b * s.K;
+    c.ci = cell / s.nx;
+    c.cj = cell - c.ci * s.nx;
+    c.x0 = cell_lo(c.cj, s.W, s.nx);
+    c.y0 = cell_lo(c.ci, s.H, s.ny);
+    c.cw = cell_lo(c.cj + 1, s.W, s.nx) - c.x0;
+    c.ch = cell_lo(c.ci + 1, s.H, s.ny) - c.y0;
+    const int P = c.cw * c.ch, chunks = (P + 63) >> 6;
+    c.t0 = 64 * (int)((long long)chunks * slice / s.spl);
+    c.t1 = min(P, 64 * (int)((long long)chunks * (slice + 1) / s.spl));
+    return c;
+}
+
+template <bool NEAR>
+__device__ __forceinline__ Eqs soft_eqs(const SoftImg& s, const SoftCell& c, const Neighbours& nb,
+                                        const float4* __restrict__ img,
+                                        const float* __restrict__ cen) {
+    Eqs eqs;
+    eqs.img = img;
+    eqs.W = s.W;
+    near_all(eqs);
+    if (!NEAR) {
+        Box box = {c.x0, c.y0, c.x0 + c.cw - 1, c.y0 + c.ch - 1};
+        for (int j = 0; j < 9; ++j) {
+            const ConstF k = (ConstF)(uintptr_t)cen + 5LL * (nb.row[j / 3] + nb.col[j % 3]);
+            box.add(round_coord(k[3], s.W - 1), round_coord(k[4], s.H - 1));
+        }
+        near_box(eqs, box);
+    }
+    eqs.lambda = s.lambda;
+    eqs.oml = 1.0f - s.lambda;
+    eqs.gamma = s.gamma;
+    eqs.spw = s.spw;
+    return eqs;
+}
+
 // One workgroup per (image, cell, slice) work item, one pixel per lane, in two
 // passes of walks as in the hard assignment (process_cell), and the softmax.
 // The softmax gives a slot Q = 0 exactly when (D - Dmin) / T > 110 in FP64.
@@ -117,44 +192,20 @@ struct SoftItem {
 // The update's sums could be taken here too, as FP64 matrix products of the Q
 // and the features of each wave's pixels, but in another order than the
 // gather's, and one centre in 10^5 then rounds to the other FP32 neighbour.
-template <int WG>
+template <int WG, bool NEAR>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_soft_assign(
     SoftImg s, const float4* __restrict__ packed, const float* __restrict__ theta_prev,
     float* __restrict__ q, float* __restrict__ fa, float* __restrict__ fb,
     unsigned short* __restrict__ pmask) {
     __shared__ SoftItem<WG> sh;
-    const int item = xcd_remap(blockIdx.x, gridDim.x);
-    const int bc = item / s.spl, slice = item - bc * s.spl;
-    const int b = bc / s.K, cell = bc - b * s.K;
-    const int tid = threadIdx.x;
+    const SoftCell it = soft_cell(s, xcd_remap(blockIdx.x, gridDim.x));
+    if (it.t1 <= it.t0) return;                                 // uniform: an empty slice
+    const int tid = threadIdx.x, b = it.b, ci = it.ci, cj = it.cj;
     const int W = s.W, H = s.H;
-    const int ci = cell / s.nx, cj = cell - ci * s.nx;
-    const int x0 = cell_lo(cj, W, s.nx), x1 = cell_lo(cj + 1, W, s.nx);
-    const int y0 = cell_lo(ci, H, s.ny), y1 = cell_lo(ci + 1, H, s.ny);
-    const int cw = x1 - x0, ch = y1 - y0, P = cw * ch;
-    const int chunks = (P + 63) >> 6;
-    const int t0 = 64 * (int)((long long)chunks * slice / s.spl);
-    const int t1 = min(P, 64 * (int)((long long)chunks * (slice + 1) / s.spl));
-    if (t1 <= t0) return;                                       // uniform: an empty slice
     const float4* __restrict__ img = packed + (long long)b * s.N;
     const float* __restrict__ cen = theta_prev + 5LL * s.K * b;
     const Neighbours nb = neighbours_of(s.nx, s.ny, ci, cj);
-    Eqs eqs;
-    eqs.img = img;
-    eqs.W = W;
-    near_all(eqs);
-    if (!s.near) {                                              // uniform
-        Box box = {x0, y0, x1 - 1, y1 - 1};
-        for (int j = 0; j < 9; ++j) {
-            const ConstF c = (ConstF)(uintptr_t)cen + 5LL * (nb.row[j / 3] + nb.col[j % 3]);
-            box.add(round_coord(c[3], W - 1), round_coord(c[4], H - 1));
-        }
-        near_box(eqs, box);
-    }
-    eqs.lambda = s.lambda;
-    eqs.oml = 1.0f - s.lambda;
-    eqs.gamma = s.gamma;
-    eqs.spw = s.spw;
+    const Eqs eqs = soft_eqs<NEAR>(s, it, nb, img, cen);
     const int k0 = (ci - 1) * s.nx + cj - 1;
     const long long base = 9LL * s.N * b;
     // D of pixel (px, py) with texel fp to slot j, its factors saved unless the
@@ -173,20 +224,18 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_
         }
         return D;
     };
-    auto limit = [&](float best) -> float {
-        return fmaxf((best + 111.0f * (float)s.temp) * (1.0f + 0x1p-15f), 0x1p-70f);
-    };
+    auto limit = [&](float best) { return soft_limit(best, s.temp); };
     if (tid == 0) sh.pairs = sh.multis = 0;
     __syncthreads();
     const bool prune = s.prune != 0;
-    const bool mine = tid < t1 - t0;
+    const bool mine = tid < it.t1 - it.t0;
     int px = 0, py = 0, first = 9;
     float D = INFINITY;
     bool again = false;
     if (mine) {
-        pixel_at(pixel_map(s.dper, cw, ch), t0 + tid, px, py);
-        px += x0;
-        py += y0;
+        pixel_at(pixel_map(s.dper, it.cw, it.ch), it.t0 + tid, px, py);
+        px += it.x0;
+        py += it.y0;
         unsigned key[9];
         const float4 fp = img[py * W + px];
         bound_keys(nb, (ConstF)(uintptr_t)cen, s.spw, fp, px, py, s.lambda, key);
@@ -230,32 +279,14 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_
         sh.D[j][id] = distance(j, img[xy.y * W + xy.x], xy.x, xy.y, cut, limit(sh.best[id]));
     }
     __syncthreads();
-    // Q_pj = softmax_j(-D_pj / T) in FP64, rounded once to FP32 (the FP32
-    // distances differ by far more than FP32's exponent range allows at small
-    // T).  A slot with (D - Dmin) / T > 110 has exp < 2^-158: added to the sum
-    // (at least 1, the minimum's term) it changes nothing in FP64, and its Q
-    // rounds to 0 in FP32, so neither the exponential nor the quotient is
-    // computed (same results, most slots at low T).
     if (tid < sh.multis) {
         const int id = (int)sh.multi[tid];
-        float v[9], dmin = INFINITY;
+        float v[9];
 #pragma unroll
-        for (int j = 0; j < 9; ++j) {
-            v[j] = sh.D[j][id];
-            dmin = fminf(dmin, v[j]);
-        }
-        double e[9], sum = 0.0;
+        for (int j = 0; j < 9; ++j) v[j] = sh.D[j][id];
+        softmax(v, s.temp);
 #pragma unroll
-        for (int j = 0; j < 9; ++j) {
-            e[j] = 0.0;
-            if (v[j] < INFINITY) {
-                const double t = ((double)v[j] - (double)dmin) / s.temp;
-                if (t <= 110.0) e[j] = exp(-t);
-            }
-            sum += e[j];
-        }
-#pragma unroll
-        for (int j = 0; j < 9; ++j) sh.D[j][id] = e[j] == 0.0 ? 0.0f : (float)(e[j] / sum);
+        for (int j = 0; j < 9; ++j) sh.D[j][id] = v[j];
     }
     __syncthreads();
     if (mine) {
@@ -268,6 +299,129 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_
             mask |= Q != 0.0f ? 1u << j : 0u;
         }
         pmask[(long long)b * s.N + (long long)py * W + px] = (unsigned short)mask;
+    }
+}
+
+// Per work item of k_soft_tables: D by slot and pixel, and a candidate's table or two
+// of half the size; 72 bytes a lane in all (see TableShared).
+template <int WG>
+struct SoftTables {
+    static constexpr int kEntries = (9 * WG - 8) / 2;
+    float D[9][WG];
+    float2 table[kEntries];
+    int box[4];
+};
+
+// The same results as k_soft_assign where most pixels walk most candidates (see
+// soft_tables): candidate by candidate, own cell first, then edges, then corners, over
+// LDS tables as in the hard form's assign_all, one pixel per lane; a candidate
+// whose bound proves that its Q is 0 is left out.
+//
+// What bounds it: VALU issue.
+template <int WG, bool NEAR>
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_soft_tables(
+    SoftImg s, const float4* __restrict__ packed, const float* __restrict__ theta_prev,
+    float* __restrict__ q, float* __restrict__ fa, float* __restrict__ fb,
+    unsigned short* __restrict__ pmask) {
+    __shared__ SoftTables<WG> sh;
+    const SoftCell it = soft_cell(s, xcd_remap(blockIdx.x, gridDim.x));
+    if (it.t1 <= it.t0) return;                                 // uniform: an empty slice
+    const int tid = threadIdx.x;
+    const int W = s.W, H = s.H;
+    const float4* __restrict__ img = packed + (long long)it.b * s.N;
+    const float* __restrict__ cen = theta_prev + 5LL * s.K * it.b;
+    const Neighbours nb = neighbours_of(s.nx, s.ny, it.ci, it.cj);
+    const Eqs eqs = soft_eqs<NEAR>(s, it, nb, img, cen);
+    if (tid == 0) {
+        sh.box[0] = sh.box[1] = INT_MAX;
+        sh.box[2] = sh.box[3] = 0;
+    }
+    __syncthreads();
+    const bool mine = tid < it.t1 - it.t0;
+    int px = INT_MAX, py = INT_MAX;
+    if (mine) {
+        pixel_at(pixel_map(s.dper, it.cw, it.ch), it.t0 + tid, px, py);
+        px += it.x0;
+        py += it.y0;
+    }
+    {
+        const int lx = wave_min_i32(px), ly = wave_min_i32(py);
+        const int hx = wave_max_i32(mine ? px : 0), hy = wave_max_i32(mine ? py : 0);
+        if ((tid & 63) == 0) {
+            atomicMin(&sh.box[0], lx);
+            atomicMin(&sh.box[1], ly);
+            atomicMax(&sh.box[2], hx);
+            atomicMax(&sh.box[3], hy);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 9; ++j) sh.D[j][tid] = INFINITY;
+    __syncthreads();
+    const Box own = {__builtin_amdgcn_readfirstlane(sh.box[0]), __builtin_amdgcn_readfirstlane(sh.box[1]),
+                     __builtin_amdgcn_readfirstlane(sh.box[2]), __builtin_amdgcn_readfirstlane(sh.box[3])};
+    const long long o = 9LL * s.N * it.b + (long long)py * W + px;
+    const int k0 = (it.ci - 1) * s.nx + it.cj - 1;
+    const bool prune = s.prune != 0, cut = prune && s.gamma <= 0x1p40f;
+    float best = INFINITY;
+    bool half = false, was_full = false;                        // uniform
+#pragma unroll 1
+    for (int i = 0; i < 9; ++i) {
+        const int j = (int)((0x862075314ULL >> (4 * i)) & 15ULL);   // 4, 1, 3, 5, 7, 0, 2, 6, 8
+        if (!((nb.inside >> j) & 1u)) continue;                 // uniform
+        const int di = (j * 11) >> 5;
+        const ConstF cp = (ConstF)(uintptr_t)cen + 5 * (k0 + di * s.nx + (j - 3 * di));
+        const float ck[5] = {cp[0], cp[1], cp[2], cp[3], cp[4]};
+        const int cx = __builtin_amdgcn_readfirstlane(round_coord(ck[3], W - 1));
+        const int cy = __builtin_amdgcn_readfirstlane(round_coord(ck[4], H - 1));
+        Box box = own;
+        box.add(cx, cy);
+        const Table t = table_of(box, SoftTables<WG>::kEntries, WG);
+        if (t.fits) {
+            const bool full = t.pitch * t.rows > SoftTables<WG>::kEntries / 2;
+            if (full || was_full) __syncthreads();              // the table before was read
+            half = !half && !full;
+            was_full = full;
+        }
+        float2* table = sh.table + (half ? SoftTables<WG>::kEntries / 2 : 0);
+        if (t.fits) {
+            fill_table<WG>(table, t, img, W, ck[0], ck[1], ck[2]);
+            __syncthreads();
+        }
+        if (!mine) continue;
+        float4 fp = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        float dcp;
+        if (t.fits) {                                           // uniform
+            dcp = table[(py - t.y0) * t.pitch + (px - t.x0)].x;
+        } else {
+            fp = img[py * W + px];
+            dcp = colour_dist(fp, ck[0], ck[1], ck[2]);
+        }
+        const float ax = (float)px - ck[3], ay = (float)py - ck[4];
+        const float lb = s.lambda * dcp + (ax * ax + ay * ay) * s.spw;   // <= D
+        if (prune && lb > soft_limit(best, s.temp)) continue;
+        float A, B;
+        const float D = t.fits ? table_distance(eqs, ck, t, table, cx, cy, px, py, A, B)
+                               : path_distance(eqs, ck, fp, cx, cy, px, py, cut,
+                                               soft_limit(best, s.temp), A, B);
+        if (D < INFINITY) {
+            sh.D[j][tid] = D;
+            fa[o + (long long)j * s.N] = A;
+            fb[o + (long long)j * s.N] = B;
+            best = fminf(best, D);
+        }
+    }
+    if (mine) {
+        float v[9];
+#pragma unroll
+        for (int j = 0; j < 9; ++j) v[j] = sh.D[j][tid];
+        softmax(v, s.temp);
+        unsigned mask = 0;
+#pragma unroll
+        for (int j = 0; j < 9; ++j) {
+            q[o + (long long)j * s.N] = v[j];
+            mask |= v[j] != 0.0f ? 1u << j : 0u;
+        }
+        pmask[(long long)it.b * s.N + (long long)py * W + px] = (unsigned short)mask;
     }
 }
 
@@ -1004,7 +1158,7 @@ static SoftImg to_img(const SoftGeom& g) {
     SoftImg s;
     s.W = g.W; s.H = g.H; s.nx = g.nx; s.ny = g.ny; s.K = g.nx * g.ny; s.B = g.B;
     s.N = (long long)g.W * g.H;
-    s.spl = assign_slices(g.W, g.H, g.nx, g.ny, g.wg, fill_slices((long long)g.B * s.K));
+    s.spl = 0;
     s.near = s.N < (1LL << 28) && g.W + g.H < 46340;
     s.bspl = soft_bwd_slices(g.W, g.H, g.nx, g.ny);
     s.inv_w = 1.0 / (double)g.W;
@@ -1035,19 +1189,59 @@ int launch_soft_init(const SoftGeom& g, const float4* packed, float* theta0, hip
 }
 
 template <int WG>
-static int soft_assign_t(const SoftImg& s, const float4* packed, const float* theta_prev, float* q,
+static int soft_assign_t(const SoftGeom& g, const float4* packed, const float* theta_prev, float* q,
                          float* fa, float* fb, unsigned short* pmask, hipStream_t st) {
-    hipLaunchKernelGGL(k_soft_assign<WG>, dim3(s.B * s.K * s.spl), dim3(WG), 0, st, s, packed,
+    SoftImg s = to_img(g);
+    s.spl = assign_slices(g.W, g.H, g.nx, g.ny, WG, fill_slices((long long)g.B * s.K));
+    const auto kernel = s.near ? k_soft_assign<WG, true> : k_soft_assign<WG, false>;
+    hipLaunchKernelGGL(kernel, dim3(s.B * s.K * s.spl), dim3(WG), 0, st, s, packed,
+                       theta_prev, q, fa, fb, pmask);
+    return hipGetLastError();
+}
+
+// Whether k_soft_tables takes the assignment: without exact pruning, or where the
+// softmax reaches so far that the bound's spatial term rules few neighbours out: 111 T
+// against the m^2 that one cell side adds to D, four times that for two (colours still
+// may).  Not in launches of few cells, nor where a table has more entries than the
+// pixels' paths samples (see walk_all).  Forward of 8 x 512x512, k = 400, at T = 0.5, 2,
+// 3.6, 5 and 50: 955, 1063, 1112, 1136 and 1392 us, 735, 1040, 1205, 1276 and 1979 by pairs;
+// 1 x 512x512, k = 1200, at 2 and 3.6: 240 and 246, 269 and 308.
+static bool soft_tables(const SoftGeom& g) {
+    const double N = (double)g.B * g.W * g.H, K = (double)g.B * g.nx * g.ny;
+    return (!g.prune || 111.0 * g.temperature >= 3.0 * g.spw * N / K) &&
+           N >= std::max(128, g.wg / 4) * K && std::max(K, N / kTablePixels) > 96;
+}
+
+// Workgroup size of the assignment.  By pairs, 512 lanes where there are no more cells
+// than compute units (2 x 97x61, T = 5: 14.4 us per assignment at 256, 13.3 at 512,
+// 13.9 at 1024; 2 x 256x256, k = 128: 34, 31, 40).  Over tables, 1024 where there are at
+// most two workgroups of that size per compute unit (forward of 512x512, k = 400, T = 50:
+// 350, 347 and 327 us; eight of them 1392, 1535 and 1512).
+static int assign_wg(const SoftGeom& g, bool tables) {
+    if (g.wg != 0) return g.wg;
+    const long long cells = (long long)g.B * g.nx * g.ny;
+    return tables ? cells <= 2 * kCUs ? 1024 : 256 : cells <= kCUs ? 512 : 256;
+}
+
+template <int WG>
+static int soft_tables_t(const SoftGeom& g, const float4* packed, const float* theta_prev, float* q,
+                         float* fa, float* fb, unsigned short* pmask, hipStream_t st) {
+    SoftImg s = to_img(g);
+    s.spl = assign_slices(g.W, g.H, g.nx, g.ny, WG, 1);
+    const auto kernel = s.near ? k_soft_tables<WG, true> : k_soft_tables<WG, false>;
+    hipLaunchKernelGGL(kernel, dim3(s.B * s.K * s.spl), dim3(WG), 0, st, s, packed,
                        theta_prev, q, fa, fb, pmask);
     return hipGetLastError();
 }
 
 int launch_soft_assign(const SoftGeom& g, const float4* packed, const float* theta_prev, float* q,
                        float* fa, float* fb, unsigned short* pmask, hipStream_t st) {
-    const SoftImg s = to_img(g);
-    if (g.wg == 1024) return soft_assign_t<1024>(s, packed, theta_prev, q, fa, fb, pmask, st);
-    if (g.wg == 512) return soft_assign_t<512>(s, packed, theta_prev, q, fa, fb, pmask, st);
-    return soft_assign_t<256>(s, packed, theta_prev, q, fa, fb, pmask, st);
+    const bool tables = soft_tables(g);
+    const int wg = assign_wg(g, tables);
+    const auto launch = wg == 1024  ? tables ? soft_tables_t<1024> : soft_assign_t<1024>
+                        : wg == 512 ? tables ? soft_tables_t<512> : soft_assign_t<512>
+                                    : tables ? soft_tables_t<256> : soft_assign_t<256>;
+    return launch(g, packed, theta_prev, q, fa, fb, pmask, st);
 }
 
 int launch_soft_update(const SoftGeom& g, const float* q, const unsigned short* pmask,

@@ -360,3 +360,51 @@ def test_soft_backward_tiles_around_the_endpoint(orc, W, H, k, T, lds):
     c_t, q_t, saved = eng.forward(L, C)
     glab, gcon = (host(t) for t in eng.backward(L, C, c_t, q_t, saved, dev(gq), dev(gth)))
     assert_grads(orc, lab, con, k, gq, gth, iters, T, glab, gcon)
+
+
+@pytest.mark.parametrize("wg", [0, 256, 512, 1024])
+@pytest.mark.parametrize("W,H,k,T,prune", [
+    (400, 400, 1250, 5.0, 1),    # the smallest cells that take tables
+    (320, 320, 100, 50.0, 1),    # cells of 1024 pixels
+    (330, 330, 100, 4.0, 1),     # one row and column more
+    (9, 9000, 90, 20.0, 1),      # narrow cells, a last strip of one column
+    (500, 400, 30, 0.5, 0),      # every candidate walked; boxes beyond the LDS
+])
+def test_soft_forward_over_tables(orc, W, H, k, T, prune, wg):
+    """The forward where most pixels walk most candidates."""
+    iters = 2
+    lab, con = _batch(1, (W, H), 12, 750)
+    th_o, q_o, _ = orc.soft_forward(lab, con, k, iterations=iters, T=T, d32=True)
+    eng = _engine(W, H, k, 1, T, iters, wg_size=wg, exact_pruning=prune)
+    say("soft over tables", W, H, k, T, prune, wg)
+    c_t, q_t, _ = eng.forward(dev(lab), dev(con))
+    assert compare_forward(host(c_t), host(q_t), th_o, q_o, W, H) == iters
+
+
+def test_soft_backward_over_tables(orc):
+    """What the forward over tables saves is what the backward reads."""
+    W, H, k, T, iters = 200, 160, 110, 5.0, 3
+    lab, con = _batch(2, (W, H), 12, 760)
+    rng = np.random.default_rng(9)
+    K = orc.grid(W, H, k).num_sp
+    gq = rng.normal(0, 1, (2, 9, H, W)).astype(np.float32)
+    gth = rng.normal(0, 1, (2, K, 5)).astype(np.float32)
+    L, C = dev(lab), dev(con)
+    for prune in (1, 0):
+        eng = _engine(W, H, k, 2, T, iters, exact_pruning=prune)
+        say("soft backward over tables", prune)
+        c_t, q_t, saved = eng.forward(L, C)
+        glab, gcon = (host(t) for t in eng.backward(L, C, c_t, q_t, saved, dev(gq), dev(gth)))
+        assert_grads(orc, lab, con, k, gq, gth, iters, T, glab, gcon)
+
+
+def test_soft_tables_and_pairs_agree(orc):
+    """Temperatures on both sides of the rule that picks the kernel, batches on both
+    sides of its sizes: the same bits as with every candidate walked."""
+    for W, H, k, B in [(160, 120, 110, 1), (160, 120, 48, 1), (160, 120, 48, 3)]:
+        lab, con = _batch(B, (W, H), 8, 770)
+        L, C = dev(lab), dev(con)
+        for T in (0.5, 2.5, 3.0, 40.0):
+            say("soft tables against pairs", W, H, k, B, T)
+            a, b = (_engine(W, H, k, B, T, 3, exact_pruning=p).forward(L, C)[:2] for p in (1, 0))
+            assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
