@@ -55,7 +55,7 @@ struct ItemShared {
     int pairs;
 };
 
-// Per work item of assign_all: a candidate's table, or two of half the size; then the
+// Per work item of walk_tables: a candidate's table, or two of half the size; then the
 // update bins.  72 bytes a lane: the LDS of as many workgroups as the registers let a
 // CU hold.
 template <int WG>
@@ -67,6 +67,13 @@ struct TableShared {
     };
     int box[4];            // of the pixels
 };
+
+// An item whose second pass would take more rounds of its lanes than this goes over
+// tables instead (walk_tables): images of noise, or whose contours are nowhere low,
+// leave most of the candidates to be walked.  10 iterations of 1920x1080, k = 2000, at
+// 4, 6 and 8 (none): the benchmark's image 732, 725 and 727 us; noise 2.52, 2.58 and 4.56 ms;
+// contours of up to 0.2 everywhere added to the benchmark's 1.68, 1.86 and 1.96.
+constexpr int kManyRounds = 6;
 
 // A descriptor read through the scalar cache, word by word (p uniform).
 __device__ __forceinline__ Img load_const(const Img* p) {
@@ -182,39 +189,29 @@ __device__ __forceinline__ Eqs item_eqs(const Img& im, const Item& it, const Nei
     return eqs;
 }
 
-// Without exact pruning every pixel of a work item walks every candidate: candidate by
-// candidate the workgroup writes (d_c, w) over the box of the pixels and the
-// candidate's endpoint, which holds every path to it, into an LDS table, and the paths
-// are walked there; over global memory where the box exceeds the LDS.  The winner is
-// the smallest (D, slot).  A lane has up to kTablePixels / WG pixels, one at a time in
-// best[0] and at[0] (x and y within the box, slot), which rotate.  Where two tables
-// fit, they alternate: one barrier a candidate.
+// A work item whose pixels walk many candidates: candidate by candidate the workgroup
+// writes (d_c, w) over the box of the pixels and the candidate's endpoint, which holds
+// every path to it, into an LDS table, and the paths are walked there; over global
+// memory where the box exceeds the LDS.  The winner is the smallest (D, slot).  A lane
+// has up to ROUNDS pixels, one at a time in best[0] and at[0] (x and y within the box,
+// slot), which rotate.  Where two tables fit, they alternate: one barrier a candidate.
+// PRUNE: the own cell's candidate first, then the edges', then the corners', and a
+// pixel leaves those out whose bound (that of bound_keys, unfused: never above D) its
+// smallest D so far rules out.
 //
 // What bounds it: VALU issue; a sample costs 5 instructions and an 8-byte LDS read.  10
-// iterations of 1920x1080, k = 2000: 1.63 ms; 4.68 by the pairs of process_cell, whose
-// samples cost 13 instructions and 16 bytes through L1.
-template <int WG, bool ACCUM, bool NEAR>
-__device__ __forceinline__ void assign_all(const Img& im, int ci, int cj, int slice,
-                                           const float4* __restrict__ packed,
-                                           const float* __restrict__ centres,
-                                           const int* __restrict__ endpoints,
-                                           int* __restrict__ labels, long long* __restrict__ acc,
-                                           float lambda, TableShared<WG>& sh) {
-    constexpr int kRounds = kTablePixels / WG;
+// iterations of 1920x1080, k = 2000, without pruning: 1.63 ms; 4.68 by the pairs of
+// process_cell, whose samples cost 13 instructions and 16 bytes through L1.
+template <int WG, bool ACCUM, int ROUNDS, bool PRUNE>
+__device__ __forceinline__ void walk_tables(const Eqs& eqs, const Img& im, const Item& it,
+                                            const Neighbours& nb, int k0,
+                                            const float* __restrict__ cen,
+                                            const int* __restrict__ end, int* __restrict__ labels,
+                                            TableShared<WG>& sh) {
+    constexpr int kRounds = ROUNDS;
     const int tid = threadIdx.x, W = im.W, H = im.H;
-    const Item it = item_of(im, ci, cj, slice);
-    if (it.t1 <= it.t0) return;                    // an empty slice
-    const float4* __restrict__ img = packed + im.pix;
-    const float* __restrict__ cen = centres + 5LL * im.sp;
-    const int* __restrict__ end = endpoints + 2LL * im.sp;
-    const Neighbours nb = neighbours_of(im.nx, im.ny, ci, cj);
-    const Eqs eqs = item_eqs<NEAR>(im, it, nb, img, end, lambda);
-    const int k0 = (ci - 1) * im.nx + cj - 1;
-    if (tid == 0) {
-        sh.box[0] = sh.box[1] = INT_MAX;
-        sh.box[2] = sh.box[3] = 0;
-    }
-    __syncthreads();
+    const float4* __restrict__ img = eqs.img;
+    const bool cut = im.gamma <= 0x1p40f;
     float best[kRounds];
     unsigned at[kRounds];
     Box own;
@@ -261,7 +258,9 @@ __device__ __forceinline__ void assign_all(const Img& im, int ci, int cj, int sl
     }
     bool half = false, was_full = false;           // uniform
 #pragma unroll 1
-    for (int j = 0; j < 9; ++j) {
+    for (int i = 0; i < 9; ++i) {
+        // ascending, or 4, 1, 3, 5, 7, 0, 2, 6, 8
+        const int j = PRUNE ? (int)((0x862075314ULL >> (4 * i)) & 15ULL) : i;
         if (!((nb.inside >> j) & 1u)) continue;    // uniform
         const int di = (j * 11) >> 5, kk = k0 + di * im.nx + (j - 3 * di);
         const ConstF cp = (ConstF)(uintptr_t)cen + 5 * kk;
@@ -286,14 +285,28 @@ __device__ __forceinline__ void assign_all(const Img& im, int ci, int cj, int sl
         for (int r = 0; r < kRounds; ++r) {
             if (at[0] != ~0u) {
                 const int px = own.x0 + (int)(at[0] & 4095u), py = own.y0 + (int)((at[0] >> 12) & 4095u);
-                float A, B, D;
-                if (t.fits)                        // uniform
-                    D = table_distance(eqs, ck, t, table, cx, cy, px, py, A, B);
-                else
-                    D = path_distance(eqs, ck, img[py * W + px], cx, cy, px, py, false, 0.0f, A, B);
-                if (D < best[0]) {                 // in ascending slot
-                    best[0] = D;
-                    at[0] = (at[0] & 0xffffffu) | ((unsigned)j << 24);
+                const int slot = (int)(at[0] >> 24);
+                float A, B, D, lb = 0.0f;
+                if (PRUNE) {
+                    float dcp;
+                    if (t.fits) {                  // uniform
+                        dcp = table[(py - t.y0) * t.pitch + (px - t.x0)].x;
+                    } else {
+                        dcp = colour_dist(img[py * W + px], ck[0], ck[1], ck[2]);
+                    }
+                    const float ax = (float)px - ck[3], ay = (float)py - ck[4];
+                    lb = eqs.lambda * dcp + (ax * ax + ay * ay) * eqs.spw;
+                }
+                if (!(PRUNE && (lb > best[0] || (lb == best[0] && j > slot)))) {
+                    if (t.fits)                    // uniform
+                        D = table_distance(eqs, ck, t, table, cx, cy, px, py, A, B);
+                    else
+                        D = path_distance(eqs, ck, img[py * W + px], cx, cy, px, py, PRUNE && cut,
+                                          threshold(best[0]), A, B);
+                    if (D < best[0] || (PRUNE && D == best[0] && j < slot)) {
+                        best[0] = D;
+                        at[0] = (at[0] & 0xffffffu) | ((unsigned)j << 24);
+                    }
                 }
             }
             const float b0 = best[0];
@@ -321,6 +334,31 @@ __device__ __forceinline__ void assign_all(const Img& im, int ci, int cj, int sl
         settle<ACCUM>(im, img, own.x0 + (int)(at[r] & 4095u), own.y0 + (int)((at[r] >> 12) & 4095u),
                       j, k0 + di * im.nx + (j - 3 * di), labels, sh.bins);
     }
+}
+
+// Without exact pruning every pixel of a work item walks every candidate, up to
+// kTablePixels of them.
+template <int WG, bool ACCUM, bool NEAR>
+__device__ __forceinline__ void assign_all(const Img& im, int ci, int cj, int slice,
+                                           const float4* __restrict__ packed,
+                                           const float* __restrict__ centres,
+                                           const int* __restrict__ endpoints,
+                                           int* __restrict__ labels, long long* __restrict__ acc,
+                                           float lambda, TableShared<WG>& sh) {
+    const Item it = item_of(im, ci, cj, slice);
+    if (it.t1 <= it.t0) return;                    // an empty slice
+    const float4* __restrict__ img = packed + im.pix;
+    const float* __restrict__ cen = centres + 5LL * im.sp;
+    const int* __restrict__ end = endpoints + 2LL * im.sp;
+    const Neighbours nb = neighbours_of(im.nx, im.ny, ci, cj);
+    const Eqs eqs = item_eqs<NEAR>(im, it, nb, img, end, lambda);
+    const int k0 = (ci - 1) * im.nx + cj - 1;
+    if (threadIdx.x == 0) {
+        sh.box[0] = sh.box[1] = INT_MAX;
+        sh.box[2] = sh.box[3] = 0;
+    }
+    __syncthreads();
+    walk_tables<WG, ACCUM, kTablePixels / WG, false>(eqs, im, it, nb, k0, cen, end, labels, sh);
     if (ACCUM) {
         __syncthreads();
         flush_bins(im, k0, sh.bins, acc);
@@ -342,8 +380,11 @@ __device__ __forceinline__ void assign_all(const Img& im, int ci, int cj, int sl
 // The first candidate decides 80 % of the pixels; the others whose bound does
 // not exceed its D, 0.2 per pixel and most of them losers, are listed and
 // walked by full waves of (pixel, slot) pairs, whose results meet in a 64-bit
-// minimum per pixel.  A walk of that second pass stops as soon as its partial
-// sums prove that D exceeds the pixel's first one (Cut).
+// minimum per pixel.  They are listed slot by slot, so that the lanes of a wave walk
+// to one endpoint: taken in the order of each pixel's bounds, an image of noise took 5.93
+// ms instead of 4.56 (10 iterations of 1920x1080), 481x321 191 us instead of 186.  A walk of
+// that second pass stops as soon as its partial sums prove that D exceeds the pixel's
+// first one (Cut).
 //
 // NEAR (near_image): the walks by 32-bit indexes alone.  The other kernels choose per
 // item (near_box); both walks in one kernel need 10 registers more and took 1 to 2 %
@@ -371,7 +412,7 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
                                              const int* __restrict__ endpoints,
                                              int* __restrict__ labels,
                                              long long* __restrict__ acc, float lambda,
-                                             ItemShared<WG>& sh) {
+                                             ItemShared<WG>& sh, TableShared<WG>& tables) {
     const int tid = threadIdx.x;
     const int W = im.W, H = im.H;
     const Item it = item_of(im, ci, cj, slice);
@@ -400,7 +441,11 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
                              py, cut, thr, A, B);
     };
 
-    if (tid == 0) sh.pairs = 0;
+    if (tid == 0) {
+        sh.pairs = 0;
+        tables.box[0] = tables.box[1] = INT_MAX;
+        tables.box[2] = tables.box[3] = 0;
+    }
     if (ACCUM) clear_bins<WG>(sh.bins);
     __syncthreads();
 
@@ -417,7 +462,7 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
         unsigned key[9];
         const float4 fp = img[py * W + px];
         bound_keys(nb, (ConstF)(uintptr_t)cen, im.spw, fp, px, py, lambda, key);
-        unsigned nk = next_key(key, kNoKey);
+        const unsigned nk = next_key(key, kNoKey);
         float best = INFINITY;
         {
             const int j = (int)(nk & 15u);
@@ -427,16 +472,18 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
                 bestj = j;
             }
         }
-        const float thr = threshold(best);
-        for (;;) {
-            nk = next_key(key, nk);
-            const bool more = nk != kNoKey && !(prune && key_bound(nk) > thr);
+        // (keys as integers: a NaN bound is above every limit, and its D is NaN, too)
+        const unsigned limit = prune ? __float_as_uint(threshold(best)) | 15u : 0x7fffffffu;
+#pragma unroll
+        for (int j = 0; j < 9; ++j) {
+            const bool more = key[j] <= limit && key[j] != nk;
             const unsigned long long m = __ballot(more);
-            if (m == 0ULL) break;                  // uniform over the lanes still here
+            if (m == 0ULL) continue;               // uniform
             const int at = wave_claim(&sh.pairs, m);
-            if (!more) break;
-            sh.list[at] = (unsigned short)(tid | ((nk & 15u) << 10));
-            again = true;
+            if (more) {
+                sh.list[at] = (unsigned short)(tid | (j << 10));
+                again = true;
+            }
         }
         if (again) {
             sh.xy[tid] = make_int2(px, py);
@@ -444,8 +491,16 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
         }
     }
     __syncthreads();
-    // second pass: the listed pairs, by full waves
     const int pairs = __builtin_amdgcn_readfirstlane(sh.pairs);
+    if (prune && pairs > kManyRounds * WG) {       // uniform
+        walk_tables<WG, ACCUM, 1, true>(eqs, im, it, nb, k0, cen, end, labels, tables);
+        if (ACCUM) {
+            __syncthreads();
+            flush_bins(im, k0, tables.bins, acc);
+        }
+        return;
+    }
+    // second pass: the listed pairs, by full waves
     const bool cut = prune && im.gamma <= 0x1p40f;
     for (int i = tid; i < pairs; i += WG) {
         const unsigned e = sh.list[i];
@@ -484,9 +539,13 @@ __device__ __forceinline__ void assign_item(const Img& im, int item, const float
         assign_all<WG, ACCUM, NEAR>(im, ci, cj, slice, packed, centres, endpoints, labels, acc, lambda,
                                     sh);
     } else {
-        __shared__ ItemShared<WG> sh;
+        __shared__ union {
+            ItemShared<WG> item;
+            TableShared<WG> tables;               // (its box behind the item's)
+        } sh;
+        static_assert(sizeof(ItemShared<WG>) <= offsetof(TableShared<WG>, box), "the box is apart");
         process_cell<WG, ACCUM, NEAR>(im, ci, cj, slice, packed, centres, endpoints, labels, acc,
-                                      lambda, sh);
+                                      lambda, sh.item, sh.tables);
     }
 }
 

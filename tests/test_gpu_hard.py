@@ -495,3 +495,60 @@ def test_every_candidate_walked_in_runs_and_batches(orc):
         for (w, h, k), i, ref in zip(shapes, imgs, refs):
             r = _scalp(w, h, k, iterations=3, exact_pruning=0, wg_size=wg).run(dev(i.lab), dev(i.contour))
             assert (host(r.labels) == ref.labels).all() and (host(r.centers) == ref.centres).all()
+
+
+@pytest.mark.parametrize("W,H,k,wg,lam,m", [
+    (256, 256, 64, 0, 0.5, 10.0),      # cells of 1024 pixels in four items
+    (200, 150, 60, 0, 0.0, 10.0),
+    (330, 250, 80, 512, 0.5, 0.0),     # m = 0: bounds of colour alone
+    (330, 250, 80, 1024, 0.5, 10.0),
+    (600, 500, 12, 0, 0.5, 1.0),       # large cells: boxes beyond the LDS
+])
+def test_items_of_many_pairs(orc, W, H, k, wg, lam, m):
+    """Noise and high contours: the bounds rule out so little that items go over
+    tables; with every ninth pixel non-finite, and the sums."""
+    rng = np.random.default_rng(W + k)
+    lab = rng.normal(0, 25, (H, W, 3)).astype(np.float32)
+    con = rng.random((H, W)).astype(np.float32)
+    g = orc.grid(W, H, k)
+    for nan in (False, True):
+        if nan:
+            lab[::9, ::9, 0] = np.nan
+        clean = np.nan_to_num(lab)
+        c, e = perturbed_state(orc, g, clean, seed=W + H, jitter=0.4 * g.r + 1, colour=2.0)
+        s = _scalp(W, H, k, wg_size=wg, lam=lam, m=m)
+        say("many pairs", W, H, k, wg, lam, m, nan)
+        ol, _, _ = orc.assign(g, lab, orc.wmap(con), c, e, lam=lam, spw=orc.spatial_weight(g, m))
+        if nan:
+            lbl = host(s.assign(dev(lab), dev(con), dev(c), dev(e)))
+            assert (lbl == ol).all(), f"{int((lbl != ol).sum())} labels differ"
+            continue
+        C, E = dev(c), dev(e)
+        L = torch.empty((H, W), dtype=torch.int32, device="cuda")
+        N = torch.zeros(g.num_sp, dtype=torch.int32, device="cuda")
+        s.init_grid(dev(lab), dev(con))                  # packs; the sums are left at zero
+        s.assign_accumulate(C, E, L)
+        s.finalize(L, C, E, N, project=0)
+        assert (host(L) == ol).all(), f"{int((host(L) != ol).sum())} labels differ"
+        oc, on = orc.update(g, lab, ol, c, mode=orc.MEAN_FIXED)
+        assert (host(C) == oc).all() and (host(N) == on).all()
+
+
+def test_runs_of_noise(orc):
+    """Whole runs and a batch on images whose items go over tables."""
+    from paper_1903_07149_amd.scalp import ScalpBatch
+    shapes = [(200, 150, 40), (257, 130, 33), (520, 510, 260)]
+    data = []
+    for i, (w, h, _) in enumerate(shapes):
+        rng = np.random.default_rng(90 + i)
+        data.append((rng.normal(0, 25, (h, w, 3)).astype(np.float32), rng.random((h, w)).astype(np.float32)))
+    refs = [orc.run(l, c, k, iterations=3, mode=orc.MEAN_FIXED) for (l, c), (_, _, k) in zip(data, shapes)]
+    say("runs of noise")
+    b = ScalpBatch(shapes, iterations=3)
+    bl = host(b.run(dev(np.concatenate([l.reshape(-1, 3) for l, _ in data])),
+                    dev(np.concatenate([c.reshape(-1) for _, c in data])))[2])
+    for (p0, p1, H, W), ref in zip(b.pixel_slices(), refs):
+        assert (bl[p0:p1].reshape(H, W) == ref.labels).all(), (W, H)
+    for (l, c), (w, h, k), ref in zip(data, shapes, refs):
+        r = _scalp(w, h, k, iterations=3).run(dev(l), dev(c))
+        assert (host(r.labels) == ref.labels).all() and (host(r.centers) == ref.centres).all()

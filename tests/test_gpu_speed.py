@@ -75,3 +75,16 @@ def test_soft_backward_of_large_cells_keeps_up():
     bwd = _time(lambda: e.backward(lab, con, ct, q, saved, gq, gt))
     print(f"forward {fwd:.3f} ms, backward {bwd:.3f} ms")
     assert bwd < 4.0 * fwd
+
+
+def test_noise_keeps_up():
+    """An image of noise, which bounds tell little about, against one of regions."""
+    lab, _ = _image(1920, 1080)
+    zero = torch.zeros(lab.shape[:2], device="cuda")
+    say("noise against regions")
+    easy = _run(1920, 1080, 2000, (lab, zero), iterations=5)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    hard = _run(1920, 1080, 2000, (30 * torch.randn(lab.shape, generator=g, device="cuda"),
+                                   torch.rand(zero.shape, generator=g, device="cuda")), iterations=5)
+    print(f"noise {hard:.3f} ms, regions {easy:.3f} ms")
+    assert hard < 6.5 * easy
