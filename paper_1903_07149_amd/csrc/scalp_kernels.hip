@@ -602,10 +602,11 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_
 // an infinite or NaN D loses to every finite one).  A pixel that no window
 // contains keeps its label.  Single images only (im.pix and im.sp are 0).
 
-constexpr int kWinTile = 16;     // a workgroup's tile is kWinTile x kWinTile pixels
+constexpr int kWinTile = 16;     // a workgroup's tile is kWinTile x kWinTile pixels, or 8 x 8
 constexpr int kWinWG = kWinTile * kWinTile;
 constexpr int kWinBatch = 15;    // candidates that a tile evaluates at a time (4-bit slots)
 constexpr int kWinIds = 512;     // longest list of a tile
+constexpr int kWinSmall = 4 * kCUs;   // most tiles of 8 pixels a side
 
 // The tiles' candidates: count[tile] (cleared before the first pass; every tile
 // clears its own again) and the first `cap` of them in list[tile * cap ...], in
@@ -613,7 +614,7 @@ constexpr int kWinIds = 512;     // longest list of a tile
 struct WinLists {
     int* count;
     int* list;
-    int cap, tx, tiles;   // tiles of a row, in all
+    int cap, tile, tx, tiles;   // pixels a side of a tile, tiles of a row, in all
 };
 
 // Adds cluster k with barycenter (x, y) to the tiles that its window meets.  The
@@ -621,8 +622,9 @@ struct WinLists {
 __device__ __forceinline__ void add_to_tiles(const Img& im, int k, float x, float y, int R,
                                              const WinLists& wl) {
     const int wx = round_coord(x, im.W - 1), wy = round_coord(y, im.H - 1);
-    const int tx0 = max(wx - R, 0) / kWinTile, tx1 = min(wx + R, im.W - 1) / kWinTile;
-    const int ty0 = max(wy - R, 0) / kWinTile, ty1 = min(wy + R, im.H - 1) / kWinTile;
+    const int sh = wl.tile == 8 ? 3 : 4;           // uniform
+    const int tx0 = max(wx - R, 0) >> sh, tx1 = min(wx + R, im.W - 1) >> sh;
+    const int ty0 = max(wy - R, 0) >> sh, ty1 = min(wy + R, im.H - 1) >> sh;
     const int nx = tx1 - tx0 + 1, n = nx * (ty1 - ty0 + 1);
     for (int i = threadIdx.x & 63; i < n; i += 64) {
         const int r = i / nx;
@@ -671,10 +673,10 @@ __device__ __forceinline__ float win_threshold(unsigned long long win) {
 // (pixel, candidate) pairs whose bound does not exceed that D.  More than kWinBatch
 // candidates are taken in batches against the smallest D so far; a tile whose list
 // overflowed, and every tile without lists, tests all clusters, kWinWG at a time.
-// TILE is kWinTile, or 8 for the smallest images, where a tile of 16 would leave
+// TILE is kWinTile, or 8 for small images (win_tile), where a tile of 16 would leave
 // most of the chip without work (the lanes without a pixel test clusters and walk
-// pairs): 97x61, k = 30, 10
-// iterations 159 us with tiles of 16, 145 with 8.
+// pairs): 10 iterations of 97x61, k = 30, 159 us with tiles of 16, 145 with 8; of 189x117,
+// k = 300, with lists, 239 and 195.
 // With ACCUM the update's sums go through bins per candidate of the tile (to global
 // memory directly for pixels that no window contains, and for winners of an earlier
 // turn of an overflowed list).
@@ -1471,16 +1473,30 @@ int launch_assign_batched(const Img* imgs, const int* item_start, int n_img, int
                   lambda, near, all, s);
 }
 
-// 8 W H bytes, but at least 256, hold the counts and a list of at least 16 ids per
-// tile: tiles / (W H) is at most 2/17 (W = 17, H = 1) unless there is one tile.
+// Side of the window form's tiles: 8 where that gives no more than kWinSmall of them, 4
+// per compute unit (300x200, k = 300, 925 tiles: 186 us in 10 iterations, 198 with tiles of
+// 16; 189x117, k = 1000, 231 and 355; 481x321, 2500 tiles, no difference).
+static int win_tile(int W, int H) {
+    const long long tiles = (long long)((W + kWinTile - 1) / kWinTile) * ((H + kWinTile - 1) / kWinTile);
+    return 4 * tiles <= kWinSmall ? 8 : kWinTile;
+}
+
+static long long win_tiles(int W, int H) {
+    const int t = win_tile(W, H);
+    return (long long)((W + t - 1) / t) * ((H + t - 1) / t);
+}
+
+// 8 W H bytes, but at least 256, hold the counts and a list of at least 12 ids per tile
+// (W = 33, H = 1, tiles of 8; a row of tiles of 16, one pixel high, has 31).
 //
 // No lists (count null) for up to kWinWG clusters: every tile tests them all in one
 // turn, which takes no longer than reading a list does, and nothing has to make them
 // (97x61, 30 clusters, 10 iterations: 172 us with lists, 165 without).
 static WinLists win_lists(const Img& im, void* mem) {
     WinLists wl = {};
-    wl.tx = (im.W + kWinTile - 1) / kWinTile;
-    wl.tiles = wl.tx * ((im.H + kWinTile - 1) / kWinTile);
+    wl.tile = win_tile(im.W, im.H);
+    wl.tx = (im.W + wl.tile - 1) / wl.tile;
+    wl.tiles = (int)win_tiles(im.W, im.H);
     const long long words = std::max(2LL * im.W * im.H, 64LL);
     if (!mem || im.nx * im.ny <= kWinWG) return wl;
     wl.cap = (int)std::min<long long>(words / wl.tiles - 1, kWinIds);
@@ -1489,24 +1505,16 @@ static WinLists win_lists(const Img& im, void* mem) {
     return wl;
 }
 
-long long window_count_words(int W, int H) {
-    return ((long long)((W + kWinTile - 1) / kWinTile) * ((H + kWinTile - 1) / kWinTile) + 1) / 2;
-}
+long long window_count_words(int W, int H) { return (win_tiles(W, H) + 1) / 2; }
 
 int launch_assign_window(const Img& im, const float4* packed, const float* centres,
                          const int* endpoints, int* labels, long long* acc, int* ctrl, void* lists,
                          int R, float lambda, bool accumulate, bool listed, hipStream_t s) {
-    WinLists wl = win_lists(im, lists);
+    const WinLists wl = win_lists(im, lists);
     const int K = im.nx * im.ny;
-    const bool near = near_image(im);
+    const bool near = near_image(im), small = wl.tile == 8;
     if (wl.count && !listed)
         hipLaunchKernelGGL(k_window_lists, dim3((K + 3) / 4), dim3(256), 0, s, im, centres, R, wl);
-    // tiles of 8 x 8 where they still number no more than the compute units
-    const bool small = !wl.count && 4 * wl.tiles <= kCUs;
-    if (small) {
-        wl.tx = (im.W + 7) / 8;
-        wl.tiles = wl.tx * ((im.H + 7) / 8);
-    }
     const int tiles = wl.tiles;
     // at most 2^22 workgroups a launch (an image one pixel high may have 2^27 tiles)
     for (int t0 = 0; t0 < tiles; t0 += 1 << 22) {

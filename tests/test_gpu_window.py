@@ -180,3 +180,19 @@ def test_window_mode_rejected_where_unsupported():
     eng = SoftScalp(32, 32, 16, 1, assign_mode=ASSIGN_WINDOW)
     with pytest.raises(L.ScalpError):
         eng.forward(torch.zeros((1, 32, 32, 3), device="cuda"), torch.zeros((1, 32, 32), device="cuda"))
+
+
+@pytest.mark.parametrize("W,H,k", [
+    (97, 61, 300), (9, 9, 81), (9, 1, 9), (256, 256, 300),    # tiles of 8 with lists, at most 1024
+    (264, 256, 300), (17, 17, 289), (1, 700, 350),            # one more; few ids per tile
+])
+def test_window_runs_of_small_tiles(orc, W, H, k):
+    img = synth.make_image(W, H, 5, 10.0, 19)
+    s = _scalp(W, H, k)
+    say("window small tiles", W, H, k)
+    lab, con = dev(img.lab), dev(img.contour)
+    ref = orc.run_window(img.lab, img.contour, k, iterations=4, mode=orc.MEAN_FIXED)
+    for rep in range(2):
+        r = s.run(lab, con, iterations=4)
+        assert (host(r.labels) == ref.labels).all(), rep
+        assert (host(r.centers) == ref.centres).all() and (host(r.endpoints) == ref.endpoints).all()
