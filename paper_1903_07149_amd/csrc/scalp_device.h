@@ -155,12 +155,13 @@ __device__ __forceinline__ void walk_path(const float4* __restrict__ base, int i
 // Increment F for minor extent am and major extent n (0 <= am <= n).  Any F with
 // 0 <= F - 2^32 am/n < 2^32/(2 n^2) steps exactly.  For n < 1023 a reciprocal good to one ulp
 // gives 2^32 am/n within 769, and adding 1025 lands in (256, 1794]: inside
-// the window for every n up to 1094.  Longer paths take the correctly
-// rounded double quotient, rounded up.
+// the window for every n up to 1094.  (The largest float below 2^32 bounds it: a diagonal
+// gives 2^32 or just above, and a path of no steps NaN; the sum then saturates to
+// 2^32 - 1.)  Longer paths take the correctly rounded double quotient, rounded up.
 __device__ __forceinline__ unsigned step_increment(int am, int n) {
     if (n < 1023) {
         const float sf = (float)am * __builtin_amdgcn_rcpf((float)n);
-        return __builtin_elementwise_add_sat((unsigned)(sf * 4294967296.0f), 1025u);
+        return __builtin_elementwise_add_sat((unsigned)fminf(sf * 4294967296.0f, 0x1.fffffep31f), 1025u);
     }
     if (am == n) return 0xffffffffu;
     return (unsigned)ceil((double)am * 4294967296.0 / (double)n);

@@ -46,3 +46,42 @@ def test_ties_round_toward_the_endpoint():
     # take the pixel nearer the endpoint
     F = _increment(2, 4)
     assert [((1 << 31) + i * F) >> 32 for i in (1, 2, 3)] == [1, 1, 2]
+
+
+f32 = np.float32
+
+
+def _short_increment(am, n, ulps):
+    """The rule for n < 1023: an FP32 reciprocal that may be `ulps` off, a product, a
+    bound below 2^32 (what it converts to an integer is in range) and a saturating sum."""
+    with np.errstate(divide="ignore", invalid="ignore"):
+        r = f32(1.0) / n.astype(f32)
+        r = (r.view(np.int32) + np.int32(ulps)).view(f32)
+        v = (am.astype(f32) * r) * f32(2.0 ** 32)
+    v = np.fmin(v, f32(float.fromhex("0x1.fffffep31")))
+    assert (v >= 0).all() and (v < 2.0 ** 32).all()
+    return np.minimum(v.astype(np.uint64) + np.uint64(1025), np.uint64(0xFFFFFFFF))
+
+
+@pytest.mark.parametrize("ulps", [-1, 0, 1])
+def test_short_paths_by_the_reciprocal(ulps):
+    """Every (minor, major) extent below 1023, at every step."""
+    for n in range(1, 1023):
+        am = np.arange(0, n + 1)
+        F = _short_increment(am, np.full(n + 1, n), ulps)
+        i = np.arange(1, n, dtype=np.uint64)
+        carries = (np.uint64(1 << 31) + i[None, :] * F[:, None]) >> np.uint64(32)
+        exact = (2 * i.astype(np.int64)[None, :] * am[:, None] + n) // (2 * n)
+        assert (carries.astype(np.int64) == exact).all(), n
+    # no steps: 0 times an infinite reciprocal is bounded, too
+    assert _short_increment(np.array([0]), np.array([0]), 0)[0] == 0xFFFFFFFF
+
+
+def test_kernel_source_bounds_the_conversion():
+    """A float of 2^32 or more, or NaN, must not reach the conversion to an integer."""
+    import os
+    import re
+    from paper_1903_07149_amd import build
+    text = open(os.path.join(build.CSRC, "scalp_device.h")).read()
+    body = re.search(r"unsigned step_increment\(int am, int n\) \{.*?\n\}", text, re.S).group(0)
+    assert "(unsigned)(sf" not in body and "fminf(sf * 4294967296.0f, 0x1.fffffep31f)" in body
