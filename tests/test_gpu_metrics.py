@@ -195,3 +195,21 @@ def test_reusable_metrics_call_matches():
         v = host(mk.run(dev(sp), dev(gt))).tolist()
         assert v[:4] == [ref["br"], ref["asa"], ref["ue"], ref["co"]]
         assert int(v[4]) == ref["gt_boundary"] and int(v[5]) == ref["sp_boundary"]
+
+
+@pytest.mark.parametrize("K,R,side,W,H", [
+    (1, 1, 900, 2900, 800), (28, 9, 97, 2900, 800), (256, 1, 5, 2900, 800),   # all pairs kept in LDS
+    (257, 1, 5, 2900, 800), (4000, 9, 16, 2900, 800),                          # a tile at a time
+    (16, 16, 7, 64, 16), (16, 16, 7, 65, 17), (16, 16, 7, 200, 33),            # 1, 4 and 12 tiles
+])
+def test_metrics_of_runs_of_tiles(K, R, side, W, H):
+    from paper_1903_07149_amd.metrics import metrics
+    rng = np.random.default_rng(K)
+    sp = np.kron(rng.integers(0, K, (H // side + 1, W // side + 1)), np.ones((side, side)))[:H, :W]
+    gt = np.kron(rng.integers(0, R, (H // 100 + 1, W // 90 + 1)), np.ones((100, 90)))[:H, :W]
+    sp, gt = np.ascontiguousarray(sp, np.int32), np.ascontiguousarray(gt, np.int32)
+    say("metrics, runs of tiles", K, R, side, W, H)
+    got = metrics(dev(sp), dev(gt), num_sp=K, num_regions=R, epsilon=2.0)
+    ref = M.all_metrics(sp, gt, 2.0)
+    assert got["br"] == ref["br"] and got["asa"] == ref["asa"] and got["ue"] == ref["ue"]
+    assert abs(got["co"] - ref["co"]) <= 1e-12 * max(1.0, ref["co"])

@@ -88,3 +88,18 @@ def test_noise_keeps_up():
                                    torch.rand(zero.shape, generator=g, device="cuda")), iterations=5)
     print(f"noise {hard:.3f} ms, regions {easy:.3f} ms")
     assert hard < 6.5 * easy
+
+
+def test_metrics_of_few_labels_keep_up():
+    """One label everywhere against many, 3840x2160."""
+    from paper_1903_07149_amd.metrics import Metrics
+    H, W = 2160, 3840
+    y, x = torch.arange(H, device="cuda")[:, None], torch.arange(W, device="cuda")[None]
+    many = ((y // 29) * (W // 29 + 1) + x // 29).int().contiguous()
+    region = ((y // 97) * (W // 93 + 1) + x // 93).int().contiguous()
+    one = torch.zeros_like(many)
+    m, n = Metrics(W, H, int(many.max()) + 1, int(region.max()) + 1), Metrics(W, H, 4, 4)
+    say("metrics of one label, time")
+    a, b = _time(lambda: m.run(many, region)), _time(lambda: n.run(one, one))
+    print(f"many labels {a:.4f} ms, one {b:.4f} ms")
+    assert b < 1.3 * a
