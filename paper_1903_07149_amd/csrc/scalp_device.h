@@ -708,15 +708,18 @@ __device__ __forceinline__ unsigned next_key(const unsigned (&key)[9], unsigned 
     return __builtin_add_overflow(min(min(a, b), c), c1, &next) ? 0xffffffffu : next;
 }
 
+// Lanes of m below this one.
+__device__ __forceinline__ int lanes_below(unsigned long long m) {
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
+
 // Adds the number of lanes in m (a ballot of the lanes here, not 0) to *count
 // and gives the n-th of them the old value + n.
 __device__ __forceinline__ int wave_claim(int* count, unsigned long long m) {
     const int leader = __ffsll((long long)m) - 1;
     int at = 0;
     if ((int)(threadIdx.x & 63) == leader) at = atomicAdd(count, __popcll(m));
-    return __builtin_amdgcn_readlane(at, leader) +
-           (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
-                                          __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+    return __builtin_amdgcn_readlane(at, leader) + lanes_below(m);
 }
 
 __device__ __forceinline__ float key_bound(unsigned key) { return __uint_as_float(key & ~15u); }

@@ -474,15 +474,25 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
         }
         // (keys as integers: a NaN bound is above every limit, and its D is NaN, too)
         const unsigned limit = prune ? __float_as_uint(threshold(best)) | 15u : 0x7fffffffu;
+        unsigned long long listed[9];
+        int total = 0;
 #pragma unroll
         for (int j = 0; j < 9; ++j) {
-            const bool more = key[j] <= limit && key[j] != nk;
-            const unsigned long long m = __ballot(more);
-            if (m == 0ULL) continue;               // uniform
-            const int at = wave_claim(&sh.pairs, m);
-            if (more) {
-                sh.list[at] = (unsigned short)(tid | (j << 10));
-                again = true;
+            listed[j] = __ballot(key[j] <= limit && key[j] != nk);
+            total += __popcll(listed[j]);
+        }
+        if (total != 0) {                          // uniform
+            int at = 0;
+            if ((tid & 63) == 0) at = atomicAdd(&sh.pairs, total);
+            at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+            for (int j = 0; j < 9; ++j) {
+                const unsigned long long m = listed[j];
+                if (key[j] <= limit && key[j] != nk) {
+                    sh.list[at + lanes_below(m)] = (unsigned short)(tid | (j << 10));
+                    again = true;
+                }
+                at += __popcll(m);
             }
         }
         if (again) {
