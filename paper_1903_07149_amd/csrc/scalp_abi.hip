@@ -79,12 +79,12 @@ Tuning tuning_of(const scalp_params_t* p, long long N, long long K, bool all) {
 
 Tuning tuning_of(const scalp_grid_t* g, const scalp_params_t* p) {
     const long long N = (long long)g->width * g->height;
-    return tuning_of(p, N, g->num_sp, walk_all(p->exact_pruning, N, g->num_sp));
+    return tuning_of(p, N, g->num_sp, walk_of(p->exact_pruning, N, g->num_sp) == Walk::kAll);
 }
 
 // Work items per cell of a single image's launch.
 int slices_of(const scalp_grid_t* g, const scalp_params_t* p) {
-    if (walk_all(p->exact_pruning, (long long)g->width * g->height, g->num_sp))
+    if (walk_of(p->exact_pruning, (long long)g->width * g->height, g->num_sp) == Walk::kAll)
         return assign_slices(g->width, g->height, g->nx, g->ny, kTablePixels, 1);
     return assign_slices(g->width, g->height, g->nx, g->ny,
                          item_pixels(g->width, g->height, g->num_sp, tuning_of(g, p).wg),
@@ -523,7 +523,8 @@ int enq_batched(const scalp_batch_desc_t* d, int n, const scalp_params_t* p, con
                 const float* contour, float* centers, int* endpoints, int* labels, int* counts,
                 void* ws, const BatchLayout& BL, hipStream_t s) {
     // (a small batch by pairs: 7 scales of 189x117, 10 iterations, 482 us, 600 over tables)
-    const bool all = walk_all(p->exact_pruning, BL.N, BL.K) && BL.N >= kFewPixels;
+    const Walk walk = BL.N < kFewPixels ? Walk::kPairs : walk_of(p->exact_pruning, BL.N, BL.K);
+    const bool all = walk == Walk::kAll;
     const Tuning t = tuning_of(p, BL.N, BL.K, all);
     const Views v = views_of(ws, BL.base);
     char* b = static_cast<char*>(ws);
@@ -585,7 +586,7 @@ int enq_batched(const scalp_batch_desc_t* d, int n, const scalp_params_t* p, con
                                                      d[i].grid.nx, d[i].grid.ny));
     for (int it = 0; e == hipSuccess && it < p->iterations; ++it) {
         e = launch_assign_batched(imgs, items, n, longest_run, v.packed, centers, endpoints, labels,
-                                  v.acc, v.ctrl, p->lambda, t, near, all, s);
+                                  v.acc, v.ctrl, p->lambda, t, near, walk, s);
         if (e == hipSuccess)
             e = p->project ? launch_finalize_project_batched(imgs, starts, n, (int)BL.K, max_block,
                                                              centers, endpoints, counts, v.acc,

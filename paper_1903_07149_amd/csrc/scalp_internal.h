@@ -75,15 +75,18 @@ constexpr int kMinAssignWG = 256;
 
 constexpr int kCUs = 256;
 
-// Pixels of a work item of a hard assignment by workgroups of wg lanes.  Where
-// paths are long (cells above 48 x 48 pixels) a pixel has several pairs in the
-// second pass: items of half a workgroup's pixels halve its rounds, and end more
-// evenly.  12 scales of 481x321 (k = 6 to 600), 256 lanes: 199 us per iteration, 234
-// with 256 pixels in all items, 213 with 64 in cells above 96 x 96.  Such a launch has
-// about 2 W H lanes, whatever wg is, and a launch holds below 2^32: beyond 2^30
-// pixels the items are not shortened.
+// Whether the work items of an image of N pixels and K cells take half a workgroup's
+// pixels.  Where paths are long (cells above 48 x 48 pixels) a pixel has several pairs
+// in the second pass: such items halve its rounds, which shortens launches of few items.
+// 10 iterations, 256 lanes, half and whole: 300x200, 12 cells, 0.38 and 0.48 ms; 481x321,
+// 40 cells, 0.43 and 0.62; 12 scales of 481x321 2.20 and 2.45.  From 2^20 pixels on the
+// idle lanes cost more: 1920x1080, 700 cells, 1.27 and 1.20; 3840x2160, 3000, 3.85 and
+// 3.12.  (A launch, 2 W H lanes with half items, also holds below 2^32.)
+inline bool half_items(long long N, long long K) { return N > 2304 * K && N < 1 << 20; }
+
+// Pixels of a work item of a hard assignment by workgroups of wg lanes.
 inline int item_pixels(long long W, long long H, long long K, int wg) {
-    return W * H > 2304 * K && W * H <= 1LL << 30 ? wg / 2 : wg;
+    return half_items(W * H, K) ? wg / 2 : wg;
 }
 
 // Without exact pruning every pixel walks every candidate: over LDS tables that a
@@ -95,8 +98,16 @@ inline int item_pixels(long long W, long long H, long long K, int wg) {
 // cell 9.48 and 3.16 ms, with 207 2.39 and 2.91, with 20 cells 28.5 and 37.7.
 constexpr int kTablePixels = 1024;
 
-inline bool walk_all(int prune, long long N, long long K) {
-    return !prune && N >= 128 * K && std::max(K, N / kTablePixels) > 96;
+// How a hard assignment walks: every candidate (ALL); the listed pairs, or over tables
+// in items that list many (MANY); or the pairs alone, also where cells are so small that
+// tables would not pay, and where items of half the lanes never list many: without the
+// tables' code and LDS 0.5 MP of cells of 4 pixels took 13.0 instead of 13.6 ms.
+enum class Walk { kPairs, kMany, kAll };
+
+inline Walk walk_of(int prune, long long N, long long K) {
+    const bool cells = N >= 128 * K;
+    if (!prune) return cells && std::max(K, N / kTablePixels) > 96 ? Walk::kAll : Walk::kPairs;
+    return cells && !half_items(N, K) ? Walk::kMany : Walk::kPairs;
 }
 
 // Items per cell: so many that no item has more than `pixels` pixels, and at least
@@ -179,11 +190,11 @@ int launch_project(const Img& im, const float* centres, const int* counts, const
 int launch_init_cells_batched(const Img* imgs, const int* cell_start, int n_img, int total_cells,
                               const float4* packed, int* labels, long long* acc, hipStream_t s);
 // longest_run: items of the longest of the 8 XCDs' runs; near: near_image of every
-// image; all: walk_all of the batch
+// image
 int launch_assign_batched(const Img* imgs, const int* item_start, int n_img, int longest_run,
                           const float4* packed, const float* centres, const int* endpoints,
                           int* labels, long long* acc, int* ctrl, float lambda, const Tuning& t,
-                          bool near, bool all, hipStream_t s);
+                          bool near, Walk walk, hipStream_t s);
 int launch_finalize_batched(const Img* imgs, const int* sp_start, int n_img, int total_sp,
                             float* centres, int* endpoints, int* counts, long long* acc,
                             const int* labels, int* ctrl, int* plist, bool project,

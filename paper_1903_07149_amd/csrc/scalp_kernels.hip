@@ -412,7 +412,7 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
                                              const int* __restrict__ endpoints,
                                              int* __restrict__ labels,
                                              long long* __restrict__ acc, float lambda,
-                                             ItemShared<WG>& sh, TableShared<WG>& tables) {
+                                             ItemShared<WG>& sh, TableShared<WG>* tables) {
     const int tid = threadIdx.x;
     const int W = im.W, H = im.H;
     const Item it = item_of(im, ci, cj, slice);
@@ -443,8 +443,10 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
 
     if (tid == 0) {
         sh.pairs = 0;
-        tables.box[0] = tables.box[1] = INT_MAX;
-        tables.box[2] = tables.box[3] = 0;
+        if (tables) {
+            tables->box[0] = tables->box[1] = INT_MAX;
+            tables->box[2] = tables->box[3] = 0;
+        }
     }
     if (ACCUM) clear_bins<WG>(sh.bins);
     __syncthreads();
@@ -502,11 +504,11 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
     }
     __syncthreads();
     const int pairs = __builtin_amdgcn_readfirstlane(sh.pairs);
-    if (prune && pairs > kManyRounds * WG) {       // uniform
-        walk_tables<WG, ACCUM, 1, true>(eqs, im, it, nb, k0, cen, end, labels, tables);
+    if (tables && prune && pairs > kManyRounds * WG) {   // uniform
+        walk_tables<WG, ACCUM, 1, true>(eqs, im, it, nb, k0, cen, end, labels, *tables);
         if (ACCUM) {
             __syncthreads();
-            flush_bins(im, k0, tables.bins, acc);
+            flush_bins(im, k0, tables->bins, acc);
         }
         return;
     }
@@ -533,8 +535,7 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
     }
 }
 
-// ALL (see walk_all): every candidate is walked, over tables.
-template <int WG, bool ACCUM, bool NEAR, bool ALL>
+template <int WG, bool ACCUM, bool NEAR, Walk WALK>
 __device__ __forceinline__ void assign_item(const Img& im, int item, const float4* __restrict__ packed,
                                             const float* __restrict__ centres,
                                             const int* __restrict__ endpoints,
@@ -544,29 +545,33 @@ __device__ __forceinline__ void assign_item(const Img& im, int item, const float
     int ci, cj;
     cell_in_strips(pos, im, ci, cj);
     const int slice = item - pos * im.spl;
-    if constexpr (ALL) {
+    if constexpr (WALK == Walk::kAll) {
         __shared__ TableShared<WG> sh;
         assign_all<WG, ACCUM, NEAR>(im, ci, cj, slice, packed, centres, endpoints, labels, acc, lambda,
                                     sh);
-    } else {
+    } else if constexpr (WALK == Walk::kMany) {
         __shared__ union {
             ItemShared<WG> item;
             TableShared<WG> tables;               // (its box behind the item's)
         } sh;
         static_assert(sizeof(ItemShared<WG>) <= offsetof(TableShared<WG>, box), "the box is apart");
         process_cell<WG, ACCUM, NEAR>(im, ci, cj, slice, packed, centres, endpoints, labels, acc,
-                                      lambda, sh.item, sh.tables);
+                                      lambda, sh.item, &sh.tables);
+    } else {
+        __shared__ ItemShared<WG> sh;
+        process_cell<WG, ACCUM, NEAR>(im, ci, cj, slice, packed, centres, endpoints, labels, acc,
+                                      lambda, sh, nullptr);
     }
 }
 
-template <int WG, bool ACCUM, bool NEAR, bool ALL>
+template <int WG, bool ACCUM, bool NEAR, Walk WALK>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_assign(
     Img im, const float4* __restrict__ packed, const float* __restrict__ centres,
     const int* __restrict__ endpoints, int* __restrict__ labels, long long* __restrict__ acc, int* ctrl,
     float lambda) {
     if (ACCUM && blockIdx.x == 0 && threadIdx.x == 0) ctrl[kCtrlProjCount] = 0;
-    assign_item<WG, ACCUM, NEAR, ALL>(im, xcd_remap(blockIdx.x, gridDim.x), packed, centres, endpoints,
-                                      labels, acc, lambda);
+    assign_item<WG, ACCUM, NEAR, WALK>(im, xcd_remap(blockIdx.x, gridDim.x), packed, centres, endpoints,
+                                       labels, acc, lambda);
 }
 
 // The assignment over a ragged batch, a workgroup per (image, cell, slice) item,
@@ -584,7 +589,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_
 // scales of 189x117, 36 instead of 22 for 3 small images; 64 images of up to 2160
 // pixels a side 2.95 ms instead of 2.93, and 12 scales of 481x321, where taking over
 // another XCD's items helped, 202 instead of 207.
-template <int WG, bool NEAR, bool ALL>
+template <int WG, bool NEAR, Walk WALK>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_assign_batched(
     const Img* __restrict__ imgs, const int* __restrict__ item_start, int n_img,
     const float4* __restrict__ packed, const float* __restrict__ centres,
@@ -600,7 +605,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_
     const Img im = load_const(imgs + i);
     const int ni = starts[i + 1] - starts[i];
     const int local = __builtin_amdgcn_readfirstlane((int)((long long)ni * x >> 3) + (h - run[i]));
-    assign_item<WG, true, NEAR, ALL>(im, local, packed, centres, endpoints, labels, acc, lambda);
+    assign_item<WG, true, NEAR, WALK>(im, local, packed, centres, endpoints, labels, acc, lambda);
 }
 
 // ---------------------------------------------------------------- window form
@@ -1429,41 +1434,43 @@ int launch_init_cells_batched(const Img* imgs, const int* cell_start, int n_img,
     return hipGetLastError();
 }
 
-template <int WG, bool ACCUM, bool ALL>
+template <int WG, bool ACCUM, Walk WALK>
 static int launch_assign_t(const Img& im, const float4* packed, const float* centres,
                            const int* endpoints, int* labels, long long* acc, int* ctrl,
                            float lambda, hipStream_t s) {
-    const auto kernel = near_image(im) ? k_assign<WG, ACCUM, true, ALL> : k_assign<WG, ACCUM, false, ALL>;
+    const auto kernel = near_image(im) ? k_assign<WG, ACCUM, true, WALK> : k_assign<WG, ACCUM, false, WALK>;
     hipLaunchKernelGGL(kernel, dim3(im.nx * im.ny * im.spl), dim3(WG), 0, s, im, packed, centres,
                        endpoints, labels, acc, ctrl, lambda);
     return hipGetLastError();
 }
 
-template <int WG>
+template <int WG, bool ACCUM>
 static int launch_assign_wg(const Img& im, const float4* packed, const float* centres,
                             const int* endpoints, int* labels, long long* acc, int* ctrl,
-                            float lambda, bool accumulate, hipStream_t s) {
-    const bool all = walk_all(im.prune, (long long)im.W * im.H, im.nx * im.ny);
-    const auto launch = all ? accumulate ? launch_assign_t<WG, true, true> : launch_assign_t<WG, false, true>
-                        : accumulate ? launch_assign_t<WG, true, false> : launch_assign_t<WG, false, false>;
+                            float lambda, hipStream_t s) {
+    const Walk walk = walk_of(im.prune, (long long)im.W * im.H, im.nx * im.ny);
+    const auto launch = walk == Walk::kAll    ? launch_assign_t<WG, ACCUM, Walk::kAll>
+                        : walk == Walk::kMany ? launch_assign_t<WG, ACCUM, Walk::kMany>
+                                              : launch_assign_t<WG, ACCUM, Walk::kPairs>;
     return launch(im, packed, centres, endpoints, labels, acc, ctrl, lambda, s);
 }
 
 int launch_assign(const Img& im, const float4* packed, const float* centres,
                   const int* endpoints, int* labels, long long* acc, int* ctrl, float lambda,
                   bool accumulate, const Tuning& t, hipStream_t s) {
-    const auto launch = t.wg == 1024 ? launch_assign_wg<1024>
-                        : t.wg == 512 ? launch_assign_wg<512> : launch_assign_wg<256>;
-    return launch(im, packed, centres, endpoints, labels, acc, ctrl, lambda, accumulate, s);
+    const auto launch =
+        t.wg == 1024  ? accumulate ? launch_assign_wg<1024, true> : launch_assign_wg<1024, false>
+        : t.wg == 512 ? accumulate ? launch_assign_wg<512, true> : launch_assign_wg<512, false>
+                      : accumulate ? launch_assign_wg<256, true> : launch_assign_wg<256, false>;
+    return launch(im, packed, centres, endpoints, labels, acc, ctrl, lambda, s);
 }
 
-template <int WG>
-static int launch_assign_batched_wg(const Img* imgs, const int* item_start, int n_img, int longest_run,
-                                    const float4* packed, const float* centres, const int* endpoints,
-                                    int* labels, long long* acc, int* ctrl, float lambda, bool near,
-                                    bool all, hipStream_t s) {
-    const auto kernel = all ? near ? k_assign_batched<WG, true, true> : k_assign_batched<WG, false, true>
-                        : near ? k_assign_batched<WG, true, false> : k_assign_batched<WG, false, false>;
+template <int WG, Walk WALK>
+static int launch_assign_batched_t(const Img* imgs, const int* item_start, int n_img, int longest_run,
+                                   const float4* packed, const float* centres, const int* endpoints,
+                                   int* labels, long long* acc, int* ctrl, float lambda, bool near,
+                                   hipStream_t s) {
+    const auto kernel = near ? k_assign_batched<WG, true, WALK> : k_assign_batched<WG, false, WALK>;
     // (a launch holds below 2^32 lanes)
     for (int h0 = 0; h0 < longest_run; h0 += 1 << 18) {
         const unsigned n = (unsigned)std::min(longest_run - h0, 1 << 18);
@@ -1473,14 +1480,26 @@ static int launch_assign_batched_wg(const Img* imgs, const int* item_start, int 
     return hipGetLastError();
 }
 
+template <int WG>
+static int launch_assign_batched_wg(const Img* imgs, const int* item_start, int n_img, int longest_run,
+                                    const float4* packed, const float* centres, const int* endpoints,
+                                    int* labels, long long* acc, int* ctrl, float lambda, bool near,
+                                    Walk walk, hipStream_t s) {
+    const auto launch = walk == Walk::kAll    ? launch_assign_batched_t<WG, Walk::kAll>
+                        : walk == Walk::kMany ? launch_assign_batched_t<WG, Walk::kMany>
+                                              : launch_assign_batched_t<WG, Walk::kPairs>;
+    return launch(imgs, item_start, n_img, longest_run, packed, centres, endpoints, labels, acc, ctrl,
+                  lambda, near, s);
+}
+
 int launch_assign_batched(const Img* imgs, const int* item_start, int n_img, int longest_run,
                           const float4* packed, const float* centres, const int* endpoints,
                           int* labels, long long* acc, int* ctrl, float lambda, const Tuning& t,
-                          bool near, bool all, hipStream_t s) {
+                          bool near, Walk walk, hipStream_t s) {
     const auto launch = t.wg == 1024 ? launch_assign_batched_wg<1024>
                         : t.wg == 512 ? launch_assign_batched_wg<512> : launch_assign_batched_wg<256>;
     return launch(imgs, item_start, n_img, longest_run, packed, centres, endpoints, labels, acc, ctrl,
-                  lambda, near, all, s);
+                  lambda, near, walk, s);
 }
 
 // Side of the window form's tiles: 8 where that gives no more than kWinSmall of them, 4

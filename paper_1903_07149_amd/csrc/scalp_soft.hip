@@ -1203,7 +1203,7 @@ static int soft_assign_t(const SoftGeom& g, const float4* packed, const float* t
 // softmax reaches so far that the bound's spatial term rules few neighbours out: 111 T
 // against the m^2 that one cell side adds to D, four times that for two (colours still
 // may).  Not in launches of few cells, nor where a table has more entries than the
-// pixels' paths samples (see walk_all).  Forward of 8 x 512x512, k = 400, at T = 0.5, 2,
+// pixels' paths samples (see walk_of).  Forward of 8 x 512x512, k = 400, at T = 0.5, 2,
 // 3.6, 5 and 50: 955, 1063, 1112, 1136 and 1392 us, 735, 1040, 1205, 1276 and 1979 by pairs;
 // 1 x 512x512, k = 1200, at 2 and 3.6: 240 and 246, 269 and 308.
 static bool soft_tables(const SoftGeom& g) {

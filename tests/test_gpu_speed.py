@@ -90,6 +90,16 @@ def test_noise_keeps_up():
     assert hard < 6.5 * easy
 
 
+def test_many_pairs_of_large_cells_keep_up():
+    """One colour at m = 0 lists every candidate: cells of 3000 pixels against 1000, whose
+    paths have 1.7 times the samples."""
+    say("large cells, every candidate listed")
+    data = torch.full((1080, 1920, 3), 50.0, device="cuda"), torch.zeros((1080, 1920), device="cuda")
+    small, large = (_run(1920, 1080, k, data, iterations=5, m=0.0) for k in (2000, 700))
+    print(f"700 cells {large:.3f} ms, 2000 {small:.3f} ms")
+    assert large < 3.5 * small
+
+
 def test_metrics_of_few_labels_keep_up():
     """One label everywhere against many, 3840x2160."""
     from paper_1903_07149_amd.metrics import Metrics
