@@ -54,9 +54,8 @@ HBM_PEAK_GBPS = 8000.0
 # Integer-heavy streams were measured slightly above it (1.19 per CU-clock,
 # profiles/peaks_mi355x.md), so it is a ceiling for FP32 work.
 VALU_ISSUE_PEAK_GINSTS = 256 * 2.4
-# LDS: 256 B per CU-clock on CDNA4 = 157.3 TB/s spec; the conflict-free
-# ds_read_b128 rate measured by peaks_probe is 107.5 TB/s.
-LDS_SPEC_TBPS = 256 * 256 * 2.4e9 / 1e12
+# LDS: the conflict-free ds_read_b128 rate measured by peaks_probe (157.3 TB/s by the
+# specification, 256 B per CU-clock).
 LDS_MEASURED_TBPS = 107.5
 
 EXTENSIONS = ("batched", "soft", "window_form", "multiscale", "contour_prior", "quality")
@@ -142,7 +141,7 @@ def binding_resource(issue, launch_s):
     that binds it (VALU issue): wave64 VALU instructions per launch from the
     committed SQ counter record over the launch time measured in this run,
     against one instruction per CU-clock; LDS bytes from the LDS instruction
-    count (8 bytes per lane: table reads and writes, bin atomics) against the
+    count (8 bytes per lane: bin atomics, results of the second pass) against the
     measured ds_read ceiling.  Marked stale, with no fractions, when the
     record was taken on other kernel sources."""
     if issue is None:
@@ -257,9 +256,9 @@ def bench_hard(torch, args):
               for it in range(iters)]
 
     # the same step with every candidate's path walked (exact_pruning = 0;
-    # the labels are the same): graph replays, then HIP events around each
-    # assignment launch
-    gr0 = s.graph(c, e, l, n, exact_pruning=0)
+    # the labels are the same), in the library's own launch shape for it: graph
+    # replays, then HIP events around each assignment launch
+    gr0 = s.graph(c, e, l, n, exact_pruning=0, wg_size=0)
     for _ in range(args.warmup):
         s.init_grid(lab, con, out=(c, e, l))
         gr0.launch()
@@ -281,7 +280,7 @@ def bench_hard(torch, args):
         s.init_grid(lab, con, out=(c, e, l))
         for it in range(iters):
             ev0[q][it][0].record()
-            s.assign_accumulate(c, e, l, exact_pruning=0)
+            s.assign_accumulate(c, e, l, exact_pruning=0, wg_size=0)
             ev0[q][it][1].record()
             s.finalize(l, c, e, n, exact_pruning=0)
     torch.cuda.synchronize()
@@ -312,8 +311,6 @@ def bench_hard(torch, args):
         "flops_per_launch": flops // iters,
         "samples_per_launch": samples // iters,
         "samples_per_px_iter": round(samples / (N * iters), 2),
-        "lds_algorithmic_TBps": round(16 * samples / kern_s / 1e12, 3),
-        "lds_algorithmic_frac": round(16 * samples / kern_s / 1e12 / LDS_SPEC_TBPS, 4),
         "kernel_source_sha256_16": digest,
     }
     if traffic is not None:
