@@ -97,9 +97,10 @@ typedef struct {
                                 assignment when they were persistent: kept for
                                 callers that set it, without effect          */
     int32_t table_mode;      /* 0 (default) or 1, else SCALP_ERR_ARG.  Chose
-                                between two table schedules of the 3x3
-                                assignment, which has no tables any more: kept
-                                for callers that set it, without effect      */
+                                between two table schedules of an earlier 3x3
+                                assignment, whose tables are now chosen by the
+                                cells and the items: kept for callers that set
+                                it, without effect                           */
 } scalp_params_t;
 
 /* Candidate rule of the assignment.

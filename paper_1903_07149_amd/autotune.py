@@ -2,7 +2,8 @@
 
 Knobs that change speed but never results (every configuration is checked
 bit-exact against the oracle by the GPU tests): the workgroup size (lanes of
-one work item, one pixel each).
+one work item; at most one pixel each, and half or a quarter of that in large
+cells and in small batches).
 
 tune() times one fused assignment pass (`scalp_assign_accumulate`) per
 configuration with HIP events on the workload's own image and superpixel

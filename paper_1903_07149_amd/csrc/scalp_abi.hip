@@ -119,7 +119,7 @@ Img image_of(const scalp_grid_t* g, const scalp_params_t* p) {
     return img_of(g, p, 0, 0, slices_of(g, p));
 }
 
-// Single-image workspace: [packed float4 N][acc int64 8K][ctrl int32 64][plist int32 K]
+// Single-image workspace: [packed float4 N][acc int64 8K][ctrl int32 kCtrlWords][plist int32 K]
 // [the window form's tile lists, 8 N]
 struct Layout {
     size_t packed, acc, ctrl, plist, lists, total;

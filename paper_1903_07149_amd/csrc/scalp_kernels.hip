@@ -382,7 +382,9 @@ __device__ __forceinline__ void assign_all(const Img& im, int ci, int cj, int sl
 // walked by full waves of (pixel, slot) pairs, whose results meet in a 64-bit
 // minimum per pixel.  They are listed slot by slot, so that the lanes of a wave walk
 // to one endpoint: taken in the order of each pixel's bounds, an image of noise took 5.93
-// ms instead of 4.56 (10 iterations of 1920x1080), 481x321 191 us instead of 186.  A walk of
+// ms instead of 4.56 (10 iterations of 1920x1080), 481x321 191 us instead of 186.  A wave
+// takes its places in the list at once for all nine slots: a place per slot, nine LDS
+// atomics in a row, 481x321 189 us instead of 179 and 97x61 139 instead of 130.  A walk of
 // that second pass stops as soon as its partial sums prove that D exceeds the pixel's
 // first one (Cut).
 //
@@ -392,9 +394,9 @@ __device__ __forceinline__ void assign_all(const Img& im, int ci, int cj, int sl
 //
 // What bounds it: VALU issue.  32.3 M wave instructions per launch at
 // 1920x1080, k = 2000 (the bounds 180 of a wave's 990, the first walk 300,
-// its evaluation 150, the second pass 200), 0.93 issued per clock in which a CU has
-// work and 0.71 per CU-clock of the whole launch, its start and end included;
-// 0.069 ms per launch.  (The settling is one piece of code for all pixels: settled
+// its evaluation 150, the second pass 200), 0.69 per CU-clock of the whole launch, its
+// start and end included, with 43 of 64 lanes active: the others wait for the longest
+// path of their wave.  0.068 ms per launch.  (The settling is one piece of code for all pixels: settled
 // in the first pass where nothing was listed, it ran twice in most waves, 1.6 % of
 // this launch and 3 % of the 64-image batch.)  Tables of (d_c, w) per candidate in
 // LDS, all nine taken in turn by the whole workgroup behind a barrier each, made a

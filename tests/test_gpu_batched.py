@@ -44,6 +44,25 @@ def test_batched_equals_single_and_oracle(orc, tune):
         assert (l[p0:p1].reshape(H, W) == ref.labels).all(), w.name
 
 
+@pytest.mark.parametrize("wg", [256, 512, 1024])
+@pytest.mark.parametrize("sizes", [[(300, 260, 200), (90, 40, 3), (200, 210, 2)],       # small: pairs alone
+                                   [(700, 500, 900), (61, 97, 30), (300, 200, 5)],
+                                   [(400, 300, 9000), (420, 360, 9)]])
+def test_batched_at_every_workgroup_size(orc, wg, sizes):
+    """Batches below and above 2^18 pixels and 128 pixels a cell, at each number of lanes."""
+    from paper_1903_07149_amd.scalp import ScalpBatch
+    imgs = [synth.workload_image(synth.Workload("", w, h, k, 10.0, i, 2, 10))
+            for i, (w, h, k) in enumerate(sizes)]
+    b = ScalpBatch(sizes, iterations=3, wg_size=wg)
+    say("batch lanes", wg, sizes)
+    c, e, l, n = (host(t) for t in b.run(dev(np.concatenate([i.lab.reshape(-1, 3) for i in imgs])),
+                                         dev(np.concatenate([i.contour.reshape(-1) for i in imgs]))))
+    for (p0, p1, H, W), (s0, s1), (_, _, k), img in zip(b.pixel_slices(), b.sp_slices(), sizes, imgs):
+        ref = orc.run(img.lab, img.contour, k, iterations=3, mode=orc.MEAN_FIXED)
+        assert (l[p0:p1].reshape(H, W) == ref.labels).all(), (W, H, k)
+        assert (c[s0:s1] == ref.centres).all()
+
+
 def test_batched_graph_replays():
     from paper_1903_07149_amd.scalp import ScalpBatch
     wls = _batch(5, 950, 40, 300, 500)
