@@ -127,11 +127,12 @@ inline long long fill_slices(long long cells) { return kCUs / cells; }
 
 // Pixels of a work item of a batch of N pixels, for its image of W x H pixels and K
 // cells.  A batch of fewer pixels than half the lanes that the chip holds takes a
-// quarter of a workgroup's: 7 scales of 189x117 (0.15 M pixels) 32 us per iteration
-// with 128 or 256 of 256 lanes, 26 with 64; 3 images of up to 480 pixels a side, 250
-// pixels a superpixel, 22.8 and 21.5.  (12 scales of 481x321, 1.9 M: 207 us as they
-// are, 256 with 64.)  Workgroups of 1024 lanes with 64 pixels each left 15 lanes of
-// 16 idle: the same 3 images 52.3 us per iteration at 1024 lanes, 34.4 with 256 pixels.
+// quarter of a workgroup's pixels: 7 scales of 189x117 (0.15 M pixels) 32 us per
+// iteration with 128 or 256 of 256 lanes, 26 with 64.  Batches of 250 pixels a
+// superpixel, 10 iterations with whole and quarter items: 0.22 M pixels 0.34 and 0.28
+// ms, 0.33 M 0.36 and 0.37, 0.53 M 0.36 and 0.45, 0.79 M 0.42 and 0.61, 1.05 M 0.47
+// and 0.77.  Workgroups of 1024 lanes with 64 pixels each left 15 lanes of 16 idle: 3
+// images of up to 480 pixels a side 52.3 us per iteration, 34.4 with 256 pixels.
 constexpr long long kFewPixels = 1 << 18;
 
 inline int batch_item_pixels(long long N, long long W, long long H, long long K, int wg) {

@@ -68,12 +68,16 @@ struct TableShared {
     int box[4];            // of the pixels
 };
 
-// An item whose second pass would take more rounds of its lanes than this goes over
-// tables instead (walk_tables): images of noise, or whose contours are nowhere low,
-// leave most of the candidates to be walked.  10 iterations of 1920x1080, k = 2000, at
-// 4, 6 and 8 (none): the benchmark's image 732, 725 and 727 us; noise 2.52, 2.58 and 4.56 ms;
-// contours of up to 0.2 everywhere added to the benchmark's 1.68, 1.86 and 1.96.
-constexpr int kManyRounds = 6;
+// An item of more pairs per pixel in its second pass than this goes over tables instead
+// (walk_tables): images of noise, or whose contours are nowhere low, leave most of the
+// candidates to be walked.  10 iterations of 1920x1080, k = 2000, at 4, 6 and 8 (none):
+// the benchmark's image 732, 725 and 727 us; noise 2.52, 2.58 and 4.56 ms; contours of up
+// to 0.2 everywhere added to the benchmark's 1.68, 1.86 and 1.96.  (By rounds of the
+// lanes instead, which an item of 192 pixels never has six of: noise at k = 4000 3.57
+// ms instead of 2.52, one colour at m = 0 4.15 instead of 1.79.)  Not items of at most
+// half the lanes, whose pairs take few rounds: 12 scales of 481x321 2.29 ms instead of
+// 2.20, 97x61 0.143 instead of 0.131.
+constexpr int kManyPairs = 6;
 
 // A descriptor read through the scalar cache, word by word (p uniform).
 __device__ __forceinline__ Img load_const(const Img* p) {
@@ -506,7 +510,8 @@ __device__ __forceinline__ void process_cell(const Img& im, int ci, int cj, int 
     }
     __syncthreads();
     const int pairs = __builtin_amdgcn_readfirstlane(sh.pairs);
-    if (tables && prune && pairs > kManyRounds * WG) {   // uniform
+    const int pixels = it.t1 - it.t0;
+    if (tables && prune && 2 * pixels > WG && pairs > kManyPairs * pixels) {   // uniform
         walk_tables<WG, ACCUM, 1, true>(eqs, im, it, nb, k0, cen, end, labels, *tables);
         if (ACCUM) {
             __syncthreads();

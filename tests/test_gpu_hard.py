@@ -503,6 +503,7 @@ def test_every_candidate_walked_in_runs_and_batches(orc):
     (330, 250, 80, 512, 0.5, 0.0),     # m = 0: bounds of colour alone
     (330, 250, 80, 1024, 0.5, 10.0),
     (600, 500, 12, 0, 0.5, 1.0),       # large cells: boxes beyond the LDS
+    (400, 300, 230, 0, 0.5, 10.0),     # items of 192 pixels
     (1100, 960, 330, 0, 0.5, 10.0),    # cells of 3200 pixels in an image of 2^20
 ])
 def test_items_of_many_pairs(orc, W, H, k, wg, lam, m):

@@ -100,6 +100,15 @@ def test_many_pairs_of_large_cells_keep_up():
     assert large < 3.5 * small
 
 
+def test_many_pairs_of_short_items_keep_up():
+    """One colour at m = 0: cells of 500 pixels, in items of 192, against 1000."""
+    say("short items, every candidate listed")
+    data = torch.full((1080, 1920, 3), 50.0, device="cuda"), torch.zeros((1080, 1920), device="cuda")
+    whole, short = (_run(1920, 1080, k, data, iterations=5, m=0.0) for k in (2000, 4000))
+    print(f"4000 cells {short:.3f} ms, 2000 {whole:.3f} ms")
+    assert short < 1.5 * whole
+
+
 def test_metrics_of_few_labels_keep_up():
     """One label everywhere against many, 3840x2160."""
     from paper_1903_07149_amd.metrics import Metrics
