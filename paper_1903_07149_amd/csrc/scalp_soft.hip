@@ -14,6 +14,8 @@
 //                  does not prove to be 0; then the FP64 softmax of -D/T over
 //                  the 9 slots.  Writes Q, the factors A (Eq. (1)) and B
 //                  (Eq. (2)) of the walked slots, and which Q are not 0.
+//   k_soft_tables  the same where most slots are walked (see soft_tables): over an
+//                  LDS table per candidate.
 //   k_soft_update  workgroup per (image, superpixel): gathers the Q that are not
 //                  0 over the 3x3 cell block in a fixed order (FP64 partial
 //                  sums, tree reduction): deterministic, no atomics.
